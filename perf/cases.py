@@ -209,18 +209,15 @@ class _State:
     pass
 
 
-def prepare(c, seed):
+def _inputs(c, seed):
+    """What the model hands over: the steps' queries, keys, values and logits, and prompt(l), called once per layer
+    in order, then prompt_q(l) the same way."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed * 1000003 + 17)
     L, B, Hq, H, D, T, V = (c[k] for k in ("layers", "batch", "q_heads", "kv_heads", "head_dim", "prompt", "vocab"))
     S, tq = c["steps"], _tokens(c)
-    tight, loose = _budgets(c)
     st = _State()
     st.case = c
-    st.kv = ConfKV(n_layers=L, batch=B, n_q_heads=Hq, n_kv_heads=H, head_dim=D, vocab=V, capacity=_capacity(c),
-                   fp16_window=c["window"], protected_window=c["protected"], n_tight=tight, n_loose=loose,
-                   scale_mode=c["scales"], rank_scope=c["scope"], max_chunk=c["chunk"] if c["chunk"] > 1 else 0,
-                   evict_page=c["page"], layout=c["layout"])
 
     def normal(*shape, dtype=torch.float16):
         return torch.randn(shape, generator=g, device="cuda", dtype=dtype)
@@ -243,17 +240,28 @@ def prepare(c, seed):
         for b in range(B):
             if _is_confident(c, b, s):
                 st.logits[s, b, (7919 * (b + 1) + s) % V] += 25.0
-    st.out = torch.empty_like(st.q)
-    st.conf = torch.empty(S, B, dtype=torch.float32, device="cuda")
-    st.sel = torch.empty(S, B, dtype=torch.uint8, device="cuda")
-    # what the model's layers hold when they call: one tensor per layer and argument
-    st.calls = [[(l, st.q[s, l], st.k[s, l], st.v[s, l], st.out[s, l]) for l in range(L)] for s in range(S)]
-    st.scored = [(st.logits[s], st.conf[s], st.sel[s]) for s in range(S)]
-
     prompt = lambda l: (keys(u[l][None, :, None, :], B, H, T), normal(B, H, T, D))
+    prompt_q = lambda l: normal(B, T, Hq, D).add_(mean[l])
+    return st, prompt, prompt_q
+
+
+def prepare(c, seed):
+    L, B = c["layers"], c["batch"]
+    tight, loose = _budgets(c)
+    st, prompt, prompt_q = _inputs(c, seed)
+    st.kv = ConfKV(n_layers=L, batch=B, n_q_heads=c["q_heads"], n_kv_heads=c["kv_heads"], head_dim=c["head_dim"],
+                   vocab=c["vocab"], capacity=_capacity(c), fp16_window=c["window"], protected_window=c["protected"],
+                   n_tight=tight, n_loose=loose, scale_mode=c["scales"], rank_scope=c["scope"],
+                   max_chunk=c["chunk"] if c["chunk"] > 1 else 0, evict_page=c["page"], layout=c["layout"])
+    st.out = torch.empty_like(st.q)
+    st.conf = torch.empty(c["steps"], B, dtype=torch.float32, device="cuda")
+    st.sel = torch.empty(c["steps"], B, dtype=torch.uint8, device="cuda")
+    # what the model's layers hold when they call: one tensor per layer and argument
+    st.calls = [[(l, st.q[s, l], st.k[s, l], st.v[s, l], st.out[s, l]) for l in range(L)] for s in range(c["steps"])]
+    st.scored = [(st.logits[s], st.conf[s], st.sel[s]) for s in range(c["steps"])]
     if c["kind"] == "prompt":
         st.prompt = [prompt(l) for l in range(L)]
-        st.prompt_q = [normal(B, T, Hq, D).add_(mean[l]) for l in range(L)] if c["observe"] else None
+        st.prompt_q = [prompt_q(l) for l in range(L)] if c["observe"] else None
         return st
     for l in range(L):
         st.kv.load_prefill(l, *prompt(l))
@@ -290,3 +298,123 @@ def run(st):
     else:
         _steps(st)
     return {"out": st.out, "conf": st.conf, "sel": st.sel}
+
+
+# ---- the same in 64 bits ----
+
+TAU, ALPHA, DECAY = (float(torch.tensor(x)) for x in (0.7, 0.65, 0.9))      # the manager's defaults, held as fp32
+
+
+def _exact_confidence(logits):
+    """0.4 (1 - H / log V) + 0.3 sigmoid(margin of the two largest) + 0.3 p_max, with the manager's fp32 weights."""
+    wh, wm, wp = (float(torch.tensor(x)) for x in (0.4, 0.3, 0.3))
+    x = logits.double()
+    logp = torch.log_softmax(x, -1)
+    p = logp.exp()
+    top = x.topk(2, -1).values
+    h = -(p * logp).sum(-1) / math.log(x.shape[-1])
+    return wh * (1 - h) + wm * torch.sigmoid(top[..., 0] - top[..., 1]) + wp * p.amax(-1)
+
+
+def _stored_int8(x, scale):
+    """What INT8 storage keeps of fp16 rows x: codes times fp16 scales, exact in fp32."""
+    s = scale.float()
+    ok = (s > 0) & s.isfinite()
+    codes = (x.double() / torch.where(ok, s, 1.0).double()).round().clamp(-127, 127)
+    return torch.where(ok, codes.float() * s, 0.0)
+
+
+class _Unit:
+    """The cache of one (layer, sequence) over all its kv-heads: rows in order of position, kept rows as indices."""
+
+    def __init__(self, c, k, v):
+        self.c = c
+        self.raw = [k, v]
+        fixed = c["scales"] == "channel"
+        amax = [x.abs().amax(1 if fixed else -1, keepdim=True) for x in self.raw]
+        self.scale = [(a.float() / 127.0).half() if fixed else None for a in amax]
+        H, T = k.shape[:2]
+        self.q8 = [self._int8(i, x) for i, x in enumerate(self.raw)]
+        self.idx = torch.arange(T, device=k.device).repeat(H, 1)
+        self.ema = torch.zeros(H, T, dtype=torch.float32, device=k.device)
+        self.is16 = torch.ones(H, T, dtype=torch.bool, device=k.device)
+        self._demote()
+
+    def _int8(self, i, x):
+        s = self.scale[i]
+        return _stored_int8(x, (x.abs().amax(-1, keepdim=True).float() / 127.0).half() if s is None else s)
+
+    def _demote(self):
+        W = self.c["window"]
+        if W >= 0:
+            self.is16 &= self.is16.flip(1).cumsum(1).flip(1) <= W
+
+    def _rows(self, i):
+        at = self.idx[..., None].expand(-1, -1, self.raw[i].shape[-1])
+        return torch.where(self.is16[..., None], self.raw[i].gather(1, at).float(), self.q8[i].gather(1, at)).double()
+
+    def attend(self, q, k=None, v=None):
+        """Causal attention of the tokens q [tq][Hq][D]: the appended ones, or (no k) the last tq cached ones."""
+        H, tq, dev = self.idx.shape[0], q.shape[0], q.device
+        G, D = q.shape[1] // H, q.shape[2]
+        if k is not None:
+            first, new = self.raw[0].shape[1], [k.transpose(0, 1), v.transpose(0, 1)]
+            self.q8 = [torch.cat([a, self._int8(i, b)], 1) for i, (a, b) in enumerate(zip(self.q8, new))]
+            self.raw = [torch.cat([a, b], 1) for a, b in zip(self.raw, new)]
+            self.idx = torch.cat([self.idx, torch.arange(first, first + tq, device=dev).repeat(H, 1)], 1)
+            self.ema = torch.cat([self.ema, torch.zeros(H, tq, device=dev)], 1)
+            self.is16 = torch.cat([self.is16, torch.ones(H, tq, dtype=torch.bool, device=dev)], 1)
+        n = self.idx.shape[1]
+        qd = q.double().reshape(tq, H, G, D).permute(1, 2, 0, 3).reshape(H, G * tq, D)
+        s = torch.bmm(qd, self._rows(0).transpose(1, 2).contiguous()).reshape(H, G, tq, n) * float(torch.tensor(1 / math.sqrt(D)))
+        s += torch.full((tq, n), -math.inf, dtype=torch.float64, device=dev).triu(n - tq + 1)
+        p = torch.softmax(s, -1)
+        late = DECAY ** torch.arange(tq - 1, -1, -1, dtype=torch.float64, device=dev)
+        mass = (p.sum(1) * late[:, None]).sum(1)
+        self.ema = (DECAY ** tq * self.ema.double() + (1 - DECAY) * mass).float()
+        out = torch.bmm(p.reshape(H, G * tq, n), self._rows(1))
+        return out.reshape(H, G, tq, D).permute(2, 0, 1, 3).reshape(tq, H * G, D)
+
+    def evict(self, budget):
+        H, n = self.idx.shape
+        cand = n - min(self.c["protected"], n)
+        e = min(n - budget, cand)
+        if e > 0:
+            a, pos = self.ema[:, :cand].double(), self.idx[:, :cand].double()
+            if self.c["scope"] == "layer":
+                a = a.sum(0, keepdim=True).expand(H, -1)
+            unit = lambda x: (x - x.amin(1, keepdim=True)) / (x.amax(1, keepdim=True) - x.amin(1, keepdim=True)).clamp(min=1e-300)
+            score = ALPHA * unit(a) + (1 - ALPHA) * unit(pos)
+            keep = torch.cat([score.sort(dim=1, stable=True).indices[:, e:].sort(1).values,
+                              torch.arange(cand, n, device=a.device).repeat(H, 1)], 1)
+            self.idx, self.ema, self.is16 = (x.gather(1, keep) for x in (self.idx, self.ema, self.is16))
+        self._demote()
+
+
+def exact(c, seed):
+    """The pass in float64 (codes, scales and stored importance as the formats define them): confidence, choices and
+    the attention outputs; no outputs where pages are evicted whole, or where it takes too long."""
+    st, prompt, prompt_q = _inputs(c, seed)
+    L, B, S = c["layers"], c["batch"], c["steps"]
+    tight, loose = _budgets(c)
+    conf = _exact_confidence(st.logits)
+    sel = conf >= TAU
+    res = {"out": None, "conf": conf, "sel": sel.to(torch.uint8)}
+    passes = 1 if c["kind"] == "prompt" else 2       # `prepare` has run one pass of the decode kinds
+    if c["page"] or L * B * S * passes > 6000 or (c["observe"] and L * B * c["q_heads"] * c["prompt"] ** 2 > 2e10):
+        return res
+    choice = sel.tolist()
+    out = torch.empty(st.q.shape, dtype=torch.float64, device="cuda")
+    prompts = [prompt(l) for l in range(L)] if c["observe"] else (prompt(l) for l in range(L))
+    for l, (k, v) in enumerate(prompts):
+        pq = prompt_q(l) if c["observe"] else None
+        for b in range(B):
+            unit = _Unit(c, k[b], v[b])
+            if c["observe"]:
+                unit.attend(pq[b])
+            for _ in range(passes):
+                for s in range(S):
+                    at = (s, l, b) if c["kind"] == "chunk" else (s, l, b, None)
+                    out[s, l, b] = unit.attend(st.q[at], st.k[at], st.v[at]).reshape(out.shape[3:])
+                    unit.evict(tight[l] if choice[s][b] else loose[l])
+    return dict(res, out=out)
