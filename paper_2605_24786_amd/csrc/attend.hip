@@ -470,7 +470,7 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
       for (int m = LPT; m < kWave; m <<= 1) t += __shfl_xor(t, m, kWave);
       st.acc[h][e] = t;
     }
-    if (lane == 0) { wm[pidx * G + h] = mw; wl[pidx * G + h] = l; }
+    if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
     if (ts == 0) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) wo_p[h * D + c * 16 + e] = st.acc[h][e];
@@ -478,44 +478,58 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
   }
 }
 
-// Arrival and the gather of the softmax statistics in one: every split publishes its (m, l)
-// per head as words tagged with the launch's tag (tag_of: the launch's number plus the base
-// on the device), and thread k polls word k of the unit until the tag is this launch's, then
-// drops the value into LDS.  The output partials travel as tagged words of their own and are
-// polled where they are used, so seeing a split's statistics says nothing about its partial.
-// Nobody does a read-modify-write, so arrivals do not serialise at the memory side.  The wait
-// is bounded; false means it expired (counted as a device error).  Contains a workgroup
-// barrier; *s_ok must have been set to 1 before the barrier that precedes the call.
-template <int G>
-__device__ __forceinline__ bool collect_ml(const CacheView &cv, const AttendLaunch &a, const Slice &sl,
-                                           int ns, float *pml, int *s_ok) {
-  const int tid = threadIdx.x;
-  const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * G * 2;
-  for (int base = 0; base < ns * G * 2; base += kAttThreads) {
-    const int idx = base + tid;
-    const bool mine = idx < ns * G * 2;
-    bool here = !mine;
-    int spins = 0;
-    for (;;) {
-      if (!here) {
-        const unsigned long long wv = ld_tagged(&words[idx]);
-        if ((unsigned)(wv >> 32) == tag_of(a)) {
-          pml[idx] = __uint_as_float((unsigned)wv);
-          here = true;
-        }
-      }
-      if (__builtin_amdgcn_ballot_w64(!here) == 0ull) break;
-      __builtin_amdgcn_s_sleep(1);
-      if (++spins > a.spin_limit) {
-        if (!here) *s_ok = 0;
-        break;
-      }
-    }
-  }
-  __syncthreads();
-  if (*s_ok == 0 && tid == 0) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
-  return *s_ok != 0;
+// max / sum over the 16 lanes of a DPP row; every lane of the row gets the result
+#define CONFKV_DPP(v, ctrl) \
+  __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, CONFKV_DPP(v, 0xB1));    // quad_perm [1,0,3,2]
+  v = fmaxf(v, CONFKV_DPP(v, 0x4E));    // quad_perm [2,3,0,1]
+  v = fmaxf(v, CONFKV_DPP(v, 0x141));   // row_half_mirror
+  v = fmaxf(v, CONFKV_DPP(v, 0x140));   // row_mirror
+  return v;
 }
+__device__ __forceinline__ float row16_sum(float v) {
+  v += CONFKV_DPP(v, 0xB1);
+  v += CONFKV_DPP(v, 0x4E);
+  v += CONFKV_DPP(v, 0x141);
+  v += CONFKV_DPP(v, 0x140);
+  return v;
+}
+
+// The same over aligned groups of gs lanes (a power of two, uniform); all 64 lanes must be active.
+// Lane moves inside a row cost a few cycles, an exchange through LDS (__shfl_xor) some hundred.
+__device__ __forceinline__ float group_max(float v, int gs) {
+  if (gs >= 2) v = fmaxf(v, CONFKV_DPP(v, 0xB1));
+  if (gs >= 4) v = fmaxf(v, CONFKV_DPP(v, 0x4E));
+  if (gs >= 8) v = fmaxf(v, CONFKV_DPP(v, 0x141));
+  if (gs >= 16) v = fmaxf(v, CONFKV_DPP(v, 0x140));
+  if (gs >= 32) v = fmaxf(v, __shfl_xor(v, 16, kWave));
+  if (gs >= 64) v = fmaxf(v, __shfl_xor(v, 32, kWave));
+  return v;
+}
+__device__ __forceinline__ float group_sum(float v, int gs) {
+  if (gs >= 2) v += CONFKV_DPP(v, 0xB1);
+  if (gs >= 4) v += CONFKV_DPP(v, 0x4E);
+  if (gs >= 8) v += CONFKV_DPP(v, 0x141);
+  if (gs >= 16) v += CONFKV_DPP(v, 0x140);
+  if (gs >= 32) v += __shfl_xor(v, 16, kWave);
+  if (gs >= 64) v += __shfl_xor(v, 32, kWave);
+  return v;
+}
+#undef CONFKV_DPP
+#define CONFKV_DPP(v, ctrl)                                                                                   \
+  __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),                         \
+                   __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true))
+__device__ __forceinline__ double group_sum(double v, int gs) {
+  if (gs >= 2) v += CONFKV_DPP(v, 0xB1);
+  if (gs >= 4) v += CONFKV_DPP(v, 0x4E);
+  if (gs >= 8) v += CONFKV_DPP(v, 0x141);
+  if (gs >= 16) v += CONFKV_DPP(v, 0x140);
+  if (gs >= 32) v += __shfl_xor(v, 16, kWave);
+  if (gs >= 64) v += __shfl_xor(v, 32, kWave);
+  return v;
+}
+#undef CONFKV_DPP
 
 // e^x for x <= 0 (-inf included, which gives 0) to about one ulp: 2^(x log2 e) with the product
 // carried in two floats, so the hardware exponential sees an argument without rounding error.
@@ -570,7 +584,7 @@ template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D>
 __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const AttendLaunch &a,
                                                 const Slice &sl, int ns, int S, float *stash,
                                                 float *wm, float *wl, float *wo, float *gm,
-                                                double *ginv, int *s_ok) {
+                                                double *ginv) {
   const int tid = threadIdx.x;
   const float NEG = -INFINITY;
   // more than 8 rows only occur in multi-token calls; otherwise rows are the heads of one token
@@ -595,13 +609,13 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   if (kPhase != 2 && exchange && tid < G) {
     float M = NEG;
 #pragma unroll
-    for (int k = 0; k < NP; ++k) M = fmaxf(M, wm[k * G + tid]);
+    for (int k = 0; k < NP; ++k) M = fmaxf(M, wm[tid * NP + k]);
     float l = 0.f;
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      const float mk = wm[k * G + tid];
+      const float mk = wm[tid * NP + k];
       const bool live = mk > NEG;
-      l = fmaf(live ? wl[k * G + tid] : 0.f, live ? __expf(mk - M) : 0.f, l);
+      l = fmaf(live ? wl[tid * NP + k] : 0.f, live ? __expf(mk - M) : 0.f, l);
     }
     if (!a.withhold || sl.j != 0) {                   // (test hook: split 0 keeps its words to itself)
       st_tagged(&ml[tid * 2], tag_of(a), M);
@@ -620,8 +634,8 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
     float mk[NP], lk[NP], ok2[NP][kEPT];
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      mk[k] = wm[k * G + h];
-      lk[k] = wl[k * G + h];
+      mk[k] = wm[h * NP + k];
+      lk[k] = wl[h * NP + k];
       // partial k belongs to wavefront k % kAttWaves
       const float *src = &wo[(k % kAttWaves) * WSTR + (k / kAttWaves) * G * D + idx];
       if constexpr (kEPT == 2) {
@@ -662,108 +676,104 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   }
   TS(19);
   if (kPhase == 1) return;
+  // The unit's global softmax statistics.  A wavefront takes one (row, split) per lane, so the gs
+  // lanes (gs = ns rounded up to a power of two) that share a row reduce to the row's (M, L) with
+  // lane moves; a unit of up to 64 (row, split) pairs is one wavefront's work.  (All wavefronts
+  // polling for themselves saves the barrier behind it and is slower: the polls then crowd out the
+  // stores they wait for -- 12.6 against 10.6 us per launch with 16 splits.)
+  const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * G * 2;
   const unsigned long long *pou = a.part_o + (size_t)sl.ul * a.max_splits * G * D;
-  float *pml = wo;                                   // [ns][G][2], reuses the merge buffer
-  // Output merge: this split normalises `per` elements of the unit's [G][D] output.  The ns
-  // partial values of one element sit in gs consecutive lanes (gs = ns rounded up to a power
-  // of two), so one load per thread fetches them in a single round trip whatever ns is, and a
-  // few lane shuffles add them up.
+  float *pml = wo;                                   // [G][gs] weights of the splits' partials, reuses the merge buffer
+  int lg = 0;
+  while ((1 << lg) < ns) ++lg;                       // <= 6: groups never straddle a wavefront
+  const int gs = 1 << lg;
+  // This split normalises `per` elements of the unit's [G][D] output; the ns partial values of
+  // one element sit in gs consecutive lanes, so one load per thread and pass fetches them.
   const int per = (G * D + ns - 1) / ns;
-  int gs = 1;
-  while (gs < ns) gs <<= 1;                          // <= 64: groups never straddle a wavefront
-  const int epp = kAttThreads / gs;                  // elements per pass over the workgroup
-  const int os = tid % gs, oe = tid / gs;            // this thread's split and element within a pass
-  unsigned long long opre = 0ull, opre2 = 0ull;
+  const int epp = kAttThreads >> lg;                 // output elements per pass over the workgroup
+  const int os = tid & (gs - 1), oe = tid >> lg;     // this thread's split and element within a pass
+  constexpr int kOut = G > 8 ? 4 : G > 4 ? 2 : 1;    // passes whose words are requested at once
+  unsigned long long opre[kOut];
+  const unsigned tag = tag_of(a);
+  __shared__ int s_ok;
   if (exchange) {
-    if (kPhase == 0) {
-      if (tid == 0) *s_ok = 1;
-      lds_barrier();                                 // the merge has read the buffer the statistics land in
-      TS(20);
-      if (!collect_ml<G>(cv, a, sl, ns, pml, s_ok)) return;
-      TS(21);
-    } else {
-      // second launch: every word of the unit was written by the first one
-      const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * G * 2;
-      for (int idx = tid; idx < ns * G * 2; idx += kAttThreads) pml[idx] = __uint_as_float((unsigned)ld_tagged(&words[idx]));
-      __syncthreads();
-    }
-    // this split's share of the unit's output partials: a first look now, checked (and asked for
-    // again if the word is not this launch's yet) only after the importance update
-    if (os < ns && oe < per && sl.j * per + oe < G * D)
-      opre = ld_tagged(&pou[(size_t)os * G * D + sl.j * per + oe]);
-    // global (M, L) of head h by wavefront h: one lane per split
-    for (int h = tid >> 6; h < G; h += kAttWaves) {
-      const int sp = tid & 63;
-      const float ms = sp < ns ? pml[(sp * G + h) * 2] : NEG;
-      // only the first gs lanes hold partials: log2(gs) exchange steps instead of six
-      const float ls = sp < ns ? pml[(sp * G + h) * 2 + 1] : 0.f;
-      float M = ms;
-      // (fixed lane distances up to four splits, so the exchanges need no index registers)
-      if (gs <= 4) {
-        if (gs > 2) M = fmaxf(M, __shfl_xor(M, 2, kWave));
-        if (gs > 1) M = fmaxf(M, __shfl_xor(M, 1, kWave));
-      } else {
-        for (int m = gs >> 1; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m, kWave));
+    const int lane = tid & 63, hpr = kWave >> lg;    // rows per round
+    if (tid == 0) s_ok = 1;
+    if (kPhase == 0) lds_barrier();                  // the merge has read the buffer the weights land in
+    else __syncthreads();
+    TS(20);
+    for (int h0 = (tid >> 6) * hpr; h0 < G; h0 += kAttWaves * hpr) {
+      const int h = h0 + (lane >> lg);
+      const bool mine = h < G && os < ns;
+      const unsigned long long *src = words + (mine ? (size_t)os * G + h : 0) * 2;
+      unsigned long long wvm, wvl;
+      bool here;
+      // the wait is bounded; in a second launch every word is there
+      for (int spins = 0;; ++spins) {
+        wvm = ld_tagged(src);
+        wvl = ld_tagged(src + 1);
+        here = !mine || ((unsigned)(wvm >> 32) == tag && (unsigned)(wvl >> 32) == tag);
+        if (__builtin_amdgcn_ballot_w64(!here) == 0ull || spins > a.spin_limit) break;
+        __builtin_amdgcn_s_sleep(1);
       }
-      const float es = ms > NEG ? exp_nonpos(ms - M) : 0.f;        // an empty partial weighs nothing
-      double L = (double)es * (double)ls;
-      if (gs <= 4) {
-        if (gs > 2) L += __shfl_xor(L, 2, kWave);
-        if (gs > 1) L += __shfl_xor(L, 1, kWave);
-      } else {
-        for (int m = gs >> 1; m >= 1; m >>= 1) L += __shfl_xor(L, m, kWave);
+      if (!here) s_ok = 0;
+      const float ms = mine ? __uint_as_float((unsigned)wvm) : NEG;
+      const float ls = mine ? __uint_as_float((unsigned)wvl) : 0.f;
+      const float M = group_max(ms, gs);
+      const float es = ms > NEG ? exp_nonpos(ms - M) : 0.f;          // an empty partial weighs nothing
+      const double inv = recip_pos(group_sum((double)es * (double)ls, gs));
+      if (mine) {
+        if (os == 0) { gm[h] = M; ginv[h] = inv; ginv[G + h] = inv * row_weight(a, tq, gq, h); }
+        // what split os's output partial of this row is multiplied by
+        pml[(h << lg) + os] = es * (float)inv;
       }
-      const double inv = recip_pos(L);
-      if (sp == 0) { gm[h] = M; ginv[h] = inv; ginv[G + h] = inv * row_weight(a, tq, gq, h); }
-      // what split sp's output partial of this row is multiplied by, in place of its maximum
-      if (sp < ns) pml[(sp * G + h) * 2] = es * (float)inv;
     }
-    lds_barrier();                                   // (the look at the output partials stays in flight)
-    // a second look, half a round trip later: by now the slowest split's words have landed, and
-    // this one too travels behind the importance update
-    if (os < ns && oe < per && sl.j * per + oe < G * D)
-      opre2 = ld_tagged(&pou[(size_t)os * G * D + sl.j * per + oe]);
+    lds_barrier();
+    TS(21);
+    if (s_ok == 0) {                                 // the wait expired
+      if (tid == 0) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
+      return;
+    }
+    // the output partials are requested now and used behind the importance arithmetic
+#pragma unroll
+    for (int p = 0; p < kOut; ++p) {
+      const int i = p * epp + oe, e = sl.j * per + i;
+      opre[p] = ld_tagged(&pou[os < ns && i < per && e < G * D ? (size_t)os * G * D + e : 0]);
+    }
   } else {
     __syncthreads();
   }
   TS(22);
   // ---- this split normalises its share of the unit's output (online-softmax merge) ----
   auto finish_output = [&]() {
-  if (exchange) {
-      for (int base = 0; base < per; base += epp) {
-        const int e = sl.j * per + base + oe;                          // element of the [G][D] output
-        const bool valid = os < ns && base + oe < per && e < G * D;
-        const unsigned long long *src = &pou[(size_t)os * G * D + (valid ? e : 0)];
-        unsigned long long wv = base == 0 ? ((unsigned)(opre >> 32) == tag_of(a) ? opre : opre2) : (valid ? ld_tagged(src) : 0ull);
-        // a word that is not this launch's yet is asked for again (bounded); in a second launch
-        // every word is there
-        bool here = !valid || (unsigned)(wv >> 32) == tag_of(a);
-        for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull; ++spins) {
-          if (spins > a.spin_limit) break;
-          __builtin_amdgcn_s_sleep(1);
-          if (!here) {
-            wv = ld_tagged(src);
-            here = (unsigned)(wv >> 32) == tag_of(a);
-          }
+    for (int p = 0; p * epp < per; ++p) {
+      const int i = p * epp + oe, e = sl.j * per + i;                // element of the [G][D] output
+      const bool valid = os < ns && i < per && e < G * D;
+      const unsigned long long *src = &pou[valid ? (size_t)os * G * D + e : 0];
+      unsigned long long wv = 0ull;
+#pragma unroll
+      for (int q = 0; q < kOut; ++q) wv = p == q ? opre[q] : wv;
+      if (p >= kOut) wv = ld_tagged(src);
+      // a word that is not this launch's yet is asked for again (bounded)
+      bool here = !valid || (unsigned)(wv >> 32) == tag;
+      for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull; ++spins) {
+        if (spins > a.spin_limit) break;
+        __builtin_amdgcn_s_sleep(1);
+        if (!here) {
+          wv = ld_tagged(src);
+          here = (unsigned)(wv >> 32) == tag;
         }
-        const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
-        if (missing) {                                                 // the wait expired: no output from this wavefront
-          if ((tid & 63) == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
-          continue;
-        }
-        const float v = __uint_as_float((unsigned)wv);
-        const int h = valid ? e / D : 0;
-        const float wgt = valid ? pml[(os * G + h) * 2] : 0.f;         // e^{m_s - M} / L of that split and row
-        float c = wgt > 0.f ? v * wgt : 0.f;                           // (an empty partial may hold anything)
-        if (gs <= 4) {                                                 // the usual case: two fixed exchanges
-          if (gs > 2) c += __shfl_xor(c, 2, kWave);
-          if (gs > 1) c += __shfl_xor(c, 1, kWave);
-        } else {
-          for (int m = gs >> 1; m >= 1; m >>= 1) c += __shfl_xor(c, m, kWave);
-        }
-        if (valid && os == 0 && h < tq * gq && a.out && e - h * D < DR)
-          a.out[out_index(cv, sl, tq, gq, h * DR + (e - h * D), DR)] = __float2half_rn(c);
       }
+      const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
+      if (missing) {                                                 // the wait expired: no output from this wavefront
+        if ((tid & 63) == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
+        continue;
+      }
+      const int h = valid ? e / D : 0;
+      const float wgt = valid ? pml[(h << lg) + os] : 0.f;           // e^{m_s - M} / L of that split and row
+      const float c = group_sum(wgt > 0.f ? __uint_as_float((unsigned)wv) * wgt : 0.f, gs);   // (an empty partial may hold anything)
+      if (valid && os == 0 && h < tq * gq && a.out && e - h * D < DR)
+        a.out[out_index(cv, sl, tq, gq, h * DR + (e - h * D), DR)] = __float2half_rn(c);
     }
   };
   // ---- mass + EMA of the slice ----
@@ -775,8 +785,9 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   const double *gw = ginv + G;
   const int first_new = sl.n - tq;
   // The new values of the first kPre slots per thread stay in registers until the output is
-  // out: a store between the look at the output partials and its use would make that use wait
-  // for the store's acknowledgement as well (loads and stores share one in-order counter).
+  // out: a store between the request of the output partials and their use would make that use
+  // wait for the store's acknowledgement as well (loads and stores share one in-order counter).
+  float ema_new[kPre + 1];
 #pragma unroll
   for (int k = 0; k < kPre; ++k) {
     const int t = tid + k * kAttThreads;
@@ -784,12 +795,21 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       double A = 0.0;
 #pragma unroll
       for (int h = 0; h < G; ++h) A += (double)exp_nonpos(stash[h * S + t] - gm[h]) * gw[h];
-      const int slot = sl.slot_of(t);
-      const double old = (slot >= first_new) ? 0.0 : (double)ema_old[k];   // a new token starts at 0
-      EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, slot)] = (float)(lam * old + oml * A);
+      const double old = (sl.slot_of(t) >= first_new) ? 0.0 : (double)ema_old[k];   // a new token starts at 0
+      ema_new[k] = (float)(lam * old + oml * A);
+      if (!exchange) EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, sl.slot_of(t))] = ema_new[k];
     }
   }
   TS(30);
+  if (exchange) {
+    finish_output();
+    TS(23);
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+      const int t = tid + k * kAttThreads;
+      if (t < sl.ntok) EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, sl.slot_of(t))] = ema_new[k];
+    }
+  }
   // the rest of the slice in batches of kBatch slots per thread: branch-free loads first (a
   // slot past the slice re-reads its last one), so a long slice costs one round trip per
   // batch, not one per slot
@@ -814,8 +834,6 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       }
     }
   }
-  TS(23);
-  finish_output();
   TS(31);
 }
 
@@ -833,11 +851,10 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   float *stash = kSpill ? a.spill + ((size_t)unit_in_layer(cv, a) * ns + split_index(a)) * G * S
                         : smem;                 // [G][S] raw scores of the slice
   float *wo = smem + (kSpill ? 0 : (size_t)G * S);   // [NP][G][D] per-wave un-normalised output
-  float *wm = wo + NP * G * D;                  // [NP][G] per-wave maximum
-  float *wl = wm + NP * G;                      // [NP][G] per-wave normaliser
+  float *wm = wo + NP * G * D;                  // [G][NP] per-wave maximum
+  float *wl = wm + NP * G;                      // [G][NP] per-wave normaliser
   float *gm = wl + NP * G;                      // [G] global maximum
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]: 1 / global normaliser, the same times the row's mass weight
-  __shared__ int s_ok;
 
   const Slice sl = make_slice(cv, a, ns, S);
   append_new_token<D>(cv, a, sl, ns);
@@ -872,7 +889,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   stream_fp16_valu<D, G>(cv, sl, a.sm_scale, qf, st, stash, S);
   store_stream_partial<D, G>(st, threadIdx.x >> 6, wm, wl, wo + (threadIdx.x >> 6) * G * D);
   __syncthreads();
-  attend_epilogue<D, G, NP, G * D, kSpill ? 1 : 0>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv, &s_ok);
+  attend_epilogue<D, G, NP, G * D, kSpill ? 1 : 0>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv);
 }
 
 // Second launch of the two-launch form: same grid; merges the published partials of the unit,
@@ -885,10 +902,9 @@ __global__ __launch_bounds__(kAttThreads) void attend_finish_kernel(const int32_
   float *pml = smem;                            // [ns][G][2]
   float *gm = pml + (size_t)ns * G * 2;         // [G]
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]
-  __shared__ int s_ok;
   const Slice sl = make_slice(cv, a, ns, S);
   float *stash = a.spill + ((size_t)unit_in_layer(cv, a) * ns + split_index(a)) * G * S;
-  attend_epilogue<D, G, 1, 0, 2, DR>(cv, a, sl, ns, S, stash, nullptr, nullptr, pml, gm, ginv, &s_ok);
+  attend_epilogue<D, G, 1, 0, 2, DR>(cv, a, sl, ns, S, stash, nullptr, nullptr, pml, gm, ginv);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -942,25 +958,6 @@ __device__ __forceinline__ half8_t cvt_i8x8_f16x8(unsigned w0, unsigned w1) {
   r[4] = p2[0]; r[5] = p2[1]; r[6] = p3[0]; r[7] = p3[1];
   return r;
 }
-
-// max / sum over the 16 lanes of a DPP row; every lane of the row gets the result
-#define CONFKV_DPP(v, ctrl) \
-  __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, CONFKV_DPP(v, 0xB1));    // quad_perm [1,0,3,2]
-  v = fmaxf(v, CONFKV_DPP(v, 0x4E));    // quad_perm [2,3,0,1]
-  v = fmaxf(v, CONFKV_DPP(v, 0x141));   // row_half_mirror
-  v = fmaxf(v, CONFKV_DPP(v, 0x140));   // row_mirror
-  return v;
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += CONFKV_DPP(v, 0xB1);
-  v += CONFKV_DPP(v, 0x4E);
-  v += CONFKV_DPP(v, 0x141);
-  v += CONFKV_DPP(v, 0x140);
-  return v;
-}
-#undef CONFKV_DPP
 
 // A 16x16 score tile leaves the matrix core with head 4 * (lane / 16) + i in element i, so at
 // G <= 4 only the first 16 lanes hold real rows and every softmax instruction would work on
@@ -1052,11 +1049,10 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   float *stash = kSpill ? a.spill + ((size_t)unit_in_layer(cv, a) * ns + split_index(a)) * G * S
                         : smem + kTileFloats;   // [G][S]
   float *gm = smem + kTileFloats + (kSpill ? 0 : (size_t)G * S);   // [G]
-  double *ginv = (double *)(gm + G + (G & 1));  // [2 G]
-  float *wm = (float *)(ginv + 2 * G);          // [NP][G]
-  float *wl = wm + NP * G;                      // [NP][G]
+  double *ginv = (double *)(gm + G + (-G & 3)); // [2 G]
+  float *wm = (float *)(ginv + 2 * G);          // [G][NP], on a 16-byte boundary: a row's NP values are two loads
+  float *wl = wm + NP * G;                      // [G][NP]
   float *wo = tiles;
-  __shared__ int s_ok;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int tq = G > 8 ? a.tq : 1, gq = G > 8 ? a.gq : G;   // tokens of the call, heads per token
@@ -1464,7 +1460,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   float *wo_w = tiles + w * (kTileBytes / 4);
 #pragma unroll
   for (int j = 0; j < NV; ++j)
-    if (t16 == 0 && hd[j] < G) { wm[w * G + hd[j]] = mrun[j]; wl[w * G + hd[j]] = lrun[j]; }
+    if (t16 == 0 && hd[j] < G) { wm[hd[j] * NP + w] = mrun[j]; wl[hd[j] * NP + w] = lrun[j]; }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int h = 4 * g4 + i;
@@ -1478,7 +1474,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   TS(17);
   __syncthreads();
   TS(18);
-  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv, &s_ok);
+  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv);
   TS_DUMP();
 }
 
