@@ -346,6 +346,11 @@ static int length_bound(const conf_kv_handle *h, int layer) {
   return h->static_plan ? std::max(h->len_ub[layer], h->n_loose[layer]) : h->len_ub[layer];
 }
 
+// Weight of a step's mass in the importance update.
+static double mass_gain(const conf_kv_handle *h) {
+  return h->cfg.mass_gain < 0.f ? 1.0 - (double)h->cfg.ema_decay : (double)h->cfg.mass_gain;
+}
+
 // LDS the attention kernel needs for the unit's block table (paged layout), in whole 16 bytes.
 static size_t table_lds(const conf_kv_handle *h) {
   return h->cv.page_lg ? ((size_t)h->cv.npages * 4 + 15) / 16 * 16 : 0;
@@ -375,7 +380,7 @@ static int plan_for_layer(conf_kv_handle *h, int layer, int tq, AttendPlan *plan
 // observe_first < 0: append tq tokens and attend; >= 0: conf_kv_observe
 static int attend_tokens(conf_kv_handle *h, int32_t layer, int32_t tq, const void *dev_q16,
                          const void *dev_knew16, const void *dev_vnew16, void *dev_out16,
-                         conf_kv_stream stream, int32_t observe_first = -1, int32_t q_tokens = 0) {
+                         conf_kv_stream stream, int32_t observe_first = -1) {
   const bool observe = observe_first >= 0;
   if (!h || !dev_q16) return CONF_KV_ERR_INVALID_ARG;
   if (!observe && (!dev_knew16 || !dev_vnew16 || !dev_out16)) return CONF_KV_ERR_INVALID_ARG;
@@ -414,10 +419,9 @@ static int attend_tokens(conf_kv_handle *h, int32_t layer, int32_t tq, const voi
   a.max_splits = kAttendMaxSplits;
   a.sm_scale = h->cfg.sm_scale;
   a.ema_decay = h->cfg.ema_decay;
-  a.mass_gain = h->cfg.mass_gain < 0.f ? 1.0 - (double)h->cfg.ema_decay : (double)h->cfg.mass_gain;
+  a.mass_gain = mass_gain(h);
   a.pos_new = 0;                                   // read on the device
   a.tq = tq;
-  a.q_tokens = q_tokens > 0 ? q_tokens : tq;
   a.gq = h->cv.G;
   a.observe_first = observe_first;
   a.kv_major = h->kv_major;
@@ -465,14 +469,13 @@ int conf_kv_observe_prompt(conf_kv_handle *h, int32_t layer, const void *dev_q16
   if (!h || !dev_q16) return CONF_KV_ERR_INVALID_ARG;
   if (layer < 0 || layer >= h->cfg.n_layers) return CONF_KV_ERR_BAD_LAYER;
   if (h->appended[layer] || h->fresh_len[layer] < 0) return CONF_KV_ERR_BAD_STATE;
-  const int T0 = h->fresh_len[layer], step = std::max(1, h->cfg.max_chunk);
-  const size_t tok = (size_t)h->cfg.n_q_heads * h->cfg.head_dim;          // elements of one token's queries
-  for (int first = 0; first < T0; first += step) {
-    const int tq = std::min(step, T0 - first);
-    int rc = attend_tokens(h, layer, tq, (const __half *)dev_q16 + (size_t)first * tok, nullptr, nullptr, nullptr,
-                           stream, first, T0);
-    if (rc != CONF_KV_OK) return rc;
-  }
+  const int T0 = h->fresh_len[layer];
+  if (T0 == 0) return CONF_KV_OK;
+  // (accepted where conf_kv_observe is)
+  if (h->cfg.max_chunk < 2 && h->cv.G <= 8) return CONF_KV_ERR_INVALID_ARG;
+  if ((uintptr_t)dev_q16 & 15) return CONF_KV_ERR_INVALID_ARG;
+  CK_HIP(h, launch_observe_prompt(h->cv, layer, (const __half *)dev_q16, T0, h->cfg.sm_scale, (double)h->cfg.ema_decay,
+                                  mass_gain(h), (float *)(h->scratch + h->kl.spill), (hipStream_t)stream));
   return CONF_KV_OK;
 }
 

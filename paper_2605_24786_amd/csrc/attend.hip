@@ -47,6 +47,7 @@
 #include <set>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 #include "confkv_dev.h"
 #include "launch.h"
@@ -1148,7 +1149,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   {
     // row t16 = (token, head) of the call's [B][tq][Hq][D] queries
     const int q_tok = t16 / gq, q_head = t16 - q_tok * gq;
-    const __half *qrow = a.q + ((((size_t)sl.b * a.q_tokens + q_tok) * cv.Hkv + sl.g) * gq + q_head) * DR;
+    const __half *qrow = a.q + ((((size_t)sl.b * a.tq + q_tok) * cv.Hkv + sl.g) * gq + q_head) * DR;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       int4 raw = make_int4(0, 0, 0, 0);
@@ -1479,6 +1480,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 }
 
 #include "attend_wide.h"
+#include "attend_observe.h"
 
 // ---------------------------------------------------------------------------------------
 // host side

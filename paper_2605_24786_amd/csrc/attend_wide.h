@@ -206,7 +206,7 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
   {
     const int ra = rb * 16 + t16;
     const int q_tok = ra / gq, q_head = ra - q_tok * gq;
-    const __half *qrow = a.q + ((((size_t)sl.b * a.q_tokens + q_tok) * cv.Hkv + sl.g) * gq + q_head) * D;
+    const __half *qrow = a.q + ((((size_t)sl.b * a.tq + q_tok) * cv.Hkv + sl.g) * gq + q_head) * D;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       int4 raw = make_int4(0, 0, 0, 0);

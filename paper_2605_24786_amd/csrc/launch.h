@@ -56,8 +56,6 @@ struct AttendLaunch {
   unsigned tag_base;       // filled in by the kernels from cv.ctl
   int pos_new;             // position of the first appended token (the kernels read it from cv.ctl)
   int tq;                  // tokens appended (and queries per head) in this call
-  int q_tokens;            // tokens per sequence in the q tensor: q is [B][q_tokens][Hq][D] and the call's
-                           // queries are its first tq tokens (tq, unless the call is a window of a longer tensor)
   int gq;                  // query heads per kv-head; the kernels' row r is (token r / gq, head r % gq)
   int observe_first;       // >= 0: the queries belong to the cached slots observe_first .. observe_first + tq - 1;
                            // nothing is appended and slots from observe_first + tq on are left alone
@@ -85,6 +83,10 @@ constexpr int kWideRowsMax = 128;
 bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits, AttendPlan *plan);
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
+// Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,
+// contiguous layout).  scratch: B * Hkv * G * (T rounded up to 16) pairs of floats.
+hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
+                                 float *scratch, hipStream_t stream);
 
 // ---- evict.hip ----
 // Per unit, written by rank_select: [0] new length, [1] new INT8 count, [2] first evicted slot,

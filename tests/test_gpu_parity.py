@@ -451,6 +451,44 @@ def test_observe_prompt_covers_every_query(lib, torch_cuda, G, T0, W, mc):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W,scales,decay,gain", [
+    (4, 1, 8, "token", 0.9, None),            # a prompt of one token
+    (2, 16, -1, "token", 0.9, None),          # one block of 16 tokens, FP16-only
+    (3, 31, 0, "token", 0.9, None),           # W = 0: every slot INT8, a partial tile
+    (8, 33, 32, "token", 0.5, None),          # one INT8 slot in front of a full FP16 tile
+    (12, 65, 17, "token", 0.9, None),         # more heads than one 16-row step of a block has pairs
+    (1, 289, 40, "token", 1.0, 1.0),          # the running sum: every query weighs the same; > 8 tiles
+    (4, 130, 33, "channel", 0.9, None),       # per-channel scales
+    (4, 1027, 128, "token", 0.0, None),       # only the last query counts
+])
+def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
+    """Tile and block edges of the prompt-phase kernels (32-slot tiles, 16-token blocks, 64-token strides).
+    An importance is a sum of probabilities whose scores carry fp32 rounding of 128 products: 1e-5 relative."""
+    torch = torch_cuda
+    H, B, D = 2, 2, 128
+    say(f"observe_prompt G={G} T0={T0} W={W} scales={scales} decay={decay}")
+    kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[max(1, T0 - 20)], n_loose=[max(1, T0 - 20)], max_chunk=2, scale_mode=scales,
+             ema_decay=decay, mass_gain=gain)
+    rng = np.random.default_rng(T0 + G)
+    K = rng.standard_normal((B, H, T0, D)).astype(np.float16)
+    V = rng.standard_normal((B, H, T0, D)).astype(np.float16)
+    q = (rng.standard_normal((B, T0, G * H, D)) * 1.5).astype(np.float16)
+    stale = torch.full((B, H, T0), 7.0, device="cuda")                # whatever a slot held before its query counts from 0
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda(), stale)
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    sm, lam = f32(1 / math.sqrt(D)), f32(decay)
+    for b in range(B):
+        for g in range(H):
+            u = O.load_prefill(K[b, g], V[b, g], W, scale_mode=scales)
+            O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, sm, lam, gain)
+            e_ref = u.ema.astype(np.float64)
+            e_err = np.abs(kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+            assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"unit {(b, g)}: EMA off, max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
+    assert kv.counters().device_errors == 0
+    kv.close()
+
+
 def test_observe_two_launch_form(lib, torch_cuda):
     _observe_case(lib, torch_cuda, 4, 2, 1, 1200, 64, 4, ((1190, 4), (1194, 4)), seed=5, two_launch=True)
 
