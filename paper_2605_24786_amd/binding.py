@@ -177,6 +177,7 @@ class ConfKV:
         if not torch.cuda.is_available():
             raise RuntimeError("ConfKV needs a GPU: the decode path has no CPU implementation")
         self._torch = torch
+        self._raw_stream, self._device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
         self.lib = load_library()
         self.cfg, self._nt, self._nl = make_config(**kw)
         sb = self.lib.conf_kv_state_bytes(C.byref(self.cfg))
@@ -197,7 +198,9 @@ class ConfKV:
         return status
 
     def _stream(self):
-        return self._torch.cuda.current_stream().cuda_stream
+        # torch.cuda.current_stream() builds a Stream object on every call: 2.9 us against 0.2 us for
+        # the handle alone, of 7 us of host time per launch
+        return self._raw_stream(self._device())
 
     def close(self):
         if getattr(self, "h", None):

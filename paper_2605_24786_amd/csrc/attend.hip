@@ -254,231 +254,6 @@ __device__ __forceinline__ void append_new_token(const CacheView &cv, const Atte
   if constexpr (kSync) __syncthreads();
 }
 
-// ---------------------------------------------------------------------------------------
-// Vector-ALU streaming body
-// ---------------------------------------------------------------------------------------
-
-// Running softmax state of one slot lane-group: per head the maximum so far, the
-// normaliser and this lane's 16 channels of the un-normalised output.
-template <int G>
-struct Stream {
-  float m[G], l[G], acc[G][16];
-  __device__ __forceinline__ void reset() {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      m[h] = -INFINITY;
-      l[h] = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[h][e] = 0.f;
-    }
-  }
-};
-
-// Fold a batch of R slots into the running state.  s[r][h] are the slots' scores,
-// vf[r] the value channels owned by this lane, vsc[r] the value scale, ok[r] validity.
-template <int G, int R>
-__device__ __forceinline__ void fold_batch(Stream<G> &st, const float (&s)[R][G],
-                                           const float (&vf)[R][16], const float (&vsc)[R],
-                                           const bool (&ok)[R]) {
-  const float NEG = -INFINITY;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float bm = NEG;
-#pragma unroll
-    for (int r = 0; r < R; ++r) bm = ok[r] ? fmaxf(bm, s[r][h]) : bm;
-    const float mn = fmaxf(st.m[h], bm);
-    const float corr = (mn == NEG) ? 1.f : __expf(st.m[h] - mn);
-    st.m[h] = mn;
-    float p[R], lsum = 0.f;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      p[r] = ok[r] ? __expf(s[r][h] - mn) : 0.f;
-      lsum += p[r];
-      p[r] *= vsc[r];
-    }
-    st.l[h] = fmaf(st.l[h], corr, lsum);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      float t = st.acc[h][e] * corr;
-#pragma unroll
-      for (int r = 0; r < R; ++r) t = fmaf(p[r], vf[r][e], t);
-      st.acc[h][e] = t;
-    }
-  }
-}
-
-template <int D, int G>
-__device__ __forceinline__ void load_q_slices(const CacheView &cv, const AttendLaunch &a,
-                                              const Slice &sl, float (&qf)[G][16]) {
-  constexpr int LPT = D / 16;
-  const int c = (threadIdx.x & 63) % LPT;
-  const int Hq = cv.Hkv * G;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const int4 *qp = (const int4 *)(a.q + ((size_t)(sl.b * Hq + sl.g * G + h)) * D + c * 16);
-    unpack_h16x16(qp[0], qp[1], qf[h]);
-  }
-}
-
-// INT8 slots [lo, hi8) on the vector ALU.
-template <int D, int G>
-__device__ __forceinline__ void stream_int8_valu(const CacheView &cv, const Slice &sl, float sm,
-                                                 const float (&qf)[G][16], Stream<G> &st,
-                                                 float *stash, int S) {
-  constexpr int LPT = D / 16, TW = kWave / LPT, TB = kAttWaves * TW, R8 = 4;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c = lane % LPT, ts = lane / LPT;
-  const int8_t *K8 = cv.k8 + (size_t)sl.u * cv.cap8 * D;
-  const int8_t *V8 = cv.v8 + (size_t)sl.u * cv.cap8 * D;
-  // per-channel scales: the caller folded the K scales into qf and applies the V scales to the
-  // accumulator afterwards; every slot then has the factors (sm, 1).  The per-token loads stay
-  // branch-free on element 0 of the unit's scale plane.
-  const bool chan = cv.chan != 0;
-  const __half *KS = cv.ks + (size_t)sl.u * (chan ? D : cv.cap8);
-  const __half *VS = cv.vs + (size_t)sl.u * (chan ? D : cv.cap8);
-  for (int base = sl.lo8; base < sl.hi8; base += TB * R8) {
-    int4 kr[R8], vr[R8];
-    unsigned short ksh[R8], vsh[R8];
-    float vsc[R8];
-    bool ok[R8];
-    // branch-free loads (rows past the slice re-read its last row and are masked below), so
-    // that all of a trip's loads are in flight before the first one is waited for
-#pragma unroll
-    for (int r = 0; r < R8; ++r) {
-      const int i = base + r * TB + w * TW + ts;
-      ok[r] = i < sl.hi8;
-      const int ic = ring_row_u(sl.h8, ok[r] ? i : sl.hi8 - 1, cv.cap8);
-      kr[r] = *(const int4 *)(K8 + (size_t)ic * D + c * 16);
-      vr[r] = *(const int4 *)(V8 + (size_t)ic * D + c * 16);
-      ksh[r] = ((const unsigned short *)KS)[chan ? 0 : ic];
-      vsh[r] = ((const unsigned short *)VS)[chan ? 0 : ic];
-    }
-    float s[R8][G], vf[R8][16];
-#pragma unroll
-    for (int r = 0; r < R8; ++r) {
-      float kf[16];
-      unpack_i8x16(kr[r], kf);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float acc = 0.f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc = fmaf(qf[h][e], kf[e], acc);
-        s[r][h] = acc;
-      }
-    }
-#pragma unroll
-    for (int m = 1; m < LPT; m <<= 1) {
-#pragma unroll
-      for (int r = 0; r < R8; ++r)
-#pragma unroll
-        for (int h = 0; h < G; ++h) s[r][h] += __shfl_xor(s[r][h], m, kWave);
-    }
-#pragma unroll
-    for (int r = 0; r < R8; ++r) {
-      const int i = base + r * TB + w * TW + ts;
-      const float f = chan ? sm : __half2float(__ushort_as_half(ksh[r])) * sm;
-      vsc[r] = chan ? 1.f : __half2float(__ushort_as_half(vsh[r]));
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        s[r][h] *= f;
-        if (ok[r] && c == 0) stash[h * S + (i - sl.lo8)] = s[r][h];
-      }
-      unpack_i8x16(vr[r], vf[r]);
-    }
-    fold_batch<G, R8>(st, s, vf, vsc, ok);
-  }
-}
-
-// FP16 ring slots [lo16, hi) on the vector ALU.
-template <int D, int G>
-__device__ __forceinline__ void stream_fp16_valu(const CacheView &cv, const Slice &sl, float sm,
-                                                 const float (&qf)[G][16], Stream<G> &st,
-                                                 float *stash, int S) {
-  constexpr int LPT = D / 16, TW = kWave / LPT, TB = kAttWaves * TW, R16 = 2;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c = lane % LPT, ts = lane / LPT;
-  const __half *K16 = cv.k16 + (size_t)sl.u * cv.cap16 * D;
-  const __half *V16 = cv.v16 + (size_t)sl.u * cv.cap16 * D;
-  for (int base = sl.lo16; base < sl.hi16; base += TB * R16) {
-    int4 kr[R16][2], vr[R16][2];
-    float vsc[R16];
-    bool ok[R16];
-#pragma unroll
-    for (int r = 0; r < R16; ++r) {
-      const int i = base + r * TB + w * TW + ts;
-      ok[r] = i < sl.hi16;
-      vsc[r] = 1.f;
-      const int ic = ok[r] ? i : sl.hi16 - 1;
-      const size_t off = (size_t)ring_row(sl.h16, ic - sl.n8, cv.cap16) * D + c * 16;
-      const int4 *pk = (const int4 *)(K16 + off), *pv = (const int4 *)(V16 + off);
-      kr[r][0] = pk[0]; kr[r][1] = pk[1];
-      vr[r][0] = pv[0]; vr[r][1] = pv[1];
-    }
-    float s[R16][G], vf[R16][16];
-#pragma unroll
-    for (int r = 0; r < R16; ++r) {
-      float kf[16];
-      unpack_h16x16(kr[r][0], kr[r][1], kf);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float acc = 0.f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc = fmaf(qf[h][e], kf[e], acc);
-        s[r][h] = acc;
-      }
-    }
-#pragma unroll
-    for (int m = 1; m < LPT; m <<= 1) {
-#pragma unroll
-      for (int r = 0; r < R16; ++r)
-#pragma unroll
-        for (int h = 0; h < G; ++h) s[r][h] += __shfl_xor(s[r][h], m, kWave);
-    }
-#pragma unroll
-    for (int r = 0; r < R16; ++r) {
-      const int i = base + r * TB + w * TW + ts;
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        s[r][h] *= sm;
-        if (ok[r] && c == 0) stash[h * S + sl.cnt8 + (i - sl.lo16)] = s[r][h];
-      }
-      unpack_h16x16(vr[r][0], vr[r][1], vf[r]);
-    }
-    fold_batch<G, R16>(st, s, vf, vsc, ok);
-  }
-}
-
-// Merge the slot lane-groups of a wavefront and store the wavefront's partial
-// (m, l, o[G][D]) as entry `pidx` of the workgroup's LDS partial arrays.
-template <int D, int G>
-__device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, float *wm, float *wl,
-                                                     float *wo_p) {
-  constexpr int LPT = D / 16;
-  const int lane = threadIdx.x & 63;
-  const int c = lane % LPT, ts = lane / LPT;
-  const float NEG = -INFINITY;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float mw = wave_max(st.m[h]);
-    const float f = (st.m[h] == NEG) ? 0.f : __expf(st.m[h] - mw);
-    float l = st.l[h] * f;
-#pragma unroll
-    for (int m = LPT; m < kWave; m <<= 1) l += __shfl_xor(l, m, kWave);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      float t = st.acc[h][e] * f;
-#pragma unroll
-      for (int m = LPT; m < kWave; m <<= 1) t += __shfl_xor(t, m, kWave);
-      st.acc[h][e] = t;
-    }
-    if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
-    if (ts == 0) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) wo_p[h * D + c * 16 + e] = st.acc[h][e];
-    }
-  }
-}
-
 // max / sum over the 16 lanes of a DPP row; every lane of the row gets the result
 #define CONFKV_DPP(v, ctrl) \
   __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
@@ -517,6 +292,24 @@ __device__ __forceinline__ float group_sum(float v, int gs) {
   if (gs >= 64) v += __shfl_xor(v, 32, kWave);
   return v;
 }
+// Sum over the lanes of a wavefront that agree modulo LPT (4 or 8): rotations inside a row of 16,
+// then swaps of whole rows.
+__device__ __forceinline__ float swap_sum16(float v) {
+  const unsigned w = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  return __uint_as_float((unsigned)r[0]) + __uint_as_float((unsigned)r[1]);
+}
+__device__ __forceinline__ float swap_sum32(float v) {
+  const unsigned w = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float((unsigned)r[0]) + __uint_as_float((unsigned)r[1]);
+}
+template <int LPT>
+__device__ __forceinline__ float stride_sum(float v) {
+  if (LPT <= 4) v += CONFKV_DPP(v, 0x124);    // row_ror:4
+  v += CONFKV_DPP(v, 0x128);                  // row_ror:8
+  return swap_sum32(swap_sum16(v));
+}
 #undef CONFKV_DPP
 #define CONFKV_DPP(v, ctrl)                                                                                   \
   __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),                         \
@@ -531,6 +324,233 @@ __device__ __forceinline__ double group_sum(double v, int gs) {
   return v;
 }
 #undef CONFKV_DPP
+
+// ---------------------------------------------------------------------------------------
+// Vector-ALU streaming body
+// ---------------------------------------------------------------------------------------
+
+// Running softmax state of one slot lane-group: per head the maximum so far, the
+// normaliser and this lane's 16 channels of the un-normalised output.
+template <int G>
+struct Stream {
+  float m[G], l[G], acc[G][16];
+  __device__ __forceinline__ void reset() {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      m[h] = -INFINITY;
+      l[h] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[h][e] = 0.f;
+    }
+  }
+};
+
+// Fold a batch of R slots into the running state.  s[r][h] are the slots' scores,
+// value(r, vf) unpacks the value channels of slot r owned by this lane, vsc[r] is the value
+// scale, ok[r] validity.
+template <int G, int R, typename Value>
+__device__ __forceinline__ void fold_batch(Stream<G> &st, const float (&s)[R][G], Value value,
+                                           const float (&vsc)[R], const bool (&ok)[R]) {
+  const float NEG = -INFINITY;
+  float p[R][G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    float bm = NEG;
+#pragma unroll
+    for (int r = 0; r < R; ++r) bm = ok[r] ? fmaxf(bm, s[r][h]) : bm;
+    const float mn = fmaxf(st.m[h], bm);
+    const float corr = (mn == NEG) ? 1.f : __expf(st.m[h] - mn);
+    st.m[h] = mn;
+    float lsum = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      p[r][h] = ok[r] ? __expf(s[r][h] - mn) : 0.f;
+      lsum += p[r][h];
+      p[r][h] *= vsc[r];
+    }
+    st.l[h] = fmaf(st.l[h], corr, lsum);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) st.acc[h][e] *= corr;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    float vf[16];
+    value(r, vf);
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) st.acc[h][e] = fmaf(p[r][h], vf[e], st.acc[h][e]);
+  }
+}
+
+template <int D, int G>
+__device__ __forceinline__ void load_q_slices(const CacheView &cv, const AttendLaunch &a,
+                                              const Slice &sl, float (&qf)[G][16]) {
+  constexpr int LPT = D / 16;
+  const int c = (threadIdx.x & 63) % LPT;
+  const int Hq = cv.Hkv * G;
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const int4 *qp = (const int4 *)(a.q + ((size_t)(sl.b * Hq + sl.g * G + h)) * D + c * 16);
+    unpack_h16x16(qp[0], qp[1], qf[h]);
+  }
+}
+
+// INT8 slots [lo, hi8) on the vector ALU.
+template <int D, int G>
+__device__ __forceinline__ void stream_int8_valu(const CacheView &cv, const Slice &sl, float sm,
+                                                 const float (&qf)[G][16], Stream<G> &st,
+                                                 float *stash, int S) {
+  constexpr int LPT = D / 16, TW = kWave / LPT, TB = kAttWaves * TW, R8 = 4;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = lane % LPT, ts = lane / LPT;
+  const int8_t *K8 = cv.k8 + (size_t)sl.u * cv.cap8 * D;
+  const int8_t *V8 = cv.v8 + (size_t)sl.u * cv.cap8 * D;
+  // per-channel scales: the caller folded the K scales into qf and applies the V scales to the
+  // accumulator afterwards; every slot then has the factors (sm, 1).  The per-token loads stay
+  // branch-free on element 0 of the unit's scale plane.
+  const bool chan = cv.chan != 0;
+  const __half *KS = cv.ks + (size_t)sl.u * (chan ? D : cv.cap8);
+  const __half *VS = cv.vs + (size_t)sl.u * (chan ? D : cv.cap8);
+  if (sl.lo8 >= sl.hi8) return;
+  int4 kr[R8], vr[R8];
+  unsigned short ksh[R8], vsh[R8];
+  // branch-free loads (rows past the slice re-read its last row and are masked below); a trip's
+  // keys are requested as soon as the previous trip's have become scores, its values behind
+  // the previous trip's sums
+  auto row_of = [&](int base, int r) { return ring_row_u(sl.h8, min(base + r * TB + w * TW + ts, sl.hi8 - 1), cv.cap8); };
+  auto load_k = [&](int base) {
+#pragma unroll
+    for (int r = 0; r < R8; ++r) {
+      const int ic = row_of(base, r);
+      kr[r] = *(const int4 *)(K8 + (size_t)ic * D + c * 16);
+      ksh[r] = ((const unsigned short *)KS)[chan ? 0 : ic];
+    }
+  };
+  auto load_v = [&](int base) {
+#pragma unroll
+    for (int r = 0; r < R8; ++r) {
+      const int ic = row_of(base, r);
+      vr[r] = *(const int4 *)(V8 + (size_t)ic * D + c * 16);
+      vsh[r] = ((const unsigned short *)VS)[chan ? 0 : ic];
+    }
+  };
+  load_k(sl.lo8);
+  load_v(sl.lo8);
+  for (int base = sl.lo8; base < sl.hi8; base += TB * R8) {
+    float s[R8][G], vsc[R8];
+    bool ok[R8];
+#pragma unroll
+    for (int r = 0; r < R8; ++r) {
+      float kf[16];
+      unpack_i8x16(kr[r], kf);
+      const float f = chan ? sm : __half2float(__ushort_as_half(ksh[r])) * sm;
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc = fmaf(qf[h][e], kf[e], acc);
+        s[r][h] = group_sum(acc, LPT) * f;
+      }
+    }
+    const bool more = base + TB * R8 < sl.hi8;
+    if (more) load_k(base + TB * R8);
+#pragma unroll
+    for (int r = 0; r < R8; ++r) {
+      const int i = base + r * TB + w * TW + ts;
+      ok[r] = i < sl.hi8;
+      vsc[r] = chan ? 1.f : __half2float(__ushort_as_half(vsh[r]));
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+        if (ok[r] && c == 0) stash[h * S + (i - sl.lo8)] = s[r][h];
+    }
+    fold_batch<G, R8>(st, s, [&](int r, float (&vf)[16]) { unpack_i8x16(vr[r], vf); }, vsc, ok);
+    if (more) load_v(base + TB * R8);
+  }
+}
+
+// FP16 ring slots [lo16, hi) on the vector ALU.
+// The new token (slot n - 1) is taken from the call's arguments, not read back from the ring.  A
+// trip covers four slots per lane-group of a single head (two where a group of heads fills the
+// registers): with two and nothing requested ahead, the 12 workgroups of a 512-slot layer of 12
+// 64-channel heads spent GPT_OLD us, most of it waiting for the next trip.
+template <int D, int G>
+__device__ __forceinline__ void stream_fp16_valu(const CacheView &cv, const AttendLaunch &a, const Slice &sl, float sm,
+                                                 const float (&qf)[G][16], Stream<G> &st,
+                                                 float *stash, int S) {
+  constexpr int LPT = D / 16, TW = kWave / LPT, TB = kAttWaves * TW, R16 = G == 1 ? 4 : 2;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = lane % LPT, ts = lane / LPT;
+  const __half *K16 = cv.k16 + (size_t)sl.u * cv.cap16 * D + c * 16;
+  const __half *V16 = cv.v16 + (size_t)sl.u * cv.cap16 * D + c * 16;
+  const size_t call_row = ((size_t)sl.b * cv.Hkv + sl.g) * D + c * 16;
+  if (sl.lo16 >= sl.hi16) return;
+  int4 kr[R16][2], vr[R16][2];
+  auto load = [&](int base, const __half *ring, const __half *call, int4 (&x)[R16][2]) {
+#pragma unroll
+    for (int r = 0; r < R16; ++r) {
+      const int i = min(base + r * TB + w * TW + ts, sl.hi16 - 1);
+      const int4 *p = (const int4 *)(i == sl.n - 1 ? call + call_row : ring + (size_t)ring_row(sl.h16, i - sl.n8, cv.cap16) * D);
+      x[r][0] = p[0];
+      x[r][1] = p[1];
+    }
+  };
+  load(sl.lo16, K16, a.knew, kr);
+  load(sl.lo16, V16, a.vnew, vr);
+  for (int base = sl.lo16; base < sl.hi16; base += TB * R16) {
+    float s[R16][G], vsc[R16];
+    bool ok[R16];
+#pragma unroll
+    for (int r = 0; r < R16; ++r) {
+      float kf[16];
+      unpack_h16x16(kr[r][0], kr[r][1], kf);
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc = fmaf(qf[h][e], kf[e], acc);
+        s[r][h] = group_sum(acc, LPT) * sm;
+      }
+    }
+    const bool more = base + TB * R16 < sl.hi16;
+    if (more) load(base + TB * R16, K16, a.knew, kr);
+#pragma unroll
+    for (int r = 0; r < R16; ++r) {
+      const int i = base + r * TB + w * TW + ts;
+      ok[r] = i < sl.hi16;
+      vsc[r] = 1.f;
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+        if (ok[r] && c == 0) stash[h * S + sl.cnt8 + (i - sl.lo16)] = s[r][h];
+    }
+    fold_batch<G, R16>(st, s, [&](int r, float (&vf)[16]) { unpack_h16x16(vr[r][0], vr[r][1], vf); }, vsc, ok);
+    if (more) load(base + TB * R16, V16, a.vnew, vr);
+  }
+}
+
+// Merge the slot lane-groups of a wavefront and store the wavefront's partial
+// (m, l, o[G][D]) as entry `pidx` of the workgroup's LDS partial arrays.
+template <int D, int G>
+__device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, float *wm, float *wl,
+                                                     float *wo_p) {
+  constexpr int LPT = D / 16;
+  const int lane = threadIdx.x & 63;
+  const int c = lane % LPT, ts = lane / LPT;
+  const float NEG = -INFINITY;
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float mw = wave_max(st.m[h]);
+    const float f = (st.m[h] == NEG) ? 0.f : __expf(st.m[h] - mw);
+    const float l = stride_sum<LPT>(st.l[h] * f);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) st.acc[h][e] = stride_sum<LPT>(st.acc[h][e] * f);
+    if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
+    if (ts == 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) wo_p[h * D + c * 16 + e] = st.acc[h][e];
+    }
+  }
+}
 
 // e^x for x <= 0 (-inf included, which gives 0) to about one ulp: 2^(x log2 e) with the product
 // carried in two floats, so the hardware exponential sees an argument without rounding error.
@@ -858,7 +878,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]: 1 / global normaliser, the same times the row's mass weight
 
   const Slice sl = make_slice(cv, a, ns, S);
-  append_new_token<D>(cv, a, sl, ns);
+  append_new_token<D, false>(cv, a, sl, ns);
 
   Stream<G> st;
   st.reset();
@@ -887,7 +907,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   } else {
     stream_int8_valu<D, G>(cv, sl, a.sm_scale, qf, st, stash, S);
   }
-  stream_fp16_valu<D, G>(cv, sl, a.sm_scale, qf, st, stash, S);
+  stream_fp16_valu<D, G>(cv, a, sl, a.sm_scale, qf, st, stash, S);
   store_stream_partial<D, G>(st, threadIdx.x >> 6, wm, wl, wo + (threadIdx.x >> 6) * G * D);
   __syncthreads();
   attend_epilogue<D, G, NP, G * D, kSpill ? 1 : 0>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv);
