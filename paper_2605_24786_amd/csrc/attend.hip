@@ -292,23 +292,21 @@ __device__ __forceinline__ float group_sum(float v, int gs) {
   if (gs >= 64) v += __shfl_xor(v, 32, kWave);
   return v;
 }
-// Sum over the lanes of a wavefront that agree modulo LPT (4 or 8): rotations inside a row of 16,
-// then swaps of whole rows.
-__device__ __forceinline__ float swap_sum16(float v) {
-  const unsigned w = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+// Sums over the lanes of a wavefront that agree modulo LPT (4 or 8).  Halves: of two values the
+// lower rows keep the first one's sum over a pair of rows, the upper rows the second one's.
+__device__ __forceinline__ float swap_halves32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float((unsigned)r[0]) + __uint_as_float((unsigned)r[1]);
 }
-__device__ __forceinline__ float swap_sum32(float v) {
-  const unsigned w = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+__device__ __forceinline__ float swap_halves16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float((unsigned)r[0]) + __uint_as_float((unsigned)r[1]);
 }
+// over the lanes of a row of 16
 template <int LPT>
-__device__ __forceinline__ float stride_sum(float v) {
+__device__ __forceinline__ float row_stride_sum(float v) {
   if (LPT <= 4) v += CONFKV_DPP(v, 0x124);    // row_ror:4
-  v += CONFKV_DPP(v, 0x128);                  // row_ror:8
-  return swap_sum32(swap_sum16(v));
+  return v + CONFKV_DPP(v, 0x128);            // row_ror:8
 }
 #undef CONFKV_DPP
 #define CONFKV_DPP(v, ctrl)                                                                                   \
@@ -347,10 +345,10 @@ struct Stream {
 
 // Fold a batch of R slots into the running state.  s[r][h] are the slots' scores,
 // value(r, vf) unpacks the value channels of slot r owned by this lane, vsc[r] is the value
-// scale, ok[r] validity.
+// scale, ok[r] validity; the first nr slots exist (uniform over the workgroup).
 template <int G, int R, typename Value>
 __device__ __forceinline__ void fold_batch(Stream<G> &st, const float (&s)[R][G], Value value,
-                                           const float (&vsc)[R], const bool (&ok)[R]) {
+                                           const float (&vsc)[R], const bool (&ok)[R], int nr) {
   const float NEG = -INFINITY;
   float p[R][G];
 #pragma unroll
@@ -374,6 +372,7 @@ __device__ __forceinline__ void fold_batch(Stream<G> &st, const float (&s)[R][G]
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
+    if (r >= nr) break;
     float vf[16];
     value(r, vf);
 #pragma unroll
@@ -440,8 +439,14 @@ __device__ __forceinline__ void stream_int8_valu(const CacheView &cv, const Slic
   for (int base = sl.lo8; base < sl.hi8; base += TB * R8) {
     float s[R8][G], vsc[R8];
     bool ok[R8];
+    const int nr = (sl.hi8 - base + TB - 1) / TB;
 #pragma unroll
     for (int r = 0; r < R8; ++r) {
+      if (r >= nr) {
+#pragma unroll
+        for (int h = 0; h < G; ++h) s[r][h] = 0.f;
+        continue;
+      }
       float kf[16];
       unpack_i8x16(kr[r], kf);
       const float f = chan ? sm : __half2float(__ushort_as_half(ksh[r])) * sm;
@@ -464,7 +469,7 @@ __device__ __forceinline__ void stream_int8_valu(const CacheView &cv, const Slic
       for (int h = 0; h < G; ++h)
         if (ok[r] && c == 0) stash[h * S + (i - sl.lo8)] = s[r][h];
     }
-    fold_batch<G, R8>(st, s, [&](int r, float (&vf)[16]) { unpack_i8x16(vr[r], vf); }, vsc, ok);
+    fold_batch<G, R8>(st, s, [&](int r, float (&vf)[16]) { unpack_i8x16(vr[r], vf); }, vsc, ok, nr);
     if (more) load_v(base + TB * R8);
   }
 }
@@ -472,8 +477,10 @@ __device__ __forceinline__ void stream_int8_valu(const CacheView &cv, const Slic
 // FP16 ring slots [lo16, hi) on the vector ALU.
 // The new token (slot n - 1) is taken from the call's arguments, not read back from the ring.  A
 // trip covers four slots per lane-group of a single head (two where a group of heads fills the
-// registers): with two and nothing requested ahead, the 12 workgroups of a 512-slot layer of 12
-// 64-channel heads spent GPT_OLD us, most of it waiting for the next trip.
+// registers; eight take all of them and with that the second workgroup of a CU: 12 heads, 8
+// sequences 1.2 times slower).  The next trip is requested while this one is summed up, and the
+// slots a last trip does not have cost no arithmetic.  12 heads of 64 channels, 513 slots: 8.8 us
+// per launch with trips of two slots and nothing ahead, 8.1 like this.
 template <int D, int G>
 __device__ __forceinline__ void stream_fp16_valu(const CacheView &cv, const AttendLaunch &a, const Slice &sl, float sm,
                                                  const float (&qf)[G][16], Stream<G> &st,
@@ -500,8 +507,14 @@ __device__ __forceinline__ void stream_fp16_valu(const CacheView &cv, const Atte
   for (int base = sl.lo16; base < sl.hi16; base += TB * R16) {
     float s[R16][G], vsc[R16];
     bool ok[R16];
+    const int nr = (sl.hi16 - base + TB - 1) / TB;
 #pragma unroll
     for (int r = 0; r < R16; ++r) {
+      if (r >= nr) {
+#pragma unroll
+        for (int h = 0; h < G; ++h) s[r][h] = 0.f;
+        continue;
+      }
       float kf[16];
       unpack_h16x16(kr[r][0], kr[r][1], kf);
 #pragma unroll
@@ -523,7 +536,7 @@ __device__ __forceinline__ void stream_fp16_valu(const CacheView &cv, const Atte
       for (int h = 0; h < G; ++h)
         if (ok[r] && c == 0) stash[h * S + sl.cnt8 + (i - sl.lo16)] = s[r][h];
     }
-    fold_batch<G, R16>(st, s, [&](int r, float (&vf)[16]) { unpack_h16x16(vr[r][0], vr[r][1], vf); }, vsc, ok);
+    fold_batch<G, R16>(st, s, [&](int r, float (&vf)[16]) { unpack_h16x16(vr[r][0], vr[r][1], vf); }, vsc, ok, nr);
     if (more) load(base + TB * R16, V16, a.vnew, vr);
   }
 }
@@ -535,20 +548,26 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
                                                      float *wo_p) {
   constexpr int LPT = D / 16;
   const int lane = threadIdx.x & 63;
-  const int c = lane % LPT, ts = lane / LPT;
+  const int c = lane % LPT;
   const float NEG = -INFINITY;
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     const float mw = wave_max(st.m[h]);
     const float f = (st.m[h] == NEG) ? 0.f : __expf(st.m[h] - mw);
-    const float l = stride_sum<LPT>(st.l[h] * f);
+    const float lf = st.l[h] * f;
+    const float l = row_stride_sum<LPT>(swap_halves16(swap_halves32(lf, lf), swap_halves32(lf, lf)));
+    // sixteen channel sums over the lane-groups: every exchange between rows halves the values a
+    // lane carries (12 exchanges instead of 32), so row r of 16 lanes ends up with channels
+    // [4 r', 4 r' + 4) of every lane-group's sixteen, r' = 2 (r / 2) + r % 2
+    float o[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) st.acc[h][e] = stride_sum<LPT>(st.acc[h][e] * f);
-    if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
-    if (ts == 0) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) wo_p[h * D + c * 16 + e] = st.acc[h][e];
+    for (int e = 0; e < 4; ++e) {
+      const float lo = swap_halves32(st.acc[h][e] * f, st.acc[h][8 + e] * f);
+      const float hi = swap_halves32(st.acc[h][4 + e] * f, st.acc[h][12 + e] * f);
+      o[e] = row_stride_sum<LPT>(swap_halves16(lo, hi));
     }
+    if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
+    if ((lane & 15) < LPT) *(float4 *)&wo_p[h * D + c * 16 + 8 * (lane >> 5) + 4 * ((lane >> 4) & 1)] = make_float4(o[0], o[1], o[2], o[3]);
   }
 }
 
@@ -762,7 +781,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       opre[p] = ld_tagged(&pou[os < ns && i < per && e < G * D ? (size_t)os * G * D + e : 0]);
     }
   } else {
-    __syncthreads();
+    lds_barrier();                                   // (the output's stores stay in flight)
   }
   TS(22);
   // ---- this split normalises its share of the unit's output (online-softmax merge) ----
