@@ -1006,10 +1006,43 @@ void rank_select_reg_kernel(CacheView cv, LayerMask appended,
 // ---------------------------------------------------------------------------------------
 constexpr int kSmallE = 4;
 
+// The end of the small ranking kernels: the survivors' sources and the selection from the e <= kSmallE
+// evicted slots ev (unused entries INT_MAX), known to all of the unit's T threads.
+template <int T>
+__device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t *sel, int32_t *__restrict__ src_all, int n,
+                                             int n8, int nx, int e, int (&ev)[kSmallE], int tid) {
+  // evicted slots in slot order
+#pragma unroll
+  for (int x = 1; x < kSmallE; ++x)
+#pragma unroll
+    for (int y = x; y > 0; --y)
+      if (ev[y] < ev[y - 1]) { const int t = ev[y]; ev[y] = ev[y - 1]; ev[y - 1] = t; }
+  const int n_new = n - e;
+  int gone8 = 0, last8 = -1;
+#pragma unroll
+  for (int q = 0; q < kSmallE; ++q) {
+    if (ev[q] < n8) ++gone8;
+    if (ev[q] < nx) last8 = ev[q];                   // unused entries are INT_MAX
+  }
+  // the compaction only looks up the source of the slots that move
+  const ShiftPlan sp = shift_plan(cv, n_new, n8, n8 - gone8, ev[0], e, last8);
+  int32_t *src = src_all + (size_t)u * cv.cap;
+  for (int j = sp.lo + tid; j < sp.hi; j += T) {
+    int sidx = j;
+#pragma unroll
+    for (int q = 0; q < kSmallE; ++q) sidx += (ev[q] <= sidx);   // unused entries are INT_MAX
+    src[j] = sidx;
+  }
+  if (tid == 0) {
+    write_selection(cv, u, sel, n_new, n8, n8 - gone8, ev[0], e, last8);
+    cv.unit_evicted[u] += (unsigned)e;
+  }
+}
+
 // kShared: the importance is the float64 sum over the kv-heads of the (layer, sequence), which
 // shared_mass_kernel left in shared_all (indexed by slot, not by ring row).
 // kBatch: loads a lane has in flight at a time (8 keeps the registers few enough for thousands of
-// units per launch; 32 covers a 2048-slot unit in one round trip per pass when there are few units).
+// units per launch; 32 covers a 2048-slot unit in one round trip per pass where there are fewer).
 template <bool kShared, int kBatch = 8, bool kRandom = false>
 __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, LayerMask appended,
                                                                 double alpha,
@@ -1122,32 +1155,153 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, La
       prev_idx = best_idx;
     }
   }
-  // evicted slots in slot order
-#pragma unroll
-  for (int x = 1; x < kSmallE; ++x)
-#pragma unroll
-    for (int y = x; y > 0; --y)
-      if (ev[y] < ev[y - 1]) { const int t = ev[y]; ev[y] = ev[y - 1]; ev[y - 1] = t; }
-  const int n_new = n - e;
-  int gone8 = 0, last8 = -1;
-#pragma unroll
-  for (int q = 0; q < kSmallE; ++q) {
-    if (ev[q] < n8) ++gone8;
-    if (ev[q] < nx) last8 = ev[q];                   // unused entries are INT_MAX
+  finish_small<kWave>(cv, u, sel, src_all, n, n8, nx, e, ev, lane);
+}
+
+// The same with a workgroup per unit, for up to 1024 units (kSmallWgUnits): the four wavefronts share the unit's
+// slots, and each keeps the importance, position and score of its first kRegs slots per lane in
+// registers (4096 slots per unit), so a unit of that length costs one memory round trip instead of
+// one per pass and batch.  From some thousand units on the chip is full with one wavefront per unit
+// and the barriers cost more than the passes: 256 units of 16 002 slots 40 -> 12.8 us per launch, 512
+// units of 2049 slots 9.7 -> 8.4, 144 units of 513 slots 9.9 -> 6.9; 2048 units of 1025 to 2049
+// slots 13 -> 19 us, 1280 units of 1778 slots 12.9 -> 14.7 (layer scope).
+constexpr int kSmallWgUnits = 1024;
+template <bool kShared, bool kRandom = false>
+__global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv, LayerMask appended, double alpha,
+                                                                   const double *__restrict__ shared_all,
+                                                                   int32_t *__restrict__ src_all,
+                                                                   int32_t *__restrict__ sel_all, RandomRank rr) {
+  constexpr int kRegs = 16, kWaves = kEvThreads / kWave;
+  typedef typename std::conditional<kShared, double, float>::type Imp;   // importance as stored
+  __shared__ Imp s_lo[kWaves], s_hi[kWaves];
+  __shared__ unsigned long long s_key[2][kWaves];
+  __shared__ int s_idx[2][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int u = blockIdx.x;
+  asm volatile("" ::"s"(cv.len), "s"(cv.n8), "s"(cv.head8), "s"(cv.budget), "s"(cv.ema), "s"(cv.pos), "s"(cv.B),
+               "s"(cv.Hkv), "s"(cv.P), "s"(cv.cap), "s"(cv.cap8), "s"(sel_all), "s"(src_all));
+  const int UPL = cv.B * cv.Hkv;
+  const int layer = u / UPL, b = (u % UPL) / cv.Hkv;
+  int32_t *sel = sel_all + (size_t)u * kSelInts;
+  const int app = appended.get(layer);
+  const UnitWords uw = load_unit_words(cv, sel, u, layer, b);
+  const int n = uw.len + app;
+  const int n8 = uw.n8;
+  const int ncand = n - min(cv.P, n);
+  const int e = min(n - uw.budget, ncand);
+  if (n <= uw.budget || e <= 0) {
+    if (tid == 0) write_selection(cv, u, sel, n, n8, n8, n, 0, -1);
+    return;
   }
-  // the compaction only looks up the source of the slots that move
-  const ShiftPlan sp = shift_plan(cv, n_new, n8, n8 - gone8, ev[0], e, last8);
-  int32_t *src = src_all + (size_t)u * cv.cap;
-  for (int j = sp.lo + lane; j < sp.hi; j += kWave) {
-    int sidx = j;
+  if (e > kSmallE) {
+    if (tid == 0) sel[7] = 0;                        // left to the general kernel
+    return;
+  }
+  const float *ema = cv.ema + (size_t)u * cv.cap;
+  const int32_t *pos = cv.pos + (size_t)u * cv.cap;
+  const double *shared = kShared ? shared_all + (size_t)(u / cv.Hkv) * cv.cap : nullptr;
+  const int hm = uw.head, cap = cv.cap;
+  const int nx = cv.cap8 == 0 ? n : n8;
+  auto load = [&](int base, Imp (&a)[kRegs], int (&ps)[kRegs]) {
 #pragma unroll
-    for (int q = 0; q < kSmallE; ++q) sidx += (ev[q] <= sidx);   // unused entries are INT_MAX
-    src[j] = sidx;
+    for (int r = 0; r < kRegs; ++r) {
+      const int slot = min(base + r * kEvThreads + tid, ncand - 1);
+      const int i = ring_row_u(hm, slot, cap);
+      if constexpr (kShared) a[r] = shared[slot];
+      else a[r] = ema[i];
+      ps[r] = pos[i];
+    }
+  };
+  Imp a0[kRegs];
+  int ps0[kRegs];
+  const int pos_first = pos[hm], pos_last = pos[ring_row_u(hm, ncand - 1, cap)];   // slots are position-sorted
+  load(0, a0, ps0);
+  Imp lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < kRegs; ++r) {
+    lo = a0[r] < lo ? a0[r] : lo;                    // (no NaN in an importance: plain compares)
+    hi = a0[r] > hi ? a0[r] : hi;
   }
-  if (lane == 0) {
-    write_selection(cv, u, sel, n_new, n8, n8 - gone8, ev[0], e, last8);
-    cv.unit_evicted[u] += (unsigned)e;
+  for (int base = kRegs * kEvThreads; base < ncand; base += kRegs * kEvThreads) {
+    Imp a[kRegs];
+    int ps[kRegs];
+    load(base, a, ps);
+#pragma unroll
+    for (int r = 0; r < kRegs; ++r) {
+      lo = a[r] < lo ? a[r] : lo;
+      hi = a[r] > hi ? a[r] : hi;
+    }
   }
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  if (lane == 0) { s_lo[w] = lo; s_hi[w] = hi; }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    lo = s_lo[k] < lo ? s_lo[k] : lo;
+    hi = s_hi[k] > hi ? s_hi[k] : hi;
+  }
+  const double a_lo = (double)lo, p_lo = (double)pos_first;
+  const double a_rng = __dsub_rn((double)hi, a_lo), p_rng = __dsub_rn((double)pos_last, p_lo);
+  const double oma = __dsub_rn(1.0, alpha);
+  const Divisor a_div = make_divisor(a_rng == 0.0 ? 1.0 : a_rng), p_div = make_divisor(p_rng == 0.0 ? 1.0 : p_rng);
+  auto key_of = [&](Imp a, int ps) -> unsigned long long {
+    if (kRandom) return random_key(rr, random_unit_key(cv, rr, u), ps);
+    const double ah = (a_rng == 0.0) ? 0.0 : quotient(__dsub_rn((double)a, a_lo), a_div);
+    const double rh = (p_rng == 0.0) ? 0.0 : quotient(__dsub_rn((double)ps, p_lo), p_div);
+    return (unsigned long long)__double_as_longlong(__dadd_rn(__dmul_rn(alpha, ah), __dmul_rn(oma, rh)));
+  };
+  unsigned long long key0[kRegs];
+#pragma unroll
+  for (int r = 0; r < kRegs; ++r) key0[r] = key_of(a0[r], ps0[r]);
+
+  int ev[kSmallE];
+  unsigned long long prev_key = 0ull;
+  int prev_idx = -1;                                 // every (key, slot) pair is above (0, -1)
+#pragma unroll
+  for (int p = 0; p < kSmallE; ++p) {
+    ev[p] = 0x7fffffff;
+    if (p < e) {                                     // uniform over the workgroup
+      unsigned long long best_key = ~0ull;
+      int best_idx = 0x7fffffff;
+      auto take = [&](unsigned long long key, int i) {
+        const bool above = key > prev_key || (key == prev_key && i > prev_idx);
+        if (i < ncand && above && key < best_key) {  // slots rise within a thread: first one wins a tie
+          best_key = key;
+          best_idx = i;
+        }
+      };
+#pragma unroll
+      for (int r = 0; r < kRegs; ++r) take(key0[r], r * kEvThreads + tid);
+      for (int base = kRegs * kEvThreads; base < ncand; base += kRegs * kEvThreads) {
+        Imp a[kRegs];
+        int ps[kRegs];
+        load(base, a, ps);
+#pragma unroll
+        for (int r = 0; r < kRegs; ++r) take(key_of(a[r], ps[r]), base + r * kEvThreads + tid);
+      }
+      auto lower = [&](unsigned long long ok, int oi) {
+        if (ok < best_key || (ok == best_key && oi < best_idx)) {
+          best_key = ok;
+          best_idx = oi;
+        }
+      };
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        const unsigned long long ok = __shfl_xor(best_key, m, kWave);
+        lower(ok, __shfl_xor(best_idx, m, kWave));
+      }
+      // (two buffers: a pass may write while a slower wavefront still reads the previous one's)
+      if (lane == 0) { s_key[p & 1][w] = best_key; s_idx[p & 1][w] = best_idx; }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) lower(s_key[p & 1][k], s_idx[p & 1][k]);
+      ev[p] = best_idx;
+      prev_key = best_key;
+      prev_idx = best_idx;
+    }
+  }
+  finish_small<kEvThreads>(cv, u, sel, src_all, n, n8, nx, e, ev, tid);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1422,7 +1576,10 @@ __global__ __launch_bounds__(kEvThreads) void compact_paged_kernel(CacheView cv,
 // end of its range asks the next call's compaction kernel to clear the tagged words, after
 // which both bases start over at 0.
 // ---------------------------------------------------------------------------------------
-template <int D>
+// kWide: a workgroup per unit, grid (U), for steps that appended several tokens: its wavefronts share
+// the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction and a store (16
+// tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in turn, 18.5 us; 4 tokens 10.5 and 7.3).
+template <int D, bool kWide = false>
 __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
                                                             const int32_t *__restrict__ sel_all, int U,
                                                             LayerMask appended, unsigned attend_launches,
@@ -1441,7 +1598,9 @@ __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
       }
     }
   }
-  const int u = blockIdx.x * (kEvThreads / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int kWaves = kEvThreads / kWave;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int u = kWide ? blockIdx.x : blockIdx.x * kWaves + w;
   if (u >= U) return;
   const int32_t *sel = sel_all + (size_t)u * kSelInts;
   const int n_new = sel[0], n8_new = sel[1], h8 = sel[6];   // slot-anchored ring head after the compaction
@@ -1450,11 +1609,14 @@ __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
   const int n16 = n_new - n8_new;
   const int cnt = (cv.W < 0) ? 0 : max(0, n16 - cv.W);
   const int32_t *tab = cv.pt + (size_t)u * cv.npages;          // paged layout (already edited by the compaction)
-  for (int t = 0; t < cnt; ++t) {
+  // items: row t of the keys, row t of the values; a lone wavefront takes both of a row in one turn
+  for (int item = kWide ? w : 0; item < 2 * cnt; item += kWide ? kWaves : 2) {
+    const int t = item >> 1;
+    const bool keys = !kWide || (item & 1) == 0, values = !kWide || (item & 1) == 1;
     const int row = ring_row(h16, t, cv.cap16);
     const int drow = cv.page_lg ? slot_row(cv, tab, 0, n8_new + t + 1, 0, n8_new + t) : ring_row(h8, n8_new + t, cv.cap8);
     const size_t dst = (size_t)u * cv.cap8 + drow;
-    if (cv.page_lg && lane == 0) {
+    if (cv.page_lg && lane == 0 && keys) {
       // the slot's EMA and position move from the FP16 slots' metadata rows to its INT8 row
       const size_t from = (size_t)u * cv.cap + cv.cap - cv.cap16 + row;
       cv.ema[(size_t)u * cv.cap + drow] = cv.ema[from];
@@ -1462,15 +1624,16 @@ __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
     }
     if constexpr (D == 128) {
       if (cv.chan) {
-        quantize_row_channels<D>(cv.k16 + ((size_t)u * cv.cap16 + row) * D, cv.k8 + dst * D, cv.ks + (size_t)u * D, lane);
-        quantize_row_channels<D>(cv.v16 + ((size_t)u * cv.cap16 + row) * D, cv.v8 + dst * D, cv.vs + (size_t)u * D, lane);
+        if (keys) quantize_row_channels<D>(cv.k16 + ((size_t)u * cv.cap16 + row) * D, cv.k8 + dst * D, cv.ks + (size_t)u * D, lane);
+        if (values) quantize_row_channels<D>(cv.v16 + ((size_t)u * cv.cap16 + row) * D, cv.v8 + dst * D, cv.vs + (size_t)u * D, lane);
         continue;
       }
     }
-    quantize_row_wave<D>(cv.k16 + ((size_t)u * cv.cap16 + row) * D, cv.k8 + dst * D, cv.ks + dst, lane);
-    quantize_row_wave<D>(cv.v16 + ((size_t)u * cv.cap16 + row) * D, cv.v8 + dst * D, cv.vs + dst, lane);
+    if (keys) quantize_row_wave<D>(cv.k16 + ((size_t)u * cv.cap16 + row) * D, cv.k8 + dst * D, cv.ks + dst, lane);
+    if (values) quantize_row_wave<D>(cv.v16 + ((size_t)u * cv.cap16 + row) * D, cv.v8 + dst * D, cv.vs + dst, lane);
   }
-  if (lane == 0) {
+  if constexpr (kWide) __syncthreads();                       // every wavefront has read the unit's counters
+  if (lane == 0 && (!kWide || w == 0)) {
     cv.len[u] = n_new;
     cv.n8[u] = n8_new + cnt;
     cv.head16[u] = ring_row(h16, cnt % cv.cap16, cv.cap16);
@@ -1526,8 +1689,12 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
     // layer-shared importance: the summed mass first, then the same three kernel shapes reading it
     hipLaunchKernelGGL(shared_mass_kernel, dim3(cv.L * cv.B, (cv.cap + kEvThreads - 1) / kEvThreads),
                        dim3(kEvThreads), 0, stream, cv, appended, opt.shared);
-    hipLaunchKernelGGL((rank_small_kernel<true, 8>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended, alpha,
-                       (const double *)opt.shared, src, sel, U, 0, rr);
+    if (U <= kSmallWgUnits)
+      hipLaunchKernelGGL((rank_small_wg_kernel<true>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended, alpha,
+                         (const double *)opt.shared, src, sel, rr);
+    else
+      hipLaunchKernelGGL((rank_small_kernel<true, 8>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended, alpha,
+                         (const double *)opt.shared, src, sel, U, 0, rr);
     if (n_max <= 256 * 20)
       hipLaunchKernelGGL((rank_select_reg_kernel<256, 20, true>), dim3(U), dim3(256), 0, stream, cv, appended,
                          alpha, src, sel, (const double *)opt.shared, rr);
@@ -1539,7 +1706,10 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
                          1, score, src, sel);
   } else if (opt.random) {
     // the random ranker: the same kernel shapes with the drawn key in place of the composite score
-    if (U <= 4096)
+    if (U <= kSmallWgUnits)
+      hipLaunchKernelGGL((rank_small_wg_kernel<false, true>), dim3(U), dim3(kEvThreads), 0, stream, cv,
+                         appended, alpha, (const double *)nullptr, src, sel, rr);
+    else if (U <= 4096)
       hipLaunchKernelGGL((rank_small_kernel<false, 32, true>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv,
                          appended, alpha, (const double *)nullptr, src, sel, U, 0, rr);
     else
@@ -1558,7 +1728,10 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
       hipLaunchKernelGGL(rank_select_kernel<1024>, dim3(U), dim3(1024), 0, stream, cv, appended, alpha, opt,
                          1, score, src, sel);
   } else {
-  if (U <= 4096)    // few wavefronts per SIMD: registers to spare for deeper batches
+  if (U <= kSmallWgUnits)
+    hipLaunchKernelGGL((rank_small_wg_kernel<false>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended,
+                       alpha, (const double *)nullptr, src, sel, rr);
+  else if (U <= 4096)    // few wavefronts per SIMD: registers to spare for deeper batches
     hipLaunchKernelGGL((rank_small_kernel<false, 32>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, U, 0, rr);
   else
@@ -1598,20 +1771,28 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
     return hipGetLastError();
   }
   const dim3 cgrid(U, paired ? 2 : 5);
+  int appended_max = 0;
+  for (int l = 0; l < cv.L; ++l) appended_max = appended.get(l) > appended_max ? appended.get(l) : appended_max;
+  const bool several = appended_max > 1 && cv.W >= 0;         // several rows to quantise per unit
+  const dim3 dgrid(several ? U : (U + 3) / 4);
   if (cv.D == 64) {
     if (after_prompt)
       hipLaunchKernelGGL((compact_kernel<64, false>), cgrid, dim3(kEvThreads), 0, stream, cv, src, sel, paired);
     else
       hipLaunchKernelGGL((compact_kernel<64, true>), cgrid, dim3(kEvThreads), 0, stream, cv, src, sel, paired);
     hipLaunchKernelGGL(demote_kernel<64>, dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, sel, U, appended,
-                       attend_launches, conf_launches);
+                       attend_launches, conf_launches);      // (several tokens per call need D = 128)
   } else {
     if (after_prompt)
       hipLaunchKernelGGL((compact_kernel<128, false>), cgrid, dim3(kEvThreads), 0, stream, cv, src, sel, paired);
     else
       hipLaunchKernelGGL((compact_kernel<128, true>), cgrid, dim3(kEvThreads), 0, stream, cv, src, sel, paired);
-    hipLaunchKernelGGL(demote_kernel<128>, dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, sel, U, appended,
-                       attend_launches, conf_launches);
+    if (several)
+      hipLaunchKernelGGL((demote_kernel<128, true>), dgrid, dim3(kEvThreads), 0, stream, cv, sel, U, appended,
+                         attend_launches, conf_launches);
+    else
+      hipLaunchKernelGGL(demote_kernel<128>, dgrid, dim3(kEvThreads), 0, stream, cv, sel, U, appended,
+                         attend_launches, conf_launches);
   }
   return hipGetLastError();
 }

@@ -489,6 +489,44 @@ def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
     kv.close()
 
 
+@pytest.mark.parametrize("T0,P,evict", [
+    (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
+    (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
+    (260, 3, 2),       # candidates just above one slot per thread
+    (9, 8, 1),         # a single candidate pair
+])
+@pytest.mark.parametrize("scope", ["kv_head", "layer"])
+def test_small_ranking_edges(lib, torch_cuda, T0, P, evict, scope):
+    """A few evictions per unit from few units: the kept sets of the workgroup-per-unit ranking kernel are the
+    oracle's (bit-equal scores from the exported importance)."""
+    torch = torch_cuda
+    H, G, D = 2, 2, 128
+    n = T0 + 1
+    N = n - evict
+    kv = _mk(lib, n_q_heads=G * H, n_kv_heads=H, fp16_window=2, capacity=(T0 + 79) // 64 * 64, protected_window=P,
+             n_tight=[N], n_loose=[N], rank_scope=scope)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T0)
+    K = torch.randn((1, H, T0, D), generator=g, device="cuda", dtype=torch.float16)
+    e0 = torch.rand((1, H, T0), generator=g, device="cuda")
+    e0[:, :, : T0 // 2] = e0[:, :, :1]              # equal importances: recency decides, ties go oldest first
+    kv.load_prefill(0, K, K, e0)
+    q = torch.randn((1, G * H, D), generator=g, device="cuda", dtype=torch.float16)
+    new = torch.randn((1, H, D), generator=g, device="cuda", dtype=torch.float16)
+    kv.attend(0, q, new, new, torch.empty_like(q))
+    ema = [kv.export(0, 0, h, planes=("ema",))["ema"].astype(np.float64) for h in range(H)]
+    kv.evict_compact()
+    for h in range(H):
+        a = (ema[0] + ema[1] if scope == "layer" else ema[h])[: n - P]
+        pos = np.arange(n - P, dtype=np.float64)
+        unit = lambda x: (x - x.min()) / (x.max() - x.min()) if x.max() > x.min() else np.zeros_like(x)
+        al = f32(0.65)
+        gone = np.argsort(al * unit(a) + (1.0 - al) * unit(pos), kind="stable")[:evict]
+        kept = np.setdiff1d(np.arange(n), gone)
+        assert np.array_equal(kv.export(0, 0, h, planes=("pos",))["pos"], kept.astype(np.int32)), f"kv-head {h}"
+    kv.close()
+
+
 def test_observe_two_launch_form(lib, torch_cuda):
     _observe_case(lib, torch_cuda, 4, 2, 1, 1200, 64, 4, ((1190, 4), (1194, 4)), seed=5, two_launch=True)
 
