@@ -233,9 +233,9 @@ __device__ __forceinline__ Slice make_slice(const CacheView &cv, const AttendLau
 }
 
 // The workgroup that owns the tail writes the new token into the FP16 ring.
-// kSync = false: the caller never reads the appended row back in this launch (it takes the new
-// token from the call's arguments), so nothing has to wait for the stores.
-template <int D, bool kSync = true>
+// Nobody reads the appended row back in this launch (the new token is taken from the call's
+// arguments), so nothing waits for the stores.
+template <int D>
 __device__ __forceinline__ void append_new_token(const CacheView &cv, const AttendLaunch &a,
                                                  const Slice &s, int ns) {
   if (s.j != ns - 1 || a.observe_first >= 0) return;
@@ -251,7 +251,6 @@ __device__ __forceinline__ void append_new_token(const CacheView &cv, const Atte
   }
   if (tid < a.tq)
     cv.pos[(size_t)s.u * cv.cap + slot_row(cv, s.tab, s.h8, s.n8, s.h16, s.n - a.tq + tid)] = a.pos_new + tid;
-  if constexpr (kSync) __syncthreads();
 }
 
 // max / sum over the 16 lanes of a DPP row; every lane of the row gets the result
@@ -897,7 +896,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]: 1 / global normaliser, the same times the row's mass weight
 
   const Slice sl = make_slice(cv, a, ns, S);
-  append_new_token<D, false>(cv, a, sl, ns);
+  append_new_token<D>(cv, a, sl, ns);
 
   Stream<G> st;
   st.reset();
@@ -1171,7 +1170,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   // the query loads
   if (w < ntiles) tr = load_tile(w);
   TS(3);
-  append_new_token<DR, false>(cv, a, sl, ns);
+  append_new_token<DR>(cv, a, sl, ns);
   const float NEG = -INFINITY;
   const float sm = a.sm_scale;
   TS(1);

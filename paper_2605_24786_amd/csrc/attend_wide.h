@@ -241,7 +241,7 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
   // ---------------- pass 1: online softmax and output per row ----------------
   TileRegs tr = {};
   if (w < nitems) tr = load_item(w, true);
-  append_new_token<D, false>(cv, a, sl, ns);
+  append_new_token<D>(cv, a, sl, ns);
   _Float16 *Pb = (_Float16 *)(tiles + (size_t)w * kWideTileBytes + kWideKBytes + kVBytes);   // [16][kPRow], this wavefront's own
   for (int i = lane; i < 16 * kPRow / 2; i += kWave) ((unsigned *)Pb)[i] = 0u;
   floatx4_t O[8];
