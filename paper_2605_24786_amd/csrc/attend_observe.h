@@ -43,14 +43,15 @@ __device__ __forceinline__ ObserveUnit observe_unit(const CacheView &cv, int u, 
 }
 
 // Eight codes with their channels' scales as fp16 head + tail: the product has 19 significant
-// bits and its last one is at least 2^-24, so the pair is exact.
+// bits and its last one is at least 2^-24, so the pair is exact.  (A channel that reaches 65504 has
+// the scale 516, and 127 * 516 rounds to infinity: the head stops at 65504, the tail holds the rest.)
 __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scales, half8_t &hi, half8_t &lo) {
   const half8_t c = cvt_i8x8_f16x8(raw.x, raw.y);
   const half8_t s = __builtin_bit_cast(half8_t, *(const int4 *)scales);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float v = (float)c[e] * (float)s[e];
-    const _Float16 h = (_Float16)v;
+    const _Float16 h = (_Float16)fminf(fmaxf(v, -65504.0f), 65504.0f);
     hi[e] = h;
     lo[e] = (_Float16)(v - (float)h);
   }

@@ -489,6 +489,32 @@ def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W", [(2, 40, 0), (4, 200, 33), (1, 97, 8)])
+def test_observe_prompt_saturated_channel(lib, torch_cuda, G, T0, W):
+    """Channels that reach +-65504 under per-channel scales: 127 times their scale is above the largest fp16."""
+    torch = torch_cuda
+    H, D = 2, 128
+    say(f"observe_prompt saturated channel G={G} T0={T0} W={W}")
+    kv = _mk(lib, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode="channel")
+    rng = np.random.default_rng(T0)
+    K = rng.standard_normal((1, H, T0, D)).astype(np.float16)
+    K[..., 5] = 65504.0
+    K[..., 77] = np.where(np.arange(T0) % 3 == 0, -65504.0, 65504.0)
+    q = rng.standard_normal((1, T0, G * H, D)).astype(np.float16)
+    q[..., [5, 77]] = 2.0 ** -15
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    for g in range(H):
+        u = O.load_prefill(K[0, g], K[0, g], W, scale_mode="channel")
+        O.observe_unit(u, q[0, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(0.9))
+        e_ref = u.ema.astype(np.float64)
+        e_got = kv.export(0, 0, g, planes=("ema",))["ema"].astype(np.float64)
+        assert np.all(np.isfinite(e_got)), "importance of a saturated channel's unit is not finite"
+        assert np.all(np.abs(e_got - e_ref) <= 1e-8 + 1e-5 * e_ref)
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
