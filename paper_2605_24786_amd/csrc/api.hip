@@ -140,7 +140,8 @@ ScratchLayout scratch_layout(const conf_kv_config *c) {
   // (the matrix-core body exchanges 128-channel partials whatever the head dimension)
   s.part_o = take(UPL * kAttendMaxSplits * R * std::max<size_t>(D, 128) * 8);
   s.zero_bytes = off;
-  s.spill = take(attend_spill_floats((int)UPL, (int)R, c->capacity) * 4);
+  s.spill = take(std::max(attend_spill_floats((int)UPL, (int)R, c->capacity),
+                          R == kChunkRows ? observe_scratch_floats((int)UPL, (int)G, c->capacity) : 0) * 4);
   s.score = take(U * c->capacity * 8);
   s.src = take(U * c->capacity * 4);
   s.sel = take(U * kSelInts * 4);

@@ -16,9 +16,17 @@ constexpr int kMassThreads = 512, kMassWaves = kMassThreads / kWave, kMassTile =
 constexpr int kObsBlocks = 1;                          // blocks of 16 rows per wavefront of the first kernel
 constexpr int kObsTileBytes = kTile * kKRow16;         // 32 slots as fp16 rows
 
-// Softmax statistics of a prompt query: the reference its exponentials are taken against and
-// 1 / (sum of the exponentials); [unit in layer][head of the group][token, padded to 16].
+// Softmax statistics of a prompt query: 1 / (sum of the exponentials) in 64 bits, then for all
+// rows the reference the exponentials are taken against; both [unit in layer][head of the
+// group][token, padded to 16].
 __host__ __device__ constexpr int observe_stride(int T) { return (T + 15) / 16 * 16; }
+struct ObserveStats {
+  double *inv;
+  float *ref;
+};
+size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
+  return (size_t)units_per_layer * G * observe_stride(cap) * 3;
+}
 
 // Causal work falls along the list of work items, so a workgroup takes two, one from either end:
 // item y and item n - 1 - y (the middle one of an odd list alone).
@@ -66,7 +74,7 @@ __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scal
 // that a score costs one multiply-add, one hardware exponential and one addition.
 template <bool kChan>
 __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
-                                                                    int T, float sm2, float2 *__restrict__ stats) {
+                                                                    int T, float sm2, ObserveStats stats) {
   constexpr int D = 128, kBuf = kObsTileBytes * (kChan ? 2 : 1);
   __shared__ __align__(16) uint8_t tiles[2][kBuf];
   __shared__ float factor[2][kTile];
@@ -230,8 +238,11 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
       const float es = __builtin_amdgcn_exp2f(m[r][i] - M);
       const double L = group_sum((ld[r][i] + (double)l[r][i]) * (double)es, 16);
       const int tok = tok0[r] + 4 * g4 + i;
-      if (live[r] && t16 == 0 && tok < T)
-        stats[((size_t)ul * G + head[r]) * observe_stride(T) + tok] = make_float2(M, (float)recip_pos(L));
+      if (live[r] && t16 == 0 && tok < T) {
+        const size_t row = ((size_t)ul * G + head[r]) * observe_stride(T) + tok;
+        stats.ref[row] = M;
+        stats.inv[row] = recip_pos(L);
+      }
     }
   }
   }
@@ -255,7 +266,7 @@ __device__ __forceinline__ double pow_count(double x, unsigned k) {
 template <bool kChan>
 __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
                                                                    float sm2, double decay, double gain,
-                                                                   const float2 *__restrict__ stats) {
+                                                                   ObserveStats stats) {
   constexpr int D = 128, kSb = kMassTile / 16;
   __shared__ double red[kMassWaves][kMassTile];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -302,18 +313,20 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
     wt[i] = tok < T && tok >= 0 ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) : 0.0;
   }
   half8_t qa[4];
-  float4 st0 = {}, st1 = {};
+  float4 ref = {};
+  double2 inv0 = {}, inv1 = {};
   const int row_step = cv.Hkv * G * D;                  // elements from a token's queries to the next token's
   const __half *q_lane = q + ((size_t)b * T * cv.Hkv + g) * G * D + g4 * 8;
-  const float2 *s_lane = stats + (size_t)ul * G * stride + 4 * g4;
+  const size_t s_lane = (size_t)ul * G * stride + 4 * g4;
   // queries and statistics of (token block, head), requested one step ahead
   auto load = [&](int tb, int h) {
     const __half *row = q_lane + (size_t)min(tb * 16 + t16, T - 1) * row_step + h * D;
 #pragma unroll
     for (int s = 0; s < 4; ++s) qa[s] = __builtin_bit_cast(half8_t, *(const int4 *)(row + 32 * s));
-    const float4 *sp = (const float4 *)(s_lane + h * stride + tb * 16);
-    st0 = sp[0];
-    st1 = sp[1];
+    const size_t at = s_lane + (size_t)h * stride + tb * 16;
+    ref = *(const float4 *)(stats.ref + at);
+    inv0 = *(const double2 *)(stats.inv + at);
+    inv1 = *(const double2 *)(stats.inv + at + 2);
   };
   int tb = ntb - 1 - w;
   if (tb >= tb_first) load(tb, 0);
@@ -326,7 +339,6 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
         wt[i] = tok + 16 * kMassWaves >= T ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) : wt[i] * step;
       }
     }
-    float hs[kSb][4] = {};
     auto heads = [&](auto edge) {
       for (int h = 0; h < G; ++h) {
         floatx4_t acc[kSb];
@@ -342,7 +354,8 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
 #pragma unroll
           for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kb[sb][s], acc[sb], 0, 0, 0);
         }
-        const float M[4] = {st0.x, st0.z, st1.x, st1.z}, inv[4] = {st0.y, st0.w, st1.y, st1.w};
+        const float M[4] = {ref.x, ref.y, ref.z, ref.w};
+        const double wi[4] = {wt[0] * inv0.x, wt[1] * inv0.y, wt[2] * inv1.x, wt[3] * inv1.y};
         if (h + 1 < G) load(tb, h + 1);
         else if (tb - kMassWaves >= tb_first) load(tb - kMassWaves, 0);
 #pragma unroll
@@ -352,17 +365,13 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
             const float e = __builtin_amdgcn_exp2f(fmaf(acc[sb][i], f[sb], -M[i]));
             const int tok = tb * 16 + 4 * g4 + i;
             // (rows past the end have no statistics)
-            if (edge) hs[sb][i] = tok >= T || base + 16 * sb + t16 > tok ? hs[sb][i] : fmaf(e, inv[i], hs[sb][i]);
-            else hs[sb][i] = fmaf(e, inv[i], hs[sb][i]);
+            const double term = (double)e * wi[i];
+            sum[sb] += edge && (tok >= T || base + 16 * sb + t16 > tok) ? 0.0 : term;
           }
       }
     };
     if (tb * 16 < base + kMassTile - 1 || tb == ntb - 1) heads(std::true_type{});
     else heads(std::false_type{});
-#pragma unroll
-    for (int sb = 0; sb < kSb; ++sb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sum[sb] += (double)hs[sb][i] * wt[i];
   }
 #pragma unroll
   for (int sb = 0; sb < kSb; ++sb) {
@@ -379,14 +388,14 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
   }
 }
 
-// dev scratch: UPL * G * observe_stride(T) float2, below the spill area's size (2 * capacity floats per row)
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
   const int pairs = (T + 15) / 16 * cv.G, per = kObsWaves * kObsBlocks;
   const dim3 rows(cv.Hkv, ((pairs + per - 1) / per + 1) / 2, cv.B);
   const dim3 slots(cv.Hkv, (T + kMassTile - 1) / kMassTile + 1, cv.B);
-  float2 *stats = (float2 *)scratch;
+  const size_t n_rows = (size_t)cv.B * cv.Hkv * cv.G * observe_stride(T);
+  const ObserveStats stats = {(double *)scratch, scratch + 2 * n_rows};
   const float sm2 = (float)((double)sm * 1.4426950408889634);          // scores in units of ln 2
   if (cv.chan) {
     hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm2, stats);

@@ -84,7 +84,8 @@ bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,
-// contiguous layout).  scratch: B * Hkv * G * (T rounded up to 16) pairs of floats.
+// contiguous layout).  scratch: observe_scratch_floats(B * Hkv, G, T) floats.
+size_t observe_scratch_floats(int units_per_layer, int G, int cap);
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, hipStream_t stream);
 

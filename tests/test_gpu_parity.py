@@ -515,6 +515,27 @@ def test_observe_prompt_saturated_channel(lib, torch_cuda, G, T0, W):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W,scales", [(1, 257, 8, "token"), (7, 300, 40, "token"), (16, 130, -1, "token"),
+                                           (1, 500, 0, "channel")])
+def test_observe_prompt_sums_in_64_bits(lib, torch_cuda, G, T0, W, scales):
+    """Zero queries under the running sum: slot i receives G / (t + 1) from every token t >= i, whatever is stored.
+    Every factor but 1 / (t + 1) is exact, so with normaliser, heads and tokens summed in 64 bits the importance is
+    the correctly rounded float32 of the sum."""
+    torch = torch_cuda
+    H, D = 2, 128
+    say(f"observe_prompt 64-bit sums G={G} T0={T0} W={W} scales={scales}")
+    kv = _mk(lib, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales, ema_decay=1.0, mass_gain=1.0)
+    K = torch.randn(1, H, T0, D, device="cuda").half()
+    kv.load_prefill(0, K, K)
+    kv.observe_prompt(0, torch.zeros(1, T0, G * H, D, dtype=torch.float16, device="cuda"))
+    want = np.cumsum(G / np.arange(T0, 0, -1, dtype=np.float64))[::-1].astype(np.float32)
+    for g in range(H):
+        got = kv.export(0, 0, g, planes=("ema",))["ema"]
+        assert np.array_equal(got, want), f"{np.count_nonzero(got != want)} of {T0} not correctly rounded"
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
