@@ -70,11 +70,12 @@ __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scal
 // of 32, staged once for all its rows as fp16 in two alternating LDS buffers (one barrier per
 // tile).  Every lane keeps a running
 // reference and sum of its own columns, so no reduction runs inside the loop; the sum goes over
-// to 64 bits every eight tiles.  Scores are in units of ln 2 (the factor of a slot holds log2 e), so
-// that a score costs one multiply-add, one hardware exponential and one addition.
+// to 64 bits every eight tiles.  A score costs a multiply-add, a product with log2 e, one hardware
+// exponential and one addition.  (log2 e folded into the slots' factors would save the product, but
+// rounds the factor once more: an error of the score, and so of a probability, that grows with it.)
 template <bool kChan>
 __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
-                                                                    int T, float sm2, ObserveStats stats) {
+                                                                    int T, float sm, ObserveStats stats) {
   constexpr int D = 128, kBuf = kObsTileBytes * (kChan ? 2 : 1);
   __shared__ __align__(16) uint8_t tiles[2][kBuf];
   __shared__ float factor[2][kTile];
@@ -141,11 +142,11 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
         dst[0] = cvt_i8x8_f16x8((unsigned)r0.x, (unsigned)r0.y);
         dst[1] = cvt_i8x8_f16x8((unsigned)r0.z, (unsigned)r0.w);
       }
-      if (lc == 0) factor[it & 1][lrow] = kChan ? sm2 : __half2float(__ushort_as_half(rs)) * sm2;
+      if (lc == 0) factor[it & 1][lrow] = kChan ? sm : __half2float(__ushort_as_half(rs)) * sm;
     } else {
       dst[0] = __builtin_bit_cast(half8_t, r0);
       dst[1] = __builtin_bit_cast(half8_t, r1);
-      if (lc == 0) factor[it & 1][lrow] = sm2;
+      if (lc == 0) factor[it & 1][lrow] = sm;
     }
   };
 
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float v0 = score(0, i), v1 = score(1, i), mn = fmaxf(m[r][i], fmaxf(v0, v1));
-            const float corr = __builtin_amdgcn_exp2f(m[r][i] - mn);
+            const float corr = __expf(m[r][i] - mn);
             m[r][i] = mn;
             l[r][i] *= corr;
             ld[r][i] *= (double)corr;
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
           }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) l[r][i] += __builtin_amdgcn_exp2f(x[0][i]) + __builtin_amdgcn_exp2f(x[1][i]);
+        for (int i = 0; i < 4; ++i) l[r][i] += __expf(x[0][i]) + __expf(x[1][i]);
       };
       if (base + kTile - 1 > tok0[r] || base + kTile > lim) fold(std::true_type{});
       else fold(std::false_type{});
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float M = row16_max(m[r][i]);
-      const float es = __builtin_amdgcn_exp2f(m[r][i] - M);
+      const float es = exp_nonpos(m[r][i] - M);
       const double L = group_sum((ld[r][i] + (double)l[r][i]) * (double)es, 16);
       const int tok = tok0[r] + 4 * g4 + i;
       if (live[r] && t16 == 0 && tok < T) {
@@ -265,7 +266,7 @@ __device__ __forceinline__ double pow_count(double x, unsigned k) {
 // kv-heads one XCD serves one of them).  // A token's weight gain * lambda^(T-1-t) is a running product in 64 bits, as is the sum.
 template <bool kChan>
 __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
-                                                                   float sm2, double decay, double gain,
+                                                                   float sm, double decay, double gain,
                                                                    ObserveStats stats) {
   constexpr int D = 128, kSb = kMassTile / 16;
   __shared__ double red[kMassWaves][kMassTile];
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
         if constexpr (kChan) scale_codes(c, un.KS + s * 32 + g4 * 8, kb[sb][s], kl[sb][s]);
         else kb[sb][s] = cvt_i8x8_f16x8(c.x, c.y);
       }
-      f[sb] = kChan ? sm2 : __half2float(un.KS[row]) * sm2;
+      f[sb] = kChan ? sm : __half2float(un.KS[row]) * sm;
     } else {
       const __half *src = un.K16 + (size_t)ring_row(un.h16, slot - un.n8, un.cap16) * D + g4 * 8;
 #pragma unroll
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
         kb[sb][s] = __builtin_bit_cast(half8_t, *(const int4 *)(src + 32 * s));
         if constexpr (kChan) kl[sb][s] = half8_t{};
       }
-      f[sb] = sm2;
+      f[sb] = sm;
     }
   }
 
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
         for (int sb = 0; sb < kSb; ++sb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(acc[sb][i], f[sb], -M[i]));
+            const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -M[i]));   // (a reference may lie up to 5 below a score)
             const int tok = tb * 16 + 4 * g4 + i;
             // (rows past the end have no statistics)
             const double term = (double)e * wi[i];
@@ -396,13 +397,12 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
   const dim3 slots(cv.Hkv, (T + kMassTile - 1) / kMassTile + 1, cv.B);
   const size_t n_rows = (size_t)cv.B * cv.Hkv * cv.G * observe_stride(T);
   const ObserveStats stats = {(double *)scratch, scratch + 2 * n_rows};
-  const float sm2 = (float)((double)sm * 1.4426950408889634);          // scores in units of ln 2
   if (cv.chan) {
-    hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm2, stats);
-    hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm2, decay, gain, stats);
+    hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, stats);
+    hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm, decay, gain, stats);
   } else {
-    hipLaunchKernelGGL(observe_stats_kernel<false>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm2, stats);
-    hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm2, decay, gain, stats);
+    hipLaunchKernelGGL(observe_stats_kernel<false>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, stats);
+    hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm, decay, gain, stats);
   }
   return hipGetLastError();
 }

@@ -536,6 +536,32 @@ def test_observe_prompt_sums_in_64_bits(lib, torch_cuda, G, T0, W, scales):
     kv.close()
 
 
+@pytest.mark.parametrize("T0,W,sm", [(200, -1, 0.125), (200, 0, 0.125), (150, 40, 0.25)])
+def test_observe_prompt_wide_scores(lib, torch_cuda, T0, W, sm):
+    """Scores that spread over 75 or 150 units and carry no rounding (one-hot integers, a power of two as softmax
+    scale): a probability is then off by the exponential (1.2e-7) and its row's normaliser, whose terms e^x have an
+    argument rounded to 7e-8 |x|: at most 7e-8 times the entropy, log 200."""
+    torch = torch_cuda
+    H, D = 2, 128
+    say(f"observe_prompt wide scores T0={T0} W={W} sm={sm}")
+    kv = _mk(lib, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, sm_scale=sm)
+    rng = np.random.default_rng(T0)
+    K = np.zeros((1, H, T0, D), np.float16)
+    K[..., 0] = rng.integers(16, 300, (1, H, T0)) * rng.choice([-1, 1], (1, H, T0))
+    q = np.zeros((1, T0, H, D), np.float16)
+    q[..., 0] = 1.0
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    for g in range(H):
+        u = O.load_prefill(K[0, g], K[0, g], W)
+        O.observe_unit(u, q[0, :, g:g + 1], 0, sm, f32(0.9))
+        e_ref = u.ema.astype(np.float64)
+        e_err = np.abs(kv.export(0, 0, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+        assert np.all(e_err <= 1e-36 + 6e-7 * e_ref), f"max rel {np.max(e_err / (e_ref + 1e-36)):.3g}"
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
