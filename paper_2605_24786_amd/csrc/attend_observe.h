@@ -192,28 +192,30 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
       if (!live[r] || base > tok0[r] + 15) continue;    // (uniform) no row of the block sees the tile
       // edge: the diagonal, or a partial tile; a masked score is -inf
       auto fold = [&](auto edge) {
-        auto score = [&](int sb, int i) {
-          const float v = acc[r][sb][i] * f[sb];
+        // the score less a reference, in one rounding here and in the second kernel: what a dominating
+        // slot's score loses must be the same in its probability and in the normaliser
+        auto above = [&](int sb, int i, float ref) {
+          const float v = fmaf(acc[r][sb][i], f[sb], -ref);
           return edge && base + 16 * sb + t16 >= min(lim, tok0[r] + 4 * g4 + i + 1) ? -INFINITY : v;
         };
         float x[2][4], top = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
-          for (int sb = 0; sb < 2; ++sb) x[sb][i] = edge ? score(sb, i) - m[r][i] : fmaf(acc[r][sb][i], f[sb], -m[r][i]);
+          for (int sb = 0; sb < 2; ++sb) x[sb][i] = above(sb, i, m[r][i]);
           top = fmaxf(top, fmaxf(x[0][i], x[1][i]));
         }
         // a lane's reference only has to stay within a few units of its columns' maximum
         if (__builtin_amdgcn_ballot_w64(top > 5.0f)) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float v0 = score(0, i), v1 = score(1, i), mn = fmaxf(m[r][i], fmaxf(v0, v1));
+            const float mn = fmaxf(m[r][i], fmaxf(above(0, i, 0.f), above(1, i, 0.f)));
             const float corr = __expf(m[r][i] - mn);
             m[r][i] = mn;
             l[r][i] *= corr;
             ld[r][i] *= (double)corr;
-            x[0][i] = v0 - mn;
-            x[1][i] = v1 - mn;
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb) x[sb][i] = above(sb, i, mn);
           }
         }
 #pragma unroll

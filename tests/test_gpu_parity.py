@@ -562,6 +562,30 @@ def test_observe_prompt_wide_scores(lib, torch_cuda, T0, W, sm):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W,scales", [(1, 17, 8, "token"), (4, 64, 0, "token"), (2, 150, -1, "token"), (1, 45, 0, "channel")])
+def test_observe_prompt_dominating_slots(lib, torch_cuda, G, T0, W, scales):
+    """Each query of all heads is a large multiple of the token's own key, whose slot then takes the whole
+    probability: what its score (some 100 units) loses to rounding has to be the same in its exponential and in the
+    normaliser.  lambda = 0.5, so a slot keeps its own query's mass: G * 0.5^(T - t), to 1.2e-7 (two exponentials of
+    one ulp, of which a dominating slot's cancel) and the final rounding."""
+    torch = torch_cuda
+    H, D = 2, 128
+    say(f"observe_prompt dominating slots G={G} T0={T0} W={W} scales={scales}")
+    kv = _mk(lib, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales, ema_decay=0.5)
+    rng = np.random.default_rng(T0)
+    K = rng.standard_normal((1, H, T0, D)).astype(np.float16)
+    q = np.repeat(K.transpose(0, 2, 1, 3) * np.float16(8), G, axis=2)
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    want = G * 0.5 ** np.arange(T0, 0, -1, dtype=np.float64)
+    for g in range(H):
+        e_err = np.abs(kv.export(0, 0, g, planes=("ema",))["ema"].astype(np.float64) / want - 1.0)
+        late = slice(T0 - 12, T0)           # (earlier slots may hold as little as what later queries spare for them)
+        assert np.all(e_err[late] <= 2e-7), f"max rel {np.max(e_err[late]):.3g}"
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
