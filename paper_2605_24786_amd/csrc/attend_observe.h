@@ -30,6 +30,8 @@ size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
 
 // Causal work falls along the list of work items, so a workgroup takes two, one from either end:
 // item y and item n - 1 - y (the middle one of an odd list alone).
+// Both grids are (kv-heads times items, 1, sequences), kv-head fastest: the y dimension ends at
+// 65536, which the row statistics of half a million tokens with 16 heads pass.
 
 // The slots of a unit in tiles of 32: first the INT8 ones, then the FP16 ones.
 struct ObserveUnit {
@@ -65,7 +67,7 @@ __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scal
   }
 }
 
-// Row statistics.  Grid (kv-heads, row groups, sequences): a wavefront owns kObsBlocks blocks of 16
+// Row statistics.  Items are groups of rows: a wavefront owns kObsBlocks blocks of 16
 // consecutive tokens of one head each, the workgroup walks the slots its last token sees in tiles
 // of 32, staged once for all its rows as fp16 in two alternating LDS buffers (one barrier per
 // tile).  Every lane keeps a running
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
   __shared__ float factor[2][kTile];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t16 = lane & 15, g4 = lane >> 4;
-  const int g = blockIdx.x, b = blockIdx.z, G = cv.G;
+  const int g = blockIdx.x % cv.Hkv, y = blockIdx.x / cv.Hkv, b = blockIdx.z, G = cv.G;
   const int ul = b * cv.Hkv + g;
   const ObserveUnit un = observe_unit(cv, layer * cv.B * cv.Hkv + ul, T);
   constexpr float kNothing = -1e30f;                    // reference of a lane that has seen no slot
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv
   // pairs (token block, head) of this workgroup
   const int npairs = (T + 15) / 16 * G, nitems = (npairs + kObsWaves * kObsBlocks - 1) / (kObsWaves * kObsBlocks);
   for (int end = 0; end < 2; ++end) {
-  const int item = end == 0 ? nitems - 1 - (int)blockIdx.y : (int)blockIdx.y;
+  const int item = end == 0 ? nitems - 1 - y : y;
   if (end == 1) {
     if (item == nitems - 1 - item) break;
     __syncthreads();                                    // the tile buffers are free
@@ -261,7 +263,7 @@ __device__ __forceinline__ double pow_count(double x, unsigned k) {
   return r;
 }
 
-// Column sums.  Grid (kv-heads, slot tiles, sequences): a workgroup keeps its 64 slots' keys in
+// Column sums.  Items are tiles of slots: a workgroup keeps its 64 slots' keys in
 // registers (every query then serves 64 slots per read: the reads of the queries, strided by the
 // heads of a token, bound this kernel -- 32 slots took 170 us instead of 106 per layer of 3001 tokens), its wavefronts take every eighth block of 16 tokens from the prompt's end back to the
 // tile, all heads of a block in turn (the queries of the unit stay in its XCD's L2: with eight
@@ -274,10 +276,10 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
   __shared__ double red[kMassWaves][kMassTile];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t16 = lane & 15, g4 = lane >> 4;
-  const int g = blockIdx.x, b = blockIdx.z, G = cv.G;
+  const int g = blockIdx.x % cv.Hkv, tile = blockIdx.x / cv.Hkv, b = blockIdx.z, G = cv.G;
   const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
   const ObserveUnit un = observe_unit(cv, u, T);
-  const int tile = blockIdx.y, ntiles8 = (un.n8 + kMassTile - 1) / kMassTile;
+  const int ntiles8 = (un.n8 + kMassTile - 1) / kMassTile;
   const bool is8 = tile < ntiles8;
   const int base = is8 ? tile * kMassTile : un.n8 + (tile - ntiles8) * kMassTile, lim = is8 ? un.n8 : T;
   if (base >= lim) return;                              // (the grid is sized for the worst rounding)
@@ -395,8 +397,8 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
                                  float *scratch, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
   const int pairs = (T + 15) / 16 * cv.G, per = kObsWaves * kObsBlocks;
-  const dim3 rows(cv.Hkv, ((pairs + per - 1) / per + 1) / 2, cv.B);
-  const dim3 slots(cv.Hkv, (T + kMassTile - 1) / kMassTile + 1, cv.B);
+  const dim3 rows(cv.Hkv * (((pairs + per - 1) / per + 1) / 2), 1, cv.B);
+  const dim3 slots(cv.Hkv * ((T + kMassTile - 1) / kMassTile + 1), 1, cv.B);
   const size_t n_rows = (size_t)cv.B * cv.Hkv * cv.G * observe_stride(T);
   const ObserveStats stats = {(double *)scratch, scratch + 2 * n_rows};
   if (cv.chan) {

@@ -536,6 +536,24 @@ def test_observe_prompt_sums_in_64_bits(lib, torch_cuda, G, T0, W, scales):
     kv.close()
 
 
+def test_observe_prompt_half_a_million_tokens(lib, torch_cuda):
+    """The most row groups: 524 320 tokens of a 16-head group (65 540 workgroups per kv-head and sequence).  Zero
+    queries, so the importances are the harmonic sums of test_observe_prompt_sums_in_64_bits; 1e-7: the final
+    rounding to fp32, and 64-bit sums of half a million terms."""
+    torch = torch_cuda
+    T0, G, D = 524320, 16, 128
+    say(f"observe_prompt G={G} T0={T0}")
+    kv = _mk(lib, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=64, capacity=T0 + 32, protected_window=4,
+             n_tight=[1000], n_loose=[1000], ema_decay=1.0, mass_gain=1.0)
+    K = torch.randn(1, 1, T0, D, device="cuda", dtype=torch.float16)
+    kv.load_prefill(0, K, K)
+    kv.observe_prompt(0, torch.zeros(1, T0, G, D, dtype=torch.float16, device="cuda"))
+    want = np.cumsum(G / np.arange(T0, 0, -1, dtype=np.float64))[::-1]
+    got = kv.export(0, 0, 0, planes=("ema",))["ema"].astype(np.float64)
+    assert np.max(np.abs(got / want - 1.0)) <= 1e-7
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,W,sm", [(200, -1, 0.125), (200, 0, 0.125), (150, 40, 0.25)])
 def test_observe_prompt_wide_scores(lib, torch_cuda, T0, W, sm):
     """Scores that spread over 75 or 150 units and carry no rounding (one-hot integers, a power of two as softmax
