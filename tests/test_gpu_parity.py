@@ -604,6 +604,37 @@ def test_observe_prompt_dominating_slots(lib, torch_cuda, G, T0, W, scales):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W,mc,scales", [
+    (1, 16, 8, 16, "token"), (1, 17, 8, 32, "token"),        # one tile of rows, and one row more
+    (4, 4, 0, 4, "channel"), (4, 5, 0, 4, "channel"),        # as long as a call may be, and one token more
+    (4, 32, 16, 32, "token"), (5, 25, -1, 25, "token"),      # the most rows of a call
+    (3, 6, 4, 8, "token"), (16, 1, 4, 0, "token"),
+])
+def test_observe_prompt_within_one_call(lib, torch_cuda, G, T0, W, mc, scales):
+    """Prompts about as long as one conf_kv_observe call may be: one launch of that kernel, or the two launches over
+    all queries.  1e-5 as in test_observe_prompt_edges."""
+    torch = torch_cuda
+    H, B, D = 2, 2, 128
+    say(f"observe_prompt G={G} T0={T0} W={W} max_chunk={mc} scales={scales}")
+    kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=128, protected_window=4,
+             n_tight=[T0], n_loose=[T0], max_chunk=mc, scale_mode=scales)
+    rng = np.random.default_rng(T0 + G)
+    K = rng.standard_normal((B, H, T0, D)).astype(np.float16)
+    q = (rng.standard_normal((B, T0, G * H, D)) * 1.5).astype(np.float16)
+    stale = torch.full((B, H, T0), 7.0, device="cuda")
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda(), stale)
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    for b in range(B):
+        for g in range(H):
+            u = O.load_prefill(K[b, g], K[b, g], W, scale_mode=scales)
+            O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(0.9))
+            e_ref = u.ema.astype(np.float64)
+            e_err = np.abs(kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+            assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"unit {(b, g)}: max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
+    assert kv.counters().device_errors == 0
+    kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
