@@ -1158,14 +1158,23 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, La
   finish_small<kWave>(cv, u, sel, src_all, n, n8, nx, e, ev, lane);
 }
 
-// The same with a workgroup per unit, for up to 1024 units (kSmallWgUnits): the four wavefronts share the unit's
+// The same with a workgroup per unit (small_wg below): the four wavefronts share the unit's
 // slots, and each keeps the importance, position and score of its first kRegs slots per lane in
 // registers (4096 slots per unit), so a unit of that length costs one memory round trip instead of
-// one per pass and batch.  From some thousand units on the chip is full with one wavefront per unit
-// and the barriers cost more than the passes: 256 units of 16 002 slots 40 -> 12.8 us per launch, 512
-// units of 2049 slots 9.7 -> 8.4, 144 units of 513 slots 9.9 -> 6.9; 2048 units of 1025 to 2049
-// slots 13 -> 19 us, 1280 units of 1778 slots 12.9 -> 14.7 (layer scope).
-constexpr int kSmallWgUnits = 1024;
+// one per pass and batch: 256 units of 16 002 slots 40 -> 12.8 us per launch, 144 units of 513 slots
+// 9.9 -> 6.9.
+// Where that is the faster one, whole conf_kv_evict_compact calls of 64 to 1024 units, 129 to 6001
+// slots and 1 to 4 evictions, one wavefront per unit against a workgroup per unit:
+//  - own importance: up to 768 units (three workgroups on every CU) 0.53 to 1.01 of the time; at 832
+//    0.78 to 1.12, and slower wherever one token of up to 2049 slots goes (513 slots 29.3 against 31.5 us);
+//  - shared importance (twice the registers, so fewer of them fit a CU, against 8-slot batches of the
+//    other form): 768 units of 2049 slots 53.0 against 48.1 us, of 4097 (four evictions) 129 against
+//    111; but of 513 slots 28.8 against 31.4, and at 1024 units up to 1.69 times slower;
+//  - random keys (their arithmetic, not the loads, is the work): up to 256 units 0.72 to 0.99; 512
+//    units of 513 slots 28.7 against 30.1 us.
+inline bool small_wg(int U, int n_max, bool shared, bool random) {
+  return random ? U <= 256 : shared ? U <= 768 && n_max >= 2048 : U <= 768;
+}
 template <bool kShared, bool kRandom = false>
 __global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv, LayerMask appended, double alpha,
                                                                    const double *__restrict__ shared_all,
@@ -1689,7 +1698,7 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
     // layer-shared importance: the summed mass first, then the same three kernel shapes reading it
     hipLaunchKernelGGL(shared_mass_kernel, dim3(cv.L * cv.B, (cv.cap + kEvThreads - 1) / kEvThreads),
                        dim3(kEvThreads), 0, stream, cv, appended, opt.shared);
-    if (U <= kSmallWgUnits)
+    if (small_wg(U, n_max, true, false))
       hipLaunchKernelGGL((rank_small_wg_kernel<true>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended, alpha,
                          (const double *)opt.shared, src, sel, rr);
     else
@@ -1706,7 +1715,7 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
                          1, score, src, sel);
   } else if (opt.random) {
     // the random ranker: the same kernel shapes with the drawn key in place of the composite score
-    if (U <= kSmallWgUnits)
+    if (small_wg(U, n_max, false, true))
       hipLaunchKernelGGL((rank_small_wg_kernel<false, true>), dim3(U), dim3(kEvThreads), 0, stream, cv,
                          appended, alpha, (const double *)nullptr, src, sel, rr);
     else if (U <= 4096)
@@ -1728,7 +1737,7 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
       hipLaunchKernelGGL(rank_select_kernel<1024>, dim3(U), dim3(1024), 0, stream, cv, appended, alpha, opt,
                          1, score, src, sel);
   } else {
-  if (U <= kSmallWgUnits)
+  if (small_wg(U, n_max, false, false))
     hipLaunchKernelGGL((rank_small_wg_kernel<false>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, rr);
   else if (U <= 4096)    // few wavefronts per SIMD: registers to spare for deeper batches
