@@ -1585,9 +1585,10 @@ __global__ __launch_bounds__(kEvThreads) void compact_paged_kernel(CacheView cv,
 // end of its range asks the next call's compaction kernel to clear the tagged words, after
 // which both bases start over at 0.
 // ---------------------------------------------------------------------------------------
-// kWide: a workgroup per unit, grid (U), for steps that appended several tokens: its wavefronts share
-// the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction and a store (16
-// tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in turn, 18.5 us; 4 tokens 10.5 and 7.3).
+// kWide: a workgroup per unit, grid (U), for steps of up to 3072 units that appended several tokens:
+// its wavefronts share the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction
+// and a store (16 tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in
+// turn, 18.5 us; 4 tokens 10.5 and 7.3).
 template <int D, bool kWide = false>
 __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
                                                             const int32_t *__restrict__ sel_all, int U,
@@ -1782,7 +1783,10 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
   const dim3 cgrid(U, paired ? 2 : 5);
   int appended_max = 0;
   for (int l = 0; l < cv.L; ++l) appended_max = appended.get(l) > appended_max ? appended.get(l) : appended_max;
-  const bool several = appended_max > 1 && cv.W >= 0;         // several rows to quantise per unit
+  // several rows to quantise per unit: a workgroup each, as long as the units alone do not fill the
+  // chip (whole call, 300 slots, 4 tokens: 256 units 41.4 -> 26.5 us, 3072 units 95.9 -> 93.5, 8192
+  // units 114.4 -> 119.1; 3 tokens: 3072 units 76.2 -> 75.0, 4096 units 86.8 -> 89.7)
+  const bool several = appended_max > 1 && cv.W >= 0 && U <= 3072;
   const dim3 dgrid(several ? U : (U + 3) / 4);
   if (cv.D == 64) {
     if (after_prompt)
