@@ -1691,11 +1691,12 @@ bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n
   const long long nv = (long long)n_ub + n16_ub;
   // One workgroup per CU measured best: the exchange between the splits of a unit (statistics
   // and partial gather) gets slower with more participants, and a grid that is not a
-  // whole number of waves over the CUs leaves a straggler round.  Two per CU only when a
-  // single split per unit would leave half of the chip idle.
+  // whole number of waves over the CUs leaves a straggler round.  That holds above half of the
+  // CUs too: 136 to 256 units of 700 to 9000 slots take 1.03 to 1.38 times as long on two
+  // workgroups each as on one (one head, 128 channels, 192 units of 2000 slots, FP16: 41.4 against
+  // 46.8 us; 64-slot window: 27.4 against 31.0).
   int want = lim.cus / units_per_layer;
   if (want < 1) want = 1;
-  if (want == 1 && 2 * units_per_layer <= 2 * lim.cus && units_per_layer > lim.cus / 2) want = 2;
   // Measured on 8- and 12-unit layers of 500 to 32768 slots: a unit below about 192 KB is
   // fastest on one workgroup (no exchange at all); above, splits down to about 32 KB each
   // (one 32-slot tile per wavefront) still pay.

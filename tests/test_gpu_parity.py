@@ -635,6 +635,20 @@ def test_observe_prompt_within_one_call(lib, torch_cuda, G, T0, W, mc, scales):
     kv.close()
 
 
+@pytest.mark.parametrize("D,W", [(64, -1), (128, 64)])
+def test_no_split_above_half_of_the_cus(lib, torch_cuda, D, W):
+    """A layer with more units than half of the CUs runs one workgroup per unit, whether or not two would fit a CU."""
+    torch = torch_cuda
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    H, T0 = 8, 2000
+    for B in (cus * 3 // 4 // H, cus // H):
+        kv = _mk(lib, batch=B, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=2048, n_tight=[T0], n_loose=[T0])
+        K = torch.randn(B, H, T0, D, device="cuda", dtype=torch.float16)
+        kv.load_prefill(0, K, K)
+        assert kv.attend_splits(0) == 1, (D, W, B * H)
+        kv.close()
+
+
 @pytest.mark.parametrize("T0,P,evict", [
     (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
     (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
