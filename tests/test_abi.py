@@ -135,3 +135,12 @@ def test_pyramid_budgets_match_the_oracle(clib):
     for bad in [(0, 4, 0.5, 96), (64, 0, 0.5, 96), (64, 4, 0.0, 96), (64, 4, 1.5, 96), (64, 4, 0.5, 0)]:
         assert clib.conf_kv_pyramid_budgets(*bad, out) == pkg.binding.ERR_INVALID_ARG
     assert clib.conf_kv_pyramid_budgets(64, 4, 0.5, 96, None) == pkg.binding.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("names", [("_cuda_getCurrentRawStream", "_cuda_getDevice"), ("_cuda_getDevice",), ()])
+def test_stream_handle_with_and_without_the_private_calls(names):
+    from types import SimpleNamespace as NS
+    private = {"_cuda_getCurrentRawStream": lambda device: 100 + device, "_cuda_getDevice": lambda: 3}
+    torch = NS(_C=NS(**{n: private[n] for n in names}),
+               cuda=NS(current_stream=lambda: NS(cuda_stream=7)))
+    assert pkg.binding._stream_getter(torch)() == (103 if len(names) == 2 else 7)
