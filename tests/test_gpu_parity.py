@@ -650,15 +650,16 @@ def test_no_split_above_half_of_the_cus(lib, torch_cuda, D, W):
 
 
 @pytest.mark.parametrize("T0,P,evict", [
-    (4098, 1, 1),      # 4098 candidates: one more than a workgroup keeps in registers, plus one
-    (4101, 8, 4),      # the most evictions the small kernels take, all candidates but one in registers
-    (260, 3, 2),       # candidates just above one slot per thread
+    (4098, 1, 1),      # 4098 candidates: two more than a workgroup keeps in registers
+    (4101, 8, 4),      # the most evictions the small kernels take, 4094 candidates, all in registers
+    (260, 3, 2),       # 258 candidates, just above one slot per thread
     (9, 8, 1),         # a single candidate pair
 ])
 @pytest.mark.parametrize("scope", ["kv_head", "layer"])
 def test_small_ranking_edges(lib, torch_cuda, T0, P, evict, scope):
-    """A few evictions per unit from few units: the kept sets of the workgroup-per-unit ranking kernel are the
-    oracle's (bit-equal scores from the exported importance)."""
+    """A few evictions per unit from few units: the kept sets of the small ranking kernels (a workgroup per unit; a
+    wavefront at lengths below 2048 with the layer scope) are the oracle's (bit-equal scores from the exported
+    importance)."""
     torch = torch_cuda
     H, G, D = 2, 2, 128
     n = T0 + 1
@@ -684,6 +685,86 @@ def test_small_ranking_edges(lib, torch_cuda, T0, P, evict, scope):
         gone = np.argsort(al * unit(a) + (1.0 - al) * unit(pos), kind="stable")[:evict]
         kept = np.setdiff1d(np.arange(n), gone)
         assert np.array_equal(kv.export(0, 0, h, planes=("pos",))["pos"], kept.astype(np.int32)), f"kv-head {h}"
+    kv.close()
+
+
+@pytest.mark.parametrize("T0,evict,alpha,low,high", [
+    (9001, 4, 1.0, (17, 4095, 4096, 8780), None),      # equal keys on both sides of what the registers hold
+    (9001, 2, 1.0, (4095, 4096, 8780), None),          # the older two of three
+    (9002, 4, 0.9, (4097, 8781, 8782, 8990), None),    # the least importance beyond the registers, to the last candidate
+    (9002, 3, 0.65, (), 8700),                         # the most importance there
+    (4111, 4, 1.0, (4096, 4097, 4098, 4099), None),    # every evicted slot in a last, nearly empty trip
+])
+@pytest.mark.parametrize("scope", ["kv_head", "layer"])
+def test_small_ranking_beyond_the_registers(lib, torch_cuda, T0, evict, alpha, low, high, scope):
+    """More than the 4096 candidates that the workgroup-per-unit ranking keeps in registers: the slots it reads again
+    on every pass count in the minimum and maximum, and are evicted, like the others.  lambda = 1 and no gain, so the
+    importance is what was loaded."""
+    torch = torch_cuda
+    H, D, P = 2, 64, 12
+    n = T0 + 1
+    say(f"ranking beyond the registers T0={T0} evict={evict} alpha={alpha} low={low} high={high} scope={scope}")
+    kv = _mk(lib, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=2, capacity=(T0 + 79) // 64 * 64, protected_window=P,
+             n_tight=[n - evict], n_loose=[n - evict], rank_scope=scope, alpha=alpha, ema_decay=1.0, mass_gain=0.0)
+    rng = np.random.default_rng(T0 + evict)
+    e0 = rng.uniform(1.0, 2.0, (1, H, T0)).astype(np.float32)
+    e0[..., list(low)] = 0.5
+    if high is not None:
+        e0[..., high] = 100.0
+    K = torch.randn((1, H, T0, D), device="cuda", dtype=torch.float16)
+    kv.load_prefill(0, K, K, torch.from_numpy(e0).cuda())
+    new = torch.randn((1, H, D), device="cuda", dtype=torch.float16)
+    kv.attend(0, new, new, new, torch.empty_like(new))
+    kv.evict_compact()
+    for h in range(H):
+        a = e0[0].astype(np.float64).sum(0) if scope == "layer" else e0[0, h].astype(np.float64)
+        s = O.rank_scores(a[: n - P], np.arange(n - P), f32(alpha))
+        gone = np.sort(np.argsort(s, kind="stable")[:evict])
+        if low:
+            assert np.array_equal(gone, low[:evict])
+        kept = np.setdiff1d(np.arange(n), gone)
+        assert np.array_equal(kv.export(0, 0, h, planes=("pos",))["pos"], kept.astype(np.int32)), f"kv-head {h}"
+    kv.close()
+
+
+@pytest.mark.parametrize("L,B,H,ranker,scope,evict", [
+    (96, 1, 8, "composite", "kv_head", 3), (97, 1, 8, "composite", "kv_head", 4),      # 768 units and 776
+    (27, 38, 4, "composite", "kv_head", 2),                                            # 4104 units
+    (97, 1, 8, "composite", "layer", 4), (27, 38, 4, "composite", "layer", 1),
+    (32, 1, 8, "random", "kv_head", 4), (33, 1, 8, "random", "kv_head", 3),            # 256 units and 264
+    (27, 38, 4, "random", "kv_head", 2),
+])
+def test_small_ranking_unit_counts(lib, torch_cuda, L, B, H, ranker, scope, evict):
+    """The small ranking kernels on both sides of the unit counts where they change: kept sets of all units against
+    the oracle's ranking, importance as loaded (lambda = 1, no gain), with ties."""
+    torch = torch_cuda
+    T0, D, P, alpha, seed = 137, 64, 5, 0.65, 9
+    n = T0 + 1
+    say(f"ranking of {L * B * H} units, {ranker} {scope} evict={evict}")
+    kv = _mk(lib, n_layers=L, batch=B, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=2, capacity=192,
+             protected_window=P, n_tight=[n - evict] * L, n_loose=[n - evict] * L, alpha=alpha, ema_decay=1.0, mass_gain=0.0,
+             ranker=ranker, ranker_seed=seed, rank_scope=scope)
+    rng = np.random.default_rng(L * B)
+    e0 = rng.integers(1, 9, (L, B, H, T0)).astype(np.float32)
+    K = torch.randn((B, H, T0, D), device="cuda", dtype=torch.float16)
+    new = torch.randn((B, H, D), device="cuda", dtype=torch.float16)
+    out = torch.empty_like(new)
+    for l in range(L):
+        kv.load_prefill(l, K, K, torch.from_numpy(e0[l]).cuda())
+        kv.attend(l, new, new, new, out)
+    kv.evict_compact()
+    pos = np.arange(n - P)
+    for l in range(L):
+        for b in range(B):
+            for h in range(H):
+                if ranker == "random":
+                    s = O.random_scores(seed, (l * B + b) * H + h, pos)
+                else:
+                    a = e0[l, b].astype(np.float64).sum(0) if scope == "layer" else e0[l, b, h].astype(np.float64)
+                    s = O.rank_scores(a[: n - P], pos, f32(alpha))
+                kept = np.setdiff1d(np.arange(n), np.argsort(s, kind="stable")[:evict])
+                got = kv.export(l, b, h, planes=("pos",))["pos"]
+                assert np.array_equal(got, kept.astype(np.int32)), (l, b, h)
     kv.close()
 
 
