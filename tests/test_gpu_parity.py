@@ -768,6 +768,38 @@ def test_small_ranking_unit_counts(lib, torch_cuda, L, B, H, ranker, scope, evic
     kv.close()
 
 
+@pytest.mark.parametrize("L,B", [(48, 8), (55, 7)])
+def test_demotion_of_several_tokens_unit_counts(lib, torch_cuda, L, B):
+    """3072 units, where a workgroup takes a unit's rows, and 3080, where a wavefront does: codes, scales and tags
+    after a call of five tokens, bit for bit."""
+    torch = torch_cuda
+    H, D, T0, W, tq = 8, 128, 20, 7, 5
+    say(f"demotion of {tq} tokens, {L * B * H} units")
+    kv = _mk(lib, n_layers=L, batch=B, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=64, protected_window=4,
+             n_tight=[40] * L, n_loose=[40] * L, max_chunk=tq)
+    rng = np.random.default_rng(L)
+    K = rng.standard_normal((L, B, H, T0, D)).astype(np.float16)
+    new = rng.standard_normal((L, B, tq, H, D)).astype(np.float16)
+    for l in range(L):
+        k, x = torch.from_numpy(K[l]).cuda(), torch.from_numpy(new[l]).cuda()
+        kv.load_prefill(l, k, -k)
+        kv.attend_chunk(l, x, x, -x, torch.empty_like(x))
+    kv.evict_compact()
+    for u in rng.choice(L * B * H, 60, replace=False).tolist() + [0, L * B * H - 1]:
+        l, b, h = u // (B * H), u // H % B, u % H
+        ref = O.load_prefill(K[l, b, h], -K[l, b, h], W)
+        for t in range(tq):
+            O.append_token(ref, new[l, b, t, h], -new[l, b, t, h], T0 + t)
+        O.demote(ref, W)
+        ex = kv.export(l, b, h)
+        assert ex["n"] == T0 + tq and np.array_equal(ex["pos"], ref.pos) and np.array_equal(ex["is16"], ref.is16)
+        m = ~ref.is16
+        for plane in ("k8", "v8", "ks", "vs"):
+            assert np.array_equal(ex[plane][m], getattr(ref, plane)[m]), (u, plane)
+        assert np.array_equal(ex["k16"][~m].view(np.uint16), ref.k16[~m].view(np.uint16))
+    kv.close()
+
+
 def test_observe_two_launch_form(lib, torch_cuda):
     _observe_case(lib, torch_cuda, 4, 2, 1, 1200, 64, 4, ((1190, 4), (1194, 4)), seed=5, two_launch=True)
 
