@@ -557,7 +557,7 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
     const float l = row_stride_sum<LPT>(swap_halves16(swap_halves32(lf, lf), swap_halves32(lf, lf)));
     // sixteen channel sums over the lane-groups: every exchange between rows halves the values a
     // lane carries (12 exchanges instead of 32), so row r of 16 lanes ends up with channels
-    // [4 r', 4 r' + 4) of every lane-group's sixteen, r' = 2 (r / 2) + r % 2
+    // [4 r, 4 r + 4) of every lane-group's sixteen
     float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -566,7 +566,7 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
       o[e] = row_stride_sum<LPT>(swap_halves16(lo, hi));
     }
     if (lane == 0) { wm[h * kAttWaves + pidx] = mw; wl[h * kAttWaves + pidx] = l; }
-    if ((lane & 15) < LPT) *(float4 *)&wo_p[h * D + c * 16 + 8 * (lane >> 5) + 4 * ((lane >> 4) & 1)] = make_float4(o[0], o[1], o[2], o[3]);
+    if ((lane & 15) < LPT) *(float4 *)&wo_p[h * D + c * 16 + 4 * (lane >> 4)] = make_float4(o[0], o[1], o[2], o[3]);
   }
 }
 
@@ -616,7 +616,7 @@ __device__ __forceinline__ double row_weight(const AttendLaunch &a, int tq, int 
 // wo + (k % kAttWaves) * WSTR + (k / kAttWaves) * G * D; stash holds the slice's raw scores.
 // kPhase 0: the whole epilogue in one kernel (merge, publish, wait for the unit's other splits,
 // gather, EMA, output).  kPhase 1: merge and publish only; kPhase 2: gather, EMA and output in a
-// later launch, which needs no wait (wm/wl are unused and wo is [ns][G][2] floats of LDS) --
+// later launch, which needs no wait (wm/wl are unused and wo holds the [G][gs] weights) --
 // the pair serves shapes whose splits cannot all be resident at once.
 // ---------------------------------------------------------------------------------------
 template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D>
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_finish_kernel(const int32_
                                                                     int S) {
   const AttendLaunch a = resolve_launch(cv, a_in);
   extern __shared__ __align__(16) float smem[];
-  float *pml = smem;                            // [ns][G][2]
+  float *pml = smem;                            // [G][gs], gs = ns rounded up to a power of two (below 2 ns)
   float *gm = pml + (size_t)ns * G * 2;         // [G]
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]
   const Slice sl = make_slice(cv, a, ns, S);
