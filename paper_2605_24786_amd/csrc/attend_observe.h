@@ -8,7 +8,7 @@
 //   a_i = gain * sum_{t >= i} lambda^(T-1-t) sum_h p_{t,h,i},
 // so two launches over all queries do: the first finds every row's softmax statistics, the second
 // every slot's weighted column sum.  Both recompute the scores on the matrix cores (nothing of
-// size T x T is stored).  A layer of that prompt with 32 query heads: 4060 -> 226 us (120 + 106).
+// size T x T is stored).  A layer of that prompt with 32 query heads: 4060 -> 239 us (121 + 118).
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
@@ -240,7 +240,7 @@ __device__ __forceinline__ double pow_count(double x, unsigned k) {
 }
 
 // Column sums.  Items are tiles of slots: a workgroup keeps its 64 slots' keys in registers, so that
-// every query read serves 64 slots (with 32 the kernel took 170 us instead of 106 per layer of 3001
+// every query read serves 64 slots (32 took 1.6 times as long; 64: 118 us per layer of 3001
 // tokens); its wavefronts take every eighth block of 16 tokens from the prompt's end back to the
 // tile, all heads of a block in turn (the queries of the unit stay in its XCD's L2: with eight
 // kv-heads one XCD serves one of them).  A token's weight gain * lambda^(T-1-t) is a running product
