@@ -570,16 +570,16 @@ __device__ __forceinline__ void store_stream_partial(Stream<G> &st, int pidx, fl
   }
 }
 
-// e^x for x <= 0 (-inf included, which gives 0) to about one ulp: 2^(x log2 e) with the product
-// carried in two floats, so the hardware exponential sees an argument without rounding error.
+// e^x for x <= 0 (-inf included, which gives 0) to about one ulp: the hardware exponential of the
+// rounded product p = x log2 e, times e^d of what the rounding lost, d = x - p ln 2 (ln 2 in two
+// floats; |d| < 1e-5, so 1 + d is exact enough).
 // No range checks: the result cannot overflow, and below 2^-126 it may flush to zero.
 __device__ __forceinline__ float exp_nonpos(float x) {
   x = fmaxf(x, -100.0f);
-  const float kHi = 1.44269502e+00f, kLo = 1.92596299e-08f;          // log2(e) = kHi + kLo
-  const float ph = x * kHi;
-  const float pl = fmaf(x, kLo, fmaf(x, kHi, -ph));
-  const float r = __builtin_amdgcn_exp2f(ph);
-  return fmaf(r, pl * 0.693147181f, r);
+  const float p = x * 1.44269502e+00f;
+  const float d = fmaf(-p, -1.90465430e-09f, fmaf(-p, 6.93147182e-01f, x));
+  const float r = __builtin_amdgcn_exp2f(p);
+  return fmaf(r, d, r);
 }
 // 1 / x for a positive, finite double to about 1e-15 relative: the fp32 reciprocal estimate and two
 // Newton steps (a correctly rounded division costs ten times the instructions and nothing

@@ -6,33 +6,72 @@
 // each re-read the whole cache: 4.1 ms per layer.  But the stored cache does not change while its
 // prompt observes it, and the windows' updates telescope to
 //   a_i = gain * sum_{t >= i} lambda^(T-1-t) sum_h p_{t,h,i},
-// so two launches over all queries do: the first finds every row's softmax statistics, the second
-// every slot's weighted column sum.  Both recompute the scores on the matrix cores (nothing of
-// size T x T is stored).  A layer of that prompt with 32 query heads: 4060 -> 239 us (121 + 118).
+// so launches over all queries do: the first finds every row's softmax statistics, the second
+// every slot's weighted column sum (in parts of the rows, which a third adds up, where the slots
+// alone would leave the chip idle).  Both recompute the scores on the matrix cores (nothing of
+// size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
+// wavefront and of 64 slots per workgroup, 174 us in these four.
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
-constexpr int kMassThreads = 512, kMassWaves = kMassThreads / kWave, kMassTile = 64;   // slots per workgroup of the second
-constexpr int kObsTileBytes = kTile * kKRow16;         // 32 slots as fp16 rows
+constexpr int kObsBlocks = 2;                          // blocks of 16 rows per wavefront of the first kernel
+constexpr int kObsItem = kObsWaves * kObsBlocks;       // blocks per workgroup
+constexpr int kMassWave = 64, kMassTile = kObsWaves * kMassWave;   // slots per wavefront and workgroup of the second
+constexpr int kMassStep = 4;                           // blocks of 16 rows it stages at a time
+constexpr int kMassPartsMax = 32, kMassGroups = 1536, kMassStart = 3, kMassSum = 5;
 
-// Softmax statistics of a prompt query: 1 / (sum of the exponentials) in 64 bits, then for all
-// rows the reference the exponentials are taken against; both [unit in layer][head of the
-// group][token, padded to 16].
+// Per prompt query (row): the reference its exponentials are taken against, and in 64 bits
+// gain * lambda^(T-1-t) over the sum of the exponentials; both [unit in layer][head of the
+// group][token, padded to 16] (padding: a reference no score reaches, weight 0).
 __host__ __device__ constexpr int observe_stride(int T) { return (T + 15) / 16 * 16; }
 struct ObserveStats {
-  double *inv;
+  double *weight;
   float *ref;
+  double *partial;                                     // [unit in layer][part][token, padded to 16] column sums
+  double *row_sum;                                     // the first kernel's parts: [part][rows] sums of exponentials
+  float *row_ref;                                      // and references
 };
+// A workgroup of the first kernel walks at most this many tiles of the slots its rows see; rows that see
+// more are cut into parts, which a small kernel joins: the causal triangle then falls into pieces of
+// about one size, two per place on the chip (three workgroups a CU).
+constexpr int kObsGroups = 1536, kObsPartMin = 8;
+static int observe_tiles_per_part(int units_per_layer, int G, int T, int tile) {
+  const long long items = ((T + 15) / 16 * G + kObsItem - 1) / kObsItem;
+  const long long tiles = (T + tile - 1) / tile + 1;      // (one more where the FP16 slots begin)
+  return (int)std::min<long long>(tiles, std::max<long long>({kObsPartMin, (tiles + 15) / 16, (items * units_per_layer * tiles / 2 + kObsGroups - 1) / kObsGroups}));
+}
+// Parts the rows of the second kernel are cut into: the count whose workgroups (the pairs of a
+// slot tile and a part that are not wholly behind the diagonal) take the least time on the chip,
+// kMassGroups of them at a time, a workgroup costing its steps and about kMassStart more to begin.
+static int observe_mass_parts(int units_per_layer, int G, int T) {
+  const long long tiles = (T + kMassTile - 1) / kMassTile, nb = (T + 15) / 16 * G, steps = (nb + kMassStep - 1) / kMassStep;
+  long long best = 0;
+  int parts = 1;
+  for (int p = 1; p <= kMassPartsMax && 2 * p <= steps + 1; ++p) {
+    const long long len = (steps + p - 1) / p;
+    long long groups = 0;
+    for (long long t = 0; t < tiles && groups <= 4 * kMassGroups; ++t)
+      groups += p - std::min<long long>(p, t * (kMassTile / 16) * G / (len * kMassStep));
+    groups *= units_per_layer;
+    if (p > 1 && groups > 4 * kMassGroups) break;
+    const long long cost = (groups + kMassGroups - 1) / kMassGroups * (len + kMassStart) + (p > 1 ? kMassSum : 0);
+    if (p == 1 || cost < best) { best = cost; parts = p; }
+  }
+  return parts;
+}
 size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
-  return (size_t)units_per_layer * G * observe_stride(cap) * 3;
+  // (at least half of units * tiles * parts are workgroups, and several parts stop at 4 kMassGroups of those)
+  const size_t partial = std::min<size_t>((size_t)units_per_layer * kMassPartsMax * observe_stride(cap),
+                                          (size_t)8 * kMassGroups * (kMassTile + 16));
+  // the first kernel's parts are done with before the second's are written.  Its parts times rows: below 1 + tiles /
+  // (tiles per part), where several parts need (rows / 128) * (tiles / 2) below kObsGroups * (tiles per part + 1),
+  // or tiles per part at its least (then rows * tiles / 256 <= kObsGroups * kObsPartMin)
+  const size_t rows = (size_t)units_per_layer * G * observe_stride(cap);
+  const size_t row_parts = std::min<size_t>(rows * 17, 2 * rows + (size_t)kObsGroups * 512);
+  return rows * 3 + 2 + std::max<size_t>(2 * partial, 3 * row_parts);
 }
 
-// Causal work falls along the list of work items, so a workgroup takes two, one from either end:
-// item y and item n - 1 - y (the middle one of an odd list alone).
-// Both grids are (kv-heads times items, 1, sequences), kv-head fastest: the y dimension ends at
-// 65536, which the row statistics of half a million tokens with 16 heads pass.
-
-// The slots of a unit in tiles of 32: first the INT8 ones, then the FP16 ones.
+// The slots of a unit come in tiles: first the INT8 ones, then the FP16 ones.
 struct ObserveUnit {
   const int8_t *K8;
   const __half *KS, *K16;
@@ -66,169 +105,6 @@ __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scal
   }
 }
 
-// Row statistics.  Items are groups of four blocks of rows: a wavefront owns a block, 16 consecutive
-// tokens of one head, and the workgroup walks the slots its last token sees in tiles of 32, staged
-// once for its four blocks as fp16 in two alternating LDS buffers (one barrier per tile).  Every
-// lane keeps a running reference and sum of its own columns, so no reduction runs inside the loop;
-// the sum goes over to 64 bits every eight tiles.  A score costs a multiply-add, a product with
-// log2 e, one hardware exponential and one addition.  (log2 e folded into the slots' factors would
-// save the product, but rounds the factor once more: an error of the score, and so of a
-// probability, that grows with it.)
-template <bool kChan>
-__global__ __launch_bounds__(kObsThreads) void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
-                                                                    int T, float sm, ObserveStats stats) {
-  constexpr int D = 128, kBuf = kObsTileBytes * (kChan ? 2 : 1);
-  __shared__ __align__(16) uint8_t tiles[2][kBuf];
-  __shared__ float factor[2][kTile];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int t16 = lane & 15, g4 = lane >> 4;
-  const int g = blockIdx.x % cv.Hkv, y = blockIdx.x / cv.Hkv, b = blockIdx.z, G = cv.G;
-  const int ul = b * cv.Hkv + g;
-  const ObserveUnit un = observe_unit(cv, layer * cv.B * cv.Hkv + ul, T);
-  constexpr float kNothing = -1e30f;                    // reference of a lane that has seen no slot
-
-  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks + kObsWaves - 1) / kObsWaves;   // blocks are (token block, head)
-  for (int end = 0; end < 2; ++end) {
-    const int item = end == 0 ? nitems - 1 - y : y;
-    if (end == 1) {
-      if (item == nitems - 1 - item) break;
-      __syncthreads();                                  // the tile buffers are free
-    }
-    const int last_block = min((item + 1) * kObsWaves, nblocks) - 1;
-    const int slots = min(T, last_block / G * 16 + 16);                // what the workgroup's last token sees
-    const int nt8 = (min(un.n8, slots) + kTile - 1) / kTile;
-    const int ntiles = nt8 + (max(0, slots - un.n8) + kTile - 1) / kTile;
-
-    const int block = item * kObsWaves + w;
-    const bool live = block < nblocks;
-    const int tok0 = (live ? block : 0) / G * 16, head = (live ? block : 0) % G;
-    half8_t qa[4];
-    {
-      const __half *row = q + (((size_t)b * T + min(tok0 + t16, T - 1)) * cv.Hkv * G + (size_t)g * G + head) * D + g4 * 8;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) qa[s] = __builtin_bit_cast(half8_t, *(const int4 *)(row + 32 * s));
-    }
-
-    // thread (row, piece): sixteen channels of one slot
-    const int lrow = tid >> 3, lc = tid & 7;
-    int4 r0 = {}, r1 = {};
-    unsigned short rs = 0;
-    auto load = [&](int it) {
-      if (it < nt8) {
-        const unsigned row = (unsigned)ring_row_u(un.h8, min(it * kTile + lrow, un.n8 - 1), un.cap8);
-        r0 = *(const int4 *)(un.K8 + (size_t)row * D + lc * 16);
-        if (!kChan) rs = ((const unsigned short *)un.KS)[row];
-      } else {
-        const int slot = min(un.n8 + (it - nt8) * kTile + lrow, T - 1);
-        const int4 *src = (const int4 *)(un.K16 + (size_t)ring_row(un.h16, slot - un.n8, un.cap16) * D + lc * 16);
-        r0 = src[0];
-        r1 = src[1];
-      }
-    };
-    auto store = [&](int it) {
-      half8_t *dst = (half8_t *)(tiles[it & 1] + lrow * kKRow16 + lc * 32);
-      half8_t *low = (half8_t *)(tiles[it & 1] + (kChan ? kObsTileBytes : 0) + lrow * kKRow16 + lc * 32);
-      if (it < nt8) {
-        if constexpr (kChan) {
-          scale_codes(make_uint2((unsigned)r0.x, (unsigned)r0.y), un.KS + lc * 16, dst[0], low[0]);
-          scale_codes(make_uint2((unsigned)r0.z, (unsigned)r0.w), un.KS + lc * 16 + 8, dst[1], low[1]);
-        } else {
-          dst[0] = cvt_i8x8_f16x8((unsigned)r0.x, (unsigned)r0.y);
-          dst[1] = cvt_i8x8_f16x8((unsigned)r0.z, (unsigned)r0.w);
-        }
-        if (lc == 0) factor[it & 1][lrow] = kChan ? sm : __half2float(__ushort_as_half(rs)) * sm;
-      } else {
-        dst[0] = __builtin_bit_cast(half8_t, r0);
-        dst[1] = __builtin_bit_cast(half8_t, r1);
-        if (lc == 0) factor[it & 1][lrow] = sm;
-      }
-    };
-
-    float m[4], l[4];
-    double ld[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { m[i] = kNothing; l[i] = 0.f; ld[i] = 0.0; }
-
-    load(0);
-    store(0);
-    if (ntiles > 1) load(1);
-    for (int it = 0; it < ntiles; ++it) {
-      __syncthreads();                                  // tile `it` is there; the buffer of tile it - 1 is free
-      const bool is8 = it < nt8;
-      const int base = is8 ? it * kTile : un.n8 + (it - nt8) * kTile, lim = is8 ? un.n8 : T;
-      const uint8_t *Kt = tiles[it & 1];
-      floatx4_t acc[2];
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        const uint8_t *krow = Kt + (16 * sb + t16) * kKRow16 + g4 * 16;
-        if (kChan && is8) {
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-            acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], *(const half8_t *)(krow + kObsTileBytes + 64 * s), acc[sb], 0, 0, 0);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], *(const half8_t *)(krow + 64 * s), acc[sb], 0, 0, 0);
-      }
-      const float f[2] = {factor[it & 1][t16], factor[it & 1][16 + t16]};
-      // edge: the diagonal, or a partial tile; a masked score is -inf
-      auto fold = [&](auto edge) {
-        // the score less a reference, in one rounding here and in the second kernel: what a dominating
-        // slot's score loses must be the same in its probability and in the normaliser
-        auto above = [&](int sb, int i, float ref) {
-          const float v = fmaf(acc[sb][i], f[sb], -ref);
-          return edge && base + 16 * sb + t16 >= min(lim, tok0 + 4 * g4 + i + 1) ? -INFINITY : v;
-        };
-        float x[2][4], top = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-          for (int sb = 0; sb < 2; ++sb) x[sb][i] = above(sb, i, m[i]);
-          top = fmaxf(top, fmaxf(x[0][i], x[1][i]));
-        }
-        // a lane's reference only has to stay within a few units of its columns' maximum
-        if (__builtin_amdgcn_ballot_w64(top > 5.0f)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float mn = fmaxf(m[i], fmaxf(above(0, i, 0.f), above(1, i, 0.f)));
-            const float corr = __expf(m[i] - mn);
-            m[i] = mn;
-            l[i] *= corr;
-            ld[i] *= (double)corr;
-#pragma unroll
-            for (int sb = 0; sb < 2; ++sb) x[sb][i] = above(sb, i, mn);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) l[i] += __expf(x[0][i]) + __expf(x[1][i]);
-      };
-      if (live && base <= tok0 + 15) {                  // (uniform over the wavefront) a row of the block sees the tile
-        if (base + kTile - 1 > tok0 || base + kTile > lim) fold(std::true_type{});
-        else fold(std::false_type{});
-      }
-      if ((it & 7) == 7) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { ld[i] += (double)l[i]; l[i] = 0.f; }
-      }
-      if (it + 1 < ntiles) store(it + 1);
-      if (it + 2 < ntiles) load(it + 2);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float M = row16_max(m[i]);
-      const float es = exp_nonpos(m[i] - M);
-      const double L = group_sum((ld[i] + (double)l[i]) * (double)es, 16);
-      const int tok = tok0 + 4 * g4 + i;
-      if (live && t16 == 0 && tok < T) {
-        const size_t row = ((size_t)ul * G + head) * observe_stride(T) + tok;
-        stats.ref[row] = M;
-        stats.inv[row] = recip_pos(L);
-      }
-    }
-  }
-}
-
 // lambda^k
 __device__ __forceinline__ double pow_count(double x, unsigned k) {
   double r = 1.0;
@@ -239,27 +115,330 @@ __device__ __forceinline__ double pow_count(double x, unsigned k) {
   return r;
 }
 
-// Column sums.  Items are tiles of slots: a workgroup keeps its 64 slots' keys in registers, so that
-// every query read serves 64 slots (32 took 1.6 times as long; 64: 118 us per layer of 3001
-// tokens); its wavefronts take every eighth block of 16 tokens from the prompt's end back to the
-// tile, all heads of a block in turn (the queries of the unit stay in its XCD's L2: with eight
-// kv-heads one XCD serves one of them).  A token's weight gain * lambda^(T-1-t) is a running product
-// in 64 bits; every probability goes into the column sum in 64 bits by itself.
+__device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row, int tok, int T, float M, double L, double decay,
+                                           double gain) {
+  stats.ref[row] = tok < T ? M : 1e30f;
+  stats.weight[row] = tok < T ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) * recip_pos(L) : 0.0;
+}
+
+// Row statistics.  A block of rows is 16 consecutive tokens of one head; a wavefront owns two, so
+// that a key fragment read from LDS serves 32 rows (with 16 the reads alone took 47 of 120 us per
+// layer of 3001 tokens and 32 heads, and the conversion of the keys five of fourteen vector
+// instructions per score), and the workgroup walks the slots its last token sees in tiles that
+// are staged once for its eight blocks as fp16 in two alternating LDS buffers (one barrier per tile).
+// Scores come transposed, a lane's rows being slots of one query: one running reference and sum
+// per lane and block, no reduction inside the loop; the sum goes over to 64 bits with every tile.
+// 120 -> 82 us per layer of 3001 tokens and 32 heads; while a CU is busy, vector ALU and matrix cores are at work in
+// turn 95 % of the time.
+// Causal work falls along the list of items: long ones are cut into parts of their slots.
+// A score costs a multiply-add, a product with log2 e, one hardware exponential and one addition.
+// (log2 e folded into the slots' factors would save the product, but rounds the factor once more: an
+// error of the score, and so of a probability, that grows with it.)
+// The grid is (kv-heads times items, 1, sequences), kv-head fastest: the y dimension ends at 65536,
+// which the row blocks of half a million tokens with 16 heads pass.
 template <bool kChan>
-__global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
-                                                                   float sm, double decay, double gain,
-                                                                   ObserveStats stats) {
-  constexpr int D = 128, kSb = kMassTile / 16;
-  __shared__ double red[kMassWaves][kMassTile];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+__global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
+                                                                    float sm, double decay, double gain, int per_part, ObserveStats stats) {
+  constexpr int D = 128, TS = kChan ? 32 : 64;         // slots per tile
+  constexpr int kTileB = TS * kKRow16, kBuf = kTileB * (kChan ? 2 : 1);
+  __shared__ __align__(16) uint8_t tiles[2][kBuf];
+  __shared__ __align__(16) float factor[2][TS];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int t16 = lane & 15, g4 = lane >> 4;
-  const int g = blockIdx.x % cv.Hkv, tile = blockIdx.x / cv.Hkv, b = blockIdx.z, G = cv.G;
+  const int g = blockIdx.x % cv.Hkv, b = blockIdx.z, G = cv.G;
+  const int ul = b * cv.Hkv + g;
+  const ObserveUnit un = observe_unit(cv, layer * cv.B * cv.Hkv + ul, T);
+  constexpr float kNothing = -1e30f;                    // reference of a lane that has seen no slot
+
+  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks + kObsItem - 1) / kObsItem;   // blocks are (token block, head)
+  const int item = nitems - 1 - (int)(blockIdx.x / cv.Hkv) % nitems, part = (int)(blockIdx.x / cv.Hkv) / nitems;
+  const int last_block = min((item + 1) * kObsItem, nblocks) - 1;
+  const int slots = min(T, last_block / G * 16 + 16);                // what the workgroup's last token sees
+  const int nt8 = (min(un.n8, slots) + TS - 1) / TS;
+  const int ntiles = nt8 + (max(0, slots - un.n8) + TS - 1) / TS;
+  const int first = part * per_part, last = min(ntiles, first + per_part);   // this workgroup's tiles
+  if (first >= last) return;
+
+  int tok0[kObsBlocks], head[kObsBlocks];
+  bool live[kObsBlocks];
+  half8_t qa[kObsBlocks][4];
+#pragma unroll
+  for (int r = 0; r < kObsBlocks; ++r) {
+    const int block = item * kObsItem + w * kObsBlocks + r;
+    live[r] = block < nblocks;
+    tok0[r] = (live[r] ? block : last_block) / G * 16;
+    head[r] = (live[r] ? block : last_block) % G;
+    const __half *row = q + (((size_t)b * T + min(tok0[r] + t16, T - 1)) * cv.Hkv * G + (size_t)g * G + head[r]) * D + g4 * 8;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qa[r][s] = __builtin_bit_cast(half8_t, *(const int4 *)(row + 32 * s));
+  }
+  const int see = __builtin_amdgcn_readfirstlane(tok0[kObsBlocks - 1] + 16);   // slots the wavefront's rows see at most
+  const int all = __builtin_amdgcn_readfirstlane(tok0[0] + 1);                 // and what every row of it sees
+
+  // thread (row, piece): sixteen channels of one slot out of every 32
+  const int lrow = tid >> 3, lc = tid & 7;
+  struct Piece {
+    confkv_v4i a, b;                                    // sixteen codes (twice), or sixteen fp16 values
+    unsigned short scale;
+  };
+  // (no branch around the loads: they would be waited for where its sides meet)
+  auto load = [&](int it, int k) -> Piece {
+    const bool is8 = it < nt8;
+    const int i = is8 ? min(it * TS + 32 * k + lrow, un.n8 - 1) : min((it - nt8) * TS + 32 * k + lrow, T - 1 - un.n8);
+    const unsigned row = is8 ? (unsigned)ring_row_u(un.h8, i, un.cap8) : (unsigned)ring_row(un.h16, i, un.cap16);
+    const char *p = (is8 ? (const char *)un.K8 : (const char *)un.K16) + (size_t)row * (is8 ? D : 2 * D) + lc * (is8 ? 16 : 32);
+    Piece r;
+    r.a = *(const confkv_v4i *)p;
+    r.b = *(const confkv_v4i *)(is8 ? p : p + 16);
+    r.scale = *(is8 && !kChan ? (const unsigned short *)un.KS + row : (const unsigned short *)q);
+    return r;
+  };
+  auto store = [&](int it, int k, const Piece &r) {
+    uint8_t *at = tiles[it & 1] + (32 * k + lrow) * kKRow16 + lc * 32;
+    half8_t *dst = (half8_t *)at, *low = (half8_t *)(at + (kChan ? kTileB : 0));
+    if (it < nt8) {
+      if constexpr (kChan) {
+        scale_codes(make_uint2((unsigned)r.a[0], (unsigned)r.a[1]), un.KS + lc * 16, dst[0], low[0]);
+        scale_codes(make_uint2((unsigned)r.a[2], (unsigned)r.a[3]), un.KS + lc * 16 + 8, dst[1], low[1]);
+      } else {
+        dst[0] = cvt_i8x8_f16x8((unsigned)r.a[0], (unsigned)r.a[1]);
+        dst[1] = cvt_i8x8_f16x8((unsigned)r.a[2], (unsigned)r.a[3]);
+      }
+      if (lc == 0) factor[it & 1][32 * k + lrow] = kChan ? sm : __half2float(__ushort_as_half(r.scale)) * sm;
+    } else {
+      dst[0] = __builtin_bit_cast(half8_t, r.a);
+      dst[1] = __builtin_bit_cast(half8_t, r.b);
+      if (lc == 0) factor[it & 1][32 * k + lrow] = sm;
+    }
+  };
+
+  float m[kObsBlocks], l[kObsBlocks];
+  double ld[kObsBlocks];
+#pragma unroll
+  for (int r = 0; r < kObsBlocks; ++r) { m[r] = kNothing; l[r] = 0.f; ld[r] = 0.0; }
+
+  Piece p0 = load(first, 0), p1 = TS > 32 ? load(first, 1) : p0;
+  for (int it = first; it < last; ++it) {
+    store(it, 0, p0);
+    if (TS > 32) store(it, 1, p1);
+    __syncthreads();                                    // tile `it` is there, and nobody reads tile it - 1 any more
+    p0 = load(min(it + 1, last - 1), 0);
+    if (TS > 32) p1 = load(min(it + 1, last - 1), 1);
+    const bool is8 = it < nt8;
+    const int tile0 = is8 ? it * TS : un.n8 + (it - nt8) * TS, lim = is8 ? un.n8 : T;
+#pragma unroll 1
+    for (int half = 0; half < TS / 32; ++half) {
+      const int base = tile0 + 32 * half;
+      if (base >= min(see, lim)) continue;              // (uniform over the wavefront) no row of it sees the slots
+      floatx4_t acc[kObsBlocks][2];
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        const uint8_t *krow = tiles[it & 1] + (32 * half + 16 * sb + t16) * kKRow16 + g4 * 16;
+#pragma unroll
+        for (int r = 0; r < kObsBlocks; ++r) acc[r][sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if (kChan && is8) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const half8_t kf = *(const half8_t *)(krow + kTileB + 64 * s);
+#pragma unroll
+            for (int r = 0; r < kObsBlocks; ++r) acc[r][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qa[r][s], acc[r][sb], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const half8_t kf = *(const half8_t *)(krow + 64 * s);
+#pragma unroll
+          for (int r = 0; r < kObsBlocks; ++r) acc[r][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qa[r][s], acc[r][sb], 0, 0, 0);
+        }
+      }
+      const float4 f4[2] = {*(const float4 *)&factor[it & 1][32 * half + 4 * g4], *(const float4 *)&factor[it & 1][32 * half + 16 + 4 * g4]};
+      const float f[2][4] = {{f4[0].x, f4[0].y, f4[0].z, f4[0].w}, {f4[1].x, f4[1].y, f4[1].z, f4[1].w}};
+      // edge: the diagonal, or a partial tile; a masked score is -inf
+      auto fold = [&](auto edge) {
+        // the score less a reference, in one rounding here and in the second kernel: what a dominating
+        // slot's score loses must be the same in its probability and in the normaliser
+        auto above = [&](int r, int sb, int i, float ref) {
+          const float v = fmaf(acc[r][sb][i], f[sb][i], -ref);
+          return edge && base + 16 * sb + 4 * g4 + i >= min(lim, tok0[r] + t16 + 1) ? -INFINITY : v;
+        };
+        float x[kObsBlocks][2][4], top[kObsBlocks];
+#pragma unroll
+        for (int r = 0; r < kObsBlocks; ++r) {
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              x[r][sb][i] = above(r, sb, i, m[r]);
+              top[r] = sb + i == 0 ? x[r][sb][i] : fmaxf(top[r], x[r][sb][i]);
+            }
+        }
+        auto sum = [&]() {
+#pragma unroll
+          for (int r = 0; r < kObsBlocks; ++r)
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+              l[r] += (__expf(x[r][sb][0]) + __expf(x[r][sb][1])) + (__expf(x[r][sb][2]) + __expf(x[r][sb][3]));
+        };
+        // a lane's reference only has to stay within a few units of its slots' maximum
+        if (__builtin_amdgcn_ballot_w64(fmaxf(top[0], top[kObsBlocks - 1]) > 5.0f)) {
+#pragma unroll
+          for (int r = 0; r < kObsBlocks; ++r) {
+            float mn = m[r];
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) mn = fmaxf(mn, above(r, sb, i, 0.f));
+            const float corr = __expf(m[r] - mn);
+            m[r] = mn;
+            l[r] *= corr;
+            ld[r] *= (double)corr;
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) x[r][sb][i] = above(r, sb, i, mn);
+          }
+          sum();
+        } else {
+          sum();                                        // (a copy of its own: joining the two would move every score)
+        }
+      };
+      if (base + 32 > min(all, lim)) fold(std::true_type{});
+      else fold(std::false_type{});
+    }
+#pragma unroll
+    for (int r = 0; r < kObsBlocks; ++r) { ld[r] += (double)l[r]; l[r] = 0.f; }
+  }
+#pragma unroll
+  for (int r = 0; r < kObsBlocks; ++r) {
+    float M = fmaxf(m[r], __shfl_xor(m[r], 16, kWave));
+    M = fmaxf(M, __shfl_xor(M, 32, kWave));
+    double L = ld[r] * (double)exp_nonpos(m[r] - M);
+    L += __shfl_xor(L, 16, kWave);
+    L += __shfl_xor(L, 32, kWave);
+    const int tok = tok0[r] + t16;
+    if (live[r] && g4 == 0) {
+      const size_t row = ((size_t)ul * G + head[r]) * observe_stride(T) + tok;
+      if (stats.row_sum) {
+        const size_t at = (size_t)part * cv.B * cv.Hkv * G * observe_stride(T) + row;
+        stats.row_ref[at] = M;
+        stats.row_sum[at] = L;
+      } else {
+        finish_row(stats, row, tok, T, M, L, decay, gain);
+      }
+    }
+  }
+}
+
+// The parts of the rows joined, in order.  (TS: slots per tile of the kernel above.)
+__global__ __launch_bounds__(kObsThreads) void observe_join_kernel(CacheView cv, int layer, int T, int TS, double decay, double gain,
+                                                                   int per_part, ObserveStats stats) {
+  const int stride = observe_stride(T), G = cv.G;
+  const size_t n_rows = (size_t)cv.B * cv.Hkv * G * stride, row = (size_t)blockIdx.x * kObsThreads + threadIdx.x;
+  if (row >= n_rows) return;
+  const int tok = (int)(row % stride), uh = (int)(row / stride), ul = uh / G;
+  const int n8 = min(cv.n8[layer * cv.B * cv.Hkv + ul], T);
+  const int nblocks = stride / 16 * G, item = (tok / 16 * G + uh % G) / kObsItem;
+  const int slots = min(T, (min((item + 1) * kObsItem, nblocks) - 1) / G * 16 + 16);
+  const int ntiles = (min(n8, slots) + TS - 1) / TS + (max(0, slots - n8) + TS - 1) / TS;
+  float M = -1e30f;
+  double L = 0.0;
+  for (int p = 0; p * per_part < ntiles; ++p) {
+    const float m = stats.row_ref[p * n_rows + row];
+    const double l = stats.row_sum[p * n_rows + row];
+    const float top = fmaxf(M, m);
+    L = L * (double)exp_nonpos(M - top) + l * (double)exp_nonpos(m - top);
+    M = top;
+  }
+  finish_row(stats, row, tok, T, M, L, decay, gain);
+}
+
+// Column sums.  A wavefront keeps 64 slots' keys in registers, its workgroup 256 slots'; the blocks of
+// 16 rows -- (token block, head), from the first that sees one of the slots, or a part of them --
+// come through LDS four at a time, staged once for the four wavefronts.  Each wavefront reading the
+// queries for itself asked 622 MB of L2 per layer of 3001 tokens and 32 heads, 5.2 TB/s, and 384 workgroups of
+// falling work ended late: 118 us, 90 now, of which the vector ALU (ten instructions a score) works 55.
+// Every probability goes into its column's sum in 64 bits by itself.
+struct MassTile {
+  int base, lim;                                       // slots [base, min(base + kMassWave, lim)) of subtile `at`
+  bool is8;
+};
+__device__ __forceinline__ MassTile mass_subtile(const ObserveUnit &un, int at, int T) {
+  const int nt8 = (un.n8 + kMassWave - 1) / kMassWave;
+  MassTile t;
+  t.is8 = at < nt8;
+  t.base = t.is8 ? at * kMassWave : un.n8 + (at - nt8) * kMassWave;
+  t.lim = t.is8 ? un.n8 : T;
+  return t;
+}
+// Blocks per part, and the first block that sees a slot of a subtile.
+__device__ __forceinline__ int mass_part_blocks(int parts, int G, int T) {
+  const int steps = ((T + 15) / 16 * G + kMassStep - 1) / kMassStep;
+  return (steps + parts - 1) / parts * kMassStep;
+}
+__device__ __forceinline__ int mass_first_block(const ObserveUnit &un, int sub, int G, int T) {
+  return mass_subtile(un, sub, T).base / 16 * G;
+}
+
+template <bool kChan>
+__global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(kChan ? 2 : 3, kChan ? 2 : 3)))
+void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, int ntiles, int width /* subtiles per workgroup */,
+                         int parts, ObserveStats stats) {
+  constexpr int D = 128, kSb = kMassWave / 16, kRows = 16 * kMassStep;
+  __shared__ __align__(16) uint8_t rows[2][kRows * kKRow16];
+  __shared__ __align__(16) float s_ref[2][kRows];
+  __shared__ __align__(16) double s_weight[2][kRows];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, g4 = lane >> 4;
+  const int g = blockIdx.x % cv.Hkv, y = blockIdx.x / cv.Hkv, tile = y % ntiles, part = y / ntiles, b = blockIdx.z, G = cv.G;
   const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
   const ObserveUnit un = observe_unit(cv, u, T);
-  const int ntiles8 = (un.n8 + kMassTile - 1) / kMassTile;
-  const bool is8 = tile < ntiles8;
-  const int base = is8 ? tile * kMassTile : un.n8 + (tile - ntiles8) * kMassTile, lim = is8 ? un.n8 : T;
-  if (base >= lim) return;                              // (the grid is sized for the worst rounding)
+  const int len = mass_part_blocks(parts, G, T);
+  const int first = max(part * len, mass_first_block(un, tile * width, G, T)), last = min((part + 1) * len, (T + 15) / 16 * G);
+  if (first >= last || mass_subtile(un, tile * width, T).base >= T) return;   // (the grid is sized for the worst rounding)
+  // (a tile of one or two subtiles: its wavefronts share the rows of a step, and their sums meet in LDS)
+  const int subs = min(width, (un.n8 + kMassWave - 1) / kMassWave + (T - un.n8 + kMassWave - 1) / kMassWave - tile * width);
+  const int across = subs >= 3 ? 4 : subs, shares = kObsWaves / across, share = w / across;
+  const MassTile mt = mass_subtile(un, tile * width + w % across, T);
+  const int base = mt.base, lim = mt.lim;
+  const bool mine = base < lim, is8 = mt.is8;
+
+  // rows of step `at`: thread (token, piece) takes sixteen bytes of each of its blocks' rows
+  const int ltok = tid >> 4, lc = tid & 15, stride = observe_stride(T);
+  static_assert(kMassStep == 4 && kRows == kWave, "four blocks of sixteen rows");
+  int4 raw0, raw1, raw2, raw3;                         // (an array would go through memory)
+  float rref = 0.f;
+  double rweight = 0.0;
+  int tb = first / G, h = first - tb * G;              // of the next block to request
+  int tbc = tb, hc = h;                                // of the next block to work on
+  const __half *q_lane = q + (size_t)g * G * D + lc * 8;
+  auto load = [&](int at) {
+    int my_tb = tb, my_h = h;
+    auto block = [&](int k) {
+      const int4 v = *(const int4 *)(q_lane + (((size_t)b * T + min(tb * 16 + ltok, T - 1)) * cv.Hkv * G + h) * D);
+      if (at + k + 1 < last) {                          // (a step's last blocks may not exist: the last one again, with weight 0)
+        const bool wrap = h + 1 == G;
+        h = wrap ? 0 : h + 1;
+        tb += wrap;
+      }
+      my_tb = tid >> 4 > k ? tb : my_tb;
+      my_h = tid >> 4 > k ? h : my_h;
+      return v;
+    };
+    raw0 = block(0);
+    raw1 = block(1);
+    raw2 = block(2);
+    raw3 = block(3);
+    if (w == 0) {
+      const size_t row = ((size_t)ul * G + my_h) * stride + my_tb * 16 + (tid & 15);
+      const bool there = at + (tid >> 4) < last;
+      const float r = stats.ref[row];
+      const double v = stats.weight[row];
+      rref = there ? r : 1e30f;
+      rweight = there ? v : 0.0;
+    }
+  };
+  load(first);
 
   half8_t kb[kSb][4], kl[kChan ? kSb : 1][4];
   float f[kSb];
@@ -276,7 +455,7 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
       }
       f[sb] = kChan ? sm : __half2float(un.KS[row]) * sm;
     } else {
-      const __half *src = un.K16 + (size_t)ring_row(un.h16, slot - un.n8, un.cap16) * D + g4 * 8;
+      const __half *src = un.K16 + (size_t)(mine ? ring_row(un.h16, slot - un.n8, un.cap16) : 0) * D + g4 * 8;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         kb[sb][s] = __builtin_bit_cast(half8_t, *(const int4 *)(src + 32 * s));
@@ -286,104 +465,137 @@ __global__ __launch_bounds__(kMassThreads) void observe_mass_kernel(CacheView cv
     }
   }
 
-  const int ntb = (T + 15) / 16, tb_first = base / 16, stride = observe_stride(T);
-  double wt[4], sum[kSb] = {};
-  const double step = pow_count(decay, 16 * kMassWaves);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tok = (ntb - 1 - w) * 16 + 4 * g4 + i;
-    wt[i] = tok < T && tok >= 0 ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) : 0.0;
-  }
-  half8_t qa[4];
-  float4 ref = {};
-  double2 inv0 = {}, inv1 = {};
-  const int row_step = cv.Hkv * G * D;                  // elements from a token's queries to the next token's
-  const __half *q_lane = q + ((size_t)b * T * cv.Hkv + g) * G * D + g4 * 8;
-  const size_t s_lane = (size_t)ul * G * stride + 4 * g4;
-  // queries and statistics of (token block, head), requested one step ahead
-  auto load = [&](int tb, int h) {
-    const __half *row = q_lane + (size_t)min(tb * 16 + t16, T - 1) * row_step + h * D;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) qa[s] = __builtin_bit_cast(half8_t, *(const int4 *)(row + 32 * s));
-    const size_t at = s_lane + (size_t)h * stride + tb * 16;
-    ref = *(const float4 *)(stats.ref + at);
-    inv0 = *(const double2 *)(stats.inv + at);
-    inv1 = *(const double2 *)(stats.inv + at + 2);
-  };
-  int tb = ntb - 1 - w;
-  if (tb >= tb_first) load(tb, 0);
-  for (bool first = true; tb >= tb_first; tb -= kMassWaves, first = false) {
-    if (!first) {
-      // (the first block may have held tokens past the end, whose weight is 0: start those over)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int tok = tb * 16 + 4 * g4 + i;
-        wt[i] = tok + 16 * kMassWaves >= T ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) : wt[i] * step;
+  double sum[kSb] = {};
+  for (int at = first, buf = 0; at < last; at += kMassStep, buf ^= 1) {
+    uint8_t *at_lane = rows[buf] + ltok * kKRow16 + lc * 16;
+    *(int4 *)at_lane = raw0;
+    *(int4 *)(at_lane + 16 * kKRow16) = raw1;
+    *(int4 *)(at_lane + 32 * kKRow16) = raw2;
+    *(int4 *)(at_lane + 48 * kKRow16) = raw3;
+    if (w == 0) { s_ref[buf][tid] = rref; s_weight[buf][tid] = rweight; }
+    __syncthreads();                                    // the step is there, and nobody reads the one before any more
+    if (at + kMassStep < last) load(at + kMassStep);
+    if (!mine) continue;
+    const int here = min(kMassStep, last - at);
+    // (one copy of the body: a cold instruction cache costs more than the loop)
+#pragma unroll 1
+    for (int k = 0; k < here; ++k) {
+      const int tok0 = tbc * 16;
+      if (++hc == G) {
+        hc = 0;
+        ++tbc;
       }
-    }
-    auto heads = [&](auto edge) {
-      for (int h = 0; h < G; ++h) {
-        floatx4_t acc[kSb];
+      if (tok0 + 15 < base || k % shares != share) continue;   // (uniform over the wavefront)
+      half8_t qa[4];
 #pragma unroll
-        for (int sb = 0; sb < kSb; ++sb) {
-          acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-          if constexpr (kChan) {
-            if (is8) {
+      for (int s = 0; s < 4; ++s) qa[s] = *(const half8_t *)(rows[buf] + (16 * k + t16) * kKRow16 + s * 64 + g4 * 16);
+      const float4 ref = *(const float4 *)&s_ref[buf][16 * k + 4 * g4];
+      const double2 w0 = *(const double2 *)&s_weight[buf][16 * k + 4 * g4], w1 = *(const double2 *)&s_weight[buf][16 * k + 4 * g4 + 2];
+      const float M[4] = {ref.x, ref.y, ref.z, ref.w};
+      const double wi[4] = {w0.x, w0.y, w1.x, w1.y};
+      floatx4_t acc[kSb];
 #pragma unroll
-              for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kl[sb][s], acc[sb], 0, 0, 0);
-            }
+      for (int sb = 0; sb < kSb; ++sb) {
+        acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if constexpr (kChan) {
+          if (is8) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kl[sb][s], acc[sb], 0, 0, 0);
           }
-#pragma unroll
-          for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kb[sb][s], acc[sb], 0, 0, 0);
         }
-        const float M[4] = {ref.x, ref.y, ref.z, ref.w};
-        const double wi[4] = {wt[0] * inv0.x, wt[1] * inv0.y, wt[2] * inv1.x, wt[3] * inv1.y};
-        if (h + 1 < G) load(tb, h + 1);
-        else if (tb - kMassWaves >= tb_first) load(tb - kMassWaves, 0);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int sb = 0; sb < kSb; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kb[sb][s], acc[sb], 0, 0, 0);
+      auto add = [&](auto edge) {
 #pragma unroll
         for (int sb = 0; sb < kSb; ++sb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -M[i]));   // (a reference may lie up to 5 below a score)
-            const int tok = tb * 16 + 4 * g4 + i;
-            // (rows past the end have no statistics)
             const double term = (double)e * wi[i];
-            sum[sb] += edge && (tok >= T || base + 16 * sb + t16 > tok) ? 0.0 : term;
+            sum[sb] += edge && base + 16 * sb + t16 > tok0 + 4 * g4 + i ? 0.0 : term;
           }
-      }
-    };
-    if (tb * 16 < base + kMassTile - 1 || tb == ntb - 1) heads(std::true_type{});
-    else heads(std::false_type{});
+      };
+      if (tok0 < base + kMassWave - 1) add(std::true_type{});
+      else add(std::false_type{});
+    }
   }
 #pragma unroll
   for (int sb = 0; sb < kSb; ++sb) {
     sum[sb] += __shfl_xor(sum[sb], 16, kWave);
     sum[sb] += __shfl_xor(sum[sb], 32, kWave);
-    if (g4 == 0) red[w][16 * sb + t16] = sum[sb];
   }
-  __syncthreads();
-  if (tid < kMassTile && base + tid < lim) {
-    double A = 0.0;
+  if (shares > 1) {
+    double *red = (double *)rows;                       // [wavefront][slot]
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kMassWaves; ++k) A += red[k][tid];
-    cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, base + tid)] = (float)A;
+    for (int sb = 0; sb < kSb; ++sb)
+      if (g4 == 0) red[w * kMassWave + 16 * sb + t16] = sum[sb];
+    __syncthreads();
+    if (share > 0) return;
+#pragma unroll
+    for (int sb = 0; sb < kSb; ++sb)
+      for (int k = 1; k < shares; ++k) sum[sb] += red[(w + k * across) * kMassWave + 16 * sb + t16];
   }
+  if (!mine) return;
+#pragma unroll
+  for (int sb = 0; sb < kSb; ++sb) {
+    const int slot = base + 16 * sb + t16;
+    if (g4 == 0 && slot < lim) {
+      if (parts > 1) stats.partial[((size_t)ul * parts + part) * stride + slot] = sum[sb];
+      else cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, slot)] = (float)sum[sb];
+    }
+  }
+}
+
+// The parts' column sums, in order.
+__global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, int layer, int T, int parts, ObserveStats stats) {
+  const int g = blockIdx.x % cv.Hkv, slot = blockIdx.x / cv.Hkv * kObsThreads + threadIdx.x, b = blockIdx.z;
+  const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
+  if (slot >= T) return;
+  const ObserveUnit un = observe_unit(cv, u, T);
+  const int nt8 = (un.n8 + kMassWave - 1) / kMassWave;
+  const int sub = slot < un.n8 ? slot / kMassWave : nt8 + (slot - un.n8) / kMassWave;
+  const int len = mass_part_blocks(parts, cv.G, T), from = mass_first_block(un, sub / kObsWaves * kObsWaves, cv.G, T) / len;
+  const int to = ((T + 15) / 16 * cv.G + len - 1) / len;               // (the last parts may be empty)
+  const double *src = stats.partial + (size_t)ul * parts * observe_stride(T) + slot;
+  double A = 0.0;
+#pragma unroll 8
+  for (int p = from; p < to; ++p) A += src[(size_t)p * observe_stride(T)];
+  cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, slot)] = (float)A;
 }
 
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
-  const int nblocks = (T + 15) / 16 * cv.G;
-  const dim3 rows(cv.Hkv * (((nblocks + kObsWaves - 1) / kObsWaves + 1) / 2), 1, cv.B);
-  const dim3 slots(cv.Hkv * ((T + kMassTile - 1) / kMassTile + 1), 1, cv.B);
-  const size_t n_rows = (size_t)cv.B * cv.Hkv * cv.G * observe_stride(T);
-  const ObserveStats stats = {(double *)scratch, scratch + 2 * n_rows};
-  if (cv.chan) {
-    hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, stats);
-    hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm, decay, gain, stats);
-  } else {
-    hipLaunchKernelGGL(observe_stats_kernel<false>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, stats);
-    hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kMassThreads), 0, stream, cv, layer, q, T, sm, decay, gain, stats);
+  const int nblocks = (T + 15) / 16 * cv.G, units = cv.B * cv.Hkv, nitems = (nblocks + kObsItem - 1) / kObsItem;
+  const int tile = cv.chan ? 32 : 64, per_part = observe_tiles_per_part(units, cv.G, T, tile);
+  const int row_parts = ((T + tile - 1) / tile + per_part) / per_part;
+  // A short prompt of few heads runs a subtile per workgroup, whose wavefronts share the rows: 64 tokens of 4 heads
+  // (four steps) 11.2 us with, 12.5 without; 130 tokens (nine) 18.2 with, 11.0 and 4.2 for the sum in parts without.
+  const bool few = T <= kMassTile && nblocks <= 4 * kMassStep;
+  const int width = few ? 1 : kObsWaves, parts = few ? 1 : observe_mass_parts(units, cv.G, T);
+  const int ntiles = (T + kMassWave * width - 1) / (kMassWave * width) + 1;
+  const dim3 rows(cv.Hkv * nitems * row_parts, 1, cv.B), slots(cv.Hkv * ntiles * parts, 1, cv.B);
+  const size_t n_rows = (size_t)units * cv.G * observe_stride(T);
+  // final statistics, then the partial ones of the rows, and over them those of the columns
+  ObserveStats stats{};
+  stats.weight = (double *)scratch;
+  stats.ref = scratch + 2 * n_rows;
+  stats.partial = (double *)scratch + (3 * n_rows + 1) / 2;
+  if (row_parts > 1) {
+    stats.row_sum = stats.partial;
+    stats.row_ref = (float *)(stats.row_sum + row_parts * n_rows);
   }
+  if (cv.chan) hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
+  else hipLaunchKernelGGL(observe_stats_kernel<false>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
+  if (row_parts > 1)
+    hipLaunchKernelGGL(observe_join_kernel, dim3((unsigned)((n_rows + kObsThreads - 1) / kObsThreads)), dim3(kObsThreads), 0, stream, cv, layer, T, tile, decay, gain, per_part, stats);
+  if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
+  else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
+  if (parts > 1)
+    hipLaunchKernelGGL(observe_sum_kernel, dim3(cv.Hkv * ((T + kObsThreads - 1) / kObsThreads), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, T, parts, stats);
   return hipGetLastError();
 }

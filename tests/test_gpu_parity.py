@@ -489,6 +489,35 @@ def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
     kv.close()
 
 
+@pytest.mark.parametrize("G,T0,W,scales", [
+    (4, 64, 32, "token"), (4, 65, 0, "token"),        # a subtile per workgroup, its wavefronts sharing the rows; one row block more: parts
+    (16, 129, 64, "token"), (1, 256, -1, "token"),    # one tile of the column kernel
+    (5, 257, 130, "token"),                           # ends of parts inside a token's heads; a tile of one subtile at the end
+    (2, 520, 8, "channel"),                           # rows cut into parts of 32-slot tiles
+    (1, 700, 100, "token"), (3, 1100, 37, "token"),   # and of 64-slot tiles, INT8 and FP16 ones; several column tiles
+])
+def test_observe_prompt_parts(lib, torch_cuda, G, T0, W, scales):
+    """One unit, so that both prompt-phase kernels cut their work into as many parts as they ever do.  1e-5 as in
+    test_observe_prompt_edges."""
+    torch = torch_cuda
+    D = 128
+    say(f"observe_prompt parts G={G} T0={T0} W={W} scales={scales}")
+    kv = _mk(lib, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64, protected_window=4,
+             n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales)
+    rng = np.random.default_rng(T0 + G)
+    K = rng.standard_normal((1, 1, T0, D)).astype(np.float16)
+    q = (rng.standard_normal((1, T0, G, D)) * 1.5).astype(np.float16)
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    u = O.load_prefill(K[0, 0], K[0, 0], W, scale_mode=scales)
+    O.observe_unit(u, q[0], 0, f32(1 / math.sqrt(D)), f32(0.9))
+    e_ref = u.ema.astype(np.float64)
+    e_err = np.abs(kv.export(0, 0, 0, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+    assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
+    assert kv.counters().device_errors == 0
+    kv.close()
+
+
 @pytest.mark.parametrize("G,T0,W", [(2, 40, 0), (4, 200, 33), (1, 97, 8)])
 def test_observe_prompt_saturated_channel(lib, torch_cuda, G, T0, W):
     """Channels that reach +-65504 under per-channel scales: 127 times their scale is above the largest fp16."""
