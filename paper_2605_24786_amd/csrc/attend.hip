@@ -1291,6 +1291,9 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
     in_code_units = false;
   };
+  // A wavefront with a single item has no earlier output to rescale (8 splits of a 1000-slot unit: 8.1 -> 7.85 us per
+  // launch).  Leaving the first of several items out as well cost units of two items per wavefront 1 %.
+  const bool several = nitems > kAttWaves;
   int tix = 0;
   for (int item = w; item < nitems; item += kAttWaves) {
     if (item >= ntiles) {
@@ -1340,7 +1343,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
         lrun[j] = fmaf(lrun[j], corr[j], p);
         pbias[j] *= corr[j];
       }
-      if (__builtin_amdgcn_ballot_w64(changed)) {
+      if (several && __builtin_amdgcn_ballot_w64(changed)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float c = rows_to_tile<G>(corr, i, g4);
@@ -1455,11 +1458,13 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
         lrun[j] *= corr[j];
         pbias[j] *= corr[j];
       }
+      if (__builtin_expect(several, 0)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float c = rows_to_tile<G>(corr, i, g4);
+        for (int i = 0; i < 4; ++i) {
+          const float c = rows_to_tile<G>(corr, i, g4);
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt) O[nt][i] *= c;
+          for (int nt = 0; nt < 8; ++nt) O[nt][i] *= c;
+        }
       }
     }
 #pragma unroll
