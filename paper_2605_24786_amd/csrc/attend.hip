@@ -1712,7 +1712,7 @@ bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n
   // preference order: want, want-1, .., 1 (fewer, always co-resident), then want+1, .. (more
   // splits shrink the LDS stash when a long unit does not fit otherwise)
   plan->two_launch = false;
-  plan->wide_rb = 0;
+  plan->wide_groups = 0;
   for (int k = 0; k < kAttendMaxSplits && !force_two_launch; ++k) {
     const int ns = k < want ? want - k : k + 1;
     // LDS is sized in steps of 256 slots so the occupancy query is cached across calls
@@ -1758,29 +1758,29 @@ bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n
   }
 }
 
-// Calls with more than 16 query rows per unit: row blocks (a power of two) and split count.  The
+// Calls with more than 16 query rows per unit: row groups (a power of two) and split count.  The
 // splits of a unit exchange partials inside the launch, so with more than one split the whole grid
 // must be resident (one workgroup per CU: the tile buffers take most of the LDS).
 bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits, AttendPlan *plan) {
   const DeviceLimits &lim = device_limits();
   if (!lim.ok || rows <= kChunkRows || rows > kWideMaxRows) return false;
-  int rb = 2;
-  while (rb * 16 < rows) rb *= 2;
+  int rg = 1;
+  while (rg * kWideRows < rows) rg *= 2;
   int ns = 1;
   while (ns * 2 <= kWideMaxSplits && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 256) ns *= 2;
   if (forced_splits > 0) {
     ns = 1;
     while (ns * 2 <= std::min(forced_splits, kWideMaxSplits) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
   }
-  AttendFn fn = rb == 2 ? (AttendFn)attend_wide_kernel<2> : rb == 4 ? (AttendFn)attend_wide_kernel<4> : (AttendFn)attend_wide_kernel<8>;
-  const size_t lds = attend_wide_lds_bytes(rb * 16, ns);
+  AttendFn fn = rg == 1 ? (AttendFn)attend_wide_kernel<1> : rg == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
+  const size_t lds = attend_wide_lds_bytes(rg * kWideRows, ns);
   if (lds > lim.max_lds || attend_occupancy(fn, lds) < 1) return false;
   plan->splits = ns;
   plan->stash_tokens = 0;
   plan->lds_bytes = lds;
   plan->mfma = true;
   plan->two_launch = false;
-  plan->wide_rb = rb;
+  plan->wide_groups = rg;
   return true;
 }
 
@@ -1808,9 +1808,9 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const At
                        plan.stash_tokens);
     return hipGetLastError();
   }
-  if (plan.wide_rb) {
-    AttendFn wide = plan.wide_rb == 2 ? (AttendFn)attend_wide_kernel<2>
-                    : plan.wide_rb == 4 ? (AttendFn)attend_wide_kernel<4> : (AttendFn)attend_wide_kernel<8>;
+  if (plan.wide_groups) {
+    AttendFn wide = plan.wide_groups == 1 ? (AttendFn)attend_wide_kernel<1>
+                    : plan.wide_groups == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
     a.dbg = nullptr;
     a.max_splits = kWideMaxSplits;
     hipLaunchKernelGGL(wide, grid, dim3(kAttThreads), plan.lds_bytes, stream, cv.len, cv.n8, cv.head16, cv.head8, a.layer * cv.B * cv.Hkv, cv.Hkv, a.kv_major, cv, a, plan.splits, 0);

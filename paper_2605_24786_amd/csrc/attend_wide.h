@@ -4,70 +4,87 @@
 // attend.hip, inside namespace confkv, after the helpers of the single-tile kernels.
 //
 // The call is DEFINED as tq single-token steps (see conf_kv_attend_chunk).  Rows r = token * G +
-// head are cut into RB blocks of 16; a workgroup of eight wavefronts is RB row blocks times
-// NS = 8 / RB tile streams.  The slice's K/V tiles (32 INT8 slots or 16 FP16 slots each) are
+// head are cut into RG groups of 32; a workgroup of eight wavefronts is RG row groups times
+// NS = 8 / RG tile streams.  The slice's K/V tiles (32 INT8 slots or 16 FP16 slots each) are
 // brought into LDS eight at a time, one per wavefront -- every K/V byte is read from memory
-// once per pass whatever the number of rows, and INT8 keys become fp16 once, when the tile is
-// stored -- and each wavefront then runs ITS row block
-// against the tiles of its stream: scores by matrix core, online softmax per row, P V by matrix
-// core.  No score is stashed (R x slots floats would not fit anywhere): after the splits have
-// exchanged their (m, l, o) per row, a second pass streams the keys again, recomputes the same
-// scores (same instructions, hence the same bits), turns them into exact probabilities with
-// the global (M, L), sums each slot's column over the rows (weights lambda^(tq-1-token)) and
-// updates the EMA.  Key bytes are therefore read twice, value bytes once.
+// once per pass whatever the number of rows, and INT8 codes become fp16 once, exactly, when the tile
+// is stored -- and each wavefront then runs ITS rows against the tiles of its stream.  Both
+// contractions are formed transposed: scores [slot][row], so that a lane holds slots of one query --
+// one reference and one sum per lane and 16 rows, and its probabilities are the operand of the output
+// contraction [channel][row] as they stand, with no trip through LDS.  No score is stashed (R x slots
+// floats would not fit anywhere): after the splits have exchanged their (m, l, o) per row, a second
+// pass gives every wavefront 32 slots at a time and all rows: it recomputes the same scores (the same
+// products in the same order), turns them into exact probabilities with the global (M, L), sums each
+// slot's column over the rows (weights lambda^(tq-1-token)) in its own registers and updates the
+// EMA: no barrier, no LDS but the rows' statistics.  Key bytes are therefore read twice, value bytes once.
+//
+// 64 rows against 64 units of 2064 slots in four splits: 38 us per launch (16 tokens of 4 heads; one sequence of 30 000
+// slots 130 us), of which 19 for the first pass -- 5 until the first tiles are in LDS, then a round of eight in
+// 3.5 to 5 -- 9 for the exchange and 7 for the second pass.  With sixteen rows per wavefront, the scores the other way
+// round, value codes converted by every reader and the second pass through the same tiles and barriers it was
+// 50 us: 20, 9 and 16 (and 208).  Requesting the second pass's keys ahead of the exchange makes the polls wait for them:
+// 41 us; three splits' partials at once 41.
 #pragma once
 
-// A tile in LDS: K as fp16 rows (the codes of an INT8 tile are converted once, by the wavefront
-// that stores the tile, not once per row block that reads it), V transposed as stored (its
-// conversion is three instructions per four codes and stays with the reader), the reading
-// wavefront's probability tile, and per slot the score factor and the value scale.
+// A tile in LDS: K as fp16 rows, in an order that makes the four slots a lane's transposed V words hold
+// adjacent: row 4 * (slot % 8) + slot / 8 of an INT8 tile, 4 * (slot % 4) + slot / 4 of an FP16 tile.
+// V transposed, 64 bytes per channel in that order (its 16-byte pieces xor-ed with the channel, groups of 16
+// channels 64 bytes further apart: neither stores nor reads then pile up on few banks); per row the
+// factor of the raw score and the value scale.
+constexpr int kWideRows = 32;                          // query rows per wavefront
+constexpr int kWideVGroup = 16 * 64 + 64;
 constexpr int kWideKBytes = kTile * kKRow16;
-constexpr int kWideCoreBytes = kWideKBytes + kVBytes + 16 * kPRow * 2;
-constexpr int kWideScaleBytes = 2 * kTile * 4;
-constexpr int kWideTileBytes = kWideCoreBytes + kWideScaleBytes;
+constexpr int kWideCoreBytes = kWideKBytes + 8 * kWideVGroup;
+constexpr int kWideTileBytes = kWideCoreBytes + 2 * kTile * 4;
+constexpr int kWidePartRow = 128 + 4;                  // floats per row of a wavefront's output partial
+static_assert(kWideRows * kWidePartRow * 4 <= kWideTileBytes, "a partial fits the wavefront's tile buffer");
 constexpr int kWideMaxRows = 128;
 constexpr int kWideMaxSplits = 8;
 
+// rows, and behind the tiles: per wavefront and row (m, l); per stream and row a weight; four words per row; the splits' (m, l)
 __host__ __device__ constexpr size_t attend_wide_lds_bytes(int R, int ns) {
-  return (size_t)kAttWaves * kWideTileBytes + ((size_t)3 * R + (size_t)kAttWaves * (R / 16) * kTile + (size_t)ns * R * 2) * 4 + 16;
+  return (size_t)kAttWaves * kWideTileBytes + ((size_t)kAttWaves * kWideRows * 3 + 4 * R + (size_t)ns * R * 2) * 4 + 16;
 }
 
-template <int RB>
+template <int RG>
 __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const int32_t *, int , int , int , CacheView cv, AttendLaunch a_in, int ns, int /*unused*/) {
+void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns, int /*unused*/) {
+  // (the unit's counters are requested first, from arguments that arrive in registers: see attend_mfma_kernel)
+  const int w_words = (((threadIdx.x & 3) == 0 ? w_len : (threadIdx.x & 3) == 1 ? w_n8 : (threadIdx.x & 3) == 2 ? w_h16 : w_h8))
+      [w_unit0 + blockIdx.z * w_hkv + (w_kvm ? blockIdx.x : blockIdx.y)];
   const AttendLaunch a = resolve_launch(cv, a_in);
-  constexpr int D = 128, NS = kAttWaves / RB, R = RB * 16;
-  constexpr int kPartFloats = 16 * D + 32;                   // a wavefront's (o, m, l) for the stream merge
-  static_assert((NS - 1) * RB * kPartFloats * 4 <= kAttWaves * kWideTileBytes, "stream merge fits the tile buffers");
+  constexpr int D = 128, NS = kAttWaves / RG, R = RG * kWideRows, RB = R / 16;
   extern __shared__ __align__(16) float smem[];
   uint8_t *tiles = (uint8_t *)smem;
-  float *Mrow = (float *)(tiles + kAttWaves * kWideTileBytes);   // [R] global maximum of a row
-  float *Irow = Mrow + R;                                        // [R] 1 / global normaliser
-  float *Frow = Irow + R;                                        // [R] the same times the row's mass weight
-  float *mass = Frow + R;                                        // [8 tiles][RB][32] column sums per tile and row block
-  float *pml = mass + kAttWaves * RB * kTile;                    // [ns][R][2] gathered statistics
+  float *stat_m = (float *)(tiles + kAttWaves * kWideTileBytes);   // [wavefront][32] reference of a row in a stream
+  float *stat_l = stat_m + kAttWaves * kWideRows;                  // [wavefront][32] sum of its exponentials
+  float *weight = stat_l + kAttWaves * kWideRows;                  // [wavefront][32] what its partial is multiplied by
+  float *Mrow = weight + kAttWaves * kWideRows;                    // [R] maximum of a row: the split's, then the unit's
+  float *Irow = Mrow + R;                                          // [R] 1 / normaliser
+  float *Frow = Irow + R;                                          // [R] the same times the row's mass weight
+  int *Srow = (int *)(Frow + R);                                   // [R] slots the row sees (padding rows: 0x7fffffff)
+  float *pml = (float *)(Srow + R);                                // [ns][R][2] gathered statistics
   __shared__ int s_ok;
+  constexpr float kNothing = -1e30f;                               // reference of a row that has seen no slot
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int rb = w % RB, st = w / RB;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = w % RG, st = w / RG;
   const int tq = a.tq, gq = a.gq;
-  const float NEG = -INFINITY;
   const float sm = a.sm_scale;
   const int t16 = lane & 15, g4 = lane >> 4;
   const int c8 = lane & 7, r8 = lane >> 3;
   const int c16 = lane & 15, r4 = lane >> 4;
-  const Slice sl = make_slice(cv, a, ns, 0x7fffffff);
+  const Slice sl = make_slice(cv, a, ns, 0x7fffffff, &w_words);
 
-  // rows of this wavefront in the accumulator layout: element i of a lane is row 4 * g4 + i of the block
-  int rowc[4], seen[4];
-  bool okc[4];
+  // a lane's rows: query t16 of each of the wavefront's two blocks.  The row of token t sees slots below
+  // n - tq + t + 1; padding rows carry a zero query, see everything and weigh nothing.
+  int seen[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    rowc[i] = rb * 16 + 4 * g4 + i;
-    const int tok = rowc[i] / gq;
-    okc[i] = tok < tq;
-    seen[i] = sl.n - tq + tok + 1;               // the row of token t sees slots below n - tq + t + 1
+  for (int r = 0; r < 2; ++r) {
+    const int tok = (rg * kWideRows + 16 * r + t16) / gq;
+    seen[r] = tok < tq ? sl.n - tq + tok + 1 : 0x7fffffff;
   }
+  const int see_all = sl.n - tq + 1;                               // slots below this are seen by every row
 
   const int8_t *K8 = cv.k8 + (size_t)sl.u * cv.cap8 * D;
   const int8_t *V8 = cv.v8 + (size_t)sl.u * cv.cap8 * D;
@@ -85,7 +102,7 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
     unsigned short ks0, ks1, vs0, vs1;
   };
   // branch-free loads (rows past the slice re-read its last row and are masked where they are used)
-  auto load_item = [&](int it, bool with_v) -> TileRegs {
+  auto load_item = [&](int it) -> TileRegs {
     TileRegs t = {};
     if (it < ntiles) {
       const int base = sl.lo8 + it * kTile, last = sl.hi8 - 1;
@@ -99,20 +116,16 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
       t.k1 = ld_stream16(K8 + o1);
       t.k2 = ld_stream16(K8 + o2);
       t.k3 = ld_stream16(K8 + o3);
-      if (with_v) {
-        t.v0 = ld_stream16(V8 + o0);
-        t.v1 = ld_stream16(V8 + o1);
-        t.v2 = ld_stream16(V8 + o2);
-        t.v3 = ld_stream16(V8 + o3);
-      }
+      t.v0 = ld_stream16(V8 + o0);
+      t.v1 = ld_stream16(V8 + o1);
+      t.v2 = ld_stream16(V8 + o2);
+      t.v3 = ld_stream16(V8 + o3);
       const unsigned j0 = (unsigned)ring_row_u(h8, min(base + t16, last), cap8);
       const unsigned j1 = (unsigned)ring_row_u(h8, min(base + 16 + t16, last), cap8);
       t.ks0 = ((const unsigned short *)KS)[j0];
       t.ks1 = ((const unsigned short *)KS)[j1];
-      if (with_v) {
-        t.vs0 = ((const unsigned short *)VS)[j0];
-        t.vs1 = ((const unsigned short *)VS)[j1];
-      }
+      t.vs0 = ((const unsigned short *)VS)[j0];
+      t.vs1 = ((const unsigned short *)VS)[j1];
     } else {
       const int base = sl.lo16 + 16 * (it - ntiles), last = sl.hi16 - 1;
       const int h16 = sl.h16, cap16 = cv.cap16, n8 = sl.n8;
@@ -131,18 +144,15 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
       t.k1 = ld_stream16(n1 >= 0 ? kn + n1 * tok : K16 + o1);
       t.k2 = ld_stream16(n2 >= 0 ? kn + n2 * tok : K16 + o2);
       t.k3 = ld_stream16(n3 >= 0 ? kn + n3 * tok : K16 + o3);
-      if (with_v) {
-        t.v0 = ld_stream16(n0 >= 0 ? vn + n0 * tok : V16 + o0);
-        t.v1 = ld_stream16(n1 >= 0 ? vn + n1 * tok : V16 + o1);
-        t.v2 = ld_stream16(n2 >= 0 ? vn + n2 * tok : V16 + o2);
-        t.v3 = ld_stream16(n3 >= 0 ? vn + n3 * tok : V16 + o3);
-      }
+      t.v0 = ld_stream16(n0 >= 0 ? vn + n0 * tok : V16 + o0);
+      t.v1 = ld_stream16(n1 >= 0 ? vn + n1 * tok : V16 + o1);
+      t.v2 = ld_stream16(n2 >= 0 ? vn + n2 * tok : V16 + o2);
+      t.v3 = ld_stream16(n3 >= 0 ? vn + n3 * tok : V16 + o3);
     }
     return t;
   };
-  // registers -> this wavefront's LDS buffer: K rows as they are, V transposed to [channel][slot],
-  // and per slot the factor of the raw score (key scale times softmax scale) and the value scale
-  auto store_item = [&](int it, const TileRegs &tr, bool with_v) {
+  // registers -> this wavefront's LDS buffer
+  auto store_item = [&](int it, const TileRegs &tr) {
     uint8_t *Kt = tiles + (size_t)w * kWideTileBytes;
     uint8_t *Vt = Kt + kWideKBytes;
     float *sc = (float *)(Kt + kWideCoreBytes);
@@ -153,261 +163,293 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
         dst[0] = cvt_i8x8_f16x8((unsigned)k.x, (unsigned)k.y);
         dst[1] = cvt_i8x8_f16x8((unsigned)k.z, (unsigned)k.w);
       };
-      put_k(r8, tr.k0);
-      put_k(8 + r8, tr.k1);
-      put_k(16 + r8, tr.k2);
-      put_k(24 + r8, tr.k3);
-      if (with_v) {
+      put_k(4 * r8, tr.k0);
+      put_k(4 * r8 + 1, tr.k1);
+      put_k(4 * r8 + 2, tr.k2);
+      put_k(4 * r8 + 3, tr.k3);
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-          const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-          const unsigned t0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u), t1 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
-          const unsigned t2 = __builtin_amdgcn_perm(x3, x2, 0x05010400u), t3 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
-          const unsigned o0 = __builtin_amdgcn_perm(t2, t0, 0x05040100u), o1 = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
-          const unsigned o2 = __builtin_amdgcn_perm(t3, t1, 0x05040100u), o3 = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
-          uint8_t *dst = Vt + (16 * c8 + 4 * q4) * kVRow + kVSkew(c8) + 4 * r8;
-          *(unsigned *)(dst) = o0;
-          *(unsigned *)(dst + kVRow) = o1;
-          *(unsigned *)(dst + 2 * kVRow) = o2;
-          *(unsigned *)(dst + 3 * kVRow) = o3;
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
+        const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
+        const unsigned t0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u), t1 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
+        const unsigned t2 = __builtin_amdgcn_perm(x3, x2, 0x05010400u), t3 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
+        // byte r of o[e] is slot 8r + r8 at channel 16*c8 + 4*q4 + e: K rows 4*r8 .. 4*r8 + 3
+        const unsigned o[4] = {__builtin_amdgcn_perm(t2, t0, 0x05040100u), __builtin_amdgcn_perm(t2, t0, 0x07060302u),
+                               __builtin_amdgcn_perm(t3, t1, 0x05040100u), __builtin_amdgcn_perm(t3, t1, 0x07060302u)};
+        // K rows 16 sb + 4 g + i are piece g, half sb of the channel's 64 bytes; r8 = 4 sb + g
+        uint8_t *dst = Vt + c8 * kWideVGroup + 4 * q4 * 64 + (((r8 & 3) ^ q4) * 16) + (r8 >> 2) * 8;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          half2_t lo, hi;
+          cvt_i8x4_f16x4(o[e], lo, hi);
+          *(uint2 *)(dst + 64 * e) = make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
         }
       }
       if (g4 == 0) {
-        sc[t16] = __half2float(__ushort_as_half(tr.ks0)) * sm;
-        sc[16 + t16] = __half2float(__ushort_as_half(tr.ks1)) * sm;
-        if (with_v) {
-          sc[kTile + t16] = __half2float(__ushort_as_half(tr.vs0));
-          sc[kTile + 16 + t16] = __half2float(__ushort_as_half(tr.vs1));
-        }
+        const int row = 4 * (t16 & 7) + (t16 >> 3);              // of slot t16; slot 16 + t16 is two further
+        sc[row] = __half2float(__ushort_as_half(tr.ks0)) * sm;
+        sc[row + 2] = __half2float(__ushort_as_half(tr.ks1)) * sm;
+        sc[kTile + row] = __half2float(__ushort_as_half(tr.vs0));
+        sc[kTile + row + 2] = __half2float(__ushort_as_half(tr.vs1));
       }
     } else {
-      *(int4 *)(Kt + (r4)*kKRow16 + c16 * 16) = tr.k0;
-      *(int4 *)(Kt + (4 + r4) * kKRow16 + c16 * 16) = tr.k1;
-      *(int4 *)(Kt + (8 + r4) * kKRow16 + c16 * 16) = tr.k2;
-      *(int4 *)(Kt + (12 + r4) * kKRow16 + c16 * 16) = tr.k3;
-      if (with_v) {
+      *(int4 *)(Kt + (4 * r4) * kKRow16 + c16 * 16) = tr.k0;
+      *(int4 *)(Kt + (4 * r4 + 1) * kKRow16 + c16 * 16) = tr.k1;
+      *(int4 *)(Kt + (4 * r4 + 2) * kKRow16 + c16 * 16) = tr.k2;
+      *(int4 *)(Kt + (4 * r4 + 3) * kKRow16 + c16 * 16) = tr.k3;
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-          const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-          unsigned *dst = (unsigned *)(Vt + (8 * c16 + 2 * q4) * kVRow + kVSkew(c16 >> 1) + 8 * r4);
-          dst[0] = __builtin_amdgcn_perm(x1, x0, 0x05040100u);
-          dst[1] = __builtin_amdgcn_perm(x3, x2, 0x05040100u);
-          dst[kVRow / 4] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
-          dst[kVRow / 4 + 1] = __builtin_amdgcn_perm(x3, x2, 0x07060302u);
-        }
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
+        const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
+        // half r of a channel's word is slot 4r + r4: K rows 4*r4 .. 4*r4 + 3, piece r4 of eight bytes
+        uint8_t *dst = Vt + (c16 >> 1) * kWideVGroup + (8 * (c16 & 1) + 2 * q4) * 64 + r4 * 8;
+        *(uint2 *)dst = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x05040100u), __builtin_amdgcn_perm(x3, x2, 0x05040100u));
+        *(uint2 *)(dst + 64) = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x07060302u), __builtin_amdgcn_perm(x3, x2, 0x07060302u));
       }
     }
   };
 
-  // A operand of the score contraction: this wavefront's 16 query rows
-  half8_t qa[4];
-  {
-    const int ra = rb * 16 + t16;
-    const int q_tok = ra / gq, q_head = ra - q_tok * gq;
-    const __half *qrow = a.q + ((((size_t)sl.b * a.tq + q_tok) * cv.Hkv + sl.g) * gq + q_head) * D;
+  // query rows as a matrix-core operand: lane (row t16, channels 32 g4 + 8 s + [0, 8))
+  auto load_rows = [&](int block, half8_t (&qf)[4]) {
+    const int row = block * 16 + t16, tok = row / gq, head = row - tok * gq;
+    const __half *src = a.q + ((((size_t)sl.b * tq + min(tok, tq - 1)) * cv.Hkv + sl.g) * gq + head) * D + g4 * 32;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      int4 raw = make_int4(0, 0, 0, 0);
-      if (q_tok < tq) raw = *(const int4 *)(qrow + g4 * 32 + 8 * s);
-      qa[s] = __builtin_bit_cast(half8_t, raw);
+      const confkv_v4i v = *(const confkv_v4i *)(src + 8 * s);
+      qf[s] = __builtin_bit_cast(half8_t, tok < tq ? v : confkv_v4i{0, 0, 0, 0});
     }
-  }
-  // raw scores of the 16 rows against the 16 slots [16 sb, 16 sb + 16) of INT8 tile buffer Kt,
-  // or against the 16 slots of an FP16 tile; masked entries come back as -inf
-  auto scores8 = [&](const uint8_t *Kt, const float *sc, int base, int sb, float (&sv)[4]) {
-    const uint8_t *krow = Kt + (16 * sb + t16) * kKRow16 + g4 * 64;
-    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], *(const half8_t *)(krow + 16 * s), acc, 0, 0, 0);
-    const int slot = base + 16 * sb + t16;
-    const float f = sc[16 * sb + t16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sv[i] = (slot < sl.hi8 && okc[i] && slot < seen[i]) ? acc[i] * f : NEG;
-  };
-  auto scores16 = [&](const uint8_t *Kt, int base, float (&sv)[4]) {
-    const uint8_t *krow = Kt + t16 * kKRow16 + g4 * 64;
-    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], *(const half8_t *)(krow + 16 * s), acc, 0, 0, 0);
-    const int slot = base + t16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sv[i] = (slot < sl.hi16 && okc[i] && slot < seen[i]) ? acc[i] * sm : NEG;
   };
 
   // ---------------- pass 1: online softmax and output per row ----------------
   TileRegs tr = {};
-  if (w < nitems) tr = load_item(w, true);
-  append_new_token<D>(cv, a, sl, ns);
-  _Float16 *Pb = (_Float16 *)(tiles + (size_t)w * kWideTileBytes + kWideKBytes + kVBytes);   // [16][kPRow], this wavefront's own
-  for (int i = lane; i < 16 * kPRow / 2; i += kWave) ((unsigned *)Pb)[i] = 0u;
-  floatx4_t O[8];
+  if (w < nitems) tr = load_item(w);
+  half8_t qa[2][4];
+  load_rows(2 * rg, qa[0]);
+  load_rows(2 * rg + 1, qa[1]);
+  floatx4_t O[2][8];                                       // [block][channel group]: channels 16 nt + 4 g4 + [0, 4) of query t16
+  float m[2], l[2];
 #pragma unroll
-  for (int nt = 0; nt < 8; ++nt) O[nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  float mrun[4], lrun[4], pbias[4];
+  for (int r = 0; r < 2; ++r) {
+    m[r] = kNothing;
+    l[r] = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { mrun[i] = NEG; lrun[i] = 0.f; pbias[i] = 0.f; }
+    for (int nt = 0; nt < 8; ++nt) O[r][nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  // One 16-slot half of a tile is N = 4 scores per lane and block; an INT8 tile is two of them.  slot(sb, i) is the
+  // slot of score i of half sb; the raw scores come in acc, factors and value scales in f and vs.  Leaves the probabilities
+  // times the value scales, rounded to fp16, in p.
+  auto soften = [&](auto halves, const floatx4_t (&acc)[2][2], const float (&f)[2][4], const float (&vs)[2][4], int lim, bool edge,
+                    auto slot, half8_t (&p)[2]) {
+    constexpr int H = decltype(halves)::value;
+    auto above = [&](int r, int sb, int i, float ref) { return fmaf(acc[r][sb][i], f[sb][i], -ref); };
+    float x[2][H][4], top = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int sb = 0; sb < H; ++sb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[r][sb][i] = above(r, sb, i, m[r]);
+    auto mask = [&]() {
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int sb = 0; sb < H; ++sb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (slot(sb, i) >= min(lim, seen[r])) x[r][sb][i] = -INFINITY;
+    };
+    if (edge) mask();
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int sb = 0; sb < H; ++sb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) top = fmaxf(top, x[r][sb][i]);
+    // lazy reference: rescale only when a score of the tile exceeds it by more than this (e^4 times the
+    // largest fp16 value scale still fits fp16)
+    if (__builtin_amdgcn_ballot_w64(top > 4.0f)) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        float mn = -INFINITY;
+#pragma unroll
+        for (int sb = 0; sb < H; ++sb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mn = fmaxf(mn, edge && slot(sb, i) >= min(lim, seen[r]) ? -INFINITY : above(r, sb, i, 0.f));
+        mn = fmaxf(mn, __shfl_xor(mn, 16, kWave));
+        mn = fmaxf(m[r], fmaxf(mn, __shfl_xor(mn, 32, kWave)));
+        const float corr = __expf(m[r] - mn);
+        m[r] = mn;
+        l[r] *= corr;
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) O[r][nt] *= corr;
+#pragma unroll
+        for (int sb = 0; sb < H; ++sb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[r][sb][i] = above(r, sb, i, mn);
+      }
+      if (edge) mask();
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int sb = 0; sb < H; ++sb) {
+        float e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          e[i] = __expf(x[r][sb][i]);
+          p[r][4 * sb + i] = (_Float16)(e[i] * vs[sb][i]);
+        }
+        l[r] += (e[0] + e[1]) + (e[2] + e[3]);
+      }
+  };
 
   for (int sup = 0; sup < nsup; ++sup) {
     const int mine = sup * kAttWaves + w;
     if (sup > 0) __syncthreads();                      // everybody has left the previous eight tiles
-    if (mine < nitems) store_item(mine, tr, true);
+    if (mine < nitems) store_item(mine, tr);
     __syncthreads();
-    if (mine + kAttWaves < nitems) tr = load_item(mine + kAttWaves, true);
+    if (mine + kAttWaves < nitems) tr = load_item(mine + kAttWaves);
+#pragma unroll 1
     for (int j = st; j < kAttWaves; j += NS) {
       const int it = sup * kAttWaves + j;
       if (it >= nitems) break;
       const uint8_t *Kt = tiles + (size_t)j * kWideTileBytes;
       const uint8_t *Vt = Kt + kWideKBytes;
       const float *sc = (const float *)(Kt + kWideCoreBytes);
+      const uint8_t *krow = Kt + t16 * kKRow16 + g4 * 64;
+      floatx4_t acc[2][2];                             // [block][half]
+      half8_t p[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[r][0] = acc[r][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const half8_t kf = *(const half8_t *)(krow + 16 * s);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) acc[r][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qa[r][s], acc[r][0], 0, 0, 0);
+      }
       if (it < ntiles) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const half8_t kf = *(const half8_t *)(krow + 16 * kKRow16 + 16 * s);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) acc[r][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qa[r][s], acc[r][1], 0, 0, 0);
+        }
         const int base = sl.lo8 + it * kTile;
-        float sv[2][4];
-        scores8(Kt, sc, base, 0, sv[0]);
-        scores8(Kt, sc, base, 1, sv[1]);
-        // lazy reference: rescale only when a score of the tile exceeds it by more than kSlack
-        constexpr float kSlack = 4.0f;
-        bool grow = false;
-        float lm[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          lm[i] = fmaxf(sv[0][i], sv[1][i]);
-          grow |= lm[i] > mrun[i] + kSlack;
-        }
-        if (__builtin_amdgcn_ballot_w64(grow)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float mn = fmaxf(mrun[i], row16_max(lm[i]));
-            const float corr = (mn == NEG) ? 1.f : __expf(mrun[i] - mn);
-            mrun[i] = mn;
-            lrun[i] *= corr;
-            pbias[i] *= corr;
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt) O[nt][i] *= corr;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-          for (int sb = 0; sb < 2; ++sb) {
-            const float p = (sv[sb][i] == NEG) ? 0.f : __expf(sv[sb][i] - mrun[i]);
-            lrun[i] += p;
-            const _Float16 ph = (_Float16)(p * sc[kTile + 16 * sb + t16]);
-            pbias[i] += (float)ph;                     // exactly what the matrix core will see
-            const int tau = 16 * sb + t16;
-            Pb[(4 * g4 + i) * kPRow + 4 * (tau & 7) + (tau >> 3)] = ph;
-          }
-        }
-        wave_lds_sync();
-        const half8_t pa = *(const half8_t *)(Pb + t16 * kPRow + 8 * g4);
+        const float4 f0 = *(const float4 *)(sc + 4 * g4), f1 = *(const float4 *)(sc + 16 + 4 * g4);
+        const float4 v0 = *(const float4 *)(sc + kTile + 4 * g4), v1 = *(const float4 *)(sc + kTile + 16 + 4 * g4);
+        const float f[2][4] = {{f0.x, f0.y, f0.z, f0.w}, {f1.x, f1.y, f1.z, f1.w}};
+        const float vs[2][4] = {{v0.x, v0.y, v0.z, v0.w}, {v1.x, v1.y, v1.z, v1.w}};
+        soften(std::integral_constant<int, 2>{}, acc, f, vs, sl.hi8, base + kTile > min(sl.hi8, see_all),
+               [&](int sb, int i) { return base + 8 * i + 4 * sb + g4; }, p);
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-          const unsigned *vb = (const unsigned *)(Vt + (16 * nt + t16) * kVRow + kVSkew(nt) + 8 * g4);
-          O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, cvt_i8x8_f16x8_biased(vb[0], vb[1]), O[nt], 0, 0, 0);
+          const half8_t vf = *(const half8_t *)(Vt + nt * kWideVGroup + t16 * 64 + ((g4 ^ (t16 >> 2)) * 16));
+#pragma unroll
+          for (int r = 0; r < 2; ++r) O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, p[r], O[r][nt], 0, 0, 0);
         }
-        wave_lds_sync();
       } else {
         const int base = sl.lo16 + 16 * (it - ntiles);
-        float sv[4];
-        scores16(Kt, base, sv);
-        bool changed = false;
-        float corr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float mn = fmaxf(mrun[i], row16_max(sv[i]));
-          corr[i] = (mn == NEG) ? 1.f : __expf(mrun[i] - mn);
-          changed |= (mn != mrun[i]);
-          mrun[i] = mn;
-          const float p = (sv[i] == NEG) ? 0.f : __expf(sv[i] - mn);
-          Pb[(4 * g4 + i) * kPRow + 4 * (t16 & 3) + (t16 >> 2)] = (_Float16)p;
-          lrun[i] = fmaf(lrun[i], corr[i], p);
-          pbias[i] *= corr[i];
-        }
-        if (__builtin_amdgcn_ballot_w64(changed)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt) O[nt][i] *= corr[i];
-        }
-        wave_lds_sync();
-        const half4_t pa = *(const half4_t *)(Pb + t16 * kPRow + 4 * g4);
+        const float f[2][4] = {{sm, sm, sm, sm}, {sm, sm, sm, sm}}, vs[2][4] = {{1.f, 1.f, 1.f, 1.f}, {1.f, 1.f, 1.f, 1.f}};
+        soften(std::integral_constant<int, 1>{}, acc, f, vs, sl.hi16, base + 16 > min(sl.hi16, see_all),
+               [&](int, int i) { return base + 4 * i + g4; }, p);
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-          const unsigned *vb = (const unsigned *)(Vt + (16 * nt + t16) * kVRow + kVSkew(nt) + 8 * g4);
-          const uint2 v2 = make_uint2(vb[0], vb[1]);
-          O[nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(pa, __builtin_bit_cast(half4_t, v2), O[nt], 0, 0, 0);
+          const half4_t vf = *(const half4_t *)(Vt + nt * kWideVGroup + t16 * 64 + g4 * 8);
+#pragma unroll
+          for (int r = 0; r < 2; ++r)
+            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{p[r][0], p[r][1], p[r][2], p[r][3]}, O[r][nt], 0, 0, 0);
         }
-        wave_lds_sync();
       }
     }
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    lrun[i] = row16_sum(lrun[i]);
-    const float bias = row16_sum(pbias[i]) * kCodeBias;   // what the biased INT8 values added per channel
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) O[nt][i] -= bias;
-  }
 
-  // ---------------- the tile streams of a row block merge in LDS ----------------
+  append_new_token<D>(cv, a, sl, ns);                    // (nobody reads the appended rows back in this launch)
+
+  // ---------------- the tile streams of a row merge in LDS ----------------
   if (tid == 0) s_ok = 1;
   __syncthreads();                                       // the tile buffers are free
-  if (NS > 1) {
-    if (st > 0) {
-      float *part = (float *)tiles + (size_t)((st - 1) * RB + rb) * kPartFloats;
+  {
+    float *part = (float *)(tiles + (size_t)w * kWideTileBytes);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) part[(4 * g4 + i) * D + 16 * nt + t16] = O[nt][i];
-        if (t16 == 0) { part[16 * D + 4 * g4 + i] = mrun[i]; part[16 * D + 16 + 4 * g4 + i] = lrun[i]; }
+    for (int r = 0; r < 2; ++r) {
+      l[r] += __shfl_xor(l[r], 16, kWave);
+      l[r] += __shfl_xor(l[r], 32, kWave);
+      if (g4 == 0) {
+        stat_m[w * kWideRows + 16 * r + t16] = m[r];
+        stat_l[w * kWideRows + 16 * r + t16] = l[r];
       }
-    }
-    __syncthreads();
-    if (st == 0) {
-      for (int s = 1; s < NS; ++s) {
-        const float *ps = (const float *)tiles + (size_t)((s - 1) * RB + rb) * kPartFloats;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float m2 = ps[16 * D + 4 * g4 + i], l2 = ps[16 * D + 16 + 4 * g4 + i];
-          const float M = fmaxf(mrun[i], m2);
-          const float f1 = mrun[i] > NEG ? __expf(mrun[i] - M) : 0.f, f2 = m2 > NEG ? __expf(m2 - M) : 0.f;
-          lrun[i] = fmaf(lrun[i], f1, m2 > NEG ? l2 * f2 : 0.f);
-#pragma unroll
-          for (int nt = 0; nt < 8; ++nt)
-            O[nt][i] = fmaf(O[nt][i], f1, m2 > NEG ? ps[(4 * g4 + i) * D + 16 * nt + t16] * f2 : 0.f);
-          mrun[i] = M;
-        }
-      }
+      for (int nt = 0; nt < 8; ++nt) *(floatx4_t *)&part[(16 * r + t16) * kWidePartRow + 16 * nt + 4 * g4] = O[r][nt];
     }
   }
+  __syncthreads();
+  const size_t row0 = ((size_t)sl.ul * a.max_splits + sl.j) * R;      // this split's first row in the exchange arrays
+  const unsigned tag = tag_of(a);
+  if (tid < R) {
+    const int at = (tid / kWideRows) * kWideRows + tid % kWideRows;   // wavefront (stream s, group): s * RG + tid / 32
+    float M = kNothing, L = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) M = fmaxf(M, stat_m[s * R + at]);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const float e = __expf(stat_m[s * R + at] - M);
+      weight[s * R + at] = e;
+      L = fmaf(stat_l[s * R + at], e, L);
+    }
+    const int tok = tid / gq;
+    Srow[tid] = tok < tq ? sl.n - tq + tok + 1 : 0x7fffffff;
+    if (ns > 1) {
+      st_tagged(&a.part_ml[(row0 + tid) * 2], tag, M);
+      st_tagged(&a.part_ml[(row0 + tid) * 2 + 1], tag, L);
+    } else {
+      const double inv = recip_pos((double)L);
+      Mrow[tid] = M;
+      Irow[tid] = (float)inv;
+      Frow[tid] = tok < tq ? (float)(inv * row_weight(a, tq, gq, tid)) : 0.f;
+    }
+  }
+  __syncthreads();
+  // A channel of a row per thread and pass: the sum over the streams replaces the first one's partial.  Split j finishes
+  // the rows [j R / ns, (j + 1) R / ns) and publishes the others (consecutive lanes, consecutive words: four words of a
+  // row per lane took 5.4 us where this takes 2.1).
+  const int ch = tid & (D - 1), own0 = sl.j * (R / ns), own1 = own0 + R / ns;
+  auto partial = [&](int wave, int row) { return (float *)(tiles + (size_t)wave * kWideTileBytes) + (row % kWideRows) * kWidePartRow + ch; };
+#pragma unroll 4
+  for (int row = tid / D; row < R; row += kAttThreads / D) {
+    float o = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int wave = s * RG + row / kWideRows;
+      o = fmaf(*partial(wave, row), weight[wave * kWideRows + row % kWideRows], o);
+    }
+    if (ns == 1) {                                       // complete here
+      if (a.out && Srow[row] != 0x7fffffff) a.out[out_index(cv, sl, tq, gq, row * D + ch, D)] = __float2half_rn(o * Irow[row]);
+    } else if (row >= own0 && row < own1) *partial(row / kWideRows, row) = o;
+    else st_tagged(&a.part_o[(row0 + row) * D + ch], tag, o);
+  }
+  // the query rows as the second pass reads them, on their way to LDS
+  constexpr int kQ = R * 16 / kAttThreads;               // 16-byte pieces per thread: 1, 2 or 4
+  confkv_v4i qreg[kQ];
+#pragma unroll
+  for (int k = 0; k < kQ; ++k) {
+    const int row = k * (kAttThreads / 16) + (tid >> 4), tok = row / gq, head = row - tok * gq;
+    const confkv_v4i v = *(const confkv_v4i *)(a.q + ((((size_t)sl.b * tq + min(tok, tq - 1)) * cv.Hkv + sl.g) * gq + head) * D + (tid & 15) * 8);
+    qreg[k] = tok < tq ? v : confkv_v4i{0, 0, 0, 0};
+  }
+  uint8_t *Qs = tiles + (size_t)RG * kWideTileBytes;     // (behind the partials that hold the own rows)
+  static_assert(R * kKRow16 <= (kAttWaves - RG) * kWideTileBytes, "the query rows fit the idle tile buffers");
 
   // ---------------- exchange between the splits of the unit ----------------
-  const size_t row0 = ((size_t)sl.ul * a.max_splits + sl.j) * R;      // this split's first row in the exchange arrays
   if (ns > 1) {
-    if (st == 0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (t16 == 0) {
-          st_tagged(&a.part_ml[(row0 + rowc[i]) * 2], tag_of(a), mrun[i]);
-          st_tagged(&a.part_ml[(row0 + rowc[i]) * 2 + 1], tag_of(a), lrun[i]);
-        }
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) st_tagged(&a.part_o[(row0 + rowc[i]) * D + 16 * nt + t16], tag_of(a), O[nt][i]);
-      }
-    }
     // every thread gathers some of the ns * R * 2 statistics words of the unit (bounded poll)
     const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * R * 2;
     for (int base = 0; base < ns * R * 2; base += kAttThreads) {
       const int idx = base + tid;
-      const bool minew = idx < ns * R * 2;
-      bool here = !minew;
+      bool here = idx >= ns * R * 2;
       for (int spins = 0;; ++spins) {
         if (!here) {
           const unsigned long long wv = ld_tagged(&words[idx]);
-          if ((unsigned)(wv >> 32) == tag_of(a)) {
+          if ((unsigned)(wv >> 32) == tag) {
             pml[idx] = __uint_as_float((unsigned)wv);
             here = true;
           }
@@ -428,138 +470,140 @@ void attend_wide_kernel(const int32_t *, const int32_t *, const int32_t *, const
     // global (M, L) of row r by thread r; the statistics of (split, row) become the weight of
     // that split's output partial
     if (tid < R) {
-      float M = NEG;
+      float M = kNothing;
       for (int s = 0; s < ns; ++s) M = fmaxf(M, pml[(s * R + tid) * 2]);
       double L = 0.0;
       for (int s = 0; s < ns; ++s) {
-        const float ms = pml[(s * R + tid) * 2];
-        const float es = ms > NEG ? exp_nonpos(ms - M) : 0.f;
+        const float es = exp_nonpos(pml[(s * R + tid) * 2] - M);
         L += (double)es * (double)pml[(s * R + tid) * 2 + 1];
         pml[(s * R + tid) * 2] = es;
       }
       const double inv = recip_pos(L);
       Mrow[tid] = M;
       Irow[tid] = (float)inv;
-      Frow[tid] = (float)(inv * row_weight(a, tq, gq, tid));
+      Frow[tid] = tid / gq < tq ? (float)(inv * row_weight(a, tq, gq, tid)) : 0.f;
     }
-    __syncthreads();
-    if (st == 0) {
-      // this split writes the channel groups nt with nt % ns == j of every row of the block
-      for (int nt = sl.j; nt < 8; nt += ns) {
-        float acc[4];
+  }
+  if (ns == 1) __syncthreads();                          // (the partials have been read)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = O[nt][i] * pml[(sl.j * R + rowc[i]) * 2];
-        for (int s = 0; s < ns; ++s) {
-          if (s == sl.j) continue;
-          const unsigned long long *src = a.part_o + (((size_t)sl.ul * a.max_splits + s) * R) * D + 16 * nt + t16;
-          unsigned long long wv[4];
+  for (int k = 0; k < kQ; ++k) *(confkv_v4i *)(Qs + (k * (kAttThreads / 16) + (tid >> 4)) * kKRow16 + (tid & 15) * 16) = qreg[k];
+  __syncthreads();
+  if (ns > 1 && a.out) {
+    constexpr int kRows = kAttThreads / D;               // rows per pass; kPass passes' words are requested at once
+    constexpr int kPass = 4;
+    for (int r0 = own0 + tid / D; r0 < own1; r0 += kRows * kPass) {
+      float o[kPass];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) wv[i] = ld_tagged(&src[(size_t)rowc[i] * D]);
-          bool here = true;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) here &= (unsigned)(wv[i] >> 32) == tag_of(a);
-          for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull; ++spins) {
-            if (spins > a.spin_limit) break;
-            __builtin_amdgcn_s_sleep(1);
-            if (!here) {
-              here = true;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                wv[i] = ld_tagged(&src[(size_t)rowc[i] * D]);
-                here &= (unsigned)(wv[i] >> 32) == tag_of(a);
-              }
-            }
-          }
-          const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
-          if (missing && lane == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float wgt = pml[(s * R + rowc[i]) * 2];
-            acc[i] += wgt > 0.f ? __uint_as_float((unsigned)wv[i]) * wgt : 0.f;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (okc[i] && a.out)
-            a.out[out_index(cv, sl, tq, gq, rowc[i] * D + 16 * nt + t16, D)] = __float2half_rn(acc[i] * Irow[rowc[i]]);
+      for (int k = 0; k < kPass; ++k) {
+        const int row = min(r0 + k * kRows, own1 - 1);
+        o[k] = *partial(row / kWideRows, row) * pml[(sl.j * R + row) * 2];
       }
-    }
-  } else {
-    if (st == 0) {
+      for (int s = 0; s < ns; ++s) {
+        if (s == sl.j) continue;
+        const unsigned long long *src = a.part_o + ((size_t)sl.ul * a.max_splits + s) * R * D + ch;
+        unsigned long long wv[kPass];
+        auto request = [&]() {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double inv = recip_pos((double)lrun[i]);
-        if (t16 == 0) {
-          Mrow[rowc[i]] = mrun[i];
-          Irow[rowc[i]] = (float)inv;
-          Frow[rowc[i]] = (float)(inv * row_weight(a, tq, gq, rowc[i]));
+          for (int k = 0; k < kPass; ++k) wv[k] = ld_tagged(src + (size_t)min(r0 + k * kRows, own1 - 1) * D);
+        };
+        auto ready = [&]() {
+          bool ok = true;
+#pragma unroll
+          for (int k = 0; k < kPass; ++k) ok &= (unsigned)(wv[k] >> 32) == tag;
+          return ok;
+        };
+        request();
+        bool here = ready();
+        for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull && spins <= a.spin_limit; ++spins) {   // (bounded)
+          __builtin_amdgcn_s_sleep(1);
+          request();
+          here = ready();
         }
-        if (okc[i] && a.out) {
+        const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
+        if (missing && lane == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
 #pragma unroll
-          for (int nt = 0; nt < 8; ++nt)
-            a.out[out_index(cv, sl, tq, gq, rowc[i] * D + 16 * nt + t16, D)] = __float2half_rn(O[nt][i] * (float)inv);
+        for (int k = 0; k < kPass; ++k) {
+          const float wgt = pml[(s * R + min(r0 + k * kRows, own1 - 1)) * 2];
+          o[k] = fmaf(wgt > 0.f ? __uint_as_float((unsigned)wv[k]) : 0.f, wgt, o[k]);
         }
       }
+#pragma unroll
+      for (int k = 0; k < kPass; ++k) {
+        const int row = r0 + k * kRows;
+        if (row < own1 && Srow[row] != 0x7fffffff) a.out[out_index(cv, sl, tq, gq, row * D + ch, D)] = __float2half_rn(o[k] * Irow[row]);
+      }
     }
-    __syncthreads();
   }
 
   // ---------------- pass 2: exact mass per slot, EMA ----------------
-  float Mi[4], Fi[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { Mi[i] = Mrow[rowc[i]]; Fi[i] = okc[i] ? Frow[rowc[i]] : 0.f; }
   double lam = 1.0;
   for (int k = 0; k < tq; ++k) lam *= (double)a.ema_decay;
-  const int first_new = sl.n - tq;
+  const int first_new = sl.n - tq;                       // a token of the call starts at 0
   float *EMA = cv.ema + (size_t)sl.u * cv.cap;
-  if (w < nitems) tr = load_item(w, false);
-  for (int sup = 0; sup < nsup; ++sup) {
-    const int mine = sup * kAttWaves + w;
-    __syncthreads();                                     // tiles and column sums of the previous round are done with
-    if (mine < nitems) store_item(mine, tr, false);
-    __syncthreads();
-    if (mine + kAttWaves < nitems) tr = load_item(mine + kAttWaves, false);
-    // thread (tile j, slot s) of the first 256 updates that slot's EMA after the column sums are in;
-    // its old value is requested now
-    const int ema_j = tid >> 5, ema_s = tid & 31;
-    bool ema_valid = false;
-    int ema_slot = 0, ema_row = 0;
-    float ema_old = 0.f;
-    if (tid < kAttWaves * kTile && sup * kAttWaves + ema_j < nitems) {
-      const int it = sup * kAttWaves + ema_j;
-      const bool is8 = it < ntiles;
-      ema_slot = is8 ? sl.lo8 + it * kTile + ema_s : sl.lo16 + 16 * (it - ntiles) + ema_s;
-      ema_valid = is8 ? ema_slot < sl.hi8 : (ema_s < 16 && ema_slot < sl.hi16);
-      if (ema_valid) {
-        ema_row = slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, ema_slot);
-        ema_old = EMA[ema_row];
+  const int subs8 = (sl.cnt8 + 31) / 32, subs = subs8 + (sl.hi16 - sl.lo16 + 31) / 32;
+  for (int t = w; t < subs; t += kAttWaves) {
+    const bool is8 = t < subs8;
+    const int base = is8 ? sl.lo8 + 32 * t : sl.lo16 + 32 * (t - subs8), lim = is8 ? sl.hi8 : sl.hi16;
+    half8_t kb[2][4];
+    float f[2];
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+      const int slot = min(base + 16 * sb + t16, lim - 1);
+      if (is8) {
+        const unsigned row = (unsigned)ring_row_u(sl.h8, slot, cv.cap8);
+        const confkv_v4i c0 = *(const confkv_v4i *)(K8 + row * D + g4 * 32), c1 = *(const confkv_v4i *)(K8 + row * D + g4 * 32 + 16);
+        kb[sb][0] = cvt_i8x8_f16x8((unsigned)c0[0], (unsigned)c0[1]);
+        kb[sb][1] = cvt_i8x8_f16x8((unsigned)c0[2], (unsigned)c0[3]);
+        kb[sb][2] = cvt_i8x8_f16x8((unsigned)c1[0], (unsigned)c1[1]);
+        kb[sb][3] = cvt_i8x8_f16x8((unsigned)c1[2], (unsigned)c1[3]);
+        f[sb] = __half2float(KS[row]) * sm;
+      } else {
+        // the call's own tokens come from the call's arguments, not from the ring
+        const int fresh = a.observe_first >= 0 ? -1 : slot - first_new;
+        const __half *src = fresh >= 0 ? a.knew + (((size_t)sl.b * tq + fresh) * cv.Hkv + sl.g) * D
+                                       : K16 + (size_t)ring_row(sl.h16, slot - sl.n8, cv.cap16) * D;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) kb[sb][s] = __builtin_bit_cast(half8_t, *(const confkv_v4i *)(src + g4 * 32 + 8 * s));
+        f[sb] = sm;
       }
     }
-    for (int j = st; j < kAttWaves; j += NS) {
-      const int it = sup * kAttWaves + j;
-      if (it >= nitems) break;
-      const uint8_t *Kt = tiles + (size_t)j * kWideTileBytes;
-      const float *sc = (const float *)(Kt + kWideCoreBytes);
-      const int halves = it < ntiles ? 2 : 1;
-      for (int sb = 0; sb < halves; ++sb) {
-        float sv[4];
-        if (it < ntiles) scores8(Kt, sc, sl.lo8 + it * kTile, sb, sv);
-        else scores16(Kt, sl.lo16 + 16 * (it - ntiles), sv);
+    // lanes of row g4 = 0 and 1 update the slots of half g4
+    const int slot_e = base + 16 * (g4 & 1) + t16;
+    const bool writes = g4 < 2 && slot_e < lim;
+    const int row_e = slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, min(slot_e, lim - 1));
+    const float old = EMA[row_e];
+    const bool edge = base + 32 > see_all;
+    double sum[2] = {0.0, 0.0};
+#pragma unroll 2
+    for (int rb = 0; rb < RB; ++rb) {
+      half8_t qf[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) qf[s] = *(const half8_t *)(Qs + (16 * rb + t16) * kKRow16 + g4 * 64 + 16 * s);
+      const float4 M4 = *(const float4 *)&Mrow[16 * rb + 4 * g4], F4 = *(const float4 *)&Frow[16 * rb + 4 * g4];
+      const int4 S4 = *(const int4 *)&Srow[16 * rb + 4 * g4];
+      const float Mi[4] = {M4.x, M4.y, M4.z, M4.w}, Fi[4] = {F4.x, F4.y, F4.z, F4.w};
+      const int Si[4] = {S4.x, S4.y, S4.z, S4.w};
+      floatx4_t acc[2] = {floatx4_t{0.f, 0.f, 0.f, 0.f}, floatx4_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qf[s], kb[sb][s], acc[sb], 0, 0, 0);
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
         float c = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) c += (sv[i] == NEG) ? 0.f : exp_nonpos(sv[i] - Mi[i]) * Fi[i];
-        c += __shfl_xor(c, 16, kWave);
-        c += __shfl_xor(c, 32, kWave);
-        // column sums of row block rb over tile j: slot 16 sb + t16
-        if (g4 == 0) mass[(size_t)(j * RB + rb) * kTile + 16 * sb + t16] = c;
+        for (int i = 0; i < 4; ++i) {
+          const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -Mi[i]));
+          c = fmaf(edge && base + 16 * sb + t16 >= Si[i] ? 0.f : e, Fi[i], c);
+        }
+        sum[sb] += (double)c;
       }
     }
-    __syncthreads();
-    if (ema_valid) {
-      double A = 0.0;
-      for (int r = 0; r < RB; ++r) A += (double)mass[(size_t)(ema_j * RB + r) * kTile + ema_s];   // fixed order: row blocks 0, 1, ..
-      const double old = ema_slot >= first_new ? 0.0 : (double)ema_old;       // a token of the call starts at 0
-      EMA[ema_row] = (float)(lam * old + a.mass_gain * A);
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+      sum[sb] += __shfl_xor(sum[sb], 16, kWave);
+      sum[sb] += __shfl_xor(sum[sb], 32, kWave);
     }
+    if (writes) EMA[row_e] = (float)(lam * (slot_e >= first_new ? 0.0 : (double)old) + a.mass_gain * (g4 == 0 ? sum[0] : sum[1]));
   }
 }

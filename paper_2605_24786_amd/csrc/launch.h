@@ -39,7 +39,7 @@ struct AttendPlan {
   size_t lds_bytes;  // dynamic LDS per workgroup
   bool mfma;         // matrix-core body for the INT8 slots
   bool two_launch;   // stream + publish, then merge + EMA in a second launch (scores in scratch)
-  int wide_rb;       // > 0: the many-rows kernel with that many blocks of 16 query rows per unit
+  int wide_groups;   // > 0: the many-rows kernel with that many groups of 32 query rows per unit
 };
 struct AttendLaunch {
   int layer;

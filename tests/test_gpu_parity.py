@@ -900,6 +900,20 @@ def test_attend_chunk_many_rows(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=17 * G + T0)
 
 
+@pytest.mark.parametrize("G,H,B,T0,W,splits,tqs", [
+    (1, 1, 1, 40, 8, 0, (17, 32)),               # one group of 32 rows, nearly half of it padding, and full
+    (1, 1, 1, 31, 0, 0, (33,)),                  # one row more than a group; an INT8 tile short of one slot
+    (1, 1, 1, 33, 0, 0, (64, 65)),               # an INT8 tile and one slot; two full groups, then four
+    (1, 1, 1, 290, 1, 2, (128,)),                # every row of four groups real, two splits
+    (7, 1, 1, 1100, 15, 4, (5, 18)),             # 35 and 126 rows: tokens' heads cross the groups; eight tiles and more per split
+    (1, 1, 1, 0, 17, 0, (17, 18)),               # FP16 tiles only, of 16 slots and one or two
+])
+def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
+    """The many-rows kernel at the edges of its groups of 32 rows, its tiles of 32 INT8 and 16 FP16 slots and its rounds of
+    eight tiles."""
+    _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=23 * G + T0)
+
+
 @pytest.mark.parametrize("G,H,B,T0,W,splits,tqs,scales", [
     (4, 2, 2, 700, 32, 3, (4, 3), "token"), (1, 1, 1, 500, 16, 5, (16, 7), "token"),
     (5, 1, 1, 900, 64, 7, (3, 3), "channel"), (2, 1, 1, 300, -1, 2, (8, 8), "token")])
