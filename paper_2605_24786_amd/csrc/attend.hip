@@ -1758,6 +1758,12 @@ bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n
   }
 }
 
+// Twice the splits pay while a split keeps 96 slots, from eight to sixteen while it keeps 160 (us per launch of one
+// sequence, eight kv-heads with four heads, 16 tokens unless stated): 300 slots in 1, 2, 4 splits of 8 tokens 19.2, 16.8, 16.4; 600
+// in 2, 4, 8 20.1, 17.6, 18.5; 1000 slots, 32 tokens in 2, 4, 8 46.5, 35.2, 30.0; 2000 in 8, 16 26.8, 28.3; 3000 30.7,
+// 29.8; 9000 54.3, 42.6; 64 units of 500 slots in 2, 4 27.7, 22.7.
+static int wide_split_slots(int ns) { return ns > 8 ? 160 : 96; }
+
 // Calls with more than 16 query rows per unit: row groups (a power of two) and split count.  The
 // splits of a unit exchange partials inside the launch, so with more than one split the whole grid
 // must be resident (one workgroup per CU: the tile buffers take most of the LDS).
@@ -1767,10 +1773,10 @@ bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits
   int rg = 1;
   while (rg * kWideRows < rows) rg *= 2;
   int ns = 1;
-  while (ns * 2 <= kWideMaxSplits && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 256) ns *= 2;
+  while (ns * 2 <= wide_max_splits(rg * kWideRows) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= wide_split_slots(ns * 2)) ns *= 2;
   if (forced_splits > 0) {
     ns = 1;
-    while (ns * 2 <= std::min(forced_splits, kWideMaxSplits) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
+    while (ns * 2 <= std::min(forced_splits, wide_max_splits(rg * kWideRows)) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
   }
   AttendFn fn = rg == 1 ? (AttendFn)attend_wide_kernel<1> : rg == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
   const size_t lds = attend_wide_lds_bytes(rg * kWideRows, ns);
@@ -1812,7 +1818,7 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const At
     AttendFn wide = plan.wide_groups == 1 ? (AttendFn)attend_wide_kernel<1>
                     : plan.wide_groups == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
     a.dbg = nullptr;
-    a.max_splits = kWideMaxSplits;
+    a.max_splits = wide_max_splits(plan.wide_groups * kWideRows);
     hipLaunchKernelGGL(wide, grid, dim3(kAttThreads), plan.lds_bytes, stream, cv.len, cv.n8, cv.head16, cv.head8, a.layer * cv.B * cv.Hkv, cv.Hkv, a.kv_major, cv, a, plan.splits, 0);
     return hipGetLastError();
   }

@@ -39,7 +39,8 @@ constexpr int kWideTileBytes = kWideCoreBytes + 2 * kTile * 4;
 constexpr int kWidePartRow = 128 + 4;                  // floats per row of a wavefront's output partial
 static_assert(kWideRows * kWidePartRow * 4 <= kWideTileBytes, "a partial fits the wavefront's tile buffer");
 constexpr int kWideMaxRows = 128;
-constexpr int kWideMaxSplits = 8;
+// (the exchange arrays hold 1024 rows of partials per unit)
+__host__ __device__ constexpr int wide_max_splits(int R) { return R <= 64 ? 16 : 8; }
 
 // rows, and behind the tiles: per wavefront and row (m, l); per stream and row a weight; four words per row; the splits' (m, l)
 __host__ __device__ constexpr size_t attend_wide_lds_bytes(int R, int ns) {
@@ -489,8 +490,9 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   for (int k = 0; k < kQ; ++k) *(confkv_v4i *)(Qs + (k * (kAttThreads / 16) + (tid >> 4)) * kKRow16 + (tid & 15) * 16) = qreg[k];
   __syncthreads();
   if (ns > 1 && a.out) {
-    constexpr int kRows = kAttThreads / D;               // rows per pass; kPass passes' words are requested at once
-    constexpr int kPass = 4;
+    // four rows of a thread at a time, one split after the other (the words of several splits requested together are
+    // asked for again as long as one of them is missing: 16 tokens of 4 heads on 64 units 40 against 38 us)
+    constexpr int kRows = kAttThreads / D, kPass = 4;
     for (int r0 = own0 + tid / D; r0 < own1; r0 += kRows * kPass) {
       float o[kPass];
 #pragma unroll

@@ -907,6 +907,8 @@ def test_attend_chunk_many_rows(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     (1, 1, 1, 290, 1, 2, (128,)),                # every row of four groups real, two splits
     (7, 1, 1, 1100, 15, 4, (5, 18)),             # 35 and 126 rows: tokens' heads cross the groups; eight tiles and more per split
     (1, 1, 1, 0, 17, 0, (17, 18)),               # FP16 tiles only, of 16 slots and one or two
+    (4, 1, 1, 1100, 20, 16, (6, 16)),            # sixteen splits of one and of two groups, down to 69 slots each
+    (1, 1, 1, 2600, 64, 0, (20, 100)),           # the default plan: sixteen splits, and the eight that four groups may have
 ])
 def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     """The many-rows kernel at the edges of its groups of 32 rows, its tiles of 32 INT8 and 16 FP16 slots and its rounds of
