@@ -475,9 +475,9 @@ int conf_kv_observe_prompt(conf_kv_handle *h, int32_t layer, const void *dev_q16
   // (accepted where conf_kv_observe is)
   if (h->cfg.max_chunk < 2 && h->cv.G <= 8) return CONF_KV_ERR_INVALID_ARG;
   if ((uintptr_t)dev_q16 & 15) return CONF_KV_ERR_INVALID_ARG;
-  // A prompt that fits one conf_kv_observe call is one launch there.  The two launches over all
+  // A prompt that fits one conf_kv_observe call is one launch there.  The kernels over all
   // queries take a group's heads in turn: eight kv-heads, 1 head of 16 tokens 10.7 us as one call
-  // and 11.8 as two launches, of 20 tokens 15.2 and 12.2 (more rows than one tile); 4 heads of 32
+  // and 11.8 as kernels over all queries, of 20 tokens 15.2 and 12.2 (more rows than one tile); 4 heads of 32
   // tokens 16.1 and 17.2; 16 heads of 8 tokens 11.2 and 27.5.
   if (T0 <= std::max(1, h->cfg.max_chunk) && (T0 * h->cv.G <= kChunkRows || h->cv.G >= 4))
     return attend_tokens(h, layer, T0, dev_q16, nullptr, nullptr, nullptr, stream, 0);
