@@ -140,6 +140,8 @@ ScratchLayout scratch_layout(const conf_kv_config *c) {
   // (the matrix-core body exchanges 128-channel partials whatever the head dimension)
   s.part_o = take(UPL * kAttendMaxSplits * R * std::max<size_t>(D, 128) * 8);
   s.zero_bytes = off;
+  // the two-launch form's scores, or the prompt-phase kernels' statistics; their parts also take the two arrays behind
+  // this one, which only conf_kv_evict_compact uses
   s.spill = take(std::max(attend_spill_floats((int)UPL, (int)R, c->capacity),
                           R == kChunkRows ? observe_scratch_floats((int)UPL, (int)G, c->capacity) : 0) * 4);
   s.score = take(U * c->capacity * 8);
@@ -482,7 +484,7 @@ int conf_kv_observe_prompt(conf_kv_handle *h, int32_t layer, const void *dev_q16
   if (T0 <= std::max(1, h->cfg.max_chunk) && (T0 * h->cv.G <= kChunkRows || h->cv.G >= 4))
     return attend_tokens(h, layer, T0, dev_q16, nullptr, nullptr, nullptr, stream, 0);
   CK_HIP(h, launch_observe_prompt(h->cv, layer, (const __half *)dev_q16, T0, h->cfg.sm_scale, (double)h->cfg.ema_decay,
-                                  mass_gain(h), (float *)(h->scratch + h->kl.spill), (hipStream_t)stream));
+                                  mass_gain(h), (float *)(h->scratch + h->kl.spill), (h->kl.sel - h->kl.spill) / 4, (hipStream_t)stream));
   return CONF_KV_OK;
 }
 

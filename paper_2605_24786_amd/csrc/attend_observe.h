@@ -43,11 +43,11 @@ static int observe_tiles_per_part(int units_per_layer, int G, int T, int tile) {
 // Parts the rows of the second kernel are cut into: the count whose workgroups (the pairs of a
 // slot tile and a part that are not wholly behind the diagonal) take the least time on the chip,
 // kMassGroups of them at a time, a workgroup costing its steps and about kMassStart more to begin.
-static int observe_mass_parts(int units_per_layer, int G, int T) {
+static int observe_mass_parts(int units_per_layer, int G, int T, int most) {
   const long long tiles = (T + kMassTile - 1) / kMassTile, nb = (T + 15) / 16 * G, steps = (nb + kMassStep - 1) / kMassStep;
   long long best = 0;
   int parts = 1;
-  for (int p = 1; p <= kMassPartsMax && 2 * p <= steps + 1; ++p) {
+  for (int p = 1; p == 1 || (p <= most && 2 * p <= steps + 1); ++p) {
     const long long len = (steps + p - 1) / p;
     long long groups = 0;
     for (long long t = 0; t < tiles && groups <= 4 * kMassGroups; ++t)
@@ -59,16 +59,40 @@ static int observe_mass_parts(int units_per_layer, int G, int T) {
   }
   return parts;
 }
+// The final statistics of `cap` tokens.  Parts take what the launch is given beyond those of its own tokens.
 size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
-  // (at least half of units * tiles * parts are workgroups, and several parts stop at 4 kMassGroups of those)
-  const size_t partial = std::min<size_t>((size_t)units_per_layer * kMassPartsMax * observe_stride(cap),
-                                          (size_t)8 * kMassGroups * (kMassTile + 16));
-  // the first kernel's parts are done with before the second's are written.  Its parts times rows: below 1 + tiles /
-  // (tiles per part), where several parts need (rows / 128) * (tiles / 2) below kObsGroups * (tiles per part + 1),
-  // or tiles per part at its least (then rows * tiles / 256 <= kObsGroups * kObsPartMin)
-  const size_t rows = (size_t)units_per_layer * G * observe_stride(cap);
-  const size_t row_parts = std::min<size_t>(rows * 17, 2 * rows + (size_t)kObsGroups * 512);
-  return rows * 3 + 2 + std::max<size_t>(2 * partial, 3 * row_parts);
+  return (size_t)units_per_layer * G * observe_stride(cap) * 3;
+}
+// What a launch over T tokens runs, with at most `have` floats of scratch: the rows' final statistics and behind them
+// the parts of one kernel at a time (the first kernel's are done with before the second's are written).
+// (A reservation for the most parts that any T could take was 0.1 to 1.6 GB larger than a launch could use on long caches.)
+struct ObservePlan {
+  int tile, per_part, row_parts;                       // first kernel: slots per tile, tiles per part, parts
+  int width, parts;                                    // second: subtiles per workgroup, parts
+  size_t n_rows, stat_floats, floats;
+};
+static ObservePlan observe_plan(int units_per_layer, int G, int T, bool chan, size_t have) {
+  ObservePlan p;
+  const int nblocks = (T + 15) / 16 * G;
+  p.n_rows = (size_t)units_per_layer * G * observe_stride(T);
+  p.stat_floats = 3 * p.n_rows;                         // (even: rows come in sixteens)
+  const size_t room = have > p.stat_floats ? have - p.stat_floats : 0;
+  p.tile = chan ? 32 : 64;
+  const int tiles = (T + p.tile - 1) / p.tile + 1;     // (one more where the FP16 slots begin)
+  const int most = (int)std::max<size_t>(1, std::min<size_t>(tiles, room / (3 * p.n_rows)));
+  p.per_part = std::max(observe_tiles_per_part(units_per_layer, G, T, p.tile), (tiles + most - 1) / most);
+  p.row_parts = (tiles + p.per_part - 1) / p.per_part;
+  // A short prompt of few heads runs a subtile per workgroup, whose wavefronts share the rows: 64 tokens of 4 heads
+  // (four steps) 11.2 us with, 12.5 without; 130 tokens (nine) 18.2 with, 11.0 and 4.2 for the sum in parts without.
+  const bool few = T <= kMassTile && nblocks <= 4 * kMassStep;
+  p.width = few ? 1 : kObsWaves;
+  const size_t column = 2 * (size_t)units_per_layer * observe_stride(T);
+  p.parts = few ? 1 : observe_mass_parts(units_per_layer, G, T, (int)std::min<size_t>(kMassPartsMax, room / column));
+  p.floats = p.stat_floats + std::max(p.row_parts > 1 ? 3 * p.row_parts * p.n_rows : 0, p.parts > 1 ? column * p.parts : 0);
+  return p;
+}
+size_t observe_plan_floats(int units_per_layer, int G, int T, int chan, size_t have) {
+  return observe_plan(units_per_layer, G, T, chan != 0, have).floats;
 }
 
 // The slots of a unit come in tiles: first the INT8 ones, then the FP16 ones.
@@ -568,23 +592,20 @@ __global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, 
 }
 
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
-                                 float *scratch, hipStream_t stream) {
+                                 float *scratch, size_t scratch_floats, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
   const int nblocks = (T + 15) / 16 * cv.G, units = cv.B * cv.Hkv, nitems = (nblocks + kObsItem - 1) / kObsItem;
-  const int tile = cv.chan ? 32 : 64, per_part = observe_tiles_per_part(units, cv.G, T, tile);
-  const int row_parts = ((T + tile - 1) / tile + per_part) / per_part;
-  // A short prompt of few heads runs a subtile per workgroup, whose wavefronts share the rows: 64 tokens of 4 heads
-  // (four steps) 11.2 us with, 12.5 without; 130 tokens (nine) 18.2 with, 11.0 and 4.2 for the sum in parts without.
-  const bool few = T <= kMassTile && nblocks <= 4 * kMassStep;
-  const int width = few ? 1 : kObsWaves, parts = few ? 1 : observe_mass_parts(units, cv.G, T);
+  const ObservePlan plan = observe_plan(units, cv.G, T, cv.chan != 0, scratch_floats);
+  if (plan.floats > scratch_floats) return hipErrorInvalidValue;
+  const int tile = plan.tile, per_part = plan.per_part, row_parts = plan.row_parts, width = plan.width, parts = plan.parts;
   const int ntiles = (T + kMassWave * width - 1) / (kMassWave * width) + 1;
   const dim3 rows(cv.Hkv * nitems * row_parts, 1, cv.B), slots(cv.Hkv * ntiles * parts, 1, cv.B);
-  const size_t n_rows = (size_t)units * cv.G * observe_stride(T);
+  const size_t n_rows = plan.n_rows;
   // final statistics, then the partial ones of the rows, and over them those of the columns
   ObserveStats stats{};
   stats.weight = (double *)scratch;
   stats.ref = scratch + 2 * n_rows;
-  stats.partial = (double *)scratch + (3 * n_rows + 1) / 2;
+  stats.partial = (double *)(scratch + plan.stat_floats);
   if (row_parts > 1) {
     stats.row_sum = stats.partial;
     stats.row_ref = (float *)(stats.row_sum + row_parts * n_rows);

@@ -84,10 +84,12 @@ bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,
-// contiguous layout).  scratch: observe_scratch_floats(B * Hkv, G, T) floats.
+// contiguous layout).  scratch: scratch_floats floats, at least observe_scratch_floats(B * Hkv, G, T); with more the
+// work is cut into parts, observe_plan_floats(B * Hkv, G, T, chan, scratch_floats) of them are used.
 size_t observe_scratch_floats(int units_per_layer, int G, int cap);
+size_t observe_plan_floats(int units_per_layer, int G, int T, int chan, size_t have);
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
-                                 float *scratch, hipStream_t stream);
+                                 float *scratch, size_t scratch_floats, hipStream_t stream);
 
 // ---- evict.hip ----
 // Per unit, written by rank_select: [0] new length, [1] new INT8 count, [2] first evicted slot,

@@ -60,6 +60,35 @@ def test_buffer_sizes(clib):
     assert U * cap * (4 * D + 8) <= sb16 <= U * cap * (4 * D + 8) + 64 * 1024
 
 
+def test_prompt_phase_scratch(clib):
+    """The prompt-phase kernels cut their work into parts only as far as the scratch that is there anyway holds them: the
+    statistics of the longest prompt (12 bytes per row) or the two-launch form's scores, and the ranking arrays."""
+    # (layers, batch, kv-heads, heads per kv-head, capacity): statistics are the larger one, then the scores
+    for L, B, H, G, cap, mb in [(1, 1, 8, 16, 32768, 61.998), (1, 8, 8, 8, 32768, 438.049), (32, 1, 8, 16, 32768, 159.523)]:
+        cfg, *_ = _cfg(n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, vocab=32000, capacity=cap, fp16_window=64,
+                       n_tight=[cap // 4] * L, n_loose=[cap // 2] * L, max_chunk=2)
+        assert clib.conf_kv_scratch_bytes(C.byref(cfg)) / 1e6 == pytest.approx(mb, abs=1e-3)
+    have = getattr(clib, "_ZN6confkv22observe_scratch_floatsEiii")
+    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiim")
+    have.restype = plan.restype = C.c_size_t
+    have.argtypes, plan.argtypes = [C.c_int] * 3, [C.c_int] * 4 + [C.c_size_t]
+    cut = 0
+    for units in (1, 2, 3, 8, 40, 64, 256, 384):
+        for G in (1, 3, 4, 8, 16):
+            for cap in (16, 64, 272, 1024, 4160, 32768, 524288):
+                rows = units * G * cap
+                assert have(units, G, cap) == 3 * rows
+                for T in {1, 15, 65, cap // 7 + 1, cap // 2 + 1, cap - 1}:
+                    if T > cap:
+                        continue
+                    for chan in (0, 1):
+                        for room in (3 * rows, 3 * rows + 5000, 6 * rows, 1 << 40):
+                            n = plan(units, G, T, chan, room)
+                            assert 3 * units * G * -(-T // 16) * 16 <= n <= room, (units, G, cap, T, chan, room)
+                            cut += n > 3 * units * G * -(-T // 16) * 16
+    assert cut > 1000
+
+
 @pytest.mark.parametrize("bad", [dict(head_dim=96), dict(n_q_heads=34, n_kv_heads=2), dict(n_q_heads=18, n_kv_heads=2, head_dim=64), dict(n_q_heads=7),
                                  dict(capacity=100), dict(capacity=128), dict(vocab=1), dict(alpha=1.5),
                                  dict(n_tight=[200, 64]), dict(protected_window=-1), dict(n_layers=0),
