@@ -68,11 +68,12 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   __shared__ int s_ok;
   constexpr float kNothing = -1e30f;                               // reference of a row that has seen no slot
 
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rg = w % RG, st = w / RG;
   const int tq = a.tq, gq = a.gq;
   const float sm = a.sm_scale;
-  const int t16 = lane & 15, g4 = lane >> 4;
+  int t16 = lane & 15, g4 = lane >> 4;
   const int c8 = lane & 7, r8 = lane >> 3;
   const int c16 = lane & 15, r4 = lane >> 4;
   const Slice sl = make_slice(cv, a, ns, 0x7fffffff, &w_words);
@@ -133,22 +134,19 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       const unsigned col = (unsigned)c16 * 8u;
       // the call's own tokens come from the call's arguments, not from the ring
       const int first_new = a.observe_first >= 0 ? 0x3fffffff : sl.n - tq;
-      const size_t tok = (size_t)cv.Hkv * D;
-      const __half *kn = a.knew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D + col;
-      const __half *vn = a.vnew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D + col;
-      const int s0 = min(base + r4, last), s1 = min(base + 4 + r4, last);
-      const int s2 = min(base + 8 + r4, last), s3 = min(base + 12 + r4, last);
-      const unsigned o0 = (unsigned)ring_row(h16, s0 - n8, cap16) * D + col, o1 = (unsigned)ring_row(h16, s1 - n8, cap16) * D + col;
-      const unsigned o2 = (unsigned)ring_row(h16, s2 - n8, cap16) * D + col, o3 = (unsigned)ring_row(h16, s3 - n8, cap16) * D + col;
-      const int n0 = s0 - first_new, n1 = s1 - first_new, n2 = s2 - first_new, n3 = s3 - first_new;
-      t.k0 = ld_stream16(n0 >= 0 ? kn + n0 * tok : K16 + o0);
-      t.k1 = ld_stream16(n1 >= 0 ? kn + n1 * tok : K16 + o1);
-      t.k2 = ld_stream16(n2 >= 0 ? kn + n2 * tok : K16 + o2);
-      t.k3 = ld_stream16(n3 >= 0 ? kn + n3 * tok : K16 + o3);
-      t.v0 = ld_stream16(n0 >= 0 ? vn + n0 * tok : V16 + o0);
-      t.v1 = ld_stream16(n1 >= 0 ? vn + n1 * tok : V16 + o1);
-      t.v2 = ld_stream16(n2 >= 0 ? vn + n2 * tok : V16 + o2);
-      t.v3 = ld_stream16(n3 >= 0 ? vn + n3 * tok : V16 + o3);
+      // (one load serves either source: no branch, and what is uniform stays scalar)
+      const __half *kn = a.knew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D, *vn = a.vnew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D;
+      const unsigned tok = (unsigned)cv.Hkv * D;
+      auto pick = [&](int r, int4 &k, int4 &v) {
+        const int s = min(base + r + r4, last), n = s - first_new;
+        const unsigned off = (n >= 0 ? (unsigned)n * tok : (unsigned)ring_row(h16, s - n8, cap16) * D) + col;
+        k = ld_stream16((n >= 0 ? kn : K16) + off);
+        v = ld_stream16((n >= 0 ? vn : V16) + off);
+      };
+      pick(0, t.k0, t.v0);
+      pick(4, t.k1, t.v1);
+      pick(8, t.k2, t.v2);
+      pick(12, t.k3, t.v3);
     }
     return t;
   };
@@ -364,6 +362,11 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
   }
 
+  // (the lane's indices anew: kept through the first pass they would spill)
+  asm("" : "+v"(tid));
+  lane = tid & 63;
+  t16 = lane & 15;
+  g4 = lane >> 4;
   append_new_token<D>(cv, a, sl, ns);                    // (nobody reads the appended rows back in this launch)
 
   // ---------------- the tile streams of a row merge in LDS ----------------

@@ -909,11 +909,31 @@ def test_attend_chunk_many_rows(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     (1, 1, 1, 0, 17, 0, (17, 18)),               # FP16 tiles only, of 16 slots and one or two
     (4, 1, 1, 1100, 20, 16, (6, 16)),            # sixteen splits of one and of two groups, down to 69 slots each
     (1, 1, 1, 2600, 64, 0, (20, 100)),           # the default plan: sixteen splits, and the eight that four groups may have
+    (8, 1, 1, 0, 20, 0, (16,)),                  # 16 slots: eight wavefronts share the rows of the second pass
+    (8, 1, 1, 30, 8, 0, (16, 16)),               # two and three subtiles of 32 slots, INT8 and FP16 ones: four, then two share
+    (4, 1, 1, 70, 8, 0, (10, 16)),               # four: two share; 40 and 64 rows
+    (2, 2, 1, 20, -1, 0, (16, 9)),               # 32 and 18 rows, which two can share at most; FP16-only
 ])
 def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     """The many-rows kernel at the edges of its groups of 32 rows, its tiles of 32 INT8 and 16 FP16 slots and its rounds of
     eight tiles."""
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=23 * G + T0)
+
+
+@pytest.mark.parametrize("RG", [1, 2, 4])
+def test_many_rows_kernel_keeps_its_registers(lib, torch_cuda, RG):
+    """No scratch memory: with every register in use, what lives past the first pass (lane indices, source pointers) spilled."""
+    import ctypes as C
+
+    class FuncAttributes(C.Structure):
+        _fields_ = [("binaryVersion", C.c_int), ("cacheModeCA", C.c_int), ("constSizeBytes", C.c_size_t), ("localSizeBytes", C.c_size_t),
+                    ("maxDynamicSharedSizeBytes", C.c_int), ("maxThreadsPerBlock", C.c_int), ("numRegs", C.c_int),
+                    ("preferredShmemCarveout", C.c_int), ("ptxVersion", C.c_int), ("sharedSizeBytes", C.c_size_t)]
+
+    clib, attr = lib.load_library(), FuncAttributes()
+    kernel = C.c_char.in_dll(clib, f"_ZN6confkv18attend_wide_kernelILi{RG}EEEvPKiS2_S2_S2_iiiNS_9CacheViewENS_12AttendLaunchEii")
+    assert clib.hipFuncGetAttributes(C.byref(attr), C.c_void_p(C.addressof(kernel))) == 0
+    assert attr.maxThreadsPerBlock == 512 and attr.localSizeBytes == 0
 
 
 @pytest.mark.parametrize("G,H,B,T0,W,splits,tqs,scales", [
