@@ -129,16 +129,6 @@ __device__ __forceinline__ void scale_codes(const uint2 &raw, const __half *scal
   }
 }
 
-// lambda^k
-__device__ __forceinline__ double pow_count(double x, unsigned k) {
-  double r = 1.0;
-  for (; k; k >>= 1) {
-    if (k & 1u) r *= x;
-    x *= x;
-  }
-  return r;
-}
-
 __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row, int tok, int T, float M, double L, double decay,
                                            double gain) {
   stats.ref[row] = tok < T ? M : 1e30f;

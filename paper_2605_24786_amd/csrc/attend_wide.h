@@ -42,9 +42,19 @@ constexpr int kWideMaxRows = 128;
 // (the exchange arrays hold 1024 rows of partials per unit)
 __host__ __device__ constexpr int wide_max_splits(int R) { return R <= 64 ? 16 : 8; }
 
-// rows, and behind the tiles: per wavefront and row (m, l); per stream and row a weight; four words per row; the splits' (m, l)
+// rows, and behind the tiles: per wavefront and row (m, l); per stream and row a weight; five words per row; the splits' (m, l)
 __host__ __device__ constexpr size_t attend_wide_lds_bytes(int R, int ns) {
-  return (size_t)kAttWaves * kWideTileBytes + ((size_t)kAttWaves * kWideRows * 3 + 4 * R + (size_t)ns * R * 2) * 4 + 16;
+  return (size_t)kAttWaves * kWideTileBytes + ((size_t)kAttWaves * kWideRows * 3 + 5 * R + (size_t)ns * R * 2) * 4 + 16;
+}
+
+// lambda^k
+__device__ __forceinline__ double pow_count(double x, unsigned k) {
+  double r = 1.0;
+  for (; k; k >>= 1) {
+    if (k & 1u) r *= x;
+    x *= x;
+  }
+  return r;
 }
 
 template <int RG>
@@ -64,14 +74,16 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   float *Irow = Mrow + R;                                          // [R] 1 / normaliser
   float *Frow = Irow + R;                                          // [R] the same times the row's mass weight
   int *Srow = (int *)(Frow + R);                                   // [R] slots the row sees (padding rows: 0x7fffffff)
-  float *pml = (float *)(Srow + R);                                // [ns][R][2] gathered statistics
+  int *Orow = Srow + R;                                            // [R] its row of the output (padding rows: -1)
+  float *pml = (float *)(Orow + R);                                // [ns][R][2] gathered statistics
   __shared__ int s_ok;
   constexpr float kNothing = -1e30f;                               // reference of a row that has seen no slot
 
   int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rg = w % RG, st = w / RG;
-  const int tq = a.tq, gq = a.gq;
+  const int tq = a.tq;
+  int gq = a.gq;
   const float sm = a.sm_scale;
   int t16 = lane & 15, g4 = lane >> 4;
   const int c8 = lane & 7, r8 = lane >> 3;
@@ -362,8 +374,9 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
   }
 
-  // (the lane's indices anew: kept through the first pass they would spill)
+  // (the lane's indices and the reciprocal of gq anew: kept through the first pass they would spill)
   asm("" : "+v"(tid));
+  asm("" : "+s"(gq));
   lane = tid & 63;
   t16 = lane & 15;
   g4 = lane >> 4;
@@ -402,6 +415,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
     const int tok = tid / gq;
     Srow[tid] = tok < tq ? sl.n - tq + tok + 1 : 0x7fffffff;
+    Orow[tid] = tok < tq ? ((sl.b * tq + tok) * cv.Hkv + sl.g) * gq + tid - tok * gq : -1;
     if (ns > 1) {
       st_tagged(&a.part_ml[(row0 + tid) * 2], tag, M);
       st_tagged(&a.part_ml[(row0 + tid) * 2 + 1], tag, L);
@@ -409,36 +423,67 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       const double inv = recip_pos((double)L);
       Mrow[tid] = M;
       Irow[tid] = (float)inv;
-      Frow[tid] = tok < tq ? (float)(inv * row_weight(a, tq, gq, tid)) : 0.f;
+      Frow[tid] = tok < tq ? (float)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - tid / gq))) : 0.f;
     }
   }
   __syncthreads();
-  // A channel of a row per thread and pass: the sum over the streams replaces the first one's partial.  Split j finishes
-  // the rows [j R / ns, (j + 1) R / ns) and publishes the others (consecutive lanes, consecutive words: four words of a
-  // row per lane took 5.4 us where this takes 2.1).
-  const int ch = tid & (D - 1), own0 = sl.j * (R / ns), own1 = own0 + R / ns;
-  auto partial = [&](int wave, int row) { return (float *)(tiles + (size_t)wave * kWideTileBytes) + (row % kWideRows) * kWidePartRow + ch; };
-#pragma unroll 4
-  for (int row = tid / D; row < R; row += kAttThreads / D) {
-    float o = 0.f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int wave = s * RG + row / kWideRows;
-      o = fmaf(*partial(wave, row), weight[wave * kWideRows + row % kWideRows], o);
-    }
-    if (ns == 1) {                                       // complete here
-      if (a.out && Srow[row] != 0x7fffffff) a.out[out_index(cv, sl, tq, gq, row * D + ch, D)] = __float2half_rn(o * Irow[row]);
-    } else if (row >= own0 && row < own1) *partial(row / kWideRows, row) = o;
-    else st_tagged(&a.part_o[(row0 + row) * D + ch], tag, o);
-  }
   // the query rows as the second pass reads them, on their way to LDS
   constexpr int kQ = R * 16 / kAttThreads;               // 16-byte pieces per thread: 1, 2 or 4
   confkv_v4i qreg[kQ];
 #pragma unroll
-  for (int k = 0; k < kQ; ++k) {
-    const int row = k * (kAttThreads / 16) + (tid >> 4), tok = row / gq, head = row - tok * gq;
-    const confkv_v4i v = *(const confkv_v4i *)(a.q + ((((size_t)sl.b * tq + min(tok, tq - 1)) * cv.Hkv + sl.g) * gq + head) * D + (tid & 15) * 8);
-    qreg[k] = tok < tq ? v : confkv_v4i{0, 0, 0, 0};
+  for (int k = 0; k < kQ; ++k) {                         // (a query's row is its output's)
+    const int from = Orow[k * (kAttThreads / 16) + (tid >> 4)];
+    const confkv_v4i v = *(const confkv_v4i *)(a.q + (size_t)max(from, 0) * D + (tid & 15) * 8);
+    qreg[k] = from >= 0 ? v : confkv_v4i{0, 0, 0, 0};
+  }
+  // The sum over the streams, complete with one split: four channels of a row per thread and pass, a row's place in the
+  // output divided out once.  Otherwise split j finishes the rows [j R / ns, (j + 1) R / ns), whose sum replaces the
+  // first stream's partial, and publishes the others: a channel per thread, consecutive lanes on consecutive words (four
+  // words of a row per lane took 5.4 us where this takes 2.1), four rows' reads before their writes.  (Read, divided and
+  // written one after the other, the 32 rows of a thread took 6 of the 19 us of a call of 128 rows on an empty cache.)
+  constexpr int kRows = kAttThreads / D, kPass = 4;
+  const int row_w = w / (D / kWave);                     // (uniform)
+  const int ch = tid & (D - 1), own0 = sl.j * (R / ns), own1 = own0 + R / ns;
+  auto partial = [&](int wave, int row) { return (float *)(tiles + (size_t)wave * kWideTileBytes) + (row % kWideRows) * kWidePartRow + ch; };
+  if (a.out && ns == 1) {
+    const int c4 = 4 * (tid & 31);
+#pragma unroll
+    for (int k = 0; k < R / 16; ++k) {
+      const int row = 16 * k + (tid >> 5);
+      floatx4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int wave = s * RG + row / kWideRows;
+        const floatx4_t v = *(const floatx4_t *)((const float *)(tiles + (size_t)wave * kWideTileBytes) + (row % kWideRows) * kWidePartRow + c4);
+        const float wgt = weight[wave * kWideRows + row % kWideRows];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = fmaf(v[i], wgt, o[i]);
+      }
+      const int to = Orow[row];
+      const half4_t h = {(_Float16)(o[0] * Irow[row]), (_Float16)(o[1] * Irow[row]), (_Float16)(o[2] * Irow[row]), (_Float16)(o[3] * Irow[row])};
+      if (to >= 0) *(half4_t *)(a.out + (size_t)to * D + c4) = h;
+    }
+  } else if (a.out) {
+#pragma unroll 1
+    for (int k0 = 0; k0 < R / kRows; k0 += kPass) {
+      float o[kPass];
+#pragma unroll
+      for (int k = 0; k < kPass; ++k) {
+        const int row = row_w + (k0 + k) * kRows;
+        o[k] = 0.f;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int wave = s * RG + row / kWideRows;
+          o[k] = fmaf(*partial(wave, row), weight[wave * kWideRows + row % kWideRows], o[k]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kPass; ++k) {
+        const int row = row_w + (k0 + k) * kRows;
+        if (row >= own0 && row < own1) *partial(row / kWideRows, row) = o[k];
+        else st_tagged(&a.part_o[(row0 + row) * D + ch], tag, o[k]);
+      }
+    }
   }
   uint8_t *Qs = tiles + (size_t)RG * kWideTileBytes;     // (behind the partials that hold the own rows)
   static_assert(R * kKRow16 <= (kAttWaves - RG) * kWideTileBytes, "the query rows fit the idle tile buffers");
@@ -485,7 +530,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       const double inv = recip_pos(L);
       Mrow[tid] = M;
       Irow[tid] = (float)inv;
-      Frow[tid] = tid / gq < tq ? (float)(inv * row_weight(a, tq, gq, tid)) : 0.f;
+      Frow[tid] = tid / gq < tq ? (float)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - tid / gq))) : 0.f;
     }
   }
   if (ns == 1) __syncthreads();                          // (the partials have been read)
@@ -495,8 +540,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   if (ns > 1 && a.out) {
     // four rows of a thread at a time, one split after the other (the words of several splits requested together are
     // asked for again as long as one of them is missing: 16 tokens of 4 heads on 64 units 40 against 38 us)
-    constexpr int kRows = kAttThreads / D, kPass = 4;
-    for (int r0 = own0 + tid / D; r0 < own1; r0 += kRows * kPass) {
+    for (int r0 = own0 + row_w; r0 < own1; r0 += kRows * kPass) {
       float o[kPass];
 #pragma unroll
       for (int k = 0; k < kPass; ++k) {
@@ -535,80 +579,102 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 #pragma unroll
       for (int k = 0; k < kPass; ++k) {
         const int row = r0 + k * kRows;
-        if (row < own1 && Srow[row] != 0x7fffffff) a.out[out_index(cv, sl, tq, gq, row * D + ch, D)] = __float2half_rn(o[k] * Irow[row]);
+        const int to = __builtin_amdgcn_readfirstlane(Orow[min(row, own1 - 1)]);
+        if (row < own1 && to >= 0) a.out[(size_t)to * D + ch] = __float2half_rn(o[k] * Irow[row]);
       }
     }
   }
 
   // ---------------- pass 2: exact mass per slot, EMA ----------------
-  double lam = 1.0;
-  for (int k = 0; k < tq; ++k) lam *= (double)a.ema_decay;
+  const double lam = pow_count((double)a.ema_decay, (unsigned)tq);
   const int first_new = sl.n - tq;                       // a token of the call starts at 0
   float *EMA = cv.ema + (size_t)sl.u * cv.cap;
   const int subs8 = (sl.cnt8 + 31) / 32, subs = subs8 + (sl.hi16 - sl.lo16 + 31) / 32;
-  for (int t = w; t < subs; t += kAttWaves) {
-    const bool is8 = t < subs8;
-    const int base = is8 ? sl.lo8 + 32 * t : sl.lo16 + 32 * (t - subs8), lim = is8 ? sl.hi8 : sl.hi16;
-    half8_t kb[2][4];
-    float f[2];
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      const int slot = min(base + 16 * sb + t16, lim - 1);
-      if (is8) {
-        const unsigned row = (unsigned)ring_row_u(sl.h8, slot, cv.cap8);
-        const confkv_v4i c0 = *(const confkv_v4i *)(K8 + row * D + g4 * 32), c1 = *(const confkv_v4i *)(K8 + row * D + g4 * 32 + 16);
-        kb[sb][0] = cvt_i8x8_f16x8((unsigned)c0[0], (unsigned)c0[1]);
-        kb[sb][1] = cvt_i8x8_f16x8((unsigned)c0[2], (unsigned)c0[3]);
-        kb[sb][2] = cvt_i8x8_f16x8((unsigned)c1[0], (unsigned)c1[1]);
-        kb[sb][3] = cvt_i8x8_f16x8((unsigned)c1[2], (unsigned)c1[3]);
-        f[sb] = __half2float(KS[row]) * sm;
-      } else {
-        // the call's own tokens come from the call's arguments, not from the ring
-        const int fresh = a.observe_first >= 0 ? -1 : slot - first_new;
-        const __half *src = fresh >= 0 ? a.knew + (((size_t)sl.b * tq + fresh) * cv.Hkv + sl.g) * D
-                                       : K16 + (size_t)ring_row(sl.h16, slot - sl.n8, cv.cap16) * D;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) kb[sb][s] = __builtin_bit_cast(half8_t, *(const confkv_v4i *)(src + g4 * 32 + 8 * s));
-        f[sb] = sm;
-      }
-    }
-    // lanes of row g4 = 0 and 1 update the slots of half g4
-    const int slot_e = base + 16 * (g4 & 1) + t16;
-    const bool writes = g4 < 2 && slot_e < lim;
-    const int row_e = slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, min(slot_e, lim - 1));
-    const float old = EMA[row_e];
-    const bool edge = base + 32 > see_all;
+  // Fewer subtiles than wavefronts: several wavefronts share a subtile's rows, and their sums meet in LDS (one wavefront
+  // took 3 us for the 128 rows of 8 slots).
+  int across = 1;
+  while (across < subs && across < kAttWaves) across *= 2;
+  const int shares = min(kAttWaves / across, RB), share = w / across;
+  double *red = (double *)stat_m;                        // [wavefront][32]: the streams' statistics are done with
+  static_assert(kAttWaves * 32 * sizeof(double) <= (size_t)kAttWaves * kWideRows * 2 * sizeof(float), "the shares' sums fit");
+  int t = w % across;
+  do {                                                   // (once where wavefronts share)
+    const bool live = share < shares && t < subs;
+    int slot_e = 0, row_e = 0;
+    bool writes = false;
+    float old = 0.f;
     double sum[2] = {0.0, 0.0};
-#pragma unroll 2
-    for (int rb = 0; rb < RB; ++rb) {
-      half8_t qf[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) qf[s] = *(const half8_t *)(Qs + (16 * rb + t16) * kKRow16 + g4 * 64 + 16 * s);
-      const float4 M4 = *(const float4 *)&Mrow[16 * rb + 4 * g4], F4 = *(const float4 *)&Frow[16 * rb + 4 * g4];
-      const int4 S4 = *(const int4 *)&Srow[16 * rb + 4 * g4];
-      const float Mi[4] = {M4.x, M4.y, M4.z, M4.w}, Fi[4] = {F4.x, F4.y, F4.z, F4.w};
-      const int Si[4] = {S4.x, S4.y, S4.z, S4.w};
-      floatx4_t acc[2] = {floatx4_t{0.f, 0.f, 0.f, 0.f}, floatx4_t{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qf[s], kb[sb][s], acc[sb], 0, 0, 0);
+    if (live) {
+      const bool is8 = t < subs8;
+      const int base = is8 ? sl.lo8 + 32 * t : sl.lo16 + 32 * (t - subs8), lim = is8 ? sl.hi8 : sl.hi16;
+      half8_t kb[2][4];
+      float f[2];
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
-        float c = 0.f;
+        const int slot = min(base + 16 * sb + t16, lim - 1);
+        if (is8) {
+          const unsigned row = (unsigned)ring_row_u(sl.h8, slot, cv.cap8);
+          const confkv_v4i c0 = *(const confkv_v4i *)(K8 + row * D + g4 * 32), c1 = *(const confkv_v4i *)(K8 + row * D + g4 * 32 + 16);
+          kb[sb][0] = cvt_i8x8_f16x8((unsigned)c0[0], (unsigned)c0[1]);
+          kb[sb][1] = cvt_i8x8_f16x8((unsigned)c0[2], (unsigned)c0[3]);
+          kb[sb][2] = cvt_i8x8_f16x8((unsigned)c1[0], (unsigned)c1[1]);
+          kb[sb][3] = cvt_i8x8_f16x8((unsigned)c1[2], (unsigned)c1[3]);
+          f[sb] = __half2float(KS[row]) * sm;
+        } else {
+          // the call's own tokens come from the call's arguments, not from the ring
+          const int fresh = a.observe_first >= 0 ? -1 : slot - first_new;
+          const __half *src = fresh >= 0 ? a.knew + (((size_t)sl.b * tq + fresh) * cv.Hkv + sl.g) * D
+                                         : K16 + (size_t)ring_row(sl.h16, slot - sl.n8, cv.cap16) * D;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -Mi[i]));
-          c = fmaf(edge && base + 16 * sb + t16 >= Si[i] ? 0.f : e, Fi[i], c);
+          for (int s = 0; s < 4; ++s) kb[sb][s] = __builtin_bit_cast(half8_t, *(const confkv_v4i *)(src + g4 * 32 + 8 * s));
+          f[sb] = sm;
         }
-        sum[sb] += (double)c;
+      }
+      // lanes of row g4 = 0 and 1 update the slots of half g4
+      slot_e = base + 16 * (g4 & 1) + t16;
+      writes = g4 < 2 && slot_e < lim;
+      row_e = slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, min(slot_e, lim - 1));
+      old = EMA[row_e];
+      const bool edge = base + 32 > see_all;
+#pragma unroll 1
+      for (int rb = share; rb < RB; rb += shares) {
+        half8_t qf[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qf[s] = *(const half8_t *)(Qs + (16 * rb + t16) * kKRow16 + g4 * 64 + 16 * s);
+        const float4 M4 = *(const float4 *)&Mrow[16 * rb + 4 * g4], F4 = *(const float4 *)&Frow[16 * rb + 4 * g4];
+        const int4 S4 = *(const int4 *)&Srow[16 * rb + 4 * g4];
+        const float Mi[4] = {M4.x, M4.y, M4.z, M4.w}, Fi[4] = {F4.x, F4.y, F4.z, F4.w};
+        const int Si[4] = {S4.x, S4.y, S4.z, S4.w};
+        floatx4_t acc[2] = {floatx4_t{0.f, 0.f, 0.f, 0.f}, floatx4_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qf[s], kb[sb][s], acc[sb], 0, 0, 0);
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+          float c = 0.f;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -Mi[i]));
+            c = fmaf(edge && base + 16 * sb + t16 >= Si[i] ? 0.f : e, Fi[i], c);
+          }
+          sum[sb] += (double)c;
+        }
+      }
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        sum[sb] += __shfl_xor(sum[sb], 16, kWave);
+        sum[sb] += __shfl_xor(sum[sb], 32, kWave);
       }
     }
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      sum[sb] += __shfl_xor(sum[sb], 16, kWave);
-      sum[sb] += __shfl_xor(sum[sb], 32, kWave);
+    double mass = g4 == 0 ? sum[0] : sum[1];
+    if (shares > 1) {
+      if (live && g4 < 2) red[w * 32 + 16 * g4 + t16] = mass;
+      __syncthreads();
+      if (share == 0 && writes)
+        for (int k = 1; k < shares; ++k) mass += red[(w + k * across) * 32 + 16 * g4 + t16];
     }
-    if (writes) EMA[row_e] = (float)(lam * (slot_e >= first_new ? 0.0 : (double)old) + a.mass_gain * (g4 == 0 ? sum[0] : sum[1]));
-  }
+    if (share == 0 && writes) EMA[row_e] = (float)(lam * (slot_e >= first_new ? 0.0 : (double)old) + a.mass_gain * mass);
+    t += across;
+  } while (t < subs);
 }
