@@ -1660,6 +1660,7 @@ static const DeviceLimits &device_limits() {
   }
   return lim;
 }
+static int device_cus() { return device_limits().cus; }
 
 // Resident workgroups per CU of a kernel with `lds` bytes of dynamic LDS.
 static int attend_occupancy(AttendFn fn, size_t lds) {

@@ -14,8 +14,8 @@
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
-constexpr int kObsBlocks = 2;                          // blocks of 16 rows per wavefront of the first kernel
-constexpr int kObsItem = kObsWaves * kObsBlocks;       // blocks per workgroup
+constexpr int kObsItem = 2 * kObsWaves;                // blocks of 16 rows per workgroup of the first kernel: two per wavefront, or
+constexpr int kObsShortItem = kObsWaves, kObsShort = 512;   // one, up to so many tokens
 constexpr int kMassWave = 64, kMassTile = kObsWaves * kMassWave;   // slots per wavefront and workgroup of the second
 constexpr int kMassStep = 4;                           // blocks of 16 rows it stages at a time
 constexpr int kMassPartsMax = 32, kMassGroups = 1536, kMassStart = 3, kMassSum = 5;
@@ -31,14 +31,27 @@ struct ObserveStats {
   double *row_sum;                                     // the first kernel's parts: [part][rows] sums of exponentials
   float *row_ref;                                      // and references
 };
-// A workgroup of the first kernel walks at most this many tiles of the slots its rows see; rows that see
-// more are cut into parts, which a small kernel joins: the causal triangle then falls into pieces of
-// about one size, two per place on the chip (three workgroups a CU).
-constexpr int kObsGroups = 1536, kObsPartMin = 8;
-static int observe_tiles_per_part(int units_per_layer, int G, int T, int tile) {
-  const long long items = ((T + 15) / 16 * G + kObsItem - 1) / kObsItem;
-  const long long tiles = (T + tile - 1) / tile + 1;      // (one more where the FP16 slots begin)
-  return (int)std::min<long long>(tiles, std::max<long long>({kObsPartMin, (tiles + 15) / 16, (items * units_per_layer * tiles / 2 + kObsGroups - 1) / kObsGroups}));
+// Parts the slots that the first kernel's rows see are cut into (a small kernel joins them): the count whose workgroups -- one
+// per item of blocks and part not wholly behind the diagonal -- take the least time.  In us: a tile 0.6 and 0.65 for
+// every workgroup that shares the CU, three at most, the join 6.5 with its launch.  Measured over 77 runs of 20 to 3001 tokens,
+// 1 to 16 heads and 1 to 256 units in 1 to 16 parts, the choice takes 1.012 times the best count's time at the mean and 1.14 at
+// most.  (At least eight tiles a part, and no price for the join: 500 tokens, 1 head and 8 kv-heads in a part of eight tiles and one
+// of one 20.1 us, in six parts 10.7; 64 units of 500 tokens, 2 heads 29.1, uncut 20.3.)
+constexpr int kObsPartsMax = 16;
+static int observe_row_parts(long long items, int tiles, int most, bool chan, int cus) {
+  const double scale = chan ? 0.55 : 1.0, work = 0.5 * items * (tiles + 1);
+  double cost[kObsPartsMax + 1], best = INFINITY;
+  most = std::max(1, std::min(most, kObsPartsMax));
+  for (int n = 1; n <= most; ++n) {
+    const int len = (tiles + n - 1) / n;
+    const double groups = 0.5 * items * (n + 1), per_cu = groups / cus;
+    cost[n] = scale * (per_cu <= 3.0 ? len * (0.6 + 0.65 * per_cu) : 0.77 * ((work + groups) / cus + 1.8 * len)) + (n > 1 ? 6.5 : 0.0);
+    if ((tiles + len - 1) / len != n) cost[n] = INFINITY;
+    best = std::min(best, cost[n]);
+  }
+  int n = 1;                                           // (the fewest within 3 %)
+  while (cost[n] > 1.03 * best) ++n;
+  return n;
 }
 // Parts the rows of the second kernel are cut into: the count whose workgroups (the pairs of a
 // slot tile and a part that are not wholly behind the diagonal) take the least time on the chip,
@@ -67,21 +80,26 @@ size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
 // the parts of one kernel at a time (the first kernel's are done with before the second's are written).
 // (A reservation for the most parts that any T could take was 0.1 to 1.6 GB larger than a launch could use on long caches.)
 struct ObservePlan {
-  int tile, per_part, row_parts;                       // first kernel: slots per tile, tiles per part, parts
+  int item, tile, per_part, row_parts;                 // first kernel: blocks per workgroup, slots per tile, tiles per part, parts
   int width, parts;                                    // second: subtiles per workgroup, parts
   size_t n_rows, stat_floats, floats;
 };
-static ObservePlan observe_plan(int units_per_layer, int G, int T, bool chan, size_t have) {
+static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool chan, size_t have, int cus) {
   ObservePlan p;
   const int nblocks = (T + 15) / 16 * G;
   p.n_rows = (size_t)units_per_layer * G * observe_stride(T);
   p.stat_floats = 3 * p.n_rows;                         // (even: rows come in sixteens)
   const size_t room = have > p.stat_floats ? have - p.stat_floats : 0;
   p.tile = chan ? 32 : 64;
-  const int tiles = (T + p.tile - 1) / p.tile + 1;     // (one more where the FP16 slots begin)
-  const int most = (int)std::max<size_t>(1, std::min<size_t>(tiles, room / (3 * p.n_rows)));
-  p.per_part = std::max(observe_tiles_per_part(units_per_layer, G, T, p.tile), (tiles + most - 1) / most);
-  p.row_parts = (tiles + p.per_part - 1) / p.per_part;
+  // First kernel.  With one block per wavefront a tile takes 0.8 us instead of 1.2 and a half as long as the chip has room for
+  // twice the workgroups: 100 tokens of 4 heads and 8 kv-heads 7.2 -> 5.5 us, 256 10.3 -> 7.8, 500 17 -> 13; 64 units of 150 tokens, 4 heads
+  // (640 workgroups) 10.9 -> 8.8, but of 500 tokens, 2 heads (1024) 20.7 -> 22.8.  Parts and their join gain nothing on it.
+  const int tiles = (n8 + p.tile - 1) / p.tile + (T - n8 + p.tile - 1) / p.tile;
+  const bool one = T <= kObsShort && (long long)units_per_layer * ((nblocks + kObsShortItem - 1) / kObsShortItem) <= 2 * cus;
+  p.item = one ? kObsShortItem : kObsItem;
+  p.row_parts = one ? 1 : observe_row_parts((long long)units_per_layer * ((nblocks + kObsItem - 1) / kObsItem), tiles,
+                                            (int)std::min<size_t>(kObsPartsMax, room / (3 * p.n_rows)), chan, cus);
+  p.per_part = (tiles + p.row_parts - 1) / p.row_parts;
   // A short prompt of few heads runs a subtile per workgroup, whose wavefronts share the rows: 64 tokens of 4 heads
   // (four steps) 11.2 us with, 12.5 without; 130 tokens (nine) 18.2 with, 11.0 and 4.2 for the sum in parts without.
   const bool few = T <= kMassTile && nblocks <= 4 * kMassStep;
@@ -91,9 +109,10 @@ static ObservePlan observe_plan(int units_per_layer, int G, int T, bool chan, si
   p.floats = p.stat_floats + std::max(p.row_parts > 1 ? 3 * p.row_parts * p.n_rows : 0, p.parts > 1 ? column * p.parts : 0);
   return p;
 }
-size_t observe_plan_floats(int units_per_layer, int G, int T, int chan, size_t have) {
-  return observe_plan(units_per_layer, G, T, chan != 0, have).floats;
+size_t observe_plan_floats(int units_per_layer, int G, int T, int n8, int chan, size_t have, int cus) {
+  return observe_plan(units_per_layer, G, T, n8, chan != 0, have, cus).floats;
 }
+static int device_cus();                                // (below, with the attention plans)
 
 // The slots of a unit come in tiles: first the INT8 ones, then the FP16 ones.
 struct ObserveUnit {
@@ -135,7 +154,7 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
   stats.weight[row] = tok < T ? gain * pow_count(decay, (unsigned)(T - 1 - tok)) * recip_pos(L) : 0.0;
 }
 
-// Row statistics.  A block of rows is 16 consecutive tokens of one head; a wavefront owns two, so
+// Row statistics.  A block of rows is 16 consecutive tokens of one head; a wavefront owns two (one of short prompts), so
 // that a key fragment read from LDS serves 32 rows (with 16 the reads alone took 47 of 120 us per
 // layer of 3001 tokens and 32 heads, and the conversion of the keys five of fourteen vector
 // instructions per score), and the workgroup walks the slots its last token sees in tiles that
@@ -150,11 +169,11 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
 // error of the score, and so of a probability, that grows with it.)
 // The grid is (kv-heads times items, 1, sequences), kv-head fastest: the y dimension ends at 65536,
 // which the row blocks of half a million tokens with 16 heads pass.
-template <bool kChan>
+template <bool kChan, int kObsBlocks>
 __global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
                                                                     float sm, double decay, double gain, int per_part, ObserveStats stats) {
-  constexpr int D = 128, TS = kChan ? 32 : 64;         // slots per tile
+  constexpr int D = 128, TS = kChan ? 32 : 64, kItem = kObsWaves * kObsBlocks;   // slots per tile, blocks per workgroup
   constexpr int kTileB = TS * kKRow16, kBuf = kTileB * (kChan ? 2 : 1);
   __shared__ __align__(16) uint8_t tiles[2][kBuf];
   __shared__ __align__(16) float factor[2][TS];
@@ -165,9 +184,9 @@ void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
   const ObserveUnit un = observe_unit(cv, layer * cv.B * cv.Hkv + ul, T);
   constexpr float kNothing = -1e30f;                    // reference of a lane that has seen no slot
 
-  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks + kObsItem - 1) / kObsItem;   // blocks are (token block, head)
+  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks + kItem - 1) / kItem;   // blocks are (token block, head)
   const int item = nitems - 1 - (int)(blockIdx.x / cv.Hkv) % nitems, part = (int)(blockIdx.x / cv.Hkv) / nitems;
-  const int last_block = min((item + 1) * kObsItem, nblocks) - 1;
+  const int last_block = min((item + 1) * kItem, nblocks) - 1;
   const int slots = min(T, last_block / G * 16 + 16);                // what the workgroup's last token sees
   const int nt8 = (min(un.n8, slots) + TS - 1) / TS;
   const int ntiles = nt8 + (max(0, slots - un.n8) + TS - 1) / TS;
@@ -179,7 +198,7 @@ void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
   half8_t qa[kObsBlocks][4];
 #pragma unroll
   for (int r = 0; r < kObsBlocks; ++r) {
-    const int block = item * kObsItem + w * kObsBlocks + r;
+    const int block = item * kItem + w * kObsBlocks + r;
     live[r] = block < nblocks;
     tok0[r] = (live[r] ? block : last_block) / G * 16;
     head[r] = (live[r] ? block : last_block) % G;
@@ -584,11 +603,13 @@ __global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, 
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, size_t scratch_floats, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
-  const int nblocks = (T + 15) / 16 * cv.G, units = cv.B * cv.Hkv, nitems = (nblocks + kObsItem - 1) / kObsItem;
-  const ObservePlan plan = observe_plan(units, cv.G, T, cv.chan != 0, scratch_floats);
+  const int nblocks = (T + 15) / 16 * cv.G, units = cv.B * cv.Hkv;
+  const int n8 = cv.W < 0 ? 0 : std::max(0, T - cv.W);    // (as the prompt was loaded)
+  const ObservePlan plan = observe_plan(units, cv.G, T, n8, cv.chan != 0, scratch_floats, device_cus());
   if (plan.floats > scratch_floats) return hipErrorInvalidValue;
   const int tile = plan.tile, per_part = plan.per_part, row_parts = plan.row_parts, width = plan.width, parts = plan.parts;
   const int ntiles = (T + kMassWave * width - 1) / (kMassWave * width) + 1;
+  const int nitems = (nblocks + plan.item - 1) / plan.item;
   const dim3 rows(cv.Hkv * nitems * row_parts, 1, cv.B), slots(cv.Hkv * ntiles * parts, 1, cv.B);
   const size_t n_rows = plan.n_rows;
   // final statistics, then the partial ones of the rows, and over them those of the columns
@@ -600,8 +621,9 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
     stats.row_sum = stats.partial;
     stats.row_ref = (float *)(stats.row_sum + row_parts * n_rows);
   }
-  if (cv.chan) hipLaunchKernelGGL(observe_stats_kernel<true>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
-  else hipLaunchKernelGGL(observe_stats_kernel<false>, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
+  const auto first = cv.chan ? plan.item == kObsShortItem ? observe_stats_kernel<true, 1> : observe_stats_kernel<true, 2>
+                             : plan.item == kObsShortItem ? observe_stats_kernel<false, 1> : observe_stats_kernel<false, 2>;
+  hipLaunchKernelGGL(first, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
   if (row_parts > 1)
     hipLaunchKernelGGL(observe_join_kernel, dim3((unsigned)((n_rows + kObsThreads - 1) / kObsThreads)), dim3(kObsThreads), 0, stream, cv, layer, T, tile, decay, gain, per_part, stats);
   if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);

@@ -69,9 +69,9 @@ def test_prompt_phase_scratch(clib):
                        n_tight=[cap // 4] * L, n_loose=[cap // 2] * L, max_chunk=2)
         assert clib.conf_kv_scratch_bytes(C.byref(cfg)) / 1e6 == pytest.approx(mb, abs=1e-3)
     have = getattr(clib, "_ZN6confkv22observe_scratch_floatsEiii")
-    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiim")
+    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiiimi")
     have.restype = plan.restype = C.c_size_t
-    have.argtypes, plan.argtypes = [C.c_int] * 3, [C.c_int] * 4 + [C.c_size_t]
+    have.argtypes, plan.argtypes = [C.c_int] * 3, [C.c_int] * 5 + [C.c_size_t, C.c_int]
     cut = 0
     for units in (1, 2, 3, 8, 40, 64, 256, 384):
         for G in (1, 3, 4, 8, 16):
@@ -83,7 +83,7 @@ def test_prompt_phase_scratch(clib):
                         continue
                     for chan in (0, 1):
                         for room in (3 * rows, 3 * rows + 5000, 6 * rows, 1 << 40):
-                            n = plan(units, G, T, chan, room)
+                            n = plan(units, G, T, T // 3, chan, room, 256)
                             assert 3 * units * G * -(-T // 16) * 16 <= n <= room, (units, G, cap, T, chan, room)
                             cut += n > 3 * units * G * -(-T // 16) * 16
     assert cut > 1000

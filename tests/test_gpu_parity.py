@@ -518,6 +518,37 @@ def test_observe_prompt_parts(lib, torch_cuda, G, T0, W, scales):
     kv.close()
 
 
+@pytest.mark.parametrize("G,H,B,T0,W,scales", [
+    (1, 1, 2, 512, 40, "token"), (1, 1, 2, 513, 40, "token"),      # one block per wavefront of the statistics, and two
+    (8, 4, 33, 33, -1, "token"),                                   # two for many units; the one behind the last block
+    (16, 1, 2, 65, 20, "token"), (1, 2, 1, 1, 8, "token"),
+])
+def test_observe_prompt_blocks(lib, torch_cuda, G, H, B, T0, W, scales):
+    """Blocks of rows per wavefront.  1e-5 as in test_observe_prompt_edges."""
+    _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
+
+
+def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales):
+    D = 128
+    say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales}")
+    kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales)
+    rng = np.random.default_rng(T0 + G)
+    K = rng.standard_normal((B, H, T0, D)).astype(np.float16)
+    q = (rng.standard_normal((B, T0, G * H, D)) * 1.5).astype(np.float16)
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
+    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    for b in range(B):
+        for g in range(H):
+            u = O.load_prefill(K[b, g], K[b, g], W, scale_mode=scales)
+            O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(0.9))
+            e_ref = u.ema.astype(np.float64)
+            e_err = np.abs(kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+            assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"unit {(b, g)}: EMA off, max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
+    assert kv.counters().device_errors == 0
+    kv.close()
+
+
 @pytest.mark.parametrize("G,T0,W", [(2, 40, 0), (4, 200, 33), (1, 97, 8)])
 def test_observe_prompt_saturated_channel(lib, torch_cuda, G, T0, W):
     """Channels that reach +-65504 under per-channel scales: 127 times their scale is above the largest fp16."""
