@@ -7,8 +7,8 @@
 // prompt observes it, and the windows' updates telescope to
 //   a_i = gain * sum_{t >= i} lambda^(T-1-t) sum_h p_{t,h,i},
 // so launches over all queries do: the first finds every row's softmax statistics, the second
-// every slot's weighted column sum (in parts of the rows, which a third adds up, where the slots
-// alone would leave the chip idle).  Both recompute the scores on the matrix cores (nothing of
+// every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
+// chip idle, which two small kernels join.  Both recompute the scores on the matrix cores (nothing of
 // size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
 // wavefront and of 64 slots per workgroup, 174 us in these four.
 #pragma once
@@ -17,6 +17,8 @@ constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
 constexpr int kObsItem = 2 * kObsWaves;                // blocks of 16 rows per workgroup of the first kernel: two per wavefront, or
 constexpr int kObsShortItem = kObsWaves, kObsShort = 512;   // one, up to so many tokens
 constexpr int kMassWave = 64, kMassTile = kObsWaves * kMassWave;   // slots per wavefront and workgroup of the second
+constexpr int kMassSb = kMassWave / 16;
+constexpr int kMassShortThreads = 512, kMassShortWaves = kMassShortThreads / kWave;   // of its form for short prompts
 constexpr int kMassStep = 4;                           // blocks of 16 rows it stages at a time
 constexpr int kMassPartsMax = 32, kMassGroups = 1536, kMassStart = 3, kMassSum = 5;
 
@@ -53,9 +55,12 @@ static int observe_row_parts(long long items, int tiles, int most, bool chan, in
   while (cost[n] > 1.03 * best) ++n;
   return n;
 }
-// Parts the rows of the second kernel are cut into: the count whose workgroups (the pairs of a
-// slot tile and a part that are not wholly behind the diagonal) take the least time on the chip,
-// kMassGroups of them at a time, a workgroup costing its steps and about kMassStart more to begin.
+// Parts the rows of the second kernel are cut into, by a cost that was fitted and does not describe the chip (768 workgroups
+// are resident, 512 with per-channel scales; a workgroup alone on its CU takes 5 us to begin and 3 per step, the sum 5):
+// groups -- the pairs of a slot tile and a part that are not wholly behind the diagonal -- in rounds of kMassGroups, each
+// as long as a part's steps and kMassStart.  Measured over 40 shapes of 100 to 3001 tokens in up to twelve part counts of 1 to 32,
+// the choice takes 1.02 times the best of those at the mean; 1.2 for 64 units of 3001 tokens, 4 heads (eight parts 515 us, the
+// three that kMassGroups allows 630) and 256 of 500 tokens, 2 heads (79, uncut 67), 1.16 with per-channel scales (1000 tokens).
 static int observe_mass_parts(int units_per_layer, int G, int T, int most) {
   const long long tiles = (T + kMassTile - 1) / kMassTile, nb = (T + 15) / 16 * G, steps = (nb + kMassStep - 1) / kMassStep;
   long long best = 0;
@@ -81,7 +86,8 @@ size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
 // (A reservation for the most parts that any T could take was 0.1 to 1.6 GB larger than a launch could use on long caches.)
 struct ObservePlan {
   int item, tile, per_part, row_parts;                 // first kernel: blocks per workgroup, slots per tile, tiles per part, parts
-  int width, parts;                                    // second: subtiles per workgroup, parts
+  bool short_form;                                     // second: the kernel of short prompts, or
+  int subtiles, width, parts;                          // subtiles of a unit, per workgroup, parts
   size_t n_rows, stat_floats, floats;
 };
 static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool chan, size_t have, int cus) {
@@ -100,12 +106,20 @@ static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool 
   p.row_parts = one ? 1 : observe_row_parts((long long)units_per_layer * ((nblocks + kObsItem - 1) / kObsItem), tiles,
                                             (int)std::min<size_t>(kObsPartsMax, room / (3 * p.n_rows)), chan, cus);
   p.per_part = (tiles + p.row_parts - 1) / p.row_parts;
-  // A short prompt of few heads runs a subtile per workgroup, whose wavefronts share the rows: 64 tokens of 4 heads
-  // (four steps) 11.2 us with, 12.5 without; 130 tokens (nine) 18.2 with, 11.0 and 4.2 for the sum in parts without.
-  const bool few = T <= kMassTile && nblocks <= 4 * kMassStep;
-  p.width = few ? 1 : kObsWaves;
+  // Second kernel.  More than eight blocks per wavefront of the form for short prompts are cut into parts where parts find idle
+  // CUs.  Otherwise that form, up to a round of workgroups, two of long ones (one of its workgroups fills a CU), and for short prompts
+  // of many units a subtile per workgroup of the other form, whose wavefronts share the rows.  Measured (us, with the sum): 8 units of
+  // 256 tokens, 8 heads 23.6 in the short form, 13.9 in 16 parts; 64 such units 24.5 and 44; 8 units of 300 tokens, 4 heads (76 blocks)
+  // 17.4 and 17.6, 2 heads (38) 13.0 and 15.8; 128 units of 200 tokens, 4 heads (two rounds) 26.6, a subtile per workgroup 32.6, parts
+  // 35.5; 256 units of 65 tokens, 4 heads 21.7 and 15.8, of 40 tokens, 1 head (a round, three blocks) 12.4 and 8.2.
+  p.subtiles = (n8 + kMassWave - 1) / kMassWave + (T - n8 + kMassWave - 1) / kMassWave;
+  const long long subtiles = (long long)units_per_layer * p.subtiles;
+  const bool tile = T <= kMassTile, cut = nblocks > 8 * kMassShortWaves && (!tile || 2 * subtiles <= cus);
+  const long long rounds2 = !tile || nblocks > 4 * kMassShortWaves ? 4 : nblocks > kMassShortWaves ? 2 : 1;   // half rounds
+  p.short_form = !cut && 2 * subtiles <= rounds2 * cus;
+  p.width = !p.short_form && !cut && tile ? 1 : kObsWaves;
   const size_t column = 2 * (size_t)units_per_layer * observe_stride(T);
-  p.parts = few ? 1 : observe_mass_parts(units_per_layer, G, T, (int)std::min<size_t>(kMassPartsMax, room / column));
+  p.parts = p.short_form || p.width == 1 ? 1 : observe_mass_parts(units_per_layer, G, T, (int)std::min<size_t>(kMassPartsMax, room / column));
   p.floats = p.stat_floats + std::max(p.row_parts > 1 ? 3 * p.row_parts * p.n_rows : 0, p.parts > 1 ? column * p.parts : 0);
   return p;
 }
@@ -413,11 +427,137 @@ __device__ __forceinline__ int mass_first_block(const ObserveUnit &un, int sub, 
   return mass_subtile(un, sub, T).base / 16 * G;
 }
 
+// The keys of a subtile as a matrix-core operand, lane (slot t16 of each sixteen, channels 32 s + 8 g4 + [0, 8)), and the
+// slots' factors.
+template <bool kChan>
+__device__ __forceinline__ void mass_keys(const ObserveUnit &un, const MassTile &mt, float sm, int t16, int g4, half8_t (&kb)[kMassSb][4],
+                                          half8_t (&kl)[kChan ? kMassSb : 1][4], float (&f)[kMassSb]) {
+#pragma unroll
+  for (int sb = 0; sb < kMassSb; ++sb) {
+    const int slot = min(mt.base + 16 * sb + t16, mt.lim - 1);
+    if (mt.is8) {
+      const unsigned row = (unsigned)ring_row_u(un.h8, slot, un.cap8);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint2 c = *(const uint2 *)(un.K8 + (size_t)row * 128 + s * 32 + g4 * 8);
+        if constexpr (kChan) scale_codes(c, un.KS + s * 32 + g4 * 8, kb[sb][s], kl[sb][s]);
+        else kb[sb][s] = cvt_i8x8_f16x8(c.x, c.y);
+      }
+      f[sb] = kChan ? sm : __half2float(un.KS[row]) * sm;
+    } else {
+      const __half *src = un.K16 + (size_t)(mt.base < mt.lim ? ring_row(un.h16, slot - un.n8, un.cap16) : 0) * 128 + g4 * 8;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        kb[sb][s] = __builtin_bit_cast(half8_t, *(const int4 *)(src + 32 * s));
+        if constexpr (kChan) kl[sb][s] = half8_t{};
+      }
+      f[sb] = sm;
+    }
+  }
+}
+// What a block of sixteen rows (queries qa of tokens tok0 .., references and weights of rows 4 g4 + [0, 4)) adds to the
+// subtile's columns.
+template <bool kChan>
+__device__ __forceinline__ void mass_block(const MassTile &mt, const half8_t (&qa)[4], const half8_t (&kb)[kMassSb][4],
+                                           const half8_t (&kl)[kChan ? kMassSb : 1][4], const float (&f)[kMassSb], const float4 &ref,
+                                           const double2 &w0, const double2 &w1, int tok0, int t16, int g4, double (&sum)[kMassSb]) {
+  const float M[4] = {ref.x, ref.y, ref.z, ref.w};
+  const double wi[4] = {w0.x, w0.y, w1.x, w1.y};
+  floatx4_t acc[kMassSb];
+#pragma unroll
+  for (int sb = 0; sb < kMassSb; ++sb) {
+    acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (kChan) {
+      if (mt.is8) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kl[sb][s], acc[sb], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int sb = 0; sb < kMassSb; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kb[sb][s], acc[sb], 0, 0, 0);
+  auto add = [&](auto edge) {
+#pragma unroll
+    for (int sb = 0; sb < kMassSb; ++sb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -M[i]));   // (a reference may lie up to 5 below a score)
+        const double term = (double)e * wi[i];
+        sum[sb] += edge && mt.base + 16 * sb + t16 > tok0 + 4 * g4 + i ? 0.0 : term;
+      }
+  };
+  if (tok0 < mt.base + kMassWave - 1) add(std::true_type{});
+  else add(std::false_type{});
+}
+
+// Short prompts: a workgroup of eight wavefronts per 64 slots, its wavefronts taking the blocks of rows in turn, each reading
+// its queries for itself, so that nobody waits for anybody before the sums meet.  In the kernel below the few steps of such
+// a prompt are latency: 100 tokens of 4 heads and 8 kv-heads 18.7 us there (13.8 in four parts with their sum), 9.4 here.
+template <bool kChan>
+__global__ __launch_bounds__(kMassShortThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void observe_mass_short_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, ObserveStats stats) {
+  constexpr int D = 128;
+  __shared__ double red[kMassShortWaves][kMassWave];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, g4 = lane >> 4;
+  const int g = blockIdx.x % cv.Hkv, b = blockIdx.z, G = cv.G;
+  const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
+  const ObserveUnit un = observe_unit(cv, u, T);
+  const MassTile mt = mass_subtile(un, blockIdx.x / cv.Hkv, T);
+  if (mt.base >= mt.lim) return;
+  const int first = mt.base / 16 * G, last = (T + 15) / 16 * G, stride = observe_stride(T);
+  struct Rows {
+    confkv_v4i q[4];
+    float4 ref;
+    double2 w0, w1;
+  };
+  auto load = [&](int block) -> Rows {
+    const int at = min(block, last - 1), tb = at / G, h = at - tb * G;
+    const __half *src = q + (((size_t)b * T + min(tb * 16 + t16, T - 1)) * cv.Hkv * G + (size_t)g * G + h) * D + g4 * 8;
+    const size_t row = ((size_t)ul * G + h) * stride + tb * 16 + 4 * g4;
+    Rows r;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) r.q[s] = *(const confkv_v4i *)(src + 32 * s);
+    r.ref = *(const float4 *)&stats.ref[row];
+    r.w0 = *(const double2 *)&stats.weight[row];
+    r.w1 = *(const double2 *)&stats.weight[row + 2];
+    return r;
+  };
+  Rows next = load(first + w);
+  half8_t kb[kMassSb][4], kl[kChan ? kMassSb : 1][4];
+  float f[kMassSb];
+  mass_keys<kChan>(un, mt, sm, t16, g4, kb, kl, f);
+  double sum[kMassSb] = {};
+  for (int block = first + w; block < last; block += kMassShortWaves) {
+    const Rows r = next;
+    next = load(block + kMassShortWaves);
+    half8_t qa[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qa[s] = __builtin_bit_cast(half8_t, r.q[s]);
+    mass_block<kChan>(mt, qa, kb, kl, f, r.ref, r.w0, r.w1, block / G * 16, t16, g4, sum);
+  }
+#pragma unroll
+  for (int sb = 0; sb < kMassSb; ++sb) {
+    sum[sb] += __shfl_xor(sum[sb], 16, kWave);
+    sum[sb] += __shfl_xor(sum[sb], 32, kWave);
+    if (g4 == 0) red[w][16 * sb + t16] = sum[sb];
+  }
+  __syncthreads();
+  const int slot = mt.base + lane;
+  if (w > 0 || slot >= mt.lim) return;
+  double A = 0.0;
+#pragma unroll
+  for (int k = 0; k < kMassShortWaves; ++k) A += red[k][lane];
+  cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, slot)] = (float)A;
+}
+
 template <bool kChan>
 __global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(kChan ? 2 : 3, kChan ? 2 : 3)))
 void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, int ntiles, int width /* subtiles per workgroup */,
                          int parts, ObserveStats stats) {
-  constexpr int D = 128, kSb = kMassWave / 16, kRows = 16 * kMassStep;
+  constexpr int D = 128, kSb = kMassSb, kRows = 16 * kMassStep;
   __shared__ __align__(16) uint8_t rows[2][kRows * kKRow16];
   __shared__ __align__(16) float s_ref[2][kRows];
   __shared__ __align__(16) double s_weight[2][kRows];
@@ -428,13 +568,13 @@ void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, 
   const ObserveUnit un = observe_unit(cv, u, T);
   const int len = mass_part_blocks(parts, G, T);
   const int first = max(part * len, mass_first_block(un, tile * width, G, T)), last = min((part + 1) * len, (T + 15) / 16 * G);
-  if (first >= last || mass_subtile(un, tile * width, T).base >= T) return;   // (the grid is sized for the worst rounding)
+  if (first >= last || mass_subtile(un, tile * width, T).base >= T) return;
   // (a tile of one or two subtiles: its wavefronts share the rows of a step, and their sums meet in LDS)
   const int subs = min(width, (un.n8 + kMassWave - 1) / kMassWave + (T - un.n8 + kMassWave - 1) / kMassWave - tile * width);
   const int across = subs >= 3 ? 4 : subs, shares = kObsWaves / across, share = w / across;
   const MassTile mt = mass_subtile(un, tile * width + w % across, T);
   const int base = mt.base, lim = mt.lim;
-  const bool mine = base < lim, is8 = mt.is8;
+  const bool mine = base < lim;
 
   // rows of step `at`: thread (token, piece) takes sixteen bytes of each of its blocks' rows
   const int ltok = tid >> 4, lc = tid & 15, stride = observe_stride(T);
@@ -475,28 +615,7 @@ void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, 
 
   half8_t kb[kSb][4], kl[kChan ? kSb : 1][4];
   float f[kSb];
-#pragma unroll
-  for (int sb = 0; sb < kSb; ++sb) {
-    const int slot = min(base + 16 * sb + t16, lim - 1);
-    if (is8) {
-      const unsigned row = (unsigned)ring_row_u(un.h8, slot, un.cap8);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const uint2 c = *(const uint2 *)(un.K8 + (size_t)row * D + s * 32 + g4 * 8);
-        if constexpr (kChan) scale_codes(c, un.KS + s * 32 + g4 * 8, kb[sb][s], kl[sb][s]);
-        else kb[sb][s] = cvt_i8x8_f16x8(c.x, c.y);
-      }
-      f[sb] = kChan ? sm : __half2float(un.KS[row]) * sm;
-    } else {
-      const __half *src = un.K16 + (size_t)(mine ? ring_row(un.h16, slot - un.n8, un.cap16) : 0) * D + g4 * 8;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        kb[sb][s] = __builtin_bit_cast(half8_t, *(const int4 *)(src + 32 * s));
-        if constexpr (kChan) kl[sb][s] = half8_t{};
-      }
-      f[sb] = sm;
-    }
-  }
+  mass_keys<kChan>(un, mt, sm, t16, g4, kb, kl, f);
 
   double sum[kSb] = {};
   for (int at = first, buf = 0; at < last; at += kMassStep, buf ^= 1) {
@@ -524,35 +643,7 @@ void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, 
       for (int s = 0; s < 4; ++s) qa[s] = *(const half8_t *)(rows[buf] + (16 * k + t16) * kKRow16 + s * 64 + g4 * 16);
       const float4 ref = *(const float4 *)&s_ref[buf][16 * k + 4 * g4];
       const double2 w0 = *(const double2 *)&s_weight[buf][16 * k + 4 * g4], w1 = *(const double2 *)&s_weight[buf][16 * k + 4 * g4 + 2];
-      const float M[4] = {ref.x, ref.y, ref.z, ref.w};
-      const double wi[4] = {w0.x, w0.y, w1.x, w1.y};
-      floatx4_t acc[kSb];
-#pragma unroll
-      for (int sb = 0; sb < kSb; ++sb) {
-        acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        if constexpr (kChan) {
-          if (is8) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kl[sb][s], acc[sb], 0, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int sb = 0; sb < kSb; ++sb) acc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], kb[sb][s], acc[sb], 0, 0, 0);
-      auto add = [&](auto edge) {
-#pragma unroll
-        for (int sb = 0; sb < kSb; ++sb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float e = exp_nonpos(fmaf(acc[sb][i], f[sb], -M[i]));   // (a reference may lie up to 5 below a score)
-            const double term = (double)e * wi[i];
-            sum[sb] += edge && base + 16 * sb + t16 > tok0 + 4 * g4 + i ? 0.0 : term;
-          }
-      };
-      if (tok0 < base + kMassWave - 1) add(std::true_type{});
-      else add(std::false_type{});
+      mass_block<kChan>(mt, qa, kb, kl, f, ref, w0, w1, tok0, t16, g4, sum);
     }
   }
 #pragma unroll
@@ -608,7 +699,9 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
   const ObservePlan plan = observe_plan(units, cv.G, T, n8, cv.chan != 0, scratch_floats, device_cus());
   if (plan.floats > scratch_floats) return hipErrorInvalidValue;
   const int tile = plan.tile, per_part = plan.per_part, row_parts = plan.row_parts, width = plan.width, parts = plan.parts;
-  const int ntiles = (T + kMassWave * width - 1) / (kMassWave * width) + 1;
+  // (an odd count: a unit's workgroups follow one another on its XCD, and with an even one the tiles of most rows always fall to
+  // the same shader engines: 64 units of 300 tokens, 8 heads 80 us with two tiles, 65 with three; of 700 tokens, 2 heads 88 with four)
+  const int ntiles = (plan.subtiles + width - 1) / width | 1;
   const int nitems = (nblocks + plan.item - 1) / plan.item;
   const dim3 rows(cv.Hkv * nitems * row_parts, 1, cv.B), slots(cv.Hkv * ntiles * parts, 1, cv.B);
   const size_t n_rows = plan.n_rows;
@@ -626,6 +719,12 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
   hipLaunchKernelGGL(first, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
   if (row_parts > 1)
     hipLaunchKernelGGL(observe_join_kernel, dim3((unsigned)((n_rows + kObsThreads - 1) / kObsThreads)), dim3(kObsThreads), 0, stream, cv, layer, T, tile, decay, gain, per_part, stats);
+  if (plan.short_form) {
+    const dim3 grid(cv.Hkv * plan.subtiles, 1, cv.B);
+    if (cv.chan) hipLaunchKernelGGL(observe_mass_short_kernel<true>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, stats);
+    else hipLaunchKernelGGL(observe_mass_short_kernel<false>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, stats);
+    return hipGetLastError();
+  }
   if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
   else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
   if (parts > 1)

@@ -528,6 +528,18 @@ def test_observe_prompt_blocks(lib, torch_cuda, G, H, B, T0, W, scales):
     _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
 
 
+@pytest.mark.parametrize("G,H,B,T0,W,scales", [
+    (4, 2, 2, 63, 16, "token"), (1, 1, 2, 64, 0, "channel"),   # one or two subtiles of 64 slots
+    (16, 1, 2, 64, 20, "token"),                                   # eight blocks per wavefront of the form for short prompts
+    (1, 2, 2, 300, -1, "token"), (2, 1, 1, 500, 130, "channel"),   # that form beyond a tile of four subtiles
+    (1, 4, 17, 33, 8, "token"), (2, 4, 33, 70, 8, "token"),        # many units: a subtile per workgroup, three and ten blocks
+    (4, 4, 33, 64, -1, "token"),                                   # half a round of the short form's workgroups; two blocks each
+])
+def test_observe_prompt_forms(lib, torch_cuda, G, H, B, T0, W, scales):
+    """Edges of the forms that the number of units and blocks chooses between.  1e-5 as in test_observe_prompt_edges."""
+    _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
+
+
 def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales):
     D = 128
     say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales}")
