@@ -477,10 +477,10 @@ int conf_kv_observe_prompt(conf_kv_handle *h, int32_t layer, const void *dev_q16
   // (accepted where conf_kv_observe is)
   if (h->cfg.max_chunk < 2 && h->cv.G <= 8) return CONF_KV_ERR_INVALID_ARG;
   if ((uintptr_t)dev_q16 & 15) return CONF_KV_ERR_INVALID_ARG;
-  // A prompt that fits one conf_kv_observe call is one launch there.  The kernels over all
-  // queries take a group's heads in turn: eight kv-heads, 1 head of 16 tokens 10.7 us as one call
-  // and 11.8 as kernels over all queries, of 20 tokens 15.2 and 12.2 (more rows than one tile); 4 heads of 32
-  // tokens 16.1 and 17.2; 16 heads of 8 tokens 11.2 and 27.5.
+  // A prompt that fits one conf_kv_observe call is one launch there.  Eight kv-heads, us as one call and as the two
+  // kernels over all queries: rows of one tile 8.3 and 10.0 (1 head of 16 tokens), 7.2 and 8.0 (4 of 4); more rows 9.4 and 9.6 (1 of
+  // 20), 12.8 and 12.0 (3 of 42), 15.9 and 13.8 (1 of 128), 11.7 and 11.4 (4 of 32), 10.4 and 10.3 (16 of 8).  So few heads, which reach
+  // many tokens, take the kernels, and groups of four the single launch (a host-bound caller up to 9 % shorter).
   if (T0 <= std::max(1, h->cfg.max_chunk) && (T0 * h->cv.G <= kChunkRows || h->cv.G >= 4))
     return attend_tokens(h, layer, T0, dev_q16, nullptr, nullptr, nullptr, stream, 0);
   CK_HIP(h, launch_observe_prompt(h->cv, layer, (const __half *)dev_q16, T0, h->cfg.sm_scale, (double)h->cfg.ema_decay,
