@@ -240,10 +240,16 @@ int conf_kv_load_prefill(conf_kv_handle *h, int32_t layer, const void *dev_k16,
  * (CONF_KV_ERR_BAD_STATE otherwise); CONF_KV_ERR_CAPACITY, before anything is launched,
  * if the unit could already hold `capacity` tokens.
  * The workgroups that share a unit exchange partial results inside the launch, so the launch
- * is sized to be resident on the device all at once.  Other kernels running at the same time
- * only delay it (its waits are bounded at several hundred milliseconds); a wait that does
- * expire leaves the call's outputs undefined and is reported by conf_kv_counters
- * (device_errors, CONF_KV_ERR_DEVICE).
+ * is sized to be resident on the device all at once.  Kernels that do not wait for one another,
+ * running at the same time, only delay it (its waits are bounded at several hundred
+ * milliseconds); a wait that does expire leaves the call's outputs undefined and is reported by
+ * conf_kv_counters (device_errors, CONF_KV_ERR_DEVICE).  Two launches of this kind on two streams
+ * (other handles: conf_kv_attend, conf_kv_attend_chunk, conf_kv_observe, conf_kv_step) may each
+ * hold compute units that the other's workgroups wait for if together they need more than the
+ * device has; order such calls by events where their grids are large.  A call of this function
+ * takes up to one workgroup per compute unit.  Calls of more than 16 / G tokens
+ * (conf_kv_attend_chunk) take more than half of them only from 256 slots and eight splits a unit
+ * on, or, with a multiple of eight kv-heads, where two such calls do not stop each other.
  */
 int conf_kv_attend(conf_kv_handle *h, int32_t layer, const void *dev_q16, const void *dev_knew16,
                    const void *dev_vnew16, void *dev_out16, conf_kv_stream stream);

@@ -1759,22 +1759,36 @@ bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n
   }
 }
 
-// Twice the splits pay while a split keeps 96 slots, from eight to sixteen while it keeps 160 (us per launch of one
-// sequence, eight kv-heads with four heads, 16 tokens unless stated): 300 slots in 1, 2, 4 splits of 8 tokens 19.2, 16.8, 16.4; 600
-// in 2, 4, 8 20.1, 17.6, 18.5; 1000 slots, 32 tokens in 2, 4, 8 46.5, 35.2, 30.0; 2000 in 8, 16 26.8, 28.3; 3000 30.7,
-// 29.8; 9000 54.3, 42.6; 64 units of 500 slots in 2, 4 27.7, 22.7.
-static int wide_split_slots(int ns) { return ns > 8 ? 160 : 96; }
+// Splits of a unit in the many-rows kernel, whose workgroups have a CU each and wait for the unit's other splits: two
+// launches on two streams that together need more CUs than there are can each hold some that the other's splits wait for, until the
+// polls expire.  256 slots a split, up to eight, are taken while the grid fits the chip.  Beyond that twice the splits pay while a
+// split keeps 96 slots, 160 from eight to sixteen, and are taken where two such launches cannot stop each other: a grid of at
+// most half of the CUs, or eight kv-heads or a multiple in the kv-head-first grid (major_kv; 0: the other grid).  An XCD then gets
+// the splits of kv/8 units in order, so that of a launch that is not all there at most kv/8 * (splits - 1) workgroups per XCD
+// wait -- all earlier units are complete and end -- and two launches leave a CU free if that is less than half of its CUs.
+// us per launch, eight kv-heads with four heads, 16 tokens: 64 units of 500 slots in 1, 2, 4 splits 31, 24.8, 20.2, of 1000
+// in 2, 4 32.1, 26.5; 32 of 1200 in 4, 8 25.8, 22.8; 16 of 5000 in 8, 16 37.3, 33.8, of 9000 52.0, 42.8; 8 of 2000 26.8, 28.3, of
+// 3000 30.7, 29.8; of 300 slots, 8 tokens in 1, 2, 4 19.2, 16.8, 16.4; of 600 in 2, 4, 8 20.1, 17.6, 18.5.
+int attend_wide_splits(int units_per_layer, int major_kv, int n_ub, int most, int cus) {
+  int ns = 1;
+  while (ns * 2 <= std::min(most, 8) && ns * 2 * units_per_layer <= cus && n_ub / (ns * 2) >= 256) ns *= 2;
+  auto beside = [&](int n) {
+    return 2 * n * units_per_layer <= cus ||
+           (n * units_per_layer <= cus && major_kv > 0 && major_kv % 8 == 0 && 2 * (major_kv / 8) * (n - 1) < cus / 8);
+  };
+  while (ns * 2 <= most && beside(ns * 2) && n_ub / (ns * 2) >= (ns * 2 > 8 ? 160 : 96)) ns *= 2;
+  return ns;
+}
 
 // Calls with more than 16 query rows per unit: row groups (a power of two) and split count.  The
 // splits of a unit exchange partials inside the launch, so with more than one split the whole grid
 // must be resident (one workgroup per CU: the tile buffers take most of the LDS).
-bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits, AttendPlan *plan) {
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int forced_splits, AttendPlan *plan) {
   const DeviceLimits &lim = device_limits();
   if (!lim.ok || rows <= kChunkRows || rows > kWideMaxRows) return false;
   int rg = 1;
   while (rg * kWideRows < rows) rg *= 2;
-  int ns = 1;
-  while (ns * 2 <= wide_max_splits(rg * kWideRows) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= wide_split_slots(ns * 2)) ns *= 2;
+  int ns = attend_wide_splits(units_per_layer, major_kv, n_ub, wide_max_splits(rg * kWideRows), lim.cus);
   if (forced_splits > 0) {
     ns = 1;
     while (ns * 2 <= std::min(forced_splits, wide_max_splits(rg * kWideRows)) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;

@@ -78,9 +78,10 @@ size_t attend_spill_floats(int units_per_layer, int G, int cap);   // scratch th
 bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n_ub, int n16_ub, int forced_splits,
                  bool force_two_launch, size_t extra_lds, AttendPlan *plan);
 // Plan of a call with more than kChunkRows query rows per unit (at most kWideRowsMax); false when
-// the shape cannot be served.
+// the shape cannot be served.  major_kv: kv-heads of the kv-head-first grid, 0 for the other.
 constexpr int kWideRowsMax = 128;
-bool attend_wide_plan(int rows, int units_per_layer, int n_ub, int forced_splits, AttendPlan *plan);
+int attend_wide_splits(int units_per_layer, int major_kv, int n_ub, int most, int cus);
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int forced_splits, AttendPlan *plan);
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,

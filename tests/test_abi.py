@@ -89,6 +89,29 @@ def test_prompt_phase_scratch(clib):
     assert cut > 1000
 
 
+def test_many_rows_splits_leave_room_for_a_second_call(clib):
+    """Workgroups of a call of many rows wait for the unit's other splits, one per CU: two such calls side by side must not
+    fill the chip with waiting ones.  Beyond the splits of 256 slots, up to eight, a call takes half of the CUs, or the number
+    of its workgroups that can wait on an XCD of 32 CUs (kv/8 units, all splits but one) stays below 16."""
+    splits = getattr(clib, "_ZN6confkv18attend_wide_splitsEiiiii")
+    full = 0
+    for kv in (1, 2, 4, 8, 12, 16, 24, 32, 64):
+        for B in (1, 2, 3, 4, 5, 8, 16, 32, 64):
+            for n in (1, 64, 191, 192, 400, 600, 1000, 2048, 2560, 5000, 30000):
+                for most in (8, 16):
+                    for major in {0, kv if kv % 8 == 0 else 0}:
+                        units, ns = kv * B, splits(kv * B, major, n, most, 256)
+                        plain = 1
+                        while 2 * plain <= 8 and 2 * plain * units <= 256 and n // (2 * plain) >= 256:
+                            plain *= 2
+                        assert plain <= ns <= most and (ns == 1 or ns * units <= 256)
+                        if ns > plain and 2 * ns * units > 256:
+                            assert major and major // 8 * (ns - 1) < 16, (kv, B, n, most, ns)
+                            full += 1
+    assert full                                                  # (64 units of 8 kv-heads in four splits, 16 in sixteen)
+    assert splits(16, 16, 2560, 16, 256) == 8 and splits(16, 8, 2560, 16, 256) == 16
+
+
 @pytest.mark.parametrize("bad", [dict(head_dim=96), dict(n_q_heads=34, n_kv_heads=2), dict(n_q_heads=18, n_kv_heads=2, head_dim=64), dict(n_q_heads=7),
                                  dict(capacity=100), dict(capacity=128), dict(vocab=1), dict(alpha=1.5),
                                  dict(n_tight=[200, 64]), dict(protected_window=-1), dict(n_layers=0),

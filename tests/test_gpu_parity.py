@@ -963,6 +963,42 @@ def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=23 * G + T0)
 
 
+@pytest.mark.parametrize("H,B", [(16, 1), (4, 4)])
+def test_many_rows_calls_on_two_streams(lib, torch_cuda, H, B):
+    """Two managers on two streams, each call half of the CUs with splits that wait for one another: the same outputs and
+    importance as one after the other, no expired wait."""
+    torch = torch_cuda
+    G, D, T0, tq, L = 4, 128, 2600, 16, 8
+    say(f"many-rows calls on two streams Hkv={H} B={B}")
+    rng = torch.Generator(device="cuda").manual_seed(H)
+    normal = lambda *shape: torch.randn(shape, generator=rng, device="cuda", dtype=torch.float16)
+    K = [normal(B, H, T0, D) for _ in range(2)]
+    q, x = [normal(B, tq, G * H, D) for _ in range(2)], [normal(B, tq, H, D) for _ in range(2)]
+    def run(streams):
+        kvs = [_mk(lib, n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=64, capacity=T0 + 56,
+                   protected_window=tq, n_tight=[T0] * L, n_loose=[T0 + tq] * L, max_chunk=tq) for _ in range(2)]
+        out = [torch.empty(L, B, tq, G * H, D, dtype=torch.float16, device="cuda") for _ in range(2)]
+        for i, kv in enumerate(kvs):
+            for l in range(L):
+                kv.load_prefill(l, K[i], K[i])
+        torch.cuda.synchronize()
+        for l in range(L):
+            for i, kv in enumerate(kvs):
+                with torch.cuda.stream(streams[i]):
+                    kv.attend_chunk(l, q[i], x[i], x[i], out[i][l])
+        torch.cuda.synchronize()
+        ema = [kv.export(L - 1, B - 1, H - 1, planes=("ema",))["ema"] for kv in kvs]
+        assert all(kv.counters().device_errors == 0 for kv in kvs)
+        for kv in kvs:
+            kv.close()
+        return out, ema
+    one = torch.cuda.current_stream()
+    ref, ref_ema = run([one, one])
+    got, ema = run([torch.cuda.Stream(), torch.cuda.Stream()])
+    for i in range(2):
+        assert torch.equal(ref[i], got[i]) and np.array_equal(ref_ema[i], ema[i])
+
+
 @pytest.mark.parametrize("RG", [1, 2, 4])
 def test_many_rows_kernel_keeps_its_registers(lib, torch_cuda, RG):
     """No scratch memory: with every register in use, what lives past the first pass (lane indices, source pointers) spilled."""
