@@ -462,7 +462,8 @@ def test_observe_prompt_covers_every_query(lib, torch_cuda, G, T0, W, mc):
     (4, 1027, 128, "token", 0.0, None),       # only the last query counts
 ])
 def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
-    """Tile and block edges of the prompt-phase kernels (32-slot tiles, 16-token blocks, 64-token strides).
+    """Tile and block edges of the prompt-phase kernels (64-slot tiles, 32 under per-channel scales; 16-token blocks; tiles of
+    four subtiles of 64 slots).
     An importance is a sum of probabilities whose scores carry fp32 rounding of 128 products: 1e-5 relative."""
     torch = torch_cuda
     H, B, D = 2, 2, 128
@@ -490,15 +491,15 @@ def test_observe_prompt_edges(lib, torch_cuda, G, T0, W, scales, decay, gain):
 
 
 @pytest.mark.parametrize("G,T0,W,scales", [
-    (4, 64, 32, "token"), (4, 65, 0, "token"),        # a subtile per workgroup, its wavefronts sharing the rows; one row block more: parts
-    (16, 129, 64, "token"), (1, 256, -1, "token"),    # one tile of the column kernel
+    (4, 64, 32, "token"), (4, 65, 0, "token"),        # the columns of short prompts: one subtile of 64 slots, a block more
+    (16, 129, 64, "token"), (1, 256, -1, "token"),    # one tile of the column kernel in parts; four subtiles of the short form
     (5, 257, 130, "token"),                           # ends of parts inside a token's heads; a tile of one subtile at the end
-    (2, 520, 8, "channel"),                           # rows cut into parts of 32-slot tiles
-    (1, 700, 100, "token"), (3, 1100, 37, "token"),   # and of 64-slot tiles, INT8 and FP16 ones; several column tiles
+    (2, 520, 8, "channel"),                           # rows over 32-slot tiles, uncut; several column tiles
+    (1, 700, 100, "token"), (3, 1100, 37, "token"),   # the short form over twelve subtiles; rows and columns both cut, INT8 and FP16 tiles
 ])
 def test_observe_prompt_parts(lib, torch_cuda, G, T0, W, scales):
-    """One unit, so that both prompt-phase kernels cut their work into as many parts as they ever do.  1e-5 as in
-    test_observe_prompt_edges."""
+    """One unit, so that the column kernel cuts its rows into as many parts as it ever does, and the row kernel those of 1100
+    tokens.  1e-5 as in test_observe_prompt_edges."""
     torch = torch_cuda
     D = 128
     say(f"observe_prompt parts G={G} T0={T0} W={W} scales={scales}")
@@ -525,6 +526,17 @@ def test_observe_prompt_parts(lib, torch_cuda, G, T0, W, scales):
 ])
 def test_observe_prompt_blocks(lib, torch_cuda, G, H, B, T0, W, scales):
     """Blocks of rows per wavefront.  1e-5 as in test_observe_prompt_edges."""
+    _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
+
+
+@pytest.mark.parametrize("G,H,B,T0,W,scales", [
+    (3, 2, 2, 1100, 37, "token"),                # rows in nine parts of two tiles, columns in 26: [part][unit][head][token]
+    (2, 2, 2, 1100, 8, "channel"),               # twelve parts of three tiles of 32 slots, 18 of the columns
+    (4, 3, 1, 700, 64, "token"),                 # eleven parts of one tile, the last of which only the last tokens reach
+])
+def test_observe_prompt_parts_of_several_units(lib, torch_cuda, G, H, B, T0, W, scales):
+    """Parts of both prompt-phase kernels with several sequences and kv-heads, every unit with data of its own, at a decay that
+    lets every query count.  1e-5 as in test_observe_prompt_edges."""
     _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
 
 
