@@ -10,7 +10,7 @@
 // every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
 // chip idle, which two small kernels join.  Both recompute the scores on the matrix cores (nothing of
 // size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
-// wavefront and of 64 slots per workgroup, 174 us in these four.
+// wavefront and of 64 slots per workgroup, 170 to 175 us in these four.
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
@@ -175,8 +175,8 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
 // are staged once for its eight blocks as fp16 in two alternating LDS buffers (one barrier per tile).
 // Scores come transposed, a lane's rows being slots of one query: one running reference and sum
 // per lane and block, no reduction inside the loop; the sum goes over to 64 bits with every tile.
-// 120 -> 82 us per layer of 3001 tokens and 32 heads; while a CU is busy, vector ALU and matrix cores are at work in
-// turn 95 % of the time.
+// 120 -> 81 us per layer of 3001 tokens and 32 heads; while a CU is busy, vector ALU and matrix cores are at work in
+// turn 93 % of the time.
 // Causal work falls along the list of items: long ones are cut into parts of their slots.
 // A score costs a multiply-add, a product with log2 e, one hardware exponential and one addition.
 // (log2 e folded into the slots' factors would save the product, but rounds the factor once more: an
