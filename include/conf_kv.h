@@ -248,8 +248,9 @@ int conf_kv_load_prefill(conf_kv_handle *h, int32_t layer, const void *dev_k16,
  * hold compute units that the other's workgroups wait for if together they need more than the
  * device has; order such calls by events where their grids are large.  A call of this function
  * takes up to one workgroup per compute unit.  Calls of more than 16 / G tokens
- * (conf_kv_attend_chunk) take more than half of them only from 256 slots and eight splits a unit
- * on, or, with a multiple of eight kv-heads, where two such calls do not stop each other.
+ * (conf_kv_attend_chunk, conf_kv_observe) take more than half of them only while a workgroup has
+ * 256 slots and a unit at most eight workgroups, or, with a multiple of eight kv-heads, where two
+ * such calls do not stop each other.
  */
 int conf_kv_attend(conf_kv_handle *h, int32_t layer, const void *dev_q16, const void *dev_knew16,
                    const void *dev_vnew16, void *dev_out16, conf_kv_stream stream);
