@@ -1011,6 +1011,44 @@ def test_many_rows_calls_on_two_streams(lib, torch_cuda, H, B):
         assert torch.equal(ref[i], got[i]) and np.array_equal(ref_ema[i], ema[i])
 
 
+@pytest.mark.parametrize("G,tq,T0", [(4, 16, 150), (8, 16, 300), (1, 32, 200)])
+def test_many_rows_largest_probability_is_exact(lib, torch_cuda, G, tq, T0):
+    """FP16 slots; every row leans on one key and 1 to 3.9 units more on a later one, eight tiles of 16 on (the same
+    wavefront).  With the reference at the row's maximum the second probability is 1 and rounds to itself, the first by at
+    most 2^-11 of it: the output is within half an ulp of its own rounding, that part of the first term, and fp32 sums of
+    values up to 4.  A probability of e^1 to e^3.9 that rounds too moves it by up to 2^-11 of the second term."""
+    torch = torch_cuda
+    D, sm = 128, 1 / math.sqrt(128)
+    say(f"largest probability of many rows G={G} tq={tq} T0={T0}")
+    rng = np.random.default_rng(G)
+    R = G * tq
+    e = np.linalg.qr(rng.standard_normal((D, D)))[0][:2]                # two directions: one key each
+    K = np.zeros((1, 1, T0, D), np.float16)
+    V = rng.standard_normal((1, 1, T0, D)).astype(np.float16)
+    K[0, 0, 5], K[0, 0, 8 * 16 + 3] = (8 * e).astype(np.float16)        # (the other keys are zero)
+    lead = rng.uniform(1.0, 3.9, R)
+    q = ((30 / (8 * sm)) * e[0] + ((30 + lead) / (8 * sm))[:, None] * e[1]).reshape(1, tq, G, D).astype(np.float16)
+    os.environ["CONF_KV_SPLITS"] = "1"
+    try:
+        kv = _mk(lib, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=-1, capacity=((T0 + tq + 71) // 64) * 64, protected_window=4,
+                 n_tight=[T0], n_loose=[T0], max_chunk=tq)
+    finally:
+        os.environ.pop("CONF_KV_SPLITS", None)
+    kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda())
+    x = torch.zeros((1, tq, 1, D), dtype=torch.float16, device="cuda")
+    out = torch.empty((1, tq, G, D), dtype=torch.float16, device="cuda")
+    kv.attend_chunk(0, torch.from_numpy(q).cuda(), x, x, out)
+    s = q.reshape(R, D).astype(np.float64) @ np.concatenate([K[0, 0], np.zeros((tq, D))]).astype(np.float64).T * float(f32(sm))
+    p = np.exp(s - s.max(-1, keepdims=True))
+    ref = (p / p.sum(-1, keepdims=True)) @ np.concatenate([V[0, 0], np.zeros((tq, D))]).astype(np.float64)
+    got = out.cpu().numpy().reshape(R, D).astype(np.float64)
+    ulp = np.exp2(np.floor(np.log2(np.maximum(np.abs(ref), 2.0 ** -14))) - 10)
+    first = (p[:, 5] / p.sum(-1))[:, None] * np.abs(V[0, 0, 5].astype(np.float64))
+    over = np.abs(got - ref) / (0.5 * ulp + 2.0 ** -11 * first + 4e-6)
+    assert over.max() <= 1.0, f"{over.max():.3f} of the bound"
+    kv.close()
+
+
 @pytest.mark.parametrize("RG", [1, 2, 4])
 def test_many_rows_kernel_keeps_its_registers(lib, torch_cuda, RG):
     """No scratch memory: with every register in use, what lives past the first pass (lane indices, source pointers) spilled."""
