@@ -19,10 +19,44 @@ namespace confkv {
 constexpr int kEvThreads = 256;
 
 // ---------------------------------------------------------------------------------------
-// Quantiser shared by the prompt loader and the demotion kernel.
-// One wavefront quantises one D-vector: scale = fl16(fl32(amax / 127)),
-// code = clamp(rint(x / scale), -127, 127) with IEEE fp32 division and round-half-even.
+// Quantiser shared by the prompt loader and the demotion kernel: per row of D values
+// scale = fl16(fl32(amax / 127)), code = clamp(rint(fl32(x / scale)), -127, 127), round-half-even.
+//
+// No division is issued for the codes (the compiler's IEEE sequence is some ten instructions, two of
+// them at a quarter of the rate; the loader was bound by them, not by memory).  With y the hardware's
+// reciprocal of the scale, q0 = x y is off by less than 2^-22 of itself and q = q0 + (x - q0 s) y, two
+// fused operations, by a few 2^-45 before its own rounding.  x and s are fp16 numbers, eleven bits
+// each: where the magnitude is below 128, x / s is a multiple of one half, which q then hits exactly,
+// or at least 2^-12 away from every one, which q cannot cross; so q rounds to the same code as the
+// correctly rounded quotient.  A scale that is zero or not finite means codes 0.
 // ---------------------------------------------------------------------------------------
+__device__ __forceinline__ float code_quotient(float x, float s, float y) {
+  const float q0 = x * y;
+  return fmaf(fmaf(-q0, s, x), y, q0);
+}
+// The code of quotient q in the low byte: adding 1.5 * 2^23 rounds half-even and leaves the integer
+// in the low bits.  (NaN gives -127.)
+__device__ __forceinline__ unsigned code_bits(float q) {
+  return __float_as_uint(fminf(fmaxf(q, -127.f), 127.f) + 12582912.f);
+}
+// Of a row's largest magnitude: the stored scale, 0 where it is dead, and its reciprocal (0 with it).
+__device__ __forceinline__ __half row_scale(float amax, float *s, float *y) {
+  const __half hs = __float2half_rn(__fdiv_rn(amax, 127.0f));
+  const float sf = __half2float(hs);
+  const bool dead = !(sf > 0.f) || isinf(sf);
+  *s = sf;
+  *y = dead ? 0.f : __builtin_amdgcn_rcpf(sf);
+  return dead ? __float2half_rn(0.f) : hs;
+}
+// Code of x against a fixed channel scale, whatever x is: the first estimate stays finite, so an
+// infinite x saturates; a channel whose scale is 0 gets code 0 (scales are finite).
+__device__ __forceinline__ unsigned channel_code_bits(float x, float s, float y) {
+  const float q0 = fminf(fmaxf(x * y, -256.f), 256.f);
+  const float q = fmaf(fmaf(-q0, s, x), y, q0);
+  return s > 0.f ? code_bits(q) : 0u;
+}
+
+// One wavefront quantises one D-vector.
 template <int D>
 __device__ __forceinline__ void quantize_row_wave(const __half *__restrict__ src,
                                                   int8_t *__restrict__ dst_codes,
@@ -40,22 +74,17 @@ __device__ __forceinline__ void quantize_row_wave(const __half *__restrict__ src
 #pragma unroll
   for (int e = 0; e < EPL; ++e) amax = fmaxf(amax, fabsf(x[e]));
   amax = wave_max(amax);
-  const __half hs = __float2half_rn(__fdiv_rn(amax, 127.0f));
-  const float sf = __half2float(hs);
-  const bool dead = !(sf > 0.f) || isinf(sf);
-  int code[EPL];
+  float s, y;
+  const __half hs = row_scale(amax, &s, &y);
+  unsigned code[EPL];
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) {
-    float r = dead ? 0.f : rintf(__fdiv_rn(x[e], sf));
-    r = fminf(fmaxf(r, -127.f), 127.f);
-    code[e] = (int)r;
-  }
+  for (int e = 0; e < EPL; ++e) code[e] = y > 0.f ? code_bits(code_quotient(x[e], s, y)) : 0u;
   if constexpr (EPL == 2) {
-    ((unsigned short *)dst_codes)[lane] = (unsigned short)((code[0] & 0xff) | ((code[1] & 0xff) << 8));
+    ((unsigned short *)dst_codes)[lane] = (unsigned short)((code[0] & 0xff) | (code[1] << 8));
   } else {
     dst_codes[lane] = (int8_t)code[0];
   }
-  if (lane == 0) *dst_scale = dead ? __float2half_rn(0.f) : hs;
+  if (lane == 0) *dst_scale = hs;
 }
 
 // The same with fixed per-channel scales ("Tiled attention and mixed precision": per head and
@@ -70,14 +99,10 @@ __device__ __forceinline__ void quantize_row_channels(const __half *__restrict__
   const __half2 sc = ((const __half2 *)scales)[lane];
   const float x[2] = {__low2float(v), __high2float(v)};
   const float sf[2] = {__low2float(sc), __high2float(sc)};
-  int code[2];
+  unsigned code[2];
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    float r = (sf[e] > 0.f) ? rintf(__fdiv_rn(x[e], sf[e])) : 0.f;
-    r = fminf(fmaxf(r, -127.f), 127.f);
-    code[e] = (int)r;
-  }
-  ((unsigned short *)dst_codes)[lane] = (unsigned short)((code[0] & 0xff) | ((code[1] & 0xff) << 8));
+  for (int e = 0; e < 2; ++e) code[e] = channel_code_bits(x[e], sf[e], __builtin_amdgcn_rcpf(sf[e]));
+  ((unsigned short *)dst_codes)[lane] = (unsigned short)((code[0] & 0xff) | (code[1] << 8));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -126,6 +151,9 @@ __global__ __launch_bounds__(1024) void channel_scales_kernel(CacheView cv, int 
 // load and store instruction covers whole rows.  Same arithmetic per element as
 // quantize_row_wave (the maximum does not depend on the order it is taken in), so the stored
 // bits are those of the one-row-per-wavefront quantiser the demotion kernel uses.
+// Bound by memory: 64 units of 4096 tokens (204 MB in and out) 38.7 us = 5.3 TB/s, what a large copy
+// reaches; with a division per code and the maxima exchanged through LDS the vector ALU was the limit
+// (47.0 us).  256 units of 2048 tokens 87.8 -> 73.1, 8 of 3001 8.8 -> 6.7.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void unpack_h8(const int4 &raw, float (&x)[8]) {
   const unsigned w[4] = {(unsigned)raw.x, (unsigned)raw.y, (unsigned)raw.z, (unsigned)raw.w};
@@ -135,13 +163,26 @@ __device__ __forceinline__ void unpack_h8(const int4 &raw, float (&x)[8]) {
     x[2 * e + 1] = __half2float(__ushort_as_half((unsigned short)(w[e] >> 16)));
   }
 }
-__device__ __forceinline__ uint2 pack_codes8(const int (&code)[8]) {
-  uint2 r;
-  r.x = (unsigned)(code[0] & 0xff) | ((unsigned)(code[1] & 0xff) << 8) | ((unsigned)(code[2] & 0xff) << 16) |
-        ((unsigned)(code[3] & 0xff) << 24);
-  r.y = (unsigned)(code[4] & 0xff) | ((unsigned)(code[5] & 0xff) << 8) | ((unsigned)(code[6] & 0xff) << 16) |
-        ((unsigned)(code[7] & 0xff) << 24);
-  return r;
+// the low bytes of eight words
+__device__ __forceinline__ uint2 pack_codes8(const unsigned (&code)[8]) {
+  unsigned w[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    w[e] = __builtin_amdgcn_perm(code[4 * e + 1], code[4 * e], 0x0c0c0400u) |
+           __builtin_amdgcn_perm(code[4 * e + 3], code[4 * e + 2], 0x04000c0cu);
+  return make_uint2(w[0], w[1]);
+}
+// Maximum over the LPR (8 or 16) lanes of a row; moves inside sixteen lanes, no trip through LDS.
+template <int LPR>
+__device__ __forceinline__ float row_lanes_max(float v) {
+#define CONFKV_DPP(ctrl) __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true))
+  static_assert(LPR == 8 || LPR == 16, "lanes per row");
+  v = fmaxf(v, CONFKV_DPP(0xB1));                      // quad_perm [1,0,3,2]
+  v = fmaxf(v, CONFKV_DPP(0x4E));                      // quad_perm [2,3,0,1]
+  v = fmaxf(v, CONFKV_DPP(0x141));                     // row_half_mirror
+  if (LPR == 16) v = fmaxf(v, CONFKV_DPP(0x140));      // row_mirror
+#undef CONFKV_DPP
+  return v;
 }
 // Eight values of a row per lane, LPR lanes per row: per-token scale of the row and the codes.
 template <int LPR>
@@ -151,33 +192,22 @@ __device__ __forceinline__ uint2 quantize_piece(const int4 &raw, __half *scale_o
   float amax = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
+  float s, y;
+  *scale_out = row_scale(row_lanes_max<LPR>(amax), &s, &y);
+  unsigned code[8];
 #pragma unroll
-  for (int m = LPR / 2; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
-  const __half hs = __float2half_rn(__fdiv_rn(amax, 127.0f));
-  const float sf = __half2float(hs);
-  const bool dead = !(sf > 0.f) || isinf(sf);
-  int code[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float r = dead ? 0.f : rintf(__fdiv_rn(x[e], sf));
-    r = fminf(fmaxf(r, -127.f), 127.f);
-    code[e] = (int)r;
-  }
-  *scale_out = dead ? __float2half_rn(0.f) : hs;
-  return pack_codes8(code);
+  for (int e = 0; e < 8; ++e) code[e] = code_bits(code_quotient(x[e], s, y));
+  const uint2 r = pack_codes8(code);
+  return y > 0.f ? r : make_uint2(0u, 0u);
 }
 // The same piece against fixed per-channel scales (eight fp16 scales of the lane's channels).
 __device__ __forceinline__ uint2 quantize_piece_channels(const int4 &raw, const int4 &scales) {
   float x[8], sf[8];
   unpack_h8(raw, x);
   unpack_h8(scales, sf);
-  int code[8];
+  unsigned code[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float r = (sf[e] > 0.f) ? rintf(__fdiv_rn(x[e], sf[e])) : 0.f;
-    r = fminf(fmaxf(r, -127.f), 127.f);
-    code[e] = (int)r;
-  }
+  for (int e = 0; e < 8; ++e) code[e] = channel_code_bits(x[e], sf[e], __builtin_amdgcn_rcpf(sf[e]));
   return pack_codes8(code);
 }
 

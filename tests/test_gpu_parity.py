@@ -125,6 +125,55 @@ def test_prefill_quantiser_bit_exact(lib, torch_cuda, D, W, T0):
     kv.close()
 
 
+@pytest.mark.parametrize("D,scales", [(128, "token"), (64, "token"), (128, "channel")])
+def test_codes_at_half_way_quotients(lib, torch_cuda, D, scales):
+    """Quotients x / scale on and next to every half-way point, for scales over the whole fp16 range (subnormal
+    ones too), in the loader and in demotion: the codes are those of a correctly rounded division."""
+    torch = torch_cuda
+    say(f"half-way quotients D={D} {scales}")
+    rng = np.random.default_rng(5)
+    T0, N, W = 192, 96, 1
+    bits = np.concatenate([np.arange(1, 40), rng.integers(40, 0x5C00, T0 + N - 39)])
+    s = bits.astype(np.uint16).view(np.float16).astype(np.float64)                     # [T0 + N] intended scales
+    m = rng.integers(-127, 127, size=(T0 + N, D)) + 0.5
+    if scales == "channel":
+        s = np.repeat(s[None, :D], T0 + N, axis=0)
+    else:
+        s = np.repeat(s[:, None], D, axis=1)
+    x = (m * s).astype(np.float16)
+    bump = rng.integers(-1, 2, size=x.shape)                                           # a neighbour of the tie, or the tie
+    x = (x.view(np.int16) + np.where(np.abs(x) > 0, bump, 0)).astype(np.int16).view(np.float16)
+    if scales == "channel":
+        x[0] = (127 * s[0]).astype(np.float16)                                         # fixes the scales
+        x[1:T0] = np.where(np.abs(x[1:T0]) <= np.abs(x[0]), x[1:T0], x[0])
+        x[T0 + 1, ::7], x[T0 + 2, ::5] = np.inf, -np.inf                               # later tokens saturate
+        x[T0 + 3, ::3] = np.float16(60000)
+    else:
+        x[:, 3] = (127 * s[:, 0]).astype(np.float16)                                   # the row's largest magnitude
+    x[5] = 0
+    kv = _mk(lib, n_q_heads=2, n_kv_heads=1, head_dim=D, fp16_window=W, capacity=320, n_tight=[319], n_loose=[319],
+             scale_mode=scales)
+    kv.load_prefill(0, torch.from_numpy(x[None, None, :T0]).cuda(), torch.from_numpy(x[None, None, :T0][..., ::-1].copy()).cuda())
+    q, out = (torch.zeros(1, 2, D, dtype=torch.float16, device="cuda") for _ in range(2))
+    for t in range(T0, T0 + N):
+        kv.attend(0, q, torch.from_numpy(x[None, None, t]).cuda(), torch.from_numpy(x[None, None, t][..., ::-1].copy()).cuda(), out)
+        kv.step(torch.zeros(1, 1000, device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.uint8, device="cuda"))
+        kv.evict_compact()
+    ex = kv.export(0, 0, 0)
+    n8 = T0 + N - W
+    assert ex["n"] == T0 + N and not ex["is16"][:n8].any()
+    for name, rows in (("k", x), ("v", x[:, ::-1])):
+        if scales == "channel":
+            sc = O.channel_scales(rows[:T0])
+            codes = np.stack([O.quantize_channels(r, sc) for r in rows[:n8]])
+        else:
+            pairs = [O.quantize_vector(r) for r in rows[:n8]]
+            codes, sc = np.stack([c for c, _ in pairs]), np.array([c for _, c in pairs], np.float16)
+            assert np.array_equal(ex[name + "s"][:n8].view(np.uint16), sc.view(np.uint16))
+        assert np.array_equal(ex[name + "8"][:n8], codes)
+    kv.close()
+
+
 # ------------------------------------------------------------------ attention + mass EMA
 
 def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_launch=False,
