@@ -372,7 +372,7 @@ static int plan_for_layer(conf_kv_handle *h, int layer, int tq, AttendPlan *plan
   }
   const bool rows16 = tq > 1 || observe || h->cv.G > 8;
   const int rows = rows16 ? kChunkRows : h->cv.G;
-  if (!attend_plan(h->cfg.head_dim, rows, h->cv.chan != 0, rows16, h->cfg.batch * h->cfg.n_kv_heads, n_ub, n16_ub,
+  if (!attend_plan(h->cfg.head_dim, rows, h->cv.chan != 0, h->cv.page_lg != 0, rows16, h->cfg.batch * h->cfg.n_kv_heads, n_ub, n16_ub,
                    h->forced_splits, h->force_two_launch, table_lds(h), plan))
     return CONF_KV_ERR_BAD_SHAPE;
   // the paged layout is read by the single-launch matrix-core kernel only

@@ -30,8 +30,8 @@
 //     [16c, 16c+16) of a slot row, so a wavefront load covers whole rows, contiguous in
 //     memory; each lane-group keeps its own running softmax state.
 //   * matrix-core body (2 <= G <= 8, D = 128) for the INT8 slots: the G query heads against a
-//     32-slot tile are two small contractions (scores: [G x 128] x [128 x 32]; output:
-//     [G x 32] x [32 x 128]) issued as v_mfma_f32_16x16x32_f16 with the head dimension
+//     32-slot tile are two small contractions (scores: [G x 128] x [128 x 32]; output, transposed:
+//     [128 x 32] x [32 x G]) issued as v_mfma_f32_16x16x32_f16 with the head dimension
 //     padded to 16.  The vector ALU then only converts int8 -> fp16 and keeps the softmax
 //     state, which is what lets the kernel stay memory-bound for grouped-query shapes.
 //     FP16 slots go through the same contractions in 16-slot tiles, no conversion needed.
@@ -171,11 +171,14 @@ struct Slice {
   __device__ __forceinline__ int slot_of(int t) const { return t < cnt8 ? lo8 + t : lo16 + (t - cnt8); }
 };
 
-// floor(x * j / ns) for x = q * ns + r (0 <= r < ns <= 64, j <= ns) without 64-bit division:
-// q * j + floor(r * j / ns), the small quotient through one reciprocal (exact: the argument is
-// below 4096 and (r j + 1/2) / ns is at least 1/128 away from every integer).
-__device__ __forceinline__ int share_cut(unsigned q, unsigned r, int j, float inv_ns) {
-  return (int)(q * (unsigned)j + (unsigned)(((float)(r * (unsigned)j) + 0.5f) * inv_ns));
+// x / ns by the launch's multiplier ceil(2^32 / ns) (0: a single split); exact while x * ns < 2^32, and slots
+// are far fewer than 2^25.  Scalar arithmetic throughout: nothing of a slice depends on the lane.
+__device__ __forceinline__ unsigned div_splits(const AttendLaunch &a, unsigned x) {
+  return a.ns_magic ? __umulhi(x, a.ns_magic) : x;
+}
+// floor(x * j / ns) for x = q * ns + r
+__device__ __forceinline__ int share_cut(const AttendLaunch &a, unsigned q, unsigned r, int j) {
+  return (int)(q * (unsigned)j + div_splits(a, r * (unsigned)j));
 }
 // The launch grid is (splits, kv-heads, sequences), or (kv-heads, splits, sequences) when
 // a.kv_major is set: workgroups go to the XCDs round-robin in linear order, so with eight
@@ -212,15 +215,14 @@ __device__ __forceinline__ Slice make_slice(const CacheView &cv, const AttendLau
   s.n = (a.observe_first >= 0 ? a.observe_first : len) + a.tq;     // the appended tokens included
   s.n8 = min(n8, s.n);                                             // n8 <= len outside observation calls
   s.n16 = s.n - s.n8;
-  const float inv_ns = __builtin_amdgcn_rcpf((float)ns);
-  const unsigned q8 = (unsigned)s.n8 / (unsigned)ns, r8 = (unsigned)s.n8 - q8 * (unsigned)ns;
-  const unsigned q16 = (unsigned)s.n16 / (unsigned)ns, r16 = (unsigned)s.n16 - q16 * (unsigned)ns;
-  s.lo8 = share_cut(q8, r8, s.j, inv_ns) & ~31;
-  s.hi8 = s.j == ns - 1 ? s.n8 : share_cut(q8, r8, s.j + 1, inv_ns) & ~31;
+  const unsigned q8 = div_splits(a, s.n8), r8 = (unsigned)s.n8 - q8 * (unsigned)ns;
+  const unsigned q16 = div_splits(a, s.n16), r16 = (unsigned)s.n16 - q16 * (unsigned)ns;
+  s.lo8 = share_cut(a, q8, r8, s.j) & ~31;
+  s.hi8 = s.j == ns - 1 ? s.n8 : share_cut(a, q8, r8, s.j + 1) & ~31;
   // outside observation calls the tail split's FP16 share is never empty (n16 >= 1), so its
   // owner holds slot n-1
-  s.lo16 = s.n8 + share_cut(q16, r16, s.j, inv_ns);
-  s.hi16 = s.n8 + share_cut(q16, r16, s.j + 1, inv_ns);
+  s.lo16 = s.n8 + share_cut(a, q16, r16, s.j);
+  s.hi16 = s.n8 + share_cut(a, q16, r16, s.j + 1);
   s.cnt8 = s.hi8 - s.lo8;
   s.ntok = s.cnt8 + (s.hi16 - s.lo16);
   if (s.ntok > S) {                       // cannot happen when the host plan is right
@@ -232,25 +234,33 @@ __device__ __forceinline__ Slice make_slice(const CacheView &cv, const AttendLau
   return s;
 }
 
+// Row of slot i in the EMA and position planes.  kPaged is the layout, known at compile time: the look-up in the block
+// table costs branches and registers wherever a row is addressed.
+template <bool kPaged>
+__device__ __forceinline__ int slot_plane_row(const CacheView &cv, const Slice &s, int i) {
+  return kPaged ? slot_row(cv, s.tab, s.h8, s.n8, s.h16, i) : ring_row_u(s.h8, i, cv.cap);
+}
+
 // The workgroup that owns the tail writes the new token into the FP16 ring.
 // Nobody reads the appended row back in this launch (the new token is taken from the call's
 // arguments), so nothing waits for the stores.
-template <int D>
+// (tq: a.tq, as a constant where the call has one token.)
+template <int D, bool kPaged = false>
 __device__ __forceinline__ void append_new_token(const CacheView &cv, const AttendLaunch &a,
-                                                 const Slice &s, int ns) {
+                                                 const Slice &s, int ns, int tq) {
   if (s.j != ns - 1 || a.observe_first >= 0) return;
   const int tid = threadIdx.x;
   constexpr int PPR = D / 8;                        // 16-byte pieces per row
   // token t of the call: K/V rows [B][tq][Hkv][D] -> FP16 ring row of slot n - tq + t
-  for (int i = tid; i < 2 * a.tq * PPR; i += kAttThreads) {
-    const int which = i / (a.tq * PPR), r = i % (a.tq * PPR), t = r / PPR, c = r % PPR;
-    const int row = ring_row(s.h16, s.n16 - a.tq + t, cv.cap16);
-    const __half *src = (which ? a.vnew : a.knew) + (((size_t)s.b * a.tq + t) * cv.Hkv + s.g) * D;
+  for (int i = tid; i < 2 * tq * PPR; i += kAttThreads) {
+    const int which = i >= tq * PPR, r = i - which * tq * PPR, t = r / PPR, c = r % PPR;
+    const int row = ring_row(s.h16, s.n16 - tq + t, cv.cap16);
+    const __half *src = (which ? a.vnew : a.knew) + (((size_t)s.b * tq + t) * cv.Hkv + s.g) * D;
     __half *dst = (which ? cv.v16 : cv.k16) + ((size_t)s.u * cv.cap16 + row) * D;
     ((int4 *)dst)[c] = ((const int4 *)src)[c];
   }
-  if (tid < a.tq)
-    cv.pos[(size_t)s.u * cv.cap + slot_row(cv, s.tab, s.h8, s.n8, s.h16, s.n - a.tq + tid)] = a.pos_new + tid;
+  if (tid < tq)
+    cv.pos[(size_t)s.u * cv.cap + slot_plane_row<kPaged>(cv, s, s.n - tq + tid)] = a.pos_new + tid;
 }
 
 // max / sum over the 16 lanes of a DPP row; every lane of the row gets the result
@@ -612,14 +622,14 @@ __device__ __forceinline__ double row_weight(const AttendLaunch &a, int tq, int 
 
 // ---------------------------------------------------------------------------------------
 // Epilogue shared by both bodies.  On entry wm/wl/wo hold NP per-wavefront partials
-// (after a workgroup barrier): partial k is [G][D] floats at
-// wo + (k % kAttWaves) * WSTR + (k / kAttWaves) * G * D; stash holds the slice's raw scores.
+// (after a workgroup barrier): partial k is [G][D] floats, rows DS apart, at
+// wo + (k % kAttWaves) * WSTR + (k / kAttWaves) * G * DS; stash holds the slice's raw scores.
 // kPhase 0: the whole epilogue in one kernel (merge, publish, wait for the unit's other splits,
 // gather, EMA, output).  kPhase 1: merge and publish only; kPhase 2: gather, EMA and output in a
 // later launch, which needs no wait (wm/wl are unused and wo holds the [G][gs] weights) --
 // the pair serves shapes whose splits cannot all be resident at once.
 // ---------------------------------------------------------------------------------------
-template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D>
+template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D, int DS = D, bool kPaged = false>
 __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const AttendLaunch &a,
                                                 const Slice &sl, int ns, int S, float *stash,
                                                 float *wm, float *wl, float *wo, float *gm,
@@ -635,82 +645,104 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   const bool exchange = kPhase != 0 || ns > 1;       // partials go through device memory
   float *EMA = cv.ema + (size_t)sl.u * cv.cap;
   float ema_old[kPre + 1];
+  auto ema_row = [&](int t) { return slot_plane_row<kPaged>(cv, sl, sl.slot_of(t)); };
 #pragma unroll
   for (int k = 0; k < kPre; ++k) {
-    // branch-free (a slot past the slice re-reads its last one; the appended token's slot
+    // no branch per lane (a slot past the slice re-reads its last one; the appended token's slot
     // holds a stale value): the uses below mask both cases
-    const int slot = sl.slot_of(max(0, min(tid + k * kAttThreads, sl.ntok - 1)));   // an empty slice reads slot lo16 < n
-    ema_old[k] = EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, slot)];
+    ema_old[k] = 0.f;
+    if (k * kAttThreads < sl.ntok) ema_old[k] = EMA[ema_row(min(tid + k * kAttThreads, sl.ntok - 1))];
   }
-  // The softmax statistics go out first: thread h merges row h's (m, l) over the wavefront
-  // partials (the same operations, in the same order, as the output merge below) and publishes
-  // them at once, so their trip to the unit's other splits runs behind the output merge.
-  if (kPhase != 2 && exchange && tid < G) {
-    float M = NEG;
+  // Weights of the workgroup merge: a wavefront's output elements all belong to one row, so a row's NP statistics lie in
+  // eight neighbouring lanes (lane k of group r: wavefront k's part of row 8 b + r) and three lane moves merge them; the
+  // weights reach the merge as scalars.  (Every thread formed the eight weights of its row for itself before, behind a thread
+  // per row that did the same for the statistics: 16 splits 1218 -> 1176 us per step of 64 launches, with the lane arithmetic
+  // of the EMA rows below.)
+  constexpr int HB = (G + 7) / 8;
+  static_assert(kPhase == 2 || NP == 8, "one group of eight lanes per row");
+  const int lane8 = tid & 63;
+  float row_m[HB], row_l[HB], part_w[HB];              // of row 8 b + lane / 8: maximum, normaliser, weight of partial lane % 8
+  if (kPhase != 2) {
 #pragma unroll
-    for (int k = 0; k < NP; ++k) M = fmaxf(M, wm[tid * NP + k]);
-    float l = 0.f;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const float mk = wm[tid * NP + k];
-      const bool live = mk > NEG;
-      l = fmaf(live ? wl[tid * NP + k] : 0.f, live ? __expf(mk - M) : 0.f, l);
+    for (int b = 0; b < HB; ++b) {
+      const int at = min(64 * b + lane8, G * NP - 1);  // (lanes past the last row repeat its last partial; nothing reads them)
+      const float mk = wm[at], lk = wl[at];
+      row_m[b] = group_max(mk, 8);
+      const bool live = mk > NEG;                      // an empty partial may hold anything and weighs nothing
+      part_w[b] = live ? __expf(mk - row_m[b]) : 0.f;
+      row_l[b] = group_sum(live ? lk * part_w[b] : 0.f, 8);
     }
-    if (!a.withhold || sl.j != 0) {                   // (test hook: split 0 keeps its words to itself)
-      st_tagged(&ml[tid * 2], tag_of(a), M);
-      st_tagged(&ml[tid * 2 + 1], tag_of(a), l);
+    // the statistics go out first: their trip to the unit's other splits runs behind the output merge
+    if (exchange && tid < kWave && (!a.withhold || sl.j != 0)) {   // (test hook: split 0 keeps its words to itself)
+#pragma unroll
+      for (int b = 0; b < HB; ++b) {
+        const int h = 8 * b + (lane8 >> 3);
+        if ((lane8 & 7) == 0 && h < G) {
+          st_tagged(&ml[h * 2], tag_of(a), row_m[b]);
+          st_tagged(&ml[h * 2 + 1], tag_of(a), row_l[b]);
+        }
+      }
     }
   }
+  // A unit with a single split is complete here: global statistics per row, uniform over the workgroup.
+  float g_m[G];
+  double g_w[G];                                       // the row's mass weight over its normaliser
+  double row_inv[HB];
+  if (kPhase == 0 && !exchange) {
+#pragma unroll
+    for (int b = 0; b < HB; ++b) row_inv[b] = recip_pos((double)row_l[b]);
+  }
+  auto lane_f = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
+  auto lane_d = [](double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+  };
   // workgroup merge of the per-wavefront output partials: kEPT channels per thread, each
   // published as a word that carries the launch's epoch, so that nobody has to wait for the
   // stores to land before announcing them
   constexpr int kEPT = G * D > kAttThreads ? 2 : 1;
-  if (kPhase != 2)
-  for (int idx = kEPT * tid; idx < G * D; idx += kEPT * kAttThreads) {
-    const int h = idx / D;
-    // branch-free, so that all LDS reads are in flight together; an empty partial (m = -inf)
-    // may hold anything and enters with weight zero through the selects
-    float mk[NP], lk[NP], ok2[NP][kEPT];
+  constexpr int kMerge = (G * D + kEPT * kAttThreads - 1) / (kEPT * kAttThreads);
+  static_assert(D % (kEPT * kWave) == 0, "a wavefront's elements belong to one row");
+  if (kPhase != 2) {
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      mk[k] = wm[h * NP + k];
-      lk[k] = wl[h * NP + k];
-      // partial k belongs to wavefront k % kAttWaves
-      const float *src = &wo[(k % kAttWaves) * WSTR + (k / kAttWaves) * G * D + idx];
-      if constexpr (kEPT == 2) {
-        const float2 t2 = *(const float2 *)src;
-        ok2[k][0] = t2.x;
-        ok2[k][kEPT - 1] = t2.y;
+    for (int p = 0; p < kMerge; ++p) {
+      const int idx = kEPT * (tid + p * kAttThreads);
+      const int h = __builtin_amdgcn_readfirstlane(idx / D);
+      if (h >= G) break;
+      // row 8 b + r: one pass of two channels per thread covers exactly eight rows, other shapes have one pass
+      const int b = p, r8 = (h - 8 * b) * 8;
+      float ok2[NP][kEPT];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        // partial k belongs to wavefront k % kAttWaves
+        const float *src = &wo[(k % kAttWaves) * WSTR + (k / kAttWaves) * G * DS + h * DS + (idx - h * D)];
+        if constexpr (kEPT == 2) {
+          const float2 t2 = *(const float2 *)src;
+          ok2[k][0] = t2.x;
+          ok2[k][kEPT - 1] = t2.y;
+        } else {
+          ok2[k][0] = *src;
+        }
+      }
+      float o[kEPT] = {};
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        const float f = lane_f(part_w[b], r8 + k);
+#pragma unroll
+        for (int e = 0; e < kEPT; ++e) o[e] = fmaf(f > 0.f ? ok2[k][e] : 0.f, f, o[e]);
+      }
+      if (!exchange) {
+        // same arithmetic as the general merge below (weight e^0 = 1), without the trip through device memory
+        const double inv = lane_d(row_inv[b], r8);
+#pragma unroll
+        for (int e = 0; e < kEPT; ++e) {
+          // (DR < D: the matrix-core body pads a 64-channel head to its 128-channel tiles)
+          if (h < tq * gq && a.out && idx + e - h * D < DR)
+            a.out[out_index(cv, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn((float)((double)o[e] * inv));
+        }
       } else {
-        ok2[k][0] = *src;
+#pragma unroll
+        for (int e = 0; e < kEPT; ++e) st_tagged(&po[idx + e], tag_of(a), o[e]);
       }
-    }
-    float M = NEG;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) M = fmaxf(M, mk[k]);
-    float o[kEPT] = {}, l = 0.f;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const bool live = mk[k] > NEG;
-      const float f = live ? __expf(mk[k] - M) : 0.f;
-#pragma unroll
-      for (int e = 0; e < kEPT; ++e) o[e] = fmaf(live ? ok2[k][e] : 0.f, f, o[e]);
-      l = fmaf(live ? lk[k] : 0.f, f, l);
-    }
-    if (!exchange) {
-      // a unit with a single split is complete here: same arithmetic as the general merge
-      // below (weight e^0 = 1), without the trip through device memory
-      const double inv = recip_pos((double)l);
-#pragma unroll
-      for (int e = 0; e < kEPT; ++e) {
-        // (DR < D: the matrix-core body pads a 64-channel head to its 128-channel tiles)
-        if (h < tq * gq && a.out && idx + e - h * D < DR)
-          a.out[out_index(cv, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn((float)((double)o[e] * inv));
-      }
-      if (idx % D == 0) { gm[h] = M; ginv[h] = inv; ginv[G + h] = inv * row_weight(a, tq, gq, h); }
-    } else {
-#pragma unroll
-      for (int e = 0; e < kEPT; ++e) st_tagged(&po[idx + e], tag_of(a), o[e]);
     }
   }
   TS(19);
@@ -726,17 +758,25 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   int lg = 0;
   while ((1 << lg) < ns) ++lg;                       // <= 6: groups never straddle a wavefront
   const int gs = 1 << lg;
-  // This split normalises `per` elements of the unit's [G][D] output; the ns partial values of
-  // one element sit in gs consecutive lanes, so one load per thread and pass fetches them.
+  // This split normalises `per` elements of the unit's [G][D] output.  A lane takes kOut of an element's ns partial values
+  // (split sub + q * lanes), the `lanes` that share an element are neighbours: the words a thread needs are requested
+  // together, and an element's address, sum and store come once (16 rows, four splits: 0.9 us from the request to the
+  // store; a pass per kOut-th element with a lane per split took 1.8).
+  constexpr int kOutLg = G > 8 ? 2 : G > 4 ? 1 : 0, kOut = 1 << kOutLg;
   const int per = (G * D + ns - 1) / ns;
-  const int epp = kAttThreads >> lg;                 // output elements per pass over the workgroup
-  const int os = tid & (gs - 1), oe = tid >> lg;     // this thread's split and element within a pass
-  constexpr int kOut = G > 8 ? 4 : G > 4 ? 2 : 1;    // passes whose words are requested at once
+  const int lgl = max(lg - kOutLg, 0);               // log2(lanes)
+  const int epp = kAttThreads >> lgl;                // output elements per pass over the workgroup
+  const int sub = tid & ((1 << lgl) - 1), oe = tid >> lgl;   // this thread's first split and element within a pass
   unsigned long long opre[kOut];
+  auto out_word = [&](int p, int q) {                // of pass p: the q-th word, or the unit's first where there is none
+    const int os = sub + (q << lgl), i = p * epp + oe, e = sl.j * per + i;
+    return &pou[os < ns && i < per && e < G * D ? (size_t)os * G * D + e : 0];
+  };
   const unsigned tag = tag_of(a);
   __shared__ int s_ok;
   if (exchange) {
     const int lane = tid & 63, hpr = kWave >> lg;    // rows per round
+    const int os = lane & (gs - 1);
     if (tid == 0) s_ok = 1;
     if (kPhase == 0) lds_barrier();                  // the merge has read the buffer the weights land in
     else __syncthreads();
@@ -775,32 +815,41 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
     }
     // the output partials are requested now and used behind the importance arithmetic
 #pragma unroll
-    for (int p = 0; p < kOut; ++p) {
-      const int i = p * epp + oe, e = sl.j * per + i;
-      opre[p] = ld_tagged(&pou[os < ns && i < per && e < G * D ? (size_t)os * G * D + e : 0]);
-    }
+    for (int q = 0; q < kOut; ++q) opre[q] = ld_tagged(out_word(0, q));
+#pragma unroll
+    for (int h = 0; h < G; ++h) { g_m[h] = gm[h]; g_w[h] = ginv[G + h]; }
   } else {
-    lds_barrier();                                   // (the output's stores stay in flight)
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      g_m[h] = lane_f(row_m[h / 8], 8 * (h & 7));
+      g_w[h] = lane_d(row_inv[h / 8], 8 * (h & 7)) * row_weight(a, tq, gq, h);
+    }
   }
   TS(22);
   // ---- this split normalises its share of the unit's output (online-softmax merge) ----
   auto finish_output = [&]() {
     for (int p = 0; p * epp < per; ++p) {
       const int i = p * epp + oe, e = sl.j * per + i;                // element of the [G][D] output
-      const bool valid = os < ns && i < per && e < G * D;
-      const unsigned long long *src = &pou[valid ? (size_t)os * G * D + e : 0];
-      unsigned long long wv = 0ull;
+      const bool mine = i < per && e < G * D;
+      if (p > 0) {
 #pragma unroll
-      for (int q = 0; q < kOut; ++q) wv = p == q ? opre[q] : wv;
-      if (p >= kOut) wv = ld_tagged(src);
+        for (int q = 0; q < kOut; ++q) opre[q] = ld_tagged(out_word(p, q));
+      }
       // a word that is not this launch's yet is asked for again (bounded)
-      bool here = !valid || (unsigned)(wv >> 32) == tag;
+      auto all_here = [&]() {
+        bool here = true;
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) here &= !mine || sub + (q << lgl) >= ns || (unsigned)(opre[q] >> 32) == tag;
+        return here;
+      };
+      bool here = all_here();
       for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull; ++spins) {
         if (spins > a.spin_limit) break;
         __builtin_amdgcn_s_sleep(1);
         if (!here) {
-          wv = ld_tagged(src);
-          here = (unsigned)(wv >> 32) == tag;
+#pragma unroll
+          for (int q = 0; q < kOut; ++q) opre[q] = ld_tagged(out_word(p, q));
+          here = all_here();
         }
       }
       const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
@@ -808,10 +857,16 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
         if ((tid & 63) == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
         continue;
       }
-      const int h = valid ? e / D : 0;
-      const float wgt = valid ? pml[(h << lg) + os] : 0.f;           // e^{m_s - M} / L of that split and row
-      const float c = group_sum(wgt > 0.f ? __uint_as_float((unsigned)wv) * wgt : 0.f, gs);   // (an empty partial may hold anything)
-      if (valid && os == 0 && h < tq * gq && a.out && e - h * D < DR)
+      const int h = mine ? e / D : 0;
+      float c = 0.f;
+#pragma unroll
+      for (int q = 0; q < kOut; ++q) {
+        const int os = sub + (q << lgl);
+        const float wgt = mine && os < ns ? pml[(h << lg) + os] : 0.f;   // e^{m_s - M} / L of that split and row
+        c += wgt > 0.f ? __uint_as_float((unsigned)opre[q]) * wgt : 0.f;   // (an empty partial may hold anything)
+      }
+      c = group_sum(c, 1 << lgl);
+      if (mine && sub == 0 && h < tq * gq && a.out && e - h * D < DR)
         a.out[out_index(cv, sl, tq, gq, h * DR + (e - h * D), DR)] = __float2half_rn(c);
     }
   };
@@ -821,7 +876,6 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   double lam = 1.0;
   for (int k = 0; k < tq; ++k) lam *= (double)a.ema_decay;
   const double oml = a.mass_gain;
-  const double *gw = ginv + G;
   const int first_new = sl.n - tq;
   // The new values of the first kPre slots per thread stay in registers until the output is
   // out: a store between the request of the output partials and their use would make that use
@@ -833,10 +887,10 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
     if (t < sl.ntok) {
       double A = 0.0;
 #pragma unroll
-      for (int h = 0; h < G; ++h) A += (double)exp_nonpos(stash[h * S + t] - gm[h]) * gw[h];
+      for (int h = 0; h < G; ++h) A += (double)exp_nonpos(stash[h * S + t] - g_m[h]) * g_w[h];
       const double old = (sl.slot_of(t) >= first_new) ? 0.0 : (double)ema_old[k];   // a new token starts at 0
       ema_new[k] = (float)(lam * old + oml * A);
-      if (!exchange) EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, sl.slot_of(t))] = ema_new[k];
+      if (!exchange) EMA[ema_row(t)] = ema_new[k];
     }
   }
   TS(30);
@@ -846,7 +900,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
 #pragma unroll
     for (int k = 0; k < kPre; ++k) {
       const int t = tid + k * kAttThreads;
-      if (t < sl.ntok) EMA[slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, sl.slot_of(t))] = ema_new[k];
+      if (t < sl.ntok) EMA[ema_row(t)] = ema_new[k];
     }
   }
   // the rest of the slice in batches of kBatch slots per thread: branch-free loads first (a
@@ -858,7 +912,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
     int row[kBatch];
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
-      row[k] = slot_row(cv, sl.tab, sl.h8, sl.n8, sl.h16, sl.slot_of(min(t0 + k * kAttThreads, sl.ntok - 1)));
+      row[k] = ema_row(min(t0 + k * kAttThreads, sl.ntok - 1));
       old[k] = EMA[row[k]];
     }
 #pragma unroll
@@ -867,7 +921,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       if (t < sl.ntok) {
         double A = 0.0;
 #pragma unroll
-        for (int h = 0; h < G; ++h) A += (double)exp_nonpos(stash[h * S + t] - gm[h]) * gw[h];
+        for (int h = 0; h < G; ++h) A += (double)exp_nonpos(stash[h * S + t] - g_m[h]) * g_w[h];
         const double prev = (sl.slot_of(t) >= first_new) ? 0.0 : (double)old[k];   // a new token starts at 0
         EMA[row[k]] = (float)(lam * prev + oml * A);
       }
@@ -896,7 +950,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]: 1 / global normaliser, the same times the row's mass weight
 
   const Slice sl = make_slice(cv, a, ns, S);
-  append_new_token<D>(cv, a, sl, ns);
+  append_new_token<D>(cv, a, sl, ns, 1);
 
   Stream<G> st;
   st.reset();
@@ -952,16 +1006,29 @@ __global__ __launch_bounds__(kAttThreads) void attend_finish_kernel(const int32_
 constexpr int kTile = 32;              // slots per wavefront tile
 constexpr int kKRow = 128 + 16;        // LDS row stride of the INT8 K tile (bytes)
 constexpr int kKRow16 = 256 + 16;      // LDS row stride of the 16-slot FP16 K tile (bytes)
-constexpr int kVRow = 32 + 4;          // LDS row stride of the transposed V tile (bytes)
-// Rows of the transposed V tile come in groups of 16 channels.  A store instruction has its
-// lanes in 8 different groups (16 rows = 144 dwords apart: only two different banks), so group g
-// is shifted by 20 g dwords: the groups then start 164 dwords = 4 banks (mod 32) apart and the
-// lanes of a half wavefront fall into 32 different banks.  A load instruction stays inside
-// one group and is not affected.
-__host__ __device__ constexpr int kVSkew(int group) { return 80 * group; }
-constexpr int kVBytes = 128 * kVRow + kVSkew(7);   // rows plus the largest shift
+constexpr int kVRow16 = 256 + 32;      // and of the FP16 V tile: the transposing read takes eight-lane pieces of four
+                                       // rows, which this stride puts on different banks
 constexpr int kPRow = 32 + 8;          // LDS row stride of the probability tile (halfs)
-constexpr int kTileBytes = kTile * kKRow + kVBytes + 16 * kPRow * 2;   // per wavefront
+constexpr int kPartRow = 128 + 4;      // LDS row stride of a wavefront's output partial (floats): a 16-byte store of
+                                       // sixteen rows meets different banks
+constexpr int kStashPad = 4;           // the same for the raw scores of sixteen rows
+// per wavefront: K, V and the scales, and for single tokens the probabilities of up to eight heads
+constexpr int kRowsTileBytes = 2 * kTile * kKRow + 2 * kTile * 4;
+constexpr int kHeadTileBytes = kRowsTileBytes + 8 * kPRow * 2;
+static_assert(16 * kKRow16 <= kTile * kKRow && 16 * kVRow16 <= kTile * kKRow, "an FP16 tile takes the room of an INT8 one");
+
+// Transposing LDS reads, per group of sixteen lanes.  tr8: lane l reads 8 bytes of row l / 2, columns 8 (l & 1) + [0, 8),
+// and gets byte l of each of the eight rows.  tr16: lane l reads four halfs of row l / 4, columns 4 (l & 3) + [0, 4),
+// and gets half l of each of the four rows.  p is the lane's own piece.
+typedef int confkv_i2 __attribute__((ext_vector_type(2)));
+typedef short confkv_s4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 lds_read_tr8(const uint8_t *p) {
+  const confkv_i2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) confkv_i2 *)p);
+  return make_uint2((unsigned)v.x, (unsigned)v.y);
+}
+__device__ __forceinline__ half4_t lds_read_tr16(const uint8_t *p) {
+  return __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) confkv_s4 *)p));
+}
 
 // 4 int8 (one dword) -> 4 fp16 (two dwords), exact: c ^ 0x80 is c + 128 as an unsigned byte,
 // 0x6400 | byte is the fp16 number 1024 + byte, and subtracting 1152 leaves c.
@@ -1003,14 +1070,11 @@ __device__ __forceinline__ half8_t cvt_i8x8_f16x8(unsigned w0, unsigned w1) {
 // three quarters of padding.  Two lane-row swaps regroup the real rows over the whole wavefront:
 //   G <= 4: one value per lane; lane row r = lane / 16 holds head r
 //   G  > 4: two values per lane; value j of lane row r holds head 2j + (r >> 1) + 4 (r & 1)
-//   G  > 8: all 16 rows are real; the matrix-core layout is kept (four values per lane)
 // The slot (tile column lane % 16) stays where it is.
 template <int G>
 struct RowMap {
-  static constexpr int NV = G <= 4 ? 1 : G <= 8 ? 2 : 4;
-  static __device__ __forceinline__ int head(int j, int r) {
-    return G <= 4 ? r : G <= 8 ? 2 * j + (r >> 1) + 4 * (r & 1) : 4 * r + j;
-  }
+  static constexpr int NV = G <= 4 ? 1 : 2;
+  static __device__ __forceinline__ int head(int j, int r) { return G <= 4 ? r : 2 * j + (r >> 1) + 4 * (r & 1); }
 };
 // rows (a0, b0, a2, b2) of the two operands
 __device__ __forceinline__ float swap16_even(float a, float b) {
@@ -1028,41 +1092,161 @@ template <int G>
 __device__ __forceinline__ void regroup_rows(const floatx4_t &acc, float (&z)[RowMap<G>::NV]) {
   if constexpr (G <= 4) {
     z[0] = swap32_low(swap16_even(acc[0], acc[1]), swap16_even(acc[2], acc[3]));
-  } else if constexpr (G <= 8) {
+  } else {
     z[0] = swap32_low(acc[0], acc[1]);
     z[1] = swap32_low(acc[2], acc[3]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) z[j] = acc[j];
   }
 }
-// A quantity that is uniform over each lane row of the regrouped layout, read back in the
-// matrix-core layout: the value of head 4 * g4 + i (rows that hold no head get anything).
-template <int G>
-__device__ __forceinline__ float rows_to_tile(const float (&x)[RowMap<G>::NV], int i, int g4) {
+// A quantity that is uniform over each lane row of the regrouped layout, for the lanes of the transposed output: the
+// value of head t16 = lane % 16 (lanes past the heads get anything).  The 16-row form holds it there already.
+template <int G, int NV>
+__device__ __forceinline__ float head_of_column(const float (&x)[NV], int t16) {
   if constexpr (G > 8) {
-    return x[i];
+    return x[0];
   } else if constexpr (G <= 4) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[0]), 16 * i));
+    auto row = [&](int r) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[0]), 16 * r)); };
+    const float lo = (t16 & 1) ? row(1) : row(0), hi = (t16 & 1) ? row(3) : row(2);
+    return (t16 & 2) ? hi : lo;
   } else {
-    const int v = __builtin_bit_cast(int, x[i >> 1]);
-    const float lo = __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 32 * (i & 1)));
-    const float hi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 32 * (i & 1) + 16));
-    return (g4 & 1) ? hi : lo;
+    const int from = 32 * (t16 & 1) + 16 * ((t16 >> 2) & 1);
+    const float v0 = __shfl(x[0], from, kWave), v1 = __shfl(x[1], from, kWave);
+    return (t16 & 2) ? v1 : v0;
   }
+}
+// maximum and sum over the four lanes that share lane % 16
+__device__ __forceinline__ float rows4_max(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float((unsigned)a[0]), __uint_as_float((unsigned)a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float((unsigned)b[0]), __uint_as_float((unsigned)b[1]));
+}
+__device__ __forceinline__ float rows4_sum(float v) {
+  v = swap_halves32(v, v);
+  return swap_halves16(v, v);
+}
+
+// ---------------------------------------------------------------------------------------
+// Requests for a slice's rows, shared by the single-tile and the many-rows kernel: item it of a slice is its it-th 32-slot
+// INT8 tile, or behind those a 16-slot FP16 tile; a wavefront takes either as 8 KB of rows, four 1 KB pieces of K and four of V.
+// ---------------------------------------------------------------------------------------
+// One item in flight: lane (piece, row) of piece q holds 16 bytes of row r8 + 8 q (INT8, r8 = lane / 8) or r4 + 4 q (FP16,
+// r4 = lane / 16), and of INT8 slots one raw scale: lanes 0..31 the K scales of the tile's slots, 32..63 the V scales.
+struct TileRegs {
+  int4 k0, k1, k2, k3, v0, v1, v2, v3;
+  unsigned short sc;
+};
+struct TileSource {
+  const int8_t *k8, *v8, *k16, *v16;     // the unit's planes
+  const unsigned short *ks, *vs;
+  const int8_t *kn, *vn;                 // calls of several tokens: their rows of this kv-head, tok bytes apart
+  unsigned tok;
+  int cap8, cap16, ntiles, first_new;    // first_new: first slot whose row comes from the call (0x3fffffff: none)
+};
+template <int DR, bool kRows>
+__device__ __forceinline__ TileSource tile_source(const CacheView &cv, const AttendLaunch &a, const Slice &sl, const int8_t *k8,
+                                                  const int8_t *v8, const __half *k16, const __half *v16, const __half *ks,
+                                                  const __half *vs, int ntiles, int tq, int first_new) {
+  TileSource t = {k8, v8, (const int8_t *)k16, (const int8_t *)v16, (const unsigned short *)ks, (const unsigned short *)vs,
+                  nullptr, nullptr, 0u, cv.cap8, cv.cap16, ntiles, first_new};
+  if constexpr (kRows) {
+    t.kn = (const int8_t *)(a.knew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * DR);
+    t.vn = (const int8_t *)(a.vnew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * DR);
+    t.tok = (unsigned)(cv.Hkv * DR * 2);
+  }
+  // (held in registers: a choice between two kernel arguments would become a load from the chosen one's address)
+  asm("" : "+s"(t.cap8), "+s"(t.cap16));
+  return t;
+}
+// A branch only chooses bases and offsets; all kinds of items share the load instructions.  (Loads in the branches
+// themselves cost the overlap: where two of them meet, the compiler waits for the data to move registers.)
+// An item whose rows are one run of the ring -- 1 KB of INT8 or of FP16 rows per piece either way -- takes its
+// place from the scalar base; others give every lane its rows; rows past the slice re-read its last one (their scores
+// are masked and their probabilities are zero).  Single tokens (kRows false) leave out the call's token: its row is put in
+// its place in LDS, and what the ring holds there is not used.
+template <int DR, bool kRows, bool kPaged, bool kScales, typename Fp16>
+__device__ __forceinline__ void load_item_rows(const CacheView &cv, const TileSource &t, const Slice &sl, int lane, int it,
+                                               Fp16 known_fp16, TileRegs &tr) {
+  const bool fp16 = known_fp16 || it >= t.ntiles;
+  const int base = fp16 ? sl.lo16 + 16 * (it - t.ntiles) : sl.lo8 + it * kTile, end = fp16 ? sl.hi16 : sl.hi8;
+  const int head = fp16 ? sl.h16 - sl.n8 : sl.h8, cap = fp16 ? t.cap16 : t.cap8;
+  const unsigned row_bytes = fp16 ? 2 * DR : DR;
+  const int slots = fp16 ? 16 : kTile;
+  const unsigned row0 = (unsigned)ring_row_u(head, base, cap);
+  const bool run = !(kPaged && !fp16) && base + slots <= (kRows && fp16 ? min(end, t.first_new) : end) && row0 + slots <= (unsigned)cap;
+  const int8_t *kb = fp16 ? t.k16 : t.k8, *vb = fp16 ? t.v16 : t.v8;
+  // row of INT8 slot i in the INT8 planes
+  auto row8 = [&](int i) -> unsigned {
+    if constexpr (kPaged) return (unsigned)((sl.tab[i >> cv.page_lg] << cv.page_lg) | (i & ((1 << cv.page_lg) - 1)));
+    else return (unsigned)ring_row_u(sl.h8, i, t.cap8);
+  };
+  // byte offsets of the lane's four rows from the (wavefront-uniform) bases; the rows of call tokens apart
+  const unsigned r = DR == 128 && run ? 0u : (unsigned)lane >> (fp16 ? 4 : 3);
+  const unsigned col = (unsigned)(lane & (fp16 ? DR / 8 - 1 : DR / 16 - 1)) * 16u;
+  unsigned o[4], so = row0 + (unsigned)(lane & 31);
+  int fresh[kRows ? 4 : 1];
+  if (run) {
+    kb += (size_t)row0 * row_bytes;
+    vb += (size_t)row0 * row_bytes;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = (DR == 128 ? (unsigned)lane * 16u : r * row_bytes + col) + q * (8 * DR);
+#pragma unroll
+    for (int q = 0; q < (kRows ? 4 : 1); ++q) fresh[q] = -1;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int slot = min(base + (int)r + q * (slots / 4), end - 1);
+      unsigned row;
+      if (kPaged && !fp16) row = row8(slot);
+      else row = (unsigned)ring_row_u(head, slot, cap);
+      o[q] = row * row_bytes + col;
+      if constexpr (kRows) fresh[q] = fp16 ? slot - t.first_new : -1;
+    }
+    if (!fp16) so = row8(min(base + (lane & 31), end - 1));
+  }
+  if constexpr (kRows) {
+    const int8_t *pk[4], *pv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const unsigned fo = (unsigned)max(fresh[q], 0) * t.tok + col;
+      pk[q] = fresh[q] >= 0 ? t.kn + fo : kb + o[q];
+      pv[q] = fresh[q] >= 0 ? t.vn + fo : vb + o[q];
+    }
+    tr.k0 = ld_stream16(pk[0]); tr.v0 = ld_stream16(pv[0]);
+    tr.k1 = ld_stream16(pk[1]); tr.v1 = ld_stream16(pv[1]);
+    tr.k2 = ld_stream16(pk[2]); tr.v2 = ld_stream16(pv[2]);
+    tr.k3 = ld_stream16(pk[3]); tr.v3 = ld_stream16(pv[3]);
+  } else {
+    tr.k0 = ld_stream16(kb + o[0]); tr.v0 = ld_stream16(vb + o[0]);
+    tr.k1 = ld_stream16(kb + o[1]); tr.v1 = ld_stream16(vb + o[1]);
+    tr.k2 = ld_stream16(kb + o[2]); tr.v2 = ld_stream16(vb + o[2]);
+    tr.k3 = ld_stream16(kb + o[3]); tr.v3 = ld_stream16(vb + o[3]);
+  }
+  // (an FP16 tile has no scales: its lanes read anything, the tile's own first bytes)
+  if (kScales && !known_fp16)
+    tr.sc = ld_stream(fp16 ? (const unsigned short *)kb + lane : (lane < 32 ? t.ks : t.vs) + so);
 }
 
 // kChan: the INT8 scales are per (unit, channel).  The K scales are folded into the query (a
-// second A operand, split into an fp16 head and tail so the fold costs no accuracy), the V
+// second query operand, split into an fp16 head and tail so the fold costs no accuracy), the V
 // scales multiply the output once, after the last INT8 tile; the FP16 slots then come last.
 // G is the number of query rows per unit: the group size for single-token calls (row = head),
 // or kChunkRows for multi-token calls, where row r is (token r / gq, head r % gq), padding rows
 // carry a zero query, and a row sees the call's own tokens causally.
 // kSpill: the first launch of the two-launch form (raw scores to device scratch, ends after
 // publishing its partial).
-template <int G, bool kChan = false, bool kSpill = false, int DR = 128>
+// kPaged: the INT8 slots live in pages (cv.page_lg), at compile time: see slot_plane_row.
+//
+// What bounds it: launches of a few MB are a chain (counters, first rows, a tile or two, merge, exchange), and every
+// instruction of that chain counts; launches of tens of MB are bound by the vector ALU (two wavefronts per SIMD) about as
+// much as by memory.  So a tile costs as few instructions as it can:
+//  - a tile that neither wraps nor ends early is loaded from one scalar base and one lane offset;
+//  - rows of K and of V go to LDS as they are; the transposing LDS read hands the output contraction its V operand (a
+//    register transpose before took 32 byte permutes and 16 stores per INT8 tile);
+//  - the output is formed transposed, [channel][row], so a lane holds four neighbouring channels of one row and a
+//    wavefront's partial leaves in eight 16-byte stores.
+template <int G, bool kChan = false, bool kSpill = false, int DR = 128, bool kPaged = false>
 __global__ __launch_bounds__(kAttThreads)
-__attribute__((amdgpu_waves_per_eu((kChan || G > 8) ? 2 : 3, (kChan || G > 8) ? 2 : 3)))
+__attribute__((amdgpu_waves_per_eu(2, 2)))
 void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns, int S) {
   // The unit's counters are requested before anything else, from leading scalar kernel arguments
   // (the four arrays, the layer's first unit, the kv-head count, the grid order): the hardware
@@ -1076,132 +1260,120 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   // contractions leave out (two k-steps over the real channels for the scores, four channel
   // groups for the output; the other channels of the partial are never written out).
   constexpr int D = 128;
+  constexpr bool kRows = G > 8;                 // the 16-row form: scores come out transposed, a lane holds slots of one row
   constexpr int kSteps = DR / 32;               // k-steps of 32 channels in the score contraction
+  constexpr int kTileBytes = kRows ? kRowsTileBytes : kHeadTileBytes;
   static_assert(DR == 64 || DR == 128, "head dimension");
   static_assert(!(kChan && DR != 128), "per-channel scales need 128 channels");
-  static_assert(G * D * 4 <= kTileBytes, "a wavefront's output partial must fit its tile buffer");
+  static_assert(!(kPaged && (kChan || kSpill || kRows)), "paged: single tokens, per-token scales, one launch");
+  static_assert(G * kPartRow * 4 <= kTileBytes, "a wavefront's output partial must fit its tile buffer");
   constexpr int NP = kAttWaves;                 // one partial per wavefront
-  constexpr int kTileFloats =
-      (kAttWaves * kTileBytes > NP * G * D * 4 ? kAttWaves * kTileBytes : NP * G * D * 4) / 4;
+  constexpr int kTileFloats = kAttWaves * kTileBytes / 4;
   extern __shared__ __align__(16) float smem[];
-  float *tiles = smem;                          // per-wave tile buffers, later [NP][G][D] partials
+  float *tiles = smem;                          // per-wave tile buffers, later [NP][G][kPartRow] partials
+  // [G] rows of raw scores; sixteen rows of LDS lie four floats further apart, on different banks
+  const int SS = S + (kRows && !kSpill ? kStashPad : 0);
   float *stash = kSpill ? a.spill + ((size_t)unit_in_layer(cv, a) * ns + split_index(a)) * G * S
-                        : smem + kTileFloats;   // [G][S]
-  float *gm = smem + kTileFloats + (kSpill ? 0 : (size_t)G * S);   // [G]
+                        : smem + kTileFloats;
+  float *gm = smem + kTileFloats + (kSpill ? 0 : (size_t)G * SS);   // [G]
   double *ginv = (double *)(gm + G + (-G & 3)); // [2 G]
-  float *wm = (float *)(ginv + 2 * G);          // [G][NP], on a 16-byte boundary: a row's NP values are two loads
+  float *wm = (float *)(ginv + 2 * G);          // [G][NP], on a 16-byte boundary
   float *wl = wm + NP * G;                      // [G][NP]
   float *wo = tiles;
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int tq = G > 8 ? a.tq : 1, gq = G > 8 ? a.gq : G;   // tokens of the call, heads per token
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tq = kRows ? a.tq : 1, gq = kRows ? a.gq : G;   // tokens of the call, heads per token
   TS_INIT();
   TS(0);
   // every kernel argument the streaming prologue needs, fetched now (one round trip) rather
   // than piecemeal between the dependent loads below
   asm volatile("" ::"s"(cv.k8), "s"(cv.v8), "s"(cv.ks), "s"(cv.vs), "s"(cv.k16), "s"(cv.v16), "s"(cv.len),
                "s"(cv.n8), "s"(cv.head16), "s"(cv.head8), "s"(cv.cap8), "s"(cv.cap16), "s"(cv.Hkv), "s"(cv.B),
-               "s"(a.layer), "s"(a.tq), "s"(a.observe_first), "s"(a.q), "s"(a.knew), "s"(a.vnew));
+               "s"(a.layer), "s"(a.tq), "s"(a.observe_first), "s"(a.q), "s"(a.knew), "s"(a.vnew), "s"(a.ns_magic), "s"(ns));
+  const int t16 = lane & 15, g4 = lane >> 4;    // MFMA operand coordinates of this lane
+  // Query operand of the score contraction; k-step s covers channels g4*32 + 8s + [0,8), matching
+  // the K bytes this lane reads from the tile below.  Rows past the heads of a group repeat the
+  // last one: a row of the contraction only reaches its own scores, and nothing reads theirs.  (Requested with the
+  // counters: the queries' place does not depend on them.)
+  half8_t qa[4];
+  {
+    // row t16 = (token, head) of the call's [B][tq][Hq][D] queries
+    const int row = kRows ? t16 : min(t16, G - 1);
+    const int q_tok = kRows ? row / gq : 0, q_head = row - q_tok * gq;
+    const bool real = !kRows || q_tok < tq;
+    const __half *qrow = a.q + ((((size_t)blockIdx.z * tq + (real ? q_tok : 0)) * cv.Hkv + kv_head_index(a)) * gq + q_head) * DR;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      // (a 64-channel head: two k-steps, step s of lane group g4 covers channels 16 g4 + 8 s + [0, 8))
+      int4 raw = make_int4(0, 0, 0, 0);
+      if (s < kSteps) raw = *(const int4 *)(qrow + g4 * (8 * kSteps) + 8 * s);
+      if (!real) raw = make_int4(0, 0, 0, 0);
+      qa[s] = __builtin_bit_cast(half8_t, raw);
+    }
+  }
   // Paged layout: the unit's block table comes into LDS (requested before the counters, so both
   // trips overlap); every INT8 row address below goes through it.
   int32_t *tab = (int32_t *)((char *)smem + a.tab_off);
-  if (cv.page_lg) {
+  if constexpr (kPaged) {
     const int32_t *gt = cv.pt + (size_t)(a.layer * cv.B * cv.Hkv + unit_in_layer(cv, a)) * cv.npages;
     for (int i = tid; i < cv.npages; i += kAttThreads) tab[i] = gt[i];
   }
   Slice sl = make_slice(cv, a, ns, S, &w_words);
-  if (cv.page_lg) {
+  if constexpr (kPaged) {
     sl.tab = tab;
     __syncthreads();
   }
   TS(2);
-  const int page_lg = cv.page_lg, page_mask = (1 << cv.page_lg) - 1;
-  // row of INT8 slot i in the INT8 planes
-  auto row8 = [&](int i) -> unsigned {
-    return page_lg ? (unsigned)((tab[i >> page_lg] << page_lg) | (i & page_mask)) : (unsigned)ring_row_u(sl.h8, i, cv.cap8);
-  };
-  const int t16 = lane & 15, g4 = lane >> 4;    // MFMA operand coordinates of this lane
-  const int c8 = lane & 7, r8 = lane >> 3;      // global-load coordinates: 16-byte piece, row
+  const int c8 = lane & 7, r8 = lane >> 3;      // load coordinates of INT8 rows: 16-byte piece, row
+  const int c16 = lane & 15, r4 = lane >> 4;    // and of FP16 rows
   const int8_t *K8 = cv.k8 + (size_t)sl.u * cv.cap8 * DR;
   const int8_t *V8 = cv.v8 + (size_t)sl.u * cv.cap8 * DR;
   const __half *KS = cv.ks + (size_t)sl.u * (kChan ? D : cv.cap8);
   const __half *VS = cv.vs + (size_t)sl.u * (kChan ? D : cv.cap8);
+  const __half *K16 = cv.k16 + (size_t)sl.u * cv.cap16 * DR;
+  const __half *V16 = cv.v16 + (size_t)sl.u * cv.cap16 * DR;
 
+  // ---------------- the slice as a list of work items ----------------
+  // Items 0 .. ntiles-1 are the 32-slot INT8 tiles, the rest the 16-slot FP16 tiles (the same
+  // 8 KB of rows each).  Wavefront w takes items w, w + 8, ..; the rows of its next item are
+  // requested as soon as the current ones have left the registers for LDS, so one item per
+  // wavefront is always in flight.
   const int ntiles = (sl.cnt8 + kTile - 1) / kTile;            // 0 when the split has no INT8 slot
-  // One INT8 tile in flight: four 128-bit K pieces, four V pieces and the raw scale bits.
-  // Loads are branch-free (rows past the slice re-read its last row; their scores are masked
-  // and their probabilities are zero), so the whole tile is in flight before any wait.
-  struct TileRegs {
-    int4 k0, k1, k2, k3, v0, v1, v2, v3;
-    unsigned short ks0, ks1, vs0, vs1;
-  };
-  auto load_tile = [&](int tile) -> TileRegs {
-    TileRegs t;
-    const int base = sl.lo8 + tile * kTile;
-    const int last = sl.hi8 - 1;
-    // 32-bit byte offsets from the unit's (wavefront-uniform) plane bases
-    const unsigned col = (unsigned)(c8 & (DR / 16 - 1)) * 16u;
-    const unsigned o0 = row8(min(base + r8, last)) * DR + col;
-    const unsigned o1 = row8(min(base + 8 + r8, last)) * DR + col;
-    const unsigned o2 = row8(min(base + 16 + r8, last)) * DR + col;
-    const unsigned o3 = row8(min(base + 24 + r8, last)) * DR + col;
-    t.k0 = ld_stream16(K8 + o0);
-    t.v0 = ld_stream16(V8 + o0);
-    t.k1 = ld_stream16(K8 + o1);
-    t.v1 = ld_stream16(V8 + o1);
-    t.k2 = ld_stream16(K8 + o2);
-    t.v2 = ld_stream16(V8 + o2);
-    t.k3 = ld_stream16(K8 + o3);
-    t.v3 = ld_stream16(V8 + o3);
-    if constexpr (!kChan) {
-      const unsigned j0 = row8(min(base + t16, last));
-      const unsigned j1 = row8(min(base + 16 + t16, last));
-      t.ks0 = ld_stream((const unsigned short *)KS + j0);
-      t.vs0 = ld_stream((const unsigned short *)VS + j0);
-      t.ks1 = ld_stream((const unsigned short *)KS + j1);
-      t.vs1 = ld_stream((const unsigned short *)VS + j1);
-    } else {
-      t.ks0 = t.ks1 = t.vs0 = t.vs1 = 0;
-    }
-    return t;
-  };
-  TileRegs tr = {};
-  // the first INT8 tile is requested before anything else: its latency covers the append and
+  const int nitems = ntiles + (sl.hi16 - sl.lo16 + 15) / 16;
+  // the call's own tokens (slots n - tq .. n - 1, at the end of the unit's last split) are
+  // taken from the call's arguments, not read back from the ring: no wait on the append's stores
+  // (an observation call appends nothing: every row comes from the ring)
+  const int first_new = a.observe_first >= 0 ? 0x3fffffff : sl.n - tq;
+  const TileSource ts = tile_source<DR, kRows>(cv, a, sl, K8, V8, K16, V16, KS, VS, ntiles, tq, first_new);
+  TileRegs tr;
+  auto load_item = [&](int it, auto known_fp16) { load_item_rows<DR, kRows, kPaged, !kChan>(cv, ts, sl, lane, it, known_fp16, tr); };
+  // the first item is requested before anything else: its latency covers the append and
   // the query loads
-  if (w < ntiles) tr = load_tile(w);
+  if (w < nitems) load_item(w, std::false_type{});
+  // Single tokens: the new token, slot n - 1, is the last row of the unit's last item.  Lanes 0..15 hold the pieces of
+  // its K row, each sixteen of the others those of its V row.
+  const bool owns_new = !kRows && sl.hi16 == sl.n && nitems > 0 && ((nitems - 1) & (kAttWaves - 1)) == w;
+  int4 new_piece;
+  if (owns_new)
+    new_piece = *(const int4 *)((r4 ? a.vnew : a.knew) + ((size_t)sl.b * cv.Hkv + sl.g) * DR + (c16 & (DR / 8 - 1)) * 8);
   TS(3);
-  append_new_token<DR>(cv, a, sl, ns);
+  append_new_token<DR, kPaged>(cv, a, sl, ns, tq);
   const float NEG = -INFINITY;
   const float sm = a.sm_scale;
   TS(1);
 
-  // ---------------- INT8 slots on the matrix cores ----------------
-  uint8_t *Kt = (uint8_t *)tiles + (size_t)w * kTileBytes;   // [32][kKRow]
-  uint8_t *Vt = Kt + kTile * kKRow;                           // [128][kVRow], slots permuted
-  _Float16 *Pb = (_Float16 *)(Vt + kVBytes);                  // [16][kPRow], rows >= G stay 0
-  for (int i = lane; i < 16 * kPRow / 2; i += kWave) ((unsigned *)Pb)[i] = 0u;
+  uint8_t *Kt = (uint8_t *)tiles + (size_t)w * kTileBytes;   // [32][kKRow], or [16][kKRow16] of FP16 slots
+  uint8_t *Vt = Kt + kTile * kKRow;                           // [32][kKRow], or [16][kVRow16]
+  float *Sc = (float *)(Vt + kTile * kKRow);                  // [32] K scales times sm, [32] V scales
+  _Float16 *Pb = (_Float16 *)(Sc + 2 * kTile);                // [kPb][kPRow] (not in the 16-row form)
+  constexpr int kPb = G <= 4 ? 4 : 8;
 
-  // A operand of the score contraction: Q padded to 16 rows; k-step s covers channels
-  // g4*32 + 8s + [0,8), matching the K bytes this lane reads from the tile below.
-  half8_t qa[4];
-  {
-    // row t16 = (token, head) of the call's [B][tq][Hq][D] queries
-    const int q_tok = t16 / gq, q_head = t16 - q_tok * gq;
-    const __half *qrow = a.q + ((((size_t)sl.b * a.tq + q_tok) * cv.Hkv + sl.g) * gq + q_head) * DR;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      int4 raw = make_int4(0, 0, 0, 0);
-      // (a 64-channel head: two k-steps, step s of lane group g4 covers channels 16 g4 + 8 s + [0, 8))
-      if (t16 < G && q_tok < tq && s < kSteps) raw = *(const int4 *)(qrow + g4 * (8 * kSteps) + 8 * s);
-      qa[s] = __builtin_bit_cast(half8_t, raw);
-    }
-  }
-  // Per-channel scales: A operand of the INT8 scores = q * s_k * 2^8 as head + tail in fp16
+  // Per-channel scales: query operand of the INT8 scores = q * s_k * 2^8 as head + tail in fp16
   // (the power of two keeps the tail of every term that matters a normal number; it is taken
-  // back in the score factor), and this lane's eight V scales (channels 16 nt + t16).
+  // back in the score factor), and the V scales of this lane's channels 16 nt + 4 g4 + [0, 4).
   constexpr float kFoldUp = 256.0f;
   half8_t qh[kChan ? 4 : 1], ql[kChan ? 4 : 1];
-  float vch[kChan ? 8 : 1];
+  half4_t vch[kChan ? 8 : 1];
   if constexpr (kChan) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -1215,227 +1387,144 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       }
     }
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) vch[nt] = __half2float(VS[16 * nt + t16]);
+    for (int nt = 0; nt < 8; ++nt) vch[nt] = *(const half4_t *)(VS + 16 * nt + 4 * g4);
   }
+  // Transposed output: element i of group nt is channel 16 nt + 4 g4 + i of row t16.
   floatx4_t O[8];
 #pragma unroll
   for (int nt = 0; nt < 8; ++nt) O[nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  // running softmax state in the regrouped layout: reference, normaliser (per-lane partial
-  // sum) and the sum of the fp16 probabilities that met biased INT8 values
-  constexpr int NV = RowMap<G>::NV;
+  // running softmax state (heads: the regrouped layout; 16 rows: row t16, the same in the four
+  // lanes of a row): reference, normaliser (per-lane partial sum) and the sum of the fp16
+  // probabilities that met biased INT8 values
+  constexpr int NV = kRows ? 1 : RowMap<G>::NV;
   float mrun[NV], lrun[NV], pbias[NV];
   int hd[NV];                                    // head of value j of this lane
 #pragma unroll
-  for (int j = 0; j < NV; ++j) { mrun[j] = NEG; lrun[j] = 0.f; pbias[j] = 0.f; hd[j] = RowMap<G>::head(j, g4); }
-  // causal order inside the call: the row of token t sees slots below n - tq + t + 1 (every
-  // slot of the unit when the call has one token)
-  int seen[NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) seen[j] = sl.n - tq + hd[j] / gq + 1;
+  for (int j = 0; j < NV; ++j) { mrun[j] = NEG; lrun[j] = 0.f; pbias[j] = 0.f; hd[j] = kRows ? t16 : RowMap<G>::head(j, g4); }
+  // causal order inside the call: row t16's token sees slots below this
+  const int seen = kRows ? sl.n - tq + t16 / gq + 1 : 0;
+  float *stash_row = kRows ? stash + (size_t)t16 * SS : stash;
 
-  // ---------------- the slice as a list of work items ----------------
-  // Items 0 .. ntiles-1 are the 32-slot INT8 tiles, the rest the 16-slot FP16 tiles (the same
-  // 8 KB of rows each).  Wavefront w takes items w, w + 8, ..; the rows of its next item are
-  // requested as soon as the current ones have left the registers for LDS, so one item per
-  // wavefront is always in flight.
-  const int base16 = sl.lo16;
-  const int ntiles16 = (sl.hi16 - sl.lo16 + 15) / 16;
-  const int nitems = ntiles + ntiles16;
-  const __half *K16 = cv.k16 + (size_t)sl.u * cv.cap16 * DR;
-  const __half *V16 = cv.v16 + (size_t)sl.u * cv.cap16 * DR;
-  const int c16 = lane & 15, r4 = lane >> 4;     // FP16 load coordinates: 16-byte piece, row
-  auto load_tile16 = [&](int f) -> TileRegs {
-    TileRegs t;
-    const int base = base16 + 16 * f, last = sl.hi16 - 1;
-    const int h16 = sl.h16, cap16 = cv.cap16, n8 = sl.n8;
-    const unsigned col = (unsigned)(c16 & (DR / 8 - 1)) * 8u;
-    const unsigned o0 = (unsigned)ring_row(h16, min(base + r4, last) - n8, cap16) * DR + col;
-    const unsigned o1 = (unsigned)ring_row(h16, min(base + 4 + r4, last) - n8, cap16) * DR + col;
-    const unsigned o2 = (unsigned)ring_row(h16, min(base + 8 + r4, last) - n8, cap16) * DR + col;
-    const unsigned o3 = (unsigned)ring_row(h16, min(base + 12 + r4, last) - n8, cap16) * DR + col;
-    // the call's own tokens (slots n - tq .. n - 1, at the end of the unit's last split) are
-    // taken from the call's arguments, not read back from the ring: no wait on the append's stores
-    // (an observation call appends nothing: every row comes from the ring)
-    const int first_new = a.observe_first >= 0 ? 0x3fffffff : sl.n - tq;
-    const size_t tok = (size_t)cv.Hkv * DR;                     // [B][tq][Hkv][D]: stride of a token
-    const __half *kn = a.knew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * DR + col;
-    const __half *vn = a.vnew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * DR + col;
-    const int s0 = min(base + r4, last) - first_new, s1 = min(base + 4 + r4, last) - first_new;
-    const int s2 = min(base + 8 + r4, last) - first_new, s3 = min(base + 12 + r4, last) - first_new;
-    t.k0 = ld_stream16(s0 >= 0 ? kn + s0 * tok : K16 + o0);
-    t.v0 = ld_stream16(s0 >= 0 ? vn + s0 * tok : V16 + o0);
-    t.k1 = ld_stream16(s1 >= 0 ? kn + s1 * tok : K16 + o1);
-    t.v1 = ld_stream16(s1 >= 0 ? vn + s1 * tok : V16 + o1);
-    t.k2 = ld_stream16(s2 >= 0 ? kn + s2 * tok : K16 + o2);
-    t.v2 = ld_stream16(s2 >= 0 ? vn + s2 * tok : V16 + o2);
-    t.k3 = ld_stream16(s3 >= 0 ? kn + s3 * tok : K16 + o3);
-    t.v3 = ld_stream16(s3 >= 0 ? vn + s3 * tok : V16 + o3);
-    t.ks0 = t.ks1 = t.vs0 = t.vs1 = 0;
-    return t;
-  };
-  auto load_item = [&](int it) -> TileRegs { return it < ntiles ? load_tile(it) : load_tile16(it - ntiles); };
-  if (w >= ntiles && w < nitems) tr = load_tile16(w - ntiles);
-  // with per-channel scales the accumulator leaves code units once, after the wavefront's last
-  // INT8 item (its FP16 items, if any, come after that)
-  bool in_code_units = kChan;
-  auto leave_code_units = [&]() {
-    // the INT8 part is complete: take the code bias out and go from code units to values
-    float pb[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) { pb[j] = row16_sum(pbias[j]) * kCodeBias; pbias[j] = 0.f; }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float bias = rows_to_tile<G>(pb, i, g4);
-#pragma unroll
-      for (int nt = 0; nt < 8; ++nt) O[nt][i] = (O[nt][i] - bias) * vch[nt];
+  // A raw score goes to its place in the stash; where there is none, to the wavefront's own scales, which are used up (no
+  // branch between the score and the softmax).
+  auto keep_score = [&](bool real, int head, int t, float v) {
+    if constexpr (kSpill) {
+      if (real) stash[(size_t)head * S + t] = v;
+    } else {
+      smem[real ? kTileFloats + head * SS + t : (int)(Sc - smem) + lane] = v;
     }
-    in_code_units = false;
+  };
+  auto rescale = [&](const float (&corr)[NV]) {
+    const float c = head_of_column<G>(corr, t16);
+#pragma unroll
+    for (int nt = 0; nt < DR / 16; ++nt) O[nt] *= c;
   };
   // A wavefront with a single item has no earlier output to rescale (8 splits of a 1000-slot unit: 8.1 -> 7.85 us per
   // launch).  Leaving the first of several items out as well cost units of two items per wavefront 1 %.
   const bool several = nitems > kAttWaves;
-  int tix = 0;
-  for (int item = w; item < nitems; item += kAttWaves) {
-    if (item >= ntiles) {
-      // ---- an FP16 tile ----
-      if constexpr (kChan) {
-        if (in_code_units) leave_code_units();
-      }
-      const int base = base16 + 16 * (item - ntiles);
-      // K rows as they are (row stride kKRow16 bytes), V transposed to [channel][slot]
-      *(int4 *)(Kt + (r4)*kKRow16 + c16 * 16) = tr.k0;
-      *(int4 *)(Kt + (4 + r4) * kKRow16 + c16 * 16) = tr.k1;
-      *(int4 *)(Kt + (8 + r4) * kKRow16 + c16 * 16) = tr.k2;
-      *(int4 *)(Kt + (12 + r4) * kKRow16 + c16 * 16) = tr.k3;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-        const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-        // half r of each pair is slot 4r + r4; it lands at column 4*r4 + r
-        unsigned *dst = (unsigned *)(Vt + (8 * c16 + 2 * q4) * kVRow + kVSkew(c16 >> 1) + 8 * r4);
-        dst[0] = __builtin_amdgcn_perm(x1, x0, 0x05040100u);
-        dst[1] = __builtin_amdgcn_perm(x3, x2, 0x05040100u);
-        dst[kVRow / 4] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
-        dst[kVRow / 4 + 1] = __builtin_amdgcn_perm(x3, x2, 0x07060302u);
-      }
-      wave_lds_sync();
-      if (item + kAttWaves < nitems) tr = load_item(item + kAttWaves);
-      const uint8_t *krow = Kt + t16 * kKRow16 + g4 * (16 * kSteps);
-      floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], *(const half8_t *)(krow + 16 * s), acc, 0, 0, 0);
-      const bool valid = base + t16 < sl.hi16;
-      float z[NV], corr[NV];
-      regroup_rows<G>(acc, z);
-      bool changed = false;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        const bool real = valid && hd[j] < G && base + t16 < seen[j];
-        const float sv = real ? z[j] * sm : NEG;
-        if (valid && hd[j] < G) stash[hd[j] * S + sl.cnt8 + (base + t16 - sl.lo16)] = sv;
-        const float mn = fmaxf(mrun[j], row16_max(sv));
-        corr[j] = (mn == NEG) ? 1.f : __expf(mrun[j] - mn);
-        changed |= (mn != mrun[j]);
-        mrun[j] = mn;
-        const float p = real ? __expf(sv - mn) : 0.f;
-        if (hd[j] < G) Pb[hd[j] * kPRow + 4 * (t16 & 3) + (t16 >> 2)] = (_Float16)p;
-        lrun[j] = fmaf(lrun[j], corr[j], p);
-        pbias[j] *= corr[j];
-      }
-      if (several && __builtin_amdgcn_ballot_w64(changed)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float c = rows_to_tile<G>(corr, i, g4);
-#pragma unroll
-          for (int nt = 0; nt < 8; ++nt) O[nt][i] *= c;
-        }
-      }
-      wave_lds_sync();
-      const half4_t pa = *(const half4_t *)(Pb + t16 * kPRow + 4 * g4);
-      // (a 64-channel head has four real channel groups: the copies in groups 4..7 are not multiplied)
-#pragma unroll
-      for (int nt = 0; nt < DR / 16; ++nt) {
-        const unsigned *vb = (const unsigned *)(Vt + (16 * nt + t16) * kVRow + kVSkew(nt) + 8 * g4);
-        const uint2 v2 = make_uint2(vb[0], vb[1]);
-        O[nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(pa, __builtin_bit_cast(half4_t, v2), O[nt], 0, 0, 0);
-      }
-      wave_lds_sync();
-      continue;
-    }
-    const int base = sl.lo8 + item * kTile;
+  // A loop per kind of item (one loop over both kinds keeps two sets of output registers and copies them in every turn).
+  int item = w;
+  [[maybe_unused]] int tix = 0;
+  for (; item < ntiles; item += kAttWaves) {
     if (tix < 6) TS(4 + 2 * tix);
-    // ---- registers -> LDS: K rows as they are, V transposed to [channel][slot] ----
+    // ---- an INT8 tile: registers -> LDS, rows as they are ----
     *(int4 *)(Kt + (r8)*kKRow + c8 * 16) = tr.k0;
     *(int4 *)(Kt + (8 + r8) * kKRow + c8 * 16) = tr.k1;
     *(int4 *)(Kt + (16 + r8) * kKRow + c8 * 16) = tr.k2;
     *(int4 *)(Kt + (24 + r8) * kKRow + c8 * 16) = tr.k3;
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-      const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-      const unsigned t0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u), t1 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
-      const unsigned t2 = __builtin_amdgcn_perm(x3, x2, 0x05010400u), t3 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
-      const unsigned o0 = __builtin_amdgcn_perm(t2, t0, 0x05040100u), o1 = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
-      const unsigned o2 = __builtin_amdgcn_perm(t3, t1, 0x05040100u), o3 = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
-      // byte r of o_e is slot 8r + r8 at channel 16*c8 + 4*q4 + e; it lands at column 4*r8 + r
-      uint8_t *dst = Vt + (16 * c8 + 4 * q4) * kVRow + kVSkew(c8) + 4 * r8;
-      *(unsigned *)(dst) = o0;
-      *(unsigned *)(dst + kVRow) = o1;
-      *(unsigned *)(dst + 2 * kVRow) = o2;
-      *(unsigned *)(dst + 3 * kVRow) = o3;
-    }
-    const float kscale[2] = {kChan ? sm * (1.0f / kFoldUp) : __half2float(__ushort_as_half(tr.ks0)) * sm,
-                             kChan ? sm * (1.0f / kFoldUp) : __half2float(__ushort_as_half(tr.ks1)) * sm};
-    const float vscale[2] = {kChan ? 1.0f : __half2float(__ushort_as_half(tr.vs0)),
-                             kChan ? 1.0f : __half2float(__ushort_as_half(tr.vs1))};
+    *(int4 *)(Vt + (r8)*kKRow + c8 * 16) = tr.v0;
+    *(int4 *)(Vt + (8 + r8) * kKRow + c8 * 16) = tr.v1;
+    *(int4 *)(Vt + (16 + r8) * kKRow + c8 * 16) = tr.v2;
+    *(int4 *)(Vt + (24 + r8) * kKRow + c8 * 16) = tr.v3;
+    if constexpr (!kChan) Sc[lane] = __half2float(__ushort_as_half(tr.sc)) * (lane < 32 ? sm : 1.0f);
     wave_lds_sync();
     if (tix < 6) TS(5 + 2 * tix);
     ++tix;
-    // the registers are free again: fetch this wavefront's next tile while computing
-    if (item + kAttWaves < nitems) tr = load_item(item + kAttWaves);
+    // the registers are free again: fetch this wavefront's next item while computing
+    if (item + kAttWaves < nitems) load_item(item + kAttWaves, std::false_type{});
 
-    // ---- scores: S[head][slot] for the two 16-slot halves of the tile ----
-    float sc[2][NV];
+    const int base = sl.lo8 + item * kTile;
+    // ---- scores of its two 16-slot halves ----
+    // heads: sc[sb][j] is slot 16 sb + t16; 16 rows: sc[sb][i] is slot 8 g4 + 4 sb + i of row t16, so that the lane's
+    // eight probabilities are the operand of the output contraction as they stand
+    constexpr int NS = kRows ? 4 : NV;
+    float sc[2][NS], vs[2][kRows ? 4 : 1], ks[2][kRows ? 4 : 1];
+    floatx4_t acc[2];
+    half8_t kb[2][4];
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb) {
-      const uint8_t *krow = Kt + (16 * sb + t16) * kKRow + g4 * (8 * kSteps);
+      const int krow_of = kRows ? 8 * (t16 >> 2) + 4 * sb + (t16 & 3) : 16 * sb + t16;
+      const uint8_t *krow = Kt + krow_of * kKRow + g4 * (8 * kSteps);
       const int4 b0 = *(const int4 *)(krow);
       int4 b1 = b0;
       if constexpr (kSteps == 4) b1 = *(const int4 *)(krow + 16);
-      floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (kSteps == 2) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[0], cvt_i8x8_f16x8(b0.x, b0.y), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[1], cvt_i8x8_f16x8(b0.z, b0.w), acc, 0, 0, 0);
-      } else if constexpr (kChan) {
-        const half8_t kb[4] = {cvt_i8x8_f16x8(b0.x, b0.y), cvt_i8x8_f16x8(b0.z, b0.w),
-                               cvt_i8x8_f16x8(b1.x, b1.y), cvt_i8x8_f16x8(b1.z, b1.w)};
+      kb[sb][0] = cvt_i8x8_f16x8(b0.x, b0.y);
+      kb[sb][1] = cvt_i8x8_f16x8(b0.z, b0.w);
+      kb[sb][2] = cvt_i8x8_f16x8(b1.x, b1.y);
+      kb[sb][3] = cvt_i8x8_f16x8(b1.z, b1.w);
+      acc[sb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (kChan) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ql[s], kb[s], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qh[s], kb[s], acc, 0, 0, 0);
-        }
+        for (int i = 0; i < (kRows ? 4 : 1); ++i) { ks[sb][i] = sm * (1.0f / kFoldUp); vs[sb][i] = 1.0f; }
+      } else if constexpr (kRows) {
+        const float4 k4 = *(const float4 *)(Sc + 8 * g4 + 4 * sb), v4 = *(const float4 *)(Sc + kTile + 8 * g4 + 4 * sb);
+        ks[sb][0] = k4.x; ks[sb][1] = k4.y; ks[sb][2] = k4.z; ks[sb][3] = k4.w;
+        vs[sb][0] = v4.x; vs[sb][1] = v4.y; vs[sb][2] = v4.z; vs[sb][3] = v4.w;
       } else {
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[0], cvt_i8x8_f16x8(b0.x, b0.y), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[1], cvt_i8x8_f16x8(b0.z, b0.w), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[2], cvt_i8x8_f16x8(b1.x, b1.y), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[3], cvt_i8x8_f16x8(b1.z, b1.w), acc, 0, 0, 0);
+        ks[sb][0] = Sc[16 * sb + t16];
+        vs[sb][0] = Sc[kTile + 16 * sb + t16];
       }
-      const bool valid = base + 16 * sb + t16 < sl.hi8;
-      float z[NV];
-      regroup_rows<G>(acc, z);
+    }
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        const bool real = valid && hd[j] < G;
-        // an INT8 slot is ahead of a query only in an observation call (appended tokens are FP16)
-        const bool ahead = G > 8 && base + 16 * sb + t16 >= seen[j];
-        const float sv = ahead ? NEG : z[j] * kscale[sb];
-        sc[sb][j] = real ? sv : NEG;
-        if (real) stash[hd[j] * S + (base + 16 * sb + t16 - sl.lo8)] = sv;
+    for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        auto contract = [&](const half8_t &q) {
+          acc[sb] = kRows ? __builtin_amdgcn_mfma_f32_16x16x32_f16(kb[sb][s], q, acc[sb], 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_16x16x32_f16(q, kb[sb][s], acc[sb], 0, 0, 0);
+        };
+        if constexpr (kChan) {
+          contract(ql[s]);
+          contract(qh[s]);
+        } else {
+          contract(qa[s]);
+        }
+      }
+    if constexpr (kRows) {
+      // an INT8 slot is ahead of a query only in an observation call (appended tokens are FP16)
+      const bool plain = base + kTile <= min(sl.hi8, sl.n - tq + 1);
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        const int slot = base + 8 * g4 + 4 * sb;
+        if (plain) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[sb][i] = acc[sb][i] * ks[sb][i];
+          *(float4 *)(stash_row + (slot - sl.lo8)) = make_float4(sc[sb][0], sc[sb][1], sc[sb][2], sc[sb][3]);
+        } else {
+          const int lim = min(seen, sl.hi8);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            sc[sb][i] = slot + i < lim ? acc[sb][i] * ks[sb][i] : NEG;
+            if (slot + i < sl.hi8) stash_row[slot + i - sl.lo8] = sc[sb][i];
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        const bool valid = base + 16 * sb + t16 < sl.hi8;
+        float z[NV];
+        regroup_rows<G>(acc[sb], z);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+          const bool real = valid && hd[j] < G;
+          sc[sb][j] = real ? z[j] * ks[sb][0] : NEG;
+          keep_score(real, hd[j], base + 16 * sb + t16 - sl.lo8, sc[sb][j]);
+        }
       }
     }
     if (tix <= 2) TS(24 + (tix - 1) * 3);
-    // ---- online softmax per head ----
+    // ---- online softmax ----
     // The running reference m only has to stay within a few units of the true maximum (the
     // merge is exact for any reference), so the row reduction and the rescale of O run only
     // when some score of the tile exceeds the reference by more than kSlack; e^kSlack times
@@ -1446,79 +1535,186 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       lm[j] = fmaxf(sc[0][j], sc[1][j]);
+      if constexpr (kRows) {
+#pragma unroll
+        for (int i = 1; i < 4; ++i) lm[0] = fmaxf(lm[0], fmaxf(sc[0][i], sc[1][i]));
+      }
       grow |= lm[j] > mrun[j] + kSlack;             // also true on the first tile (m = -inf)
     }
     if (__builtin_amdgcn_ballot_w64(grow)) {
       float corr[NV];
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
-        const float mn = fmaxf(mrun[j], row16_max(lm[j]));
+        const float mn = fmaxf(mrun[j], kRows ? rows4_max(lm[j]) : row16_max(lm[j]));
         corr[j] = (mn == NEG) ? 1.f : __expf(mrun[j] - mn);
         mrun[j] = mn;
         lrun[j] *= corr[j];
         pbias[j] *= corr[j];
       }
-      if (__builtin_expect(several, 0)) {
+      if (__builtin_expect(several, 0)) rescale(corr);
+    }
+    half8_t pa;
+    if constexpr (kRows) {
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float c = rows_to_tile<G>(corr, i, g4);
+          const float p = (sc[sb][i] == NEG) ? 0.f : __expf(sc[sb][i] - mrun[0]);
+          lrun[0] += p;
+          const _Float16 ph = (_Float16)(p * vs[sb][i]);
+          pbias[0] += (float)ph;                             // exactly what the matrix core will see
+          pa[4 * sb + i] = ph;
+        }
+    } else {
 #pragma unroll
-          for (int nt = 0; nt < 8; ++nt) O[nt][i] *= c;
+      for (int j = 0; j < NV; ++j) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+          const float p = (sc[sb][j] == NEG) ? 0.f : __expf(sc[sb][j] - mrun[j]);
+          lrun[j] += p;
+          const _Float16 ph = (_Float16)(p * vs[sb][0]);
+          pbias[j] += (float)ph;                             // exactly what the matrix core will see
+          Pb[hd[j] * kPRow + 16 * sb + t16] = ph;            // (rows past the heads of the group: zeros)
         }
       }
+      wave_lds_sync();
+      // (columns past the heads of the group repeat others; a column only reaches its own output)
+      pa = *(const half8_t *)(Pb + (t16 & (kPb - 1)) * kPRow + 8 * g4);
     }
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        const float p = (sc[sb][j] == NEG) ? 0.f : __expf(sc[sb][j] - mrun[j]);
-        lrun[j] += p;
-        const _Float16 ph = (_Float16)(p * vscale[sb]);
-        pbias[j] += (float)ph;                             // exactly what the matrix core will see
-        const int tau = 16 * sb + t16;                     // slot within the tile
-        if (hd[j] < G) Pb[hd[j] * kPRow + 4 * (tau & 7) + (tau >> 3)] = ph;
-      }
-    }
-    wave_lds_sync();
     if (tix <= 2) TS(25 + (tix - 1) * 3);
-    // ---- output: O[head][channel] += P[head][slot] V[slot][channel] ----
-    const half8_t pa = *(const half8_t *)(Pb + t16 * kPRow + 8 * g4);
+    // ---- output: O[channel][row] += V[slot][channel] P[slot][row] ----
+    // lane t16 of a group of sixteen reads eight channels of row 8 g4 + t16 / 2 and gets the eight slots of channel t16
+    const uint8_t *vrow = Vt + (8 * g4 + (t16 >> 1)) * kKRow + 8 * (t16 & 1);
 #pragma unroll
     for (int nt = 0; nt < DR / 16; ++nt) {
-      const unsigned *vb = (const unsigned *)(Vt + (16 * nt + t16) * kVRow + kVSkew(nt) + 8 * g4);   // 4-byte aligned
-      O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, cvt_i8x8_f16x8_biased(vb[0], vb[1]), O[nt], 0, 0, 0);
+      const uint2 v = lds_read_tr8(vrow + 16 * nt);
+      O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cvt_i8x8_f16x8_biased(v.x, v.y), pa, O[nt], 0, 0, 0);
     }
     wave_lds_sync();
   }
   if constexpr (kChan) {
-    if (in_code_units) leave_code_units();
+    // The accumulator leaves code units behind the wavefront's last INT8 item: the code bias goes out and the V scales come in.
+    float pb[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      pb[j] = (kRows ? rows4_sum(pbias[j]) : row16_sum(pbias[j])) * kCodeBias;
+      pbias[j] = 0.f;
+    }
+    const float bias = head_of_column<G>(pb, t16);
+#pragma unroll
+    for (int nt = 0; nt < 8; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[nt][i] = (O[nt][i] - bias) * (float)vch[nt][i];
+  }
+  // (everything requested so far, the queries among it, is awaited here: later waits would take the next rows in)
+  if constexpr (!kChan) asm volatile("" ::"v"(tr.sc));
+  for (; item < nitems; item += kAttWaves) {
+    // ---- an FP16 tile: 16 slots ----
+    *(int4 *)(Kt + (r4)*kKRow16 + c16 * 16) = tr.k0;
+    *(int4 *)(Kt + (4 + r4) * kKRow16 + c16 * 16) = tr.k1;
+    *(int4 *)(Kt + (8 + r4) * kKRow16 + c16 * 16) = tr.k2;
+    *(int4 *)(Kt + (12 + r4) * kKRow16 + c16 * 16) = tr.k3;
+    *(int4 *)(Vt + (r4)*kVRow16 + c16 * 16) = tr.v0;
+    *(int4 *)(Vt + (4 + r4) * kVRow16 + c16 * 16) = tr.v1;
+    *(int4 *)(Vt + (8 + r4) * kVRow16 + c16 * 16) = tr.v2;
+    *(int4 *)(Vt + (12 + r4) * kVRow16 + c16 * 16) = tr.v3;
+    if (owns_new && item == nitems - 1) {
+      // behind the rows above: LDS keeps a wavefront's order.  Its V row takes the rows past the slice too: those hold
+      // what the ring had there, and a zero probability does not silence a NaN.
+      const int row = sl.n - 1 - (sl.lo16 + 16 * (item - ntiles));
+      if (r4 == 0) *(int4 *)(Kt + row * kKRow16 + c16 * 16) = new_piece;
+      else
+        for (int r = row + r4 - 1; r < 16; r += 3) *(int4 *)(Vt + r * kVRow16 + c16 * 16) = new_piece;
+    }
+    wave_lds_sync();
+    if (item + kAttWaves < nitems) load_item(item + kAttWaves, std::true_type{});
+
+    const int base = sl.lo16 + 16 * (item - ntiles);
+    const uint8_t *krow = Kt + t16 * kKRow16 + g4 * (16 * kSteps);
+    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+    half4_t pa;
+    bool changed = false;
+    float corr[NV];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      const half8_t k = *(const half8_t *)(krow + 16 * s);
+      acc = kRows ? __builtin_amdgcn_mfma_f32_16x16x32_f16(k, qa[s], acc, 0, 0, 0)
+                  : __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], k, acc, 0, 0, 0);
+    }
+    if constexpr (kRows) {
+      // element i: slot base + 4 g4 + i of row t16
+      const int slot = base + 4 * g4, lim = min(seen, sl.hi16);
+      float sv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sv[i] = slot + i < lim ? acc[i] * sm : NEG;
+        if (slot + i < sl.hi16) stash_row[sl.cnt8 + (slot + i - sl.lo16)] = sv[i];
+      }
+      const float mn = fmaxf(mrun[0], rows4_max(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]))));
+      corr[0] = (mn == NEG) ? 1.f : __expf(mrun[0] - mn);
+      changed = mn != mrun[0];
+      mrun[0] = mn;
+      lrun[0] *= corr[0];
+      pbias[0] *= corr[0];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = sv[i] == NEG ? 0.f : __expf(sv[i] - mn);
+        lrun[0] += p;
+        pa[i] = (_Float16)p;
+      }
+    } else {
+      const bool valid = base + t16 < sl.hi16;
+      float z[NV];
+      regroup_rows<G>(acc, z);
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const bool real = valid && hd[j] < G;
+        const float sv = real ? z[j] * sm : NEG;
+        keep_score(real, hd[j], sl.cnt8 + (base + t16 - sl.lo16), sv);
+        const float mn = fmaxf(mrun[j], row16_max(sv));
+        corr[j] = (mn == NEG) ? 1.f : __expf(mrun[j] - mn);
+        changed |= (mn != mrun[j]);
+        mrun[j] = mn;
+        const float p = real ? __expf(sv - mn) : 0.f;
+        Pb[hd[j] * kPRow + t16] = (_Float16)p;
+        lrun[j] = fmaf(lrun[j], corr[j], p);
+        pbias[j] *= corr[j];
+      }
+    }
+    if (several && __builtin_amdgcn_ballot_w64(changed)) rescale(corr);
+    if constexpr (!kRows) {
+      wave_lds_sync();
+      pa = *(const half4_t *)(Pb + (t16 & (kPb - 1)) * kPRow + 4 * g4);
+    }
+    // lane t16 of a group of sixteen reads four channels of row 4 g4 + t16 / 4 and gets the four slots of channel t16
+    // (a 64-channel head has four real channel groups: the copies in groups 4..7 are not multiplied)
+    const uint8_t *vrow = Vt + (4 * g4 + (t16 >> 2)) * kVRow16 + 8 * (t16 & 3);
+#pragma unroll
+    for (int nt = 0; nt < DR / 16; ++nt)
+      O[nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(lds_read_tr16(vrow + 32 * nt), pa, O[nt], 0, 0, 0);
+    wave_lds_sync();
   }
   TS(16);
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    lrun[j] = row16_sum(lrun[j]);
-    pbias[j] = row16_sum(pbias[j]) * kCodeBias;     // what the biased INT8 values added per channel
-  }
-
-  // the wavefront's matrix-core partial goes into its own (now idle) tile buffer
+  // the wavefront's partial goes into its own (now idle) tile buffer
   float *wo_w = tiles + w * (kTileBytes / 4);
 #pragma unroll
-  for (int j = 0; j < NV; ++j)
-    if (t16 == 0 && hd[j] < G) { wm[hd[j] * NP + w] = mrun[j]; wl[hd[j] * NP + w] = lrun[j]; }
+  for (int j = 0; j < NV; ++j) {
+    lrun[j] = kRows ? rows4_sum(lrun[j]) : row16_sum(lrun[j]);
+    pbias[j] = (kRows ? rows4_sum(pbias[j]) : row16_sum(pbias[j])) * kCodeBias;   // what the biased INT8 values added per channel
+    if ((kRows ? g4 == 0 : t16 == 0) && hd[j] < G) { wm[hd[j] * NP + w] = mrun[j]; wl[hd[j] * NP + w] = lrun[j]; }
+  }
+  const float bias = head_of_column<G>(pbias, t16);
+  if (t16 < G) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int h = 4 * g4 + i;
-    const float bias = rows_to_tile<G>(pbias, i, g4);
-    if (h < G) {
-#pragma unroll
-      for (int nt = 0; nt < 8; ++nt) wo_w[h * D + 16 * nt + t16] = O[nt][i] - bias;
-    }
+    for (int nt = 0; nt < 8; ++nt)
+      *(float4 *)(wo_w + t16 * kPartRow + 16 * nt + 4 * g4) =
+          make_float4(O[nt][0] - bias, O[nt][1] - bias, O[nt][2] - bias, O[nt][3] - bias);
   }
 
   TS(17);
   __syncthreads();
   TS(18);
-  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv);
+  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR, kPartRow, kPaged>(cv, a, sl, ns, SS, stash, wm, wl, wo, gm, ginv);
   TS_DUMP();
 }
 
@@ -1590,6 +1786,18 @@ static AttendFn attend_fn_mfma(int D, int G, bool chan) {
 #undef CONFKV_CASE
 }
 
+// The same of the paged layout (single tokens, per-token scales).
+static AttendFn attend_fn_paged(int D, int G) {
+#define CONFKV_CASE(g) \
+  case g: return D == 64 ? (AttendFn)attend_mfma_kernel<g, false, false, 64, true> : (AttendFn)attend_mfma_kernel<g, false, false, 128, true>;
+  if (D != 64 && D != 128) return nullptr;
+  switch (G) {
+    CONFKV_CASE(2) CONFKV_CASE(3) CONFKV_CASE(4) CONFKV_CASE(5) CONFKV_CASE(6) CONFKV_CASE(7) CONFKV_CASE(8)
+    default: return nullptr;
+  }
+#undef CONFKV_CASE
+}
+
 static AttendFn attend_fn_mfma_spill(int D, int G, bool chan) {
   if (D == 64 && !chan) {
 #define CONFKV_CASE(g) \
@@ -1625,8 +1833,8 @@ bool attend_supported(int D, int G) {
 static size_t attend_lds_bytes(int D, int G, int S, bool mfma) {
   if (mfma) {
     const int NP = kAttWaves;
-    size_t floats = (size_t)G * S + G + 2 + 2 * NP * G;
-    size_t tiles = std::max<size_t>((size_t)kAttWaves * kTileBytes, (size_t)NP * G * 128 * sizeof(float));
+    size_t floats = (size_t)G * (S + (G > 8 ? kStashPad : 0)) + G + 2 + 2 * NP * G;
+    size_t tiles = (size_t)kAttWaves * (G > 8 ? kRowsTileBytes : kHeadTileBytes);
     return (floats * sizeof(float) + (size_t)2 * G * sizeof(double) + tiles + 32 + 15) / 16 * 16;
   }
   size_t floats = (size_t)G * S + (size_t)kAttWaves * G * D + 2 * kAttWaves * G + G + 2;
@@ -1687,13 +1895,14 @@ static int attend_occupancy(AttendFn fn, size_t lds) {
   return nb;
 }
 
-bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n_ub, int n16_ub, int forced_splits,
+bool attend_plan(int D, int G, bool chan, bool paged, bool chunk, int units_per_layer, int n_ub, int n16_ub, int forced_splits,
                  bool force_two_launch, size_t extra_lds, AttendPlan *plan) {
   const DeviceLimits &lim = device_limits();
   if (!lim.ok) return false;
   if (chunk ? attend_fn_mfma(D, G, chan) == nullptr : attend_fn_valu(D, G) == nullptr) return false;
   const bool mfma = chunk || wants_mfma(D, G, n16_ub < n_ub);
-  AttendFn fn = mfma ? attend_fn_mfma(D, G, chan) : attend_fn_valu(D, G);
+  AttendFn fn = mfma ? (paged ? attend_fn_paged(D, G) : attend_fn_mfma(D, G, chan)) : attend_fn_valu(D, G);
+  if (!fn) return false;
   const long long nv = (long long)n_ub + n16_ub;
   // One workgroup per CU measured best: the exchange between the splits of a unit (statistics
   // and partial gather) gets slower with more participants, and a grid that is not a
@@ -1813,6 +2022,7 @@ size_t attend_spill_floats(int units_per_layer, int G, int cap) {
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const AttendPlan &plan,
                          hipStream_t stream) {
   AttendLaunch a = a_in;
+  a.ns_magic = plan.splits > 1 ? 0xFFFFFFFFu / (unsigned)plan.splits + 1u : 0u;
   if (plan.two_launch || !plan.mfma) a.dbg = nullptr;      // only the single matrix-core kernel is traced
   const dim3 grid = a.kv_major ? dim3(cv.Hkv, plan.splits, cv.B) : dim3(plan.splits, cv.Hkv, cv.B);
   if (plan.two_launch) {
@@ -1840,7 +2050,8 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const At
   const bool rows16 = a.tq > 1 || a.observe_first >= 0 || cv.G > 8;
   const int rows = rows16 ? kChunkRows : cv.G;
   if (rows16 && !plan.mfma) return hipErrorInvalidValue;
-  AttendFn fn = plan.mfma ? attend_fn_mfma(cv.D, rows, cv.chan != 0) : attend_fn_valu(cv.D, cv.G);
+  AttendFn fn = plan.mfma ? (cv.page_lg ? attend_fn_paged(cv.D, rows) : attend_fn_mfma(cv.D, rows, cv.chan != 0))
+                          : attend_fn_valu(cv.D, cv.G);
   if (!fn) return hipErrorInvalidValue;
 #ifdef CONFKV_TRACE
   if (a.dbg && plan.mfma) {             // time stamps live in LDS behind the kernel's own

@@ -112,57 +112,9 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   const int nitems = ntiles + ntiles16;
   const int nsup = (nitems + kAttWaves - 1) / kAttWaves;
 
-  struct TileRegs {
-    int4 k0, k1, k2, k3, v0, v1, v2, v3;
-    unsigned short ks0, ks1, vs0, vs1;
-  };
-  // branch-free loads (rows past the slice re-read its last row and are masked where they are used)
-  auto load_item = [&](int it) -> TileRegs {
-    TileRegs t = {};
-    if (it < ntiles) {
-      const int base = sl.lo8 + it * kTile, last = sl.hi8 - 1;
-      const unsigned col = (unsigned)c8 * 16u;
-      const int h8 = sl.h8, cap8 = cv.cap8;
-      const unsigned o0 = (unsigned)ring_row_u(h8, min(base + r8, last), cap8) * D + col;
-      const unsigned o1 = (unsigned)ring_row_u(h8, min(base + 8 + r8, last), cap8) * D + col;
-      const unsigned o2 = (unsigned)ring_row_u(h8, min(base + 16 + r8, last), cap8) * D + col;
-      const unsigned o3 = (unsigned)ring_row_u(h8, min(base + 24 + r8, last), cap8) * D + col;
-      t.k0 = ld_stream16(K8 + o0);
-      t.k1 = ld_stream16(K8 + o1);
-      t.k2 = ld_stream16(K8 + o2);
-      t.k3 = ld_stream16(K8 + o3);
-      t.v0 = ld_stream16(V8 + o0);
-      t.v1 = ld_stream16(V8 + o1);
-      t.v2 = ld_stream16(V8 + o2);
-      t.v3 = ld_stream16(V8 + o3);
-      const unsigned j0 = (unsigned)ring_row_u(h8, min(base + t16, last), cap8);
-      const unsigned j1 = (unsigned)ring_row_u(h8, min(base + 16 + t16, last), cap8);
-      t.ks0 = ((const unsigned short *)KS)[j0];
-      t.ks1 = ((const unsigned short *)KS)[j1];
-      t.vs0 = ((const unsigned short *)VS)[j0];
-      t.vs1 = ((const unsigned short *)VS)[j1];
-    } else {
-      const int base = sl.lo16 + 16 * (it - ntiles), last = sl.hi16 - 1;
-      const int h16 = sl.h16, cap16 = cv.cap16, n8 = sl.n8;
-      const unsigned col = (unsigned)c16 * 8u;
-      // the call's own tokens come from the call's arguments, not from the ring
-      const int first_new = a.observe_first >= 0 ? 0x3fffffff : sl.n - tq;
-      // (one load serves either source: no branch, and what is uniform stays scalar)
-      const __half *kn = a.knew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D, *vn = a.vnew + ((size_t)sl.b * tq * cv.Hkv + sl.g) * D;
-      const unsigned tok = (unsigned)cv.Hkv * D;
-      auto pick = [&](int r, int4 &k, int4 &v) {
-        const int s = min(base + r + r4, last), n = s - first_new;
-        const unsigned off = (n >= 0 ? (unsigned)n * tok : (unsigned)ring_row(h16, s - n8, cap16) * D) + col;
-        k = ld_stream16((n >= 0 ? kn : K16) + off);
-        v = ld_stream16((n >= 0 ? vn : V16) + off);
-      };
-      pick(0, t.k0, t.v0);
-      pick(4, t.k1, t.v1);
-      pick(8, t.k2, t.v2);
-      pick(12, t.k3, t.v3);
-    }
-    return t;
-  };
+  // the call's own tokens come from the call's arguments, not from the ring
+  const TileSource ts = tile_source<D, true>(cv, a, sl, K8, V8, K16, V16, KS, VS, ntiles, tq,
+                                             a.observe_first >= 0 ? 0x3fffffff : sl.n - tq);
   // registers -> this wavefront's LDS buffer
   auto store_item = [&](int it, const TileRegs &tr) {
     uint8_t *Kt = tiles + (size_t)w * kWideTileBytes;
@@ -197,13 +149,8 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
           *(uint2 *)(dst + 64 * e) = make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
         }
       }
-      if (g4 == 0) {
-        const int row = 4 * (t16 & 7) + (t16 >> 3);              // of slot t16; slot 16 + t16 is two further
-        sc[row] = __half2float(__ushort_as_half(tr.ks0)) * sm;
-        sc[row + 2] = __half2float(__ushort_as_half(tr.ks1)) * sm;
-        sc[kTile + row] = __half2float(__ushort_as_half(tr.vs0));
-        sc[kTile + row + 2] = __half2float(__ushort_as_half(tr.vs1));
-      }
+      // row 4 * (slot % 8) + slot / 8 of slot lane % 32
+      sc[(lane & 32) + 4 * (lane & 7) + ((lane >> 3) & 3)] = __half2float(__ushort_as_half(tr.sc)) * (lane < 32 ? sm : 1.0f);
     } else {
       *(int4 *)(Kt + (4 * r4) * kKRow16 + c16 * 16) = tr.k0;
       *(int4 *)(Kt + (4 * r4 + 1) * kKRow16 + c16 * 16) = tr.k1;
@@ -233,8 +180,9 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   };
 
   // ---------------- pass 1: online softmax and output per row ----------------
-  TileRegs tr = {};
-  if (w < nitems) tr = load_item(w);
+  TileRegs tr;
+  auto load_item = [&](int it) { load_item_rows<D, true, false, true>(cv, ts, sl, lane, it, std::false_type{}, tr); };
+  if (w < nitems) load_item(w);
   half8_t qa[2][4];
   load_rows(2 * rg, qa[0]);
   load_rows(2 * rg + 1, qa[1]);
@@ -322,7 +270,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     if (sup > 0) __syncthreads();                      // everybody has left the previous eight tiles
     if (mine < nitems) store_item(mine, tr);
     __syncthreads();
-    if (mine + kAttWaves < nitems) tr = load_item(mine + kAttWaves);
+    if (mine + kAttWaves < nitems) load_item(mine + kAttWaves);
 #pragma unroll 1
     for (int j = st; j < kAttWaves; j += NS) {
       const int it = sup * kAttWaves + j;
@@ -383,7 +331,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   lane = tid & 63;
   t16 = lane & 15;
   g4 = lane >> 4;
-  append_new_token<D>(cv, a, sl, ns);                    // (nobody reads the appended rows back in this launch)
+  append_new_token<D>(cv, a, sl, ns, a.tq);                    // (nobody reads the appended rows back in this launch)
 
   // ---------------- the tile streams of a row merge in LDS ----------------
   if (tid == 0) s_ok = 1;

@@ -51,6 +51,7 @@ struct AttendLaunch {
                            // cv.ctl: the sum tags the words the launch publishes (never 0, never reused)
   int spin_limit;          // polls before a wait for the other splits gives up (device error)
   int max_splits;
+  unsigned ns_magic;       // ceil(2^32 / splits), 0 for one split: the kernels' division by the split count
   float sm_scale, ema_decay;
   double mass_gain;        // weight of the step's mass in the EMA update
   unsigned tag_base;       // filled in by the kernels from cv.ctl
@@ -75,7 +76,7 @@ size_t attend_spill_floats(int units_per_layer, int G, int cap);   // scratch th
 // of which at most n16_ub are FP16.  G = query rows per unit (the group size, or kChunkRows for
 // a multi-token call, which only has the single-launch matrix-core form).  Returns false when no plan fits the device.
 // extra_lds: bytes the launch needs behind the kernel's own dynamic LDS (the block table of the paged layout).
-bool attend_plan(int D, int G, bool chan, bool chunk, int units_per_layer, int n_ub, int n16_ub, int forced_splits,
+bool attend_plan(int D, int G, bool chan, bool paged, bool chunk, int units_per_layer, int n_ub, int n16_ub, int forced_splits,
                  bool force_two_launch, size_t extra_lds, AttendPlan *plan);
 // Plan of a call with more than kChunkRows query rows per unit (at most kWideRowsMax); false when
 // the shape cannot be served.  major_kv: kv-heads of the kv-head-first grid, 0 for the other.

@@ -177,7 +177,7 @@ def test_codes_at_half_way_quotients(lib, torch_cuda, D, scales):
 # ------------------------------------------------------------------ attention + mass EMA
 
 def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_launch=False,
-                 scale_mode="token", late_gain=1.0):
+                 scale_mode="token", late_gain=1.0, steps=3):
     say(f"attend D={D} G={G} Hkv={H} B={B} T0={T0} W={W} splits={splits} two_launch={two_launch} "
         f"scales={scale_mode}")
     if splits:
@@ -187,7 +187,7 @@ def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_l
     if two_launch:
         os.environ["CONF_KV_TWO_LAUNCH"] = "1"
     try:
-        cap = ((T0 + 8 + 63) // 64) * 64
+        cap = ((T0 + 5 + steps + 63) // 64) * 64
         kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap,
                  protected_window=4, n_tight=[cap - 2], n_loose=[cap - 1], scale_mode=scale_mode)
     finally:
@@ -209,7 +209,7 @@ def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_l
              for b in range(B) for g in range(H)}
     out = torch.zeros((B, G * H, D), dtype=torch.float16, device="cuda")
     sm, lam = f32(1 / math.sqrt(D)), f32(0.9)
-    for t in range(3):
+    for t in range(steps):
         q = (rng.standard_normal((B, G * H, D)) * scale_q).astype(np.float16)
         kn = (rng.standard_normal((B, H, D)) * late_gain).astype(np.float16)   # late_gain > 1: codes saturate
         vn = (rng.standard_normal((B, H, D)) * late_gain).astype(np.float16)
@@ -269,6 +269,20 @@ def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_l
 ])
 def test_attend_matches_oracle(lib, torch_cuda, D, G, H, B, T0, W, splits):
     _attend_case(lib, torch_cuda, D, G, H, B, T0, W, splits, seed=D + G + T0)
+
+
+@pytest.mark.parametrize("D,G,T0,W,splits,scales,two_launch", [
+    (128, 4, 40, 20, 0, "token", False),      # one split: INT8 tile and two FP16 tiles, the last with 1 .. 5 slots
+    (128, 5, 300, 17, 3, "token", False), (128, 8, 61, 33, 1, "token", False), (128, 3, 33, 0, 1, "token", False),
+    (64, 8, 90, 15, 2, "token", False), (64, 4, 3, -1, 0, "token", False),
+    (128, 4, 200, 33, 4, "channel", False), (128, 12, 70, 18, 2, "token", False), (128, 4, 300, 20, 3, "token", True),
+])
+def test_new_token_at_every_place_of_a_tile(lib, torch_cuda, monkeypatch, D, G, T0, W, splits, scales, two_launch):
+    """The rings turn over and the appended token takes every place of an FP16 tile, its first and last ones too, in a
+    cache whose unwritten rows are NaN: what a ring holds where the new token goes, or past the slice, never shows."""
+    torch, empty = torch_cuda, torch_cuda.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: empty(*a, **k).fill_(255) if k.get("dtype") is torch.uint8 else empty(*a, **k))
+    _attend_case(lib, torch, D, G, 1, 1, T0, W, splits, seed=T0 + G, scale_mode=scales, two_launch=two_launch, steps=36)
 
 
 @pytest.mark.parametrize("D,G,H,B,T0,W,splits", [
@@ -378,7 +392,7 @@ def _observe_case(lib, torch, G, H, B, T0, W, splits, windows, seed, scale_mode=
     if two_launch:
         os.environ["CONF_KV_TWO_LAUNCH"] = "1"
     try:
-        cap = ((T0 + 8 + 63) // 64) * 64
+        cap = ((T0 + 5 + steps + 63) // 64) * 64
         kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap,
                  protected_window=4, n_tight=[T0 - 20], n_loose=[T0 - 20], scale_mode=scale_mode,
                  max_chunk=max(2, max(tq for _, tq in windows)))
