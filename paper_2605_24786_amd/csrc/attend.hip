@@ -629,30 +629,41 @@ __device__ __forceinline__ double row_weight(const AttendLaunch &a, int tq, int 
 // later launch, which needs no wait (wm/wl are unused and wo holds the [G][gs] weights) --
 // the pair serves shapes whose splits cannot all be resident at once.
 // ---------------------------------------------------------------------------------------
+// ---------------------------------------------------------------------------------------
+constexpr int kEmaAhead = 4;                         // slots per thread whose EMA is requested ahead
+// The EMA values a thread will update, requested behind the first rows and used behind the exchange.
+template <bool kPaged>
+__device__ __forceinline__ void request_ema(const CacheView &cv, const Slice &sl, float (&ema_old)[kEmaAhead]) {
+  const float *EMA = cv.ema + (size_t)sl.u * cv.cap;
+#pragma unroll
+  for (int k = 0; k < kEmaAhead; ++k) {
+    // no branch per lane (a slot past the slice re-reads its last one; the appended token's slot
+    // holds a stale value): the uses mask both cases
+    ema_old[k] = 0.f;
+    const int t = threadIdx.x + k * kAttThreads;
+    if (k * kAttThreads < sl.ntok) ema_old[k] = EMA[slot_plane_row<kPaged>(cv, sl, sl.slot_of(min(t, sl.ntok - 1)))];
+  }
+}
+
 template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D, int DS = D, bool kPaged = false>
 __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const AttendLaunch &a,
                                                 const Slice &sl, int ns, int S, float *stash,
                                                 float *wm, float *wl, float *wo, float *gm,
-                                                double *ginv) {
+                                                double *ginv, float (&ema_old)[kEmaAhead]) {
   const int tid = threadIdx.x;
   const float NEG = -INFINITY;
   // more than 8 rows only occur in multi-token calls; otherwise rows are the heads of one token
   const int tq = G > 8 ? a.tq : 1, gq = G > 8 ? a.gq : G;
   unsigned long long *ml = a.part_ml + ((size_t)sl.ul * a.max_splits + sl.j) * G * 2;
   unsigned long long *po = a.part_o + ((size_t)sl.ul * a.max_splits + sl.j) * G * D;
-  // the EMA values this thread will update: requested now, needed after the wait
-  constexpr int kPre = kPhase == 0 ? 4 : 0;
+  constexpr int kPre = kPhase == 0 ? kEmaAhead : 0;
   const bool exchange = kPhase != 0 || ns > 1;       // partials go through device memory
   float *EMA = cv.ema + (size_t)sl.u * cv.cap;
-  float ema_old[kPre + 1];
   auto ema_row = [&](int t) { return slot_plane_row<kPaged>(cv, sl, sl.slot_of(t)); };
+  // The EMA values requested at the start are taken here: loads and stores share one in-order counter, so that a wait for
+  // them further down would be one for the published words and the gathered partials too.
 #pragma unroll
-  for (int k = 0; k < kPre; ++k) {
-    // no branch per lane (a slot past the slice re-reads its last one; the appended token's slot
-    // holds a stale value): the uses below mask both cases
-    ema_old[k] = 0.f;
-    if (k * kAttThreads < sl.ntok) ema_old[k] = EMA[ema_row(min(tid + k * kAttThreads, sl.ntok - 1))];
-  }
+  for (int k = 0; k < kPre; ++k) asm volatile("" : "+v"(ema_old[k]));
   // Weights of the workgroup merge: a wavefront's output elements all belong to one row, so a row's NP statistics lie in
   // eight neighbouring lanes (lane k of group r: wavefront k's part of row 8 b + r) and three lane moves merge them; the
   // weights reach the merge as scalars.  (Every thread formed the eight weights of its row for itself before, behind a thread
@@ -737,7 +748,11 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
         for (int e = 0; e < kEPT; ++e) {
           // (DR < D: the matrix-core body pads a 64-channel head to its 128-channel tiles)
           if (h < tq * gq && a.out && idx + e - h * D < DR)
-            a.out[out_index(cv, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn((float)((double)o[e] * inv));
+          {
+            float v = (float)((double)o[e] * inv);
+            asm("" : "+v"(v));                          // (else one rounding from 64 to 16 bits, forty instructions)
+            a.out[out_index(cv, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn(v);
+          }
         }
       } else {
 #pragma unroll
@@ -755,15 +770,14 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * G * 2;
   const unsigned long long *pou = a.part_o + (size_t)sl.ul * a.max_splits * G * D;
   float *pml = wo;                                   // [G][gs] weights of the splits' partials, reuses the merge buffer
-  int lg = 0;
-  while ((1 << lg) < ns) ++lg;                       // <= 6: groups never straddle a wavefront
+  const int lg = ns > 1 ? 32 - __builtin_clz(ns - 1) : 0;   // <= 6: groups never straddle a wavefront
   const int gs = 1 << lg;
   // This split normalises `per` elements of the unit's [G][D] output.  A lane takes kOut of an element's ns partial values
   // (split sub + q * lanes), the `lanes` that share an element are neighbours: the words a thread needs are requested
   // together, and an element's address, sum and store come once (16 rows, four splits: 0.9 us from the request to the
   // store; a pass per kOut-th element with a lane per split took 1.8).
   constexpr int kOutLg = G > 8 ? 2 : G > 4 ? 1 : 0, kOut = 1 << kOutLg;
-  const int per = (G * D + ns - 1) / ns;
+  const int per = (int)div_splits(a, G * D + ns - 1);
   const int lgl = max(lg - kOutLg, 0);               // log2(lanes)
   const int epp = kAttThreads >> lgl;                // output elements per pass over the workgroup
   const int sub = tid & ((1 << lgl) - 1), oe = tid >> lgl;   // this thread's first split and element within a pass
@@ -951,6 +965,8 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
 
   const Slice sl = make_slice(cv, a, ns, S);
   append_new_token<D>(cv, a, sl, ns, 1);
+  float ema_old[kEmaAhead];
+  if (!kSpill) request_ema<false>(cv, sl, ema_old);
 
   Stream<G> st;
   st.reset();
@@ -982,7 +998,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   stream_fp16_valu<D, G>(cv, a, sl, a.sm_scale, qf, st, stash, S);
   store_stream_partial<D, G>(st, threadIdx.x >> 6, wm, wl, wo + (threadIdx.x >> 6) * G * D);
   __syncthreads();
-  attend_epilogue<D, G, NP, G * D, kSpill ? 1 : 0>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv);
+  attend_epilogue<D, G, NP, G * D, kSpill ? 1 : 0>(cv, a, sl, ns, S, stash, wm, wl, wo, gm, ginv, ema_old);
 }
 
 // Second launch of the two-launch form: same grid; merges the published partials of the unit,
@@ -997,7 +1013,8 @@ __global__ __launch_bounds__(kAttThreads) void attend_finish_kernel(const int32_
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]
   const Slice sl = make_slice(cv, a, ns, S);
   float *stash = a.spill + ((size_t)unit_in_layer(cv, a) * ns + split_index(a)) * G * S;
-  attend_epilogue<D, G, 1, 0, 2, DR>(cv, a, sl, ns, S, stash, nullptr, nullptr, pml, gm, ginv);
+  float unused[kEmaAhead];
+  attend_epilogue<D, G, 1, 0, 2, DR>(cv, a, sl, ns, S, stash, nullptr, nullptr, pml, gm, ginv, unused);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1104,8 +1121,11 @@ __device__ __forceinline__ float head_of_column(const float (&x)[NV], int t16) {
   if constexpr (G > 8) {
     return x[0];
   } else if constexpr (G <= 4) {
-    auto row = [&](int r) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[0]), 16 * r)); };
-    const float lo = (t16 & 1) ? row(1) : row(0), hi = (t16 & 1) ? row(3) : row(2);
+    // (all four read before the choice: a read inside it becomes a branch)
+    float row[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[0]), 16 * r));
+    const float lo = (t16 & 1) ? row[1] : row[0], hi = (t16 & 1) ? row[3] : row[2];
     return (t16 & 2) ? hi : lo;
   } else {
     const int from = 32 * (t16 & 1) + 16 * ((t16 >> 2) & 1);
@@ -1356,6 +1376,8 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   int4 new_piece;
   if (owns_new)
     new_piece = *(const int4 *)((r4 ? a.vnew : a.knew) + ((size_t)sl.b * cv.Hkv + sl.g) * DR + (c16 & (DR / 8 - 1)) * 8);
+  float ema_old[kEmaAhead];
+  if (!kSpill) request_ema<kPaged>(cv, sl, ema_old);
   TS(3);
   append_new_token<DR, kPaged>(cv, a, sl, ns, tq);
   const float NEG = -INFINITY;
@@ -1714,7 +1736,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   TS(17);
   __syncthreads();
   TS(18);
-  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR, kPartRow, kPaged>(cv, a, sl, ns, SS, stash, wm, wl, wo, gm, ginv);
+  attend_epilogue<D, G, NP, kTileBytes / 4, kSpill ? 1 : 0, DR, kPartRow, kPaged>(cv, a, sl, ns, SS, stash, wm, wl, wo, gm, ginv, ema_old);
   TS_DUMP();
 }
 

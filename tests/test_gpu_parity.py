@@ -392,7 +392,7 @@ def _observe_case(lib, torch, G, H, B, T0, W, splits, windows, seed, scale_mode=
     if two_launch:
         os.environ["CONF_KV_TWO_LAUNCH"] = "1"
     try:
-        cap = ((T0 + 5 + steps + 63) // 64) * 64
+        cap = ((T0 + 8 + 63) // 64) * 64
         kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap,
                  protected_window=4, n_tight=[T0 - 20], n_loose=[T0 - 20], scale_mode=scale_mode,
                  max_chunk=max(2, max(tq for _, tq in windows)))
