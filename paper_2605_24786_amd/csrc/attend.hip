@@ -600,26 +600,37 @@ __device__ __forceinline__ double recip_pos(double x) {
   return r * (2.0 - x * r);
 }
 
+// lambda^k
+__device__ __forceinline__ double pow_count(double x, unsigned k) {
+  double r = 1.0;
+  for (; k; k >>= 1) {
+    if (k & 1u) r *= x;
+    x *= x;
+  }
+  return r;
+}
+// r / gq for a row r < 16 (gq_mul = 65536 / gq + 1)
+__device__ __forceinline__ int token_of_row(const AttendLaunch &a, int r) { return (int)((unsigned)(r * a.gq_mul) >> 16); }
+// Weight of row r's mass in the importance update of a call with tq tokens:
+// lambda^(tq - 1 - token), 0 for padding rows; for a single token (G rows, one per head) exactly 1.
+template <int G>
+__device__ __forceinline__ double row_weight(const AttendLaunch &a, int r) {
+  if constexpr (G <= 8) return 1.0;
+  const int left = a.tq - 1 - token_of_row(a, r);
+  return left < 0 ? 0.0 : pow_count((double)a.ema_decay, (unsigned)left);
+}
+
 // Query row r of a unit is (token r / gq of the call, head r % gq of the group); rows past
 // tq * gq are padding.  Element e = r * D + d of the unit's [rows][D] output lives at
 // out[b][token][g * gq + head][d].
-__device__ __forceinline__ size_t out_index(const CacheView &cv, const Slice &sl, int tq, int gq,
+template <bool kRows>
+__device__ __forceinline__ size_t out_index(const CacheView &cv, const AttendLaunch &a, const Slice &sl, int tq, int gq,
                                             int e, int D) {
   // (32-bit arithmetic: the output of one call stays far below 2^31 elements)
   const unsigned r = (unsigned)e / (unsigned)D, d = (unsigned)e - r * (unsigned)D;
-  const unsigned t = r / (unsigned)gq, hq = r - t * (unsigned)gq;
+  const unsigned t = kRows ? (unsigned)token_of_row(a, (int)r) : 0u, hq = r - t * (unsigned)gq;   // (r < gq of a single token)
   return (size_t)(((((unsigned)sl.b * (unsigned)tq + t) * (unsigned)cv.Hkv + (unsigned)sl.g) * (unsigned)gq + hq) * (unsigned)D + d);
 }
-// Weight of row r's mass in the importance update of a call with tq tokens:
-// lambda^(tq - 1 - token), 0 for padding rows; for tq = 1 it is exactly 1.
-__device__ __forceinline__ double row_weight(const AttendLaunch &a, int tq, int gq, int r) {
-  const int t = r / gq;
-  if (t >= tq) return 0.0;
-  double w = 1.0;
-  for (int k = t + 1; k < tq; ++k) w *= (double)a.ema_decay;
-  return w;
-}
-
 // ---------------------------------------------------------------------------------------
 // Epilogue shared by both bodies.  On entry wm/wl/wo hold NP per-wavefront partials
 // (after a workgroup barrier): partial k is [G][D] floats, rows DS apart, at
@@ -698,10 +709,13 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
   // A unit with a single split is complete here: global statistics per row, uniform over the workgroup.
   float g_m[G];
   double g_w[G];                                       // the row's mass weight over its normaliser
-  double row_inv[HB];
+  double row_inv[HB], row_w[HB];
   if (kPhase == 0 && !exchange) {
 #pragma unroll
-    for (int b = 0; b < HB; ++b) row_inv[b] = recip_pos((double)row_l[b]);
+    for (int b = 0; b < HB; ++b) {
+      row_inv[b] = recip_pos((double)row_l[b]);
+      row_w[b] = row_inv[b] * row_weight<G>(a, 8 * b + (lane8 >> 3));
+    }
   }
   auto lane_f = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
   auto lane_d = [](double v, int l) {
@@ -739,7 +753,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       for (int k = 0; k < NP; ++k) {
         const float f = lane_f(part_w[b], r8 + k);
 #pragma unroll
-        for (int e = 0; e < kEPT; ++e) o[e] = fmaf(f > 0.f ? ok2[k][e] : 0.f, f, o[e]);
+        for (int e = 0; e < kEPT; ++e) o[e] = __float_as_int(f) != 0 ? fmaf(ok2[k][e], f, o[e]) : o[e];
       }
       if (!exchange) {
         // same arithmetic as the general merge below (weight e^0 = 1), without the trip through device memory
@@ -751,7 +765,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
           {
             float v = (float)((double)o[e] * inv);
             asm("" : "+v"(v));                          // (else one rounding from 64 to 16 bits, forty instructions)
-            a.out[out_index(cv, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn(v);
+            a.out[out_index<(G > 8)>(cv, a, sl, tq, gq, h * DR + (idx + e - h * D), DR)] = __float2half_rn(v);
           }
         }
       } else {
@@ -816,7 +830,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       const float es = ms > NEG ? exp_nonpos(ms - M) : 0.f;          // an empty partial weighs nothing
       const double inv = recip_pos(group_sum((double)es * (double)ls, gs));
       if (mine) {
-        if (os == 0) { gm[h] = M; ginv[h] = inv; ginv[G + h] = inv * row_weight(a, tq, gq, h); }
+        if (os == 0) { gm[h] = M; ginv[h] = inv; ginv[G + h] = inv * row_weight<G>(a, h); }
         // what split os's output partial of this row is multiplied by
         pml[(h << lg) + os] = es * (float)inv;
       }
@@ -836,7 +850,7 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       g_m[h] = lane_f(row_m[h / 8], 8 * (h & 7));
-      g_w[h] = lane_d(row_inv[h / 8], 8 * (h & 7)) * row_weight(a, tq, gq, h);
+      g_w[h] = lane_d(row_w[h / 8], 8 * (h & 7));
     }
   }
   TS(22);
@@ -881,14 +895,13 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
       }
       c = group_sum(c, 1 << lgl);
       if (mine && sub == 0 && h < tq * gq && a.out && e - h * D < DR)
-        a.out[out_index(cv, sl, tq, gq, h * DR + (e - h * D), DR)] = __float2half_rn(c);
+        a.out[out_index<(G > 8)>(cv, a, sl, tq, gq, h * DR + (e - h * D), DR)] = __float2half_rn(c);
     }
   };
   // ---- mass + EMA of the slice ----
   // a <- lambda^tq a + gain * sum over the rows of lambda^(tq-1-token) p; ginv[G + h] holds
   // row h's weight over its normaliser.  Slots appended by this call start at 0.
-  double lam = 1.0;
-  for (int k = 0; k < tq; ++k) lam *= (double)a.ema_decay;
+  const double lam = pow_count((double)a.ema_decay, (unsigned)tq);
   const double oml = a.mass_gain;
   const int first_new = sl.n - tq;
   // The new values of the first kPre slots per thread stay in registers until the output is
@@ -1319,7 +1332,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   {
     // row t16 = (token, head) of the call's [B][tq][Hq][D] queries
     const int row = kRows ? t16 : min(t16, G - 1);
-    const int q_tok = kRows ? row / gq : 0, q_head = row - q_tok * gq;
+    const int q_tok = kRows ? token_of_row(a, row) : 0, q_head = row - q_tok * gq;
     const bool real = !kRows || q_tok < tq;
     const __half *qrow = a.q + ((((size_t)blockIdx.z * tq + (real ? q_tok : 0)) * cv.Hkv + kv_head_index(a)) * gq + q_head) * DR;
 #pragma unroll
@@ -1424,7 +1437,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 #pragma unroll
   for (int j = 0; j < NV; ++j) { mrun[j] = NEG; lrun[j] = 0.f; pbias[j] = 0.f; hd[j] = kRows ? t16 : RowMap<G>::head(j, g4); }
   // causal order inside the call: row t16's token sees slots below this
-  const int seen = kRows ? sl.n - tq + t16 / gq + 1 : 0;
+  const int seen = kRows ? sl.n - tq + token_of_row(a, t16) + 1 : 0;
   float *stash_row = kRows ? stash + (size_t)t16 * SS : stash;
 
   // A raw score goes to its place in the stash; where there is none, to the wavefront's own scales, which are used up (no
@@ -1717,6 +1730,9 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     wave_lds_sync();
   }
   TS(16);
+  // Everything requested has arrived -- which the compiler cannot know of the rows: without this it waits further down, where
+  // their registers are used anew, for the published words as well (16 rows: 0.8 us).
+  __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
   // the wavefront's partial goes into its own (now idle) tile buffer
   float *wo_w = tiles + w * (kTileBytes / 4);
 #pragma unroll
@@ -2044,6 +2060,7 @@ size_t attend_spill_floats(int units_per_layer, int G, int cap) {
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const AttendPlan &plan,
                          hipStream_t stream) {
   AttendLaunch a = a_in;
+  a.gq_mul = 65536 / std::max(1, a.gq) + 1;
   a.ns_magic = plan.splits > 1 ? 0xFFFFFFFFu / (unsigned)plan.splits + 1u : 0u;
   if (plan.two_launch || !plan.mfma) a.dbg = nullptr;      // only the single matrix-core kernel is traced
   const dim3 grid = a.kv_major ? dim3(cv.Hkv, plan.splits, cv.B) : dim3(plan.splits, cv.Hkv, cv.B);

@@ -48,16 +48,6 @@ __host__ __device__ constexpr size_t attend_wide_lds_bytes(int R, int ns) {
   return (size_t)kAttWaves * kWideTileBytes + ((size_t)kAttWaves * kWideRows * 3 + 5 * R + (size_t)ns * R * 2) * 4 + 16;
 }
 
-// lambda^k
-__device__ __forceinline__ double pow_count(double x, unsigned k) {
-  double r = 1.0;
-  for (; k; k >>= 1) {
-    if (k & 1u) r *= x;
-    x *= x;
-  }
-  return r;
-}
-
 template <int RG>
 __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns, int /*unused*/) {

@@ -58,6 +58,7 @@ struct AttendLaunch {
   int pos_new;             // position of the first appended token (the kernels read it from cv.ctl)
   int tq;                  // tokens appended (and queries per head) in this call
   int gq;                  // query heads per kv-head; the kernels' row r is (token r / gq, head r % gq)
+  int gq_mul;              // 65536 / gq + 1: the single-tile kernels' division of a row number by gq
   int observe_first;       // >= 0: the queries belong to the cached slots observe_first .. observe_first + tq - 1;
                            // nothing is appended and slots from observe_first + tq on are left alone
   int withhold;            // test hook: split 0 of every unit does not publish its statistics, so the
