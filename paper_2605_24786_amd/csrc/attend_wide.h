@@ -321,6 +321,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   lane = tid & 63;
   t16 = lane & 15;
   g4 = lane >> 4;
+  __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0): nothing is outstanding, which the compiler cannot know
   append_new_token<D>(cv, a, sl, ns, a.tq);                    // (nobody reads the appended rows back in this launch)
 
   // ---------------- the tile streams of a row merge in LDS ----------------
@@ -531,15 +532,19 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   const int first_new = sl.n - tq;                       // a token of the call starts at 0
   float *EMA = cv.ema + (size_t)sl.u * cv.cap;
   const int subs8 = (sl.cnt8 + 31) / 32, subs = subs8 + (sl.hi16 - sl.lo16 + 31) / 32;
-  // Fewer subtiles than wavefronts: several wavefronts share a subtile's rows, and their sums meet in LDS (one wavefront
-  // took 3 us for the 128 rows of 8 slots).
+  // Eight subtiles at a time, one per wavefront; of those left over (all, where there are fewer than eight) several
+  // wavefronts share a subtile's rows, and their sums meet in LDS.  (One wavefront took 3 us for the 128 rows of 8 slots, and
+  // the seventeenth of 17 subtiles cost a third round.)
+  const int whole = subs & ~(kAttWaves - 1), rest = subs - whole;
   int across = 1;
-  while (across < subs && across < kAttWaves) across *= 2;
-  const int shares = min(kAttWaves / across, RB), share = w / across;
+  while (across < rest) across *= 2;
+  const int rest_shares = rest ? min(kAttWaves / across, RB) : 1;
   double *red = (double *)stat_m;                        // [wavefront][32]: the streams' statistics are done with
   static_assert(kAttWaves * 32 * sizeof(double) <= (size_t)kAttWaves * kWideRows * 2 * sizeof(float), "the shares' sums fit");
-  int t = w % across;
-  do {                                                   // (once where wavefronts share)
+  for (int first = 0; first < subs; first += kAttWaves) {
+    const bool split_rows = first == whole;
+    const int shares = split_rows ? rest_shares : 1, share = split_rows ? w / across : 0;
+    const int t = first + (split_rows ? w % across : w);
     const bool live = share < shares && t < subs;
     int slot_e = 0, row_e = 0;
     bool writes = false;
@@ -609,13 +614,12 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       }
     }
     double mass = g4 == 0 ? sum[0] : sum[1];
-    if (shares > 1) {
+    if (shares > 1) {                                    // (the last turn: every wavefront takes it)
       if (live && g4 < 2) red[w * 32 + 16 * g4 + t16] = mass;
       __syncthreads();
       if (share == 0 && writes)
         for (int k = 1; k < shares; ++k) mass += red[(w + k * across) * 32 + 16 * g4 + t16];
     }
     if (share == 0 && writes) EMA[row_e] = (float)(lam * (slot_e >= first_new ? 0.0 : (double)old) + a.mass_gain * mass);
-    t += across;
-  } while (t < subs);
+  }
 }
