@@ -5,7 +5,7 @@
 // "Tiled attention and mixed precision" -- symmetric INT8 with scale max|x|/127 outside
 // the FP16 window; Algorithm 1, per-layer tail).
 //
-// Three launches cover every layer:
+// A decode loop on up to 768 units takes one launch for all of it (evict_unit_kernel); otherwise these cover every layer:
 //   rank_select   one 1024-thread workgroup per unit: float64 scores, radix select of the eviction
 //                 cut-off, ordered survivor list
 //   compact       one workgroup per (unit, plane): in-place, order-preserving gather
@@ -704,12 +704,9 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {   // set bits
 // kShared: the importance is the layer-shared float64 sum in shared_all (see rank_small_kernel).
 // kRandom: the random ranker's key per slot instead of the composite score (rr says how it is drawn).
 template <int T, int E, bool kShared = false, bool kRandom = false>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 && !kShared ? 4 : 1, T == 256 && !kShared ? 4 : 8)))
-void rank_select_reg_kernel(CacheView cv, LayerMask appended,
-                                                            double alpha,
-                                                            int32_t *__restrict__ src_all,
-                                                            int32_t *__restrict__ sel_all,
-                                                            const double *__restrict__ shared_all, RandomRank rr) {
+__device__ __forceinline__ void rank_select_reg_unit(int u, const CacheView &cv, const LayerMask &appended, double alpha,
+                                                     int32_t *src_all, int32_t *sel_all, const double *shared_all,
+                                                     const RandomRank &rr) {
   typedef typename std::conditional<kShared, double, float>::type Imp;   // importance as stored
   constexpr int kRsWaves = T / kWave;
   // width of the first radix pass: 11 bits where a workgroup has the threads to scan 2048 bins
@@ -727,7 +724,6 @@ void rank_select_reg_kernel(CacheView cv, LayerMask appended,
   __shared__ unsigned long long s_prefix, s_kmin[kRsWaves], s_kmax[kRsWaves];
   __shared__ int s_krem, s_done, s_hole[kRsWaves], s_k8[kRsWaves], s_last8[kRsWaves];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int u = blockIdx.x;
   // the kernel arguments of the prologue in one fetch
   asm volatile("" ::"s"(cv.len), "s"(cv.n8), "s"(cv.head8), "s"(cv.budget), "s"(cv.ema), "s"(cv.pos), "s"(cv.B),
                "s"(cv.Hkv), "s"(cv.P), "s"(cv.cap), "s"(cv.cap8), "s"(sel_all), "s"(src_all));
@@ -1026,6 +1022,13 @@ void rank_select_reg_kernel(CacheView cv, LayerMask appended,
   }
 }
 
+template <int T, int E, bool kShared = false, bool kRandom = false>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 && !kShared ? 4 : 1, T == 256 && !kShared ? 4 : 8)))
+void rank_select_reg_kernel(CacheView cv, LayerMask appended, double alpha, int32_t *__restrict__ src_all,
+                            int32_t *__restrict__ sel_all, const double *__restrict__ shared_all, RandomRank rr) {
+  rank_select_reg_unit<T, E, kShared, kRandom>(blockIdx.x, cv, appended, alpha, src_all, sel_all, shared_all, rr);
+}
+
 // ---------------------------------------------------------------------------------------
 // rank_small: grid (U / 4), one wavefront per unit.  Runs first and settles every unit that
 // evicts nothing or at most kSmallE slots -- the steady state of a decode loop, where a unit
@@ -1039,7 +1042,7 @@ constexpr int kSmallE = 4;
 // The end of the small ranking kernels: the survivors' sources and the selection from the e <= kSmallE
 // evicted slots ev (unused entries INT_MAX), known to all of the unit's T threads.
 template <int T>
-__device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t *sel, int32_t *__restrict__ src_all, int n,
+__device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t *sel, int32_t *src_all, int n,
                                              int n8, int nx, int e, int (&ev)[kSmallE], int tid) {
   // evicted slots in slot order
 #pragma unroll
@@ -1206,17 +1209,15 @@ inline bool small_wg(int U, int n_max, bool shared, bool random) {
   return random ? U <= 256 : shared ? U <= 768 && n_max >= 2048 : U <= 768;
 }
 template <bool kShared, bool kRandom = false>
-__global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv, LayerMask appended, double alpha,
-                                                                   const double *__restrict__ shared_all,
-                                                                   int32_t *__restrict__ src_all,
-                                                                   int32_t *__restrict__ sel_all, RandomRank rr) {
+__device__ __forceinline__ void rank_small_wg_unit(int u, const CacheView &cv, const LayerMask &appended, double alpha,
+                                                   const double *shared_all, int32_t *src_all, int32_t *sel_all,
+                                                   const RandomRank &rr) {
   constexpr int kRegs = 16, kWaves = kEvThreads / kWave;
   typedef typename std::conditional<kShared, double, float>::type Imp;   // importance as stored
   __shared__ Imp s_lo[kWaves], s_hi[kWaves];
   __shared__ unsigned long long s_key[2][kWaves];
   __shared__ int s_idx[2][kWaves];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int u = blockIdx.x;
   asm volatile("" ::"s"(cv.len), "s"(cv.n8), "s"(cv.head8), "s"(cv.budget), "s"(cv.ema), "s"(cv.pos), "s"(cv.B),
                "s"(cv.Hkv), "s"(cv.P), "s"(cv.cap), "s"(cv.cap8), "s"(sel_all), "s"(src_all));
   const int UPL = cv.B * cv.Hkv;
@@ -1343,6 +1344,14 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv,
   finish_small<kEvThreads>(cv, u, sel, src_all, n, n8, nx, e, ev, tid);
 }
 
+template <bool kShared, bool kRandom = false>
+__global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv, LayerMask appended, double alpha,
+                                                                   const double *__restrict__ shared_all,
+                                                                   int32_t *__restrict__ src_all,
+                                                                   int32_t *__restrict__ sel_all, RandomRank rr) {
+  rank_small_wg_unit<kShared, kRandom>(blockIdx.x, cv, appended, alpha, shared_all, src_all, sel_all, rr);
+}
+
 // ---------------------------------------------------------------------------------------
 // compact: grid (U, 2) or (U, 5), 256 threads.  Survivor j (new slot number) comes from old slot
 // src[j] >= j.  Left shift (heads stay): a workgroup walks its plane front to back in chunks
@@ -1366,7 +1375,7 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_wg_kernel(CacheView cv,
 // drow(j) that of new slot j.  Loads are grouped (source slots of all passes, then all rows of
 // both planes), so a chunk costs two memory round trips; lanes past the range issue nothing.
 template <int ROWB, typename SrcRow, typename DstRow>
-__device__ __forceinline__ void move_rows(uint8_t *base_ptr, uint8_t *base2, const int32_t *__restrict__ src,
+__device__ __forceinline__ void move_rows(uint8_t *base_ptr, uint8_t *base2, const int32_t *src,
                                           int lo, int hi, bool right, SrcRow srow, DstRow drow) {
   constexpr int LPR = ROWB / 16, RPP = kEvThreads / LPR, PASSES = 4;
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
@@ -1413,14 +1422,11 @@ __device__ __forceinline__ void clear_tagged_if_asked(const CacheView &cv) {
 // instance without it for the step that follows a prompt load, where every unit moves hundreds of
 // rows and the extra path only costs the chunked walk registers and schedule.
 template <int D, bool kSmall>
-__global__ __launch_bounds__(kEvThreads) void compact_kernel(CacheView cv,
-                                                             const int32_t *__restrict__ src_all,
-                                                             const int32_t *__restrict__ sel_all, int paired) {
-  const int u = blockIdx.x, tid = threadIdx.x;
-  clear_tagged_if_asked(cv);
+__device__ __forceinline__ void compact_unit(int u, int y, const CacheView &cv, const int32_t *src_all, const int32_t *sel_all,
+                                             int paired) {
+  const int tid = threadIdx.x;
   // what this workgroup moves: the payload rows of the ring the holes lie in (K, V or both),
   // the per-slot planes, the FP16 rows of a mixed cache (K, V or both)
-  const int y = blockIdx.y;
   const bool do_k = paired ? y == 0 : (y == 0 || y == 3), do_v = paired ? y == 0 : (y == 1 || y == 4);
   const bool do_meta = paired ? y == 1 : y == 2;
   const bool late16 = paired ? y == 1 : y >= 3;     // FP16 rows of a mixed cache
@@ -1564,6 +1570,13 @@ __global__ __launch_bounds__(kEvThreads) void compact_kernel(CacheView cv,
   if (!fp16_only && late16 && evicted != e8) move_fp16_rows(paired || y == 3, paired || y == 4);
 }
 
+template <int D, bool kSmall>
+__global__ __launch_bounds__(kEvThreads) void compact_kernel(CacheView cv, const int32_t *__restrict__ src_all,
+                                                             const int32_t *__restrict__ sel_all, int paired) {
+  clear_tagged_if_asked(cv);
+  compact_unit<D, kSmall>(blockIdx.x, blockIdx.y, cv, src_all, sel_all, paired);
+}
+
 // ---------------------------------------------------------------------------------------
 // Paged layout: the compaction is an edit of the unit's block table ("Compatibility with
 // serving systems": evicting whole blocks frees them without a gather).  Grid (U / 4), one
@@ -1619,29 +1632,27 @@ __global__ __launch_bounds__(kEvThreads) void compact_paged_kernel(CacheView cv,
 // its wavefronts share the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction
 // and a store (16 tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in
 // turn, 18.5 us; 4 tokens 10.5 and 7.3).
-template <int D, bool kWide = false>
-__global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
-                                                            const int32_t *__restrict__ sel_all, int U,
-                                                            LayerMask appended, unsigned attend_launches,
-                                                            unsigned conf_launches) {
-  if (blockIdx.x == 0 && threadIdx.x < kWave) {
-    for (int l = threadIdx.x; l < cv.L; l += kWave)
-      if (const int c = appended.get(l)) cv.ctl[kCtlPos + l] += (unsigned)c;
-    if (threadIdx.x == 0) {
-      if (cv.ctl[kCtlClear]) {
-        cv.ctl[kCtlTag] = cv.ctl[kCtlConfTag] = cv.ctl[kCtlClear] = 0u;
-      } else {
-        const unsigned t = cv.ctl[kCtlTag] + attend_launches, c = cv.ctl[kCtlConfTag] + conf_launches;
-        cv.ctl[kCtlTag] = t;
-        cv.ctl[kCtlConfTag] = c;
-        if (t > kTagRestart || c > kTagRestart) cv.ctl[kCtlClear] = 1u;
-      }
+// The step state, by the first wavefront of the launch.
+__device__ __forceinline__ void commit_ctl(const CacheView &cv, const LayerMask &appended, unsigned attend_launches,
+                                           unsigned conf_launches) {
+  for (int l = threadIdx.x; l < cv.L; l += kWave)
+    if (const int c = appended.get(l)) cv.ctl[kCtlPos + l] += (unsigned)c;
+  if (threadIdx.x == 0) {
+    if (cv.ctl[kCtlClear]) {
+      cv.ctl[kCtlTag] = cv.ctl[kCtlConfTag] = cv.ctl[kCtlClear] = 0u;
+    } else {
+      const unsigned t = cv.ctl[kCtlTag] + attend_launches, c = cv.ctl[kCtlConfTag] + conf_launches;
+      cv.ctl[kCtlTag] = t;
+      cv.ctl[kCtlConfTag] = c;
+      if (t > kTagRestart || c > kTagRestart) cv.ctl[kCtlClear] = 1u;
     }
   }
+}
+
+template <int D, bool kWide = false>
+__device__ __forceinline__ void demote_unit(int u, const CacheView &cv, const int32_t *sel_all) {
   constexpr int kWaves = kEvThreads / kWave;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int u = kWide ? blockIdx.x : blockIdx.x * kWaves + w;
-  if (u >= U) return;
   const int32_t *sel = sel_all + (size_t)u * kSelInts;
   const int n_new = sel[0], n8_new = sel[1], h8 = sel[6];   // slot-anchored ring head after the compaction
   // an FP16-only cache that closed its holes from the front has advanced its FP16 ring too
@@ -1682,6 +1693,40 @@ __global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
   }
 }
 
+template <int D, bool kWide = false>
+__global__ __launch_bounds__(kEvThreads) void demote_kernel(CacheView cv,
+                                                            const int32_t *__restrict__ sel_all, int U,
+                                                            LayerMask appended, unsigned attend_launches,
+                                                            unsigned conf_launches) {
+  if (blockIdx.x == 0 && threadIdx.x < kWave) commit_ctl(cv, appended, attend_launches, conf_launches);
+  const int u = kWide ? blockIdx.x : blockIdx.x * (kEvThreads / kWave) + (threadIdx.x >> 6);
+  if (u < U) demote_unit<D, kWide>(u, cv, sel_all);
+}
+
+// ---------------------------------------------------------------------------------------
+// The whole call in one launch: grid (U), a workgroup per unit, which ranks, closes the holes, demotes and commits (the parts
+// above, one after the other; they hand over through the unit's own words in memory).
+// A unit of a decode loop costs the four launches little more than their own starts and first trips to memory.
+// ---------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void evict_unit_kernel(CacheView cv, LayerMask appended, double alpha, int32_t *src_all, int32_t *sel_all,
+                       unsigned attend_launches, unsigned conf_launches, RandomRank rr) {
+  const int u = blockIdx.x;
+  // (the first workgroup, which commits the flag, clears all of the words itself: once in 2^32 launches)
+  if (u == 0 && cv.ctl[kCtlClear] != 0u)
+    for (size_t i = threadIdx.x; i < cv.n_tagged; i += kEvThreads) cv.tagged[i] = 0ull;
+  rank_small_wg_unit<false>(u, cv, appended, alpha, nullptr, src_all, sel_all, rr);
+  __syncthreads();
+  rank_select_reg_unit<256, 20>(u, cv, appended, alpha, src_all, sel_all, nullptr, rr);   // (leaves at once where that settled it)
+  __syncthreads();
+  compact_unit<D, true>(u, 0, cv, src_all, sel_all, 1);
+  compact_unit<D, true>(u, 1, cv, src_all, sel_all, 1);
+  __syncthreads();
+  if (u == 0 && threadIdx.x < kWave) commit_ctl(cv, appended, attend_launches, conf_launches);
+  demote_unit<D, true>(u, cv, sel_all);
+}
+
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
@@ -1699,6 +1744,19 @@ hipError_t launch_load_prefill(const CacheView &cv, int layer, const __half *k16
   return hipGetLastError();
 }
 
+// Calls that one launch serves: the plain ranker on a contiguous cache, as many units as rank with a workgroup each
+// (small_wg: three on every CU), units the register form of the general ranking holds, and not the step behind a prompt, whose
+// long moves are spread over a workgroup per plane.  Whole calls in one launch against four, us: 64 units of 130 slots 12.8
+// against 19.1, 144 of 515 (FP16-only, 64 channels) 12.9 and 18.2, 256 of 1003 18.4 and 23.9, 512 of 2050 26.0 and 34.1, 768 of
+// 5000 45.0 and 63.7, 768 of 1003 losing 16 tokens 48.6 and 58.8.  Beyond 768 units the workgroups take turns: 1024 units
+// 0.81 to 1.11 times as long as four launches, 2048 1.06 to 1.23, 8192 1.3 to 2.5.
+static bool evict_in_one(const CacheView &cv, const RankOptions &opt, int U, int n_max, int after_prompt) {
+  if (const char *e = getenv("CONF_KV_EVICT_ONE"))             // test hook: 0 takes the separate launches
+    if (atoi(e) == 0) return false;
+  return !cv.page_lg && opt.page <= 1 && !opt.shared && !opt.random && !after_prompt && small_wg(U, n_max, false, false) &&
+         n_max <= 256 * 20;
+}
+
 hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, double alpha,
                                 const RankOptions &opt, double *score, int32_t *src, int32_t *sel,
                                 int n_max, unsigned attend_launches, unsigned conf_launches, int after_prompt,
@@ -1711,6 +1769,16 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
   rr.layer_scope = opt.shared != nullptr;
   rr.seed = opt.seed;
   const bool shared_imp = opt.shared && !opt.random;          // the ranking reads the summed importance
+  // a decode loop on few units: one launch
+  if (evict_in_one(cv, opt, U, n_max, after_prompt)) {
+    if (cv.D == 64)
+      hipLaunchKernelGGL(evict_unit_kernel<64>, dim3(U), dim3(kEvThreads), 0, stream, cv, appended, alpha, src, sel,
+                         attend_launches, conf_launches, rr);
+    else
+      hipLaunchKernelGGL(evict_unit_kernel<128>, dim3(U), dim3(kEvThreads), 0, stream, cv, appended, alpha, src, sel,
+                         attend_launches, conf_launches, rr);
+    return hipGetLastError();
+  }
   if (opt.page > 1) {
     // whole pages: the general kernel, behind the one-wavefront kernel that settles the units
     // that evict nothing (with pages of g slots a unit evicts once in g steps)

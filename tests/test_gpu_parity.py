@@ -174,6 +174,53 @@ def test_codes_at_half_way_quotients(lib, torch_cuda, D, scales):
     kv.close()
 
 
+@pytest.mark.parametrize("L,B,H,G,D,W,N,tight,tq", [
+    (4, 2, 2, 4, 128, 20, 90, 90, 1),       # one token over the budget
+    (3, 1, 3, 1, 64, -1, 200, 120, 1),      # FP16-only, falling to a tight budget: the general ranking, both shifts
+    (2, 2, 2, 2, 128, 0, 130, 125, 3),      # a window of 0, three tokens, four or more evictions
+    (2, 1, 2, 4, 128, 33, 700, 400, 16),    # sixteen tokens, hundreds of evictions: long moves
+    (12, 8, 8, 1, 64, 16, 70, 69, 1),       # 768 units, the last count that one launch takes
+])
+def test_evict_in_one_launch_matches_the_separate_ones(lib, torch_cuda, monkeypatch, L, B, H, G, D, W, N, tight, tq):
+    """Ranking, compaction, demotion and commit in one launch leave the state that the separate launches leave, bit for bit."""
+    torch = torch_cuda
+    say(f"evict in one launch U={L * B * H} D={D} W={W} N={N} tq={tq}")
+    cap = (N + 2 * tq + 63) // 64 * 64
+    kvs = [_mk(lib, n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap, vocab=1000,
+               protected_window=8, n_tight=[tight] * L, n_loose=[N] * L, max_chunk=tq if tq > 1 else 0) for _ in range(2)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + W)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda").half()
+    for l in range(L):
+        k, v = rn(B, H, N, D), rn(B, H, N, D)
+        e = torch.rand(B, H, N, generator=g, device="cuda")
+        for kv in kvs:
+            kv.load_prefill(l, k, v, e)
+    toks = (B,) if tq == 1 else (B, tq)
+    for t in range(5):
+        logits = torch.randn(B, 1000, generator=g, device="cuda")
+        if t % 2:
+            logits[:, 7] += 30                                  # confident: the tight budget
+        args = [(rn(*toks, G * H, D), rn(*toks, H, D), rn(*toks, H, D)) for _ in range(L)]
+        for one, kv in enumerate(kvs):
+            out = torch.empty(*toks, G * H, D, dtype=torch.float16, device="cuda")
+            for l in range(L):
+                (kv.attend_chunk if tq > 1 else kv.attend)(l, *args[l], out)
+            kv.step(logits, torch.zeros(B, device="cuda"), torch.zeros(B, dtype=torch.uint8, device="cuda"))
+            monkeypatch.setenv("CONF_KV_EVICT_ONE", str(one))
+            kv.evict_compact()
+        for l, b, h in {(0, 0, 0), (L - 1, B - 1, H - 1), (L // 2, B // 2, H // 2), (0, B - 1, 0)}:
+            a, c = (kv.export(l, b, h) for kv in kvs)
+            assert a["n"] == c["n"]
+            for name, x in a.items():
+                if isinstance(x, np.ndarray):
+                    assert np.array_equal(x.view(np.uint8), c[name].view(np.uint8)), f"step {t} unit {(l, b, h)}: {name}"
+    a, c = (kv.counters() for kv in kvs)
+    assert (a.evicted, a.demoted, a.device_errors) == (c.evicted, c.demoted, 0)
+    for kv in kvs:
+        kv.close()
+
+
 # ------------------------------------------------------------------ attention + mass EMA
 
 def _attend_case(lib, torch, D, G, H, B, T0, W, splits, seed, scale_q=1.0, two_launch=False,
