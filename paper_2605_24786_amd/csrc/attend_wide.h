@@ -79,10 +79,20 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   int t16 = lane & 15, g4 = lane >> 4;
   const int c8 = lane & 7, r8 = lane >> 3;
   const int c16 = lane & 15, r4 = lane >> 4;
+  // Query rows as a matrix-core operand: lane (row t16, channels 32 g4 + 8 s + [0, 8)).  Requested with the counters, which
+  // their place does not depend on.  Padding rows repeat the last token's: nothing reads what comes of them.
+  half8_t qa[2][4];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int row = (2 * rg + r) * 16 + t16, tok = row / gq, head = row - tok * gq;
+    const __half *src = a.q + ((((size_t)blockIdx.z * tq + min(tok, tq - 1)) * cv.Hkv + kv_head_index(a)) * gq + head) * D + g4 * 32;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qa[r][s] = __builtin_bit_cast(half8_t, *(const confkv_v4i *)(src + 8 * s));
+  }
   const Slice sl = make_slice(cv, a, ns, 0x7fffffff, &w_words);
 
   // a lane's rows: query t16 of each of the wavefront's two blocks.  The row of token t sees slots below
-  // n - tq + t + 1; padding rows carry a zero query, see everything and weigh nothing.
+  // n - tq + t + 1; padding rows see everything and weigh nothing.
   int seen[2];
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
@@ -158,24 +168,10 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
   };
 
-  // query rows as a matrix-core operand: lane (row t16, channels 32 g4 + 8 s + [0, 8))
-  auto load_rows = [&](int block, half8_t (&qf)[4]) {
-    const int row = block * 16 + t16, tok = row / gq, head = row - tok * gq;
-    const __half *src = a.q + ((((size_t)sl.b * tq + min(tok, tq - 1)) * cv.Hkv + sl.g) * gq + head) * D + g4 * 32;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const confkv_v4i v = *(const confkv_v4i *)(src + 8 * s);
-      qf[s] = __builtin_bit_cast(half8_t, tok < tq ? v : confkv_v4i{0, 0, 0, 0});
-    }
-  };
-
   // ---------------- pass 1: online softmax and output per row ----------------
   TileRegs tr;
   auto load_item = [&](int it) { load_item_rows<D, true, false, true>(cv, ts, sl, lane, it, std::false_type{}, tr); };
   if (w < nitems) load_item(w);
-  half8_t qa[2][4];
-  load_rows(2 * rg, qa[0]);
-  load_rows(2 * rg + 1, qa[1]);
   floatx4_t O[2][8];                                       // [block][channel group]: channels 16 nt + 4 g4 + [0, 4) of query t16
   float m[2], l[2];
 #pragma unroll
@@ -255,6 +251,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       }
   };
 
+  __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0): queries and first rows, so that no wait for them is in the loop
   for (int sup = 0; sup < nsup; ++sup) {
     const int mine = sup * kAttWaves + w;
     if (sup > 0) __syncthreads();                      // everybody has left the previous eight tiles
@@ -363,7 +360,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       st_tagged(&a.part_ml[(row0 + tid) * 2 + 1], tag, L);
     } else {
       const double inv = recip_pos((double)L);
-      Mrow[tid] = M;
+      Mrow[tid] = tok < tq ? M : 0.f;                      // (the second pass has zero queries in padding rows)
       Irow[tid] = (float)inv;
       Frow[tid] = tok < tq ? (float)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - tid / gq))) : 0.f;
     }
@@ -470,7 +467,7 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
         pml[(s * R + tid) * 2] = es;
       }
       const double inv = recip_pos(L);
-      Mrow[tid] = M;
+      Mrow[tid] = tid / gq < tq ? M : 0.f;
       Irow[tid] = (float)inv;
       Frow[tid] = tid / gq < tq ? (float)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - tid / gq))) : 0.f;
     }
