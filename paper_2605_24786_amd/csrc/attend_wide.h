@@ -18,9 +18,9 @@
 // slot's column over the rows (weights lambda^(tq-1-token)) in its own registers and updates the
 // EMA: no barrier, no LDS but the rows' statistics.  Key bytes are therefore read twice, value bytes once.
 //
-// 64 rows against 64 units of 2064 slots in four splits (16 tokens of 4 heads): 36 us per launch in the kernel trace, of which
-// 18 for the first pass -- 5 until the first tiles are in LDS, then a round of eight in 3.5 to 5 -- 4.5 for the merge and
-// publishing, 5 for the exchange and 7 for the second pass; one sequence of 30 000 slots 79 us.  It uses all 256 registers, and
+// 64 rows against 64 units of 2064 slots in four splits (16 tokens of 4 heads): 35.5 us per launch in the kernel trace, of which
+// 17 for the first pass -- 5 until the first tiles are in LDS, then a round of eight in 3.5 to 5 -- 4.5 for the merge and
+// publishing, 4.5 for the exchange and 8 for the second pass; one sequence of 30 000 slots 79 us.  It uses all 256 registers, and
 // what must outlive the first pass is formed anew behind it: with 7 to 10 of them spilled the launch was 40 us.  With sixteen
 // rows per wavefront, the scores the other way round, value codes converted by every reader and the second pass through
 // the same tiles and barriers it was 50 us (and 203).  Slower too: the second pass's keys requested ahead of the exchange, whose
