@@ -965,6 +965,9 @@ __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const Atten
 template <int D, int G, bool kSpill = false>
 __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns,
                                                              int S) {
+  // (the unit's counters are requested first, from arguments that arrive in registers: see attend_mfma_kernel)
+  const int w_words = (((threadIdx.x & 3) == 0 ? w_len : (threadIdx.x & 3) == 1 ? w_n8 : (threadIdx.x & 3) == 2 ? w_h16 : w_h8))
+      [w_unit0 + blockIdx.z * w_hkv + (w_kvm ? blockIdx.x : blockIdx.y)];
   const AttendLaunch a = resolve_launch(cv, a_in);
   constexpr int NP = kAttWaves;
   extern __shared__ __align__(16) float smem[];
@@ -976,7 +979,17 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   float *gm = wl + NP * G;                      // [G] global maximum
   double *ginv = (double *)(gm + G + (G & 1));  // [2 G]: 1 / global normaliser, the same times the row's mass weight
 
-  const Slice sl = make_slice(cv, a, ns, S);
+  // the queries with them: their place does not depend on the counters
+  constexpr int LPT = D / 16;
+  const int c = (threadIdx.x & 63) % LPT;
+  int4 qraw[G][2];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const int4 *qp = (const int4 *)(a.q + ((size_t)(blockIdx.z * cv.Hkv + kv_head_index(a)) * G + h) * D + c * 16);
+    qraw[h][0] = qp[0];
+    qraw[h][1] = qp[1];
+  }
+  const Slice sl = make_slice(cv, a, ns, S, &w_words);
   append_new_token<D>(cv, a, sl, ns, 1);
   float ema_old[kEmaAhead];
   if (!kSpill) request_ema<false>(cv, sl, ema_old);
@@ -984,12 +997,11 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(const int32_t *w_le
   Stream<G> st;
   st.reset();
   float qf[G][16];
-  load_q_slices<D, G>(cv, a, sl, qf);
+#pragma unroll
+  for (int h = 0; h < G; ++h) unpack_h16x16(qraw[h][0], qraw[h][1], qf[h]);
   if (cv.chan) {
     // per-channel scales: fold the K scales of this lane's 16 channels into the query for the
     // INT8 slots, scale the accumulated INT8 output by the V scales, reload the plain query
-    constexpr int LPT = D / 16;
-    const int c = (threadIdx.x & 63) % LPT;
     float sc[16];
     const int4 *kp = (const int4 *)(cv.ks + (size_t)sl.u * D + c * 16);
     unpack_h16x16(kp[0], kp[1], sc);
