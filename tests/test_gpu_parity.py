@@ -332,6 +332,27 @@ def test_new_token_at_every_place_of_a_tile(lib, torch_cuda, monkeypatch, D, G, 
     _attend_case(lib, torch, D, G, 1, 1, T0, W, splits, seed=T0 + G, scale_mode=scales, two_launch=two_launch, steps=36)
 
 
+def test_single_split_output_is_rounded_once(lib, torch_cuda, monkeypatch):
+    """9001 slots of equal score whose values in a channel are k or k + 1, all sums exact: the mean k + c / 9001 lies
+    1/18002 from the fp16 tie k + 1/2, closer than half an fp32 step (2^-14), so only a rounding straight to fp16 is right."""
+    torch = torch_cuda
+    say("single split, means next to fp16 ties")
+    n, D = 9001, 64
+    monkeypatch.setenv("CONF_KV_SPLITS", "1")
+    kv = _mk(lib, n_q_heads=1, n_kv_heads=1, head_dim=D, fp16_window=-1, capacity=9024, n_tight=[9010], n_loose=[9010])
+    rng = np.random.default_rng(11)
+    k = rng.integers(1024, 2**24 // n - 1, D)
+    up = rng.integers(0, 2, D)                              # 4500 or 4501 of the values are k + 1
+    v = np.stack([rng.permutation(np.arange(n) < n // 2 + u) for u in up], axis=1) + k
+    v = torch.from_numpy(v.astype(np.float16)[None, None]).cuda()
+    zero, out = (torch.zeros(1, 1, D, dtype=torch.float16, device="cuda") for _ in range(2))
+    kv.load_prefill(0, torch.zeros_like(v[:, :, 1:]), v[:, :, 1:].contiguous())
+    assert kv.attend_splits(0) == 1
+    kv.attend(0, zero, zero, v[:, :, 0].contiguous(), out)
+    assert np.array_equal(out.cpu().numpy()[0, 0].astype(np.int64), k + up)
+    kv.close()
+
+
 @pytest.mark.parametrize("D,G,H,B,T0,W,splits", [
     (128, 4, 2, 2, 700, 32, 3), (128, 4, 1, 1, 300, 16, 1), (64, 1, 3, 1, 333, -1, 4),
     (128, 5, 2, 1, 1000, 64, 7), (64, 2, 2, 2, 150, 0, 2), (128, 8, 1, 1, 520, 200, 5),
