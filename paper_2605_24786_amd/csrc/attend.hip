@@ -1229,16 +1229,18 @@ __device__ __forceinline__ void load_item_rows(const CacheView &cv, const TileSo
     if constexpr (kPaged) return (unsigned)((sl.tab[i >> cv.page_lg] << cv.page_lg) | (i & ((1 << cv.page_lg) - 1)));
     else return (unsigned)ring_row_u(sl.h8, i, t.cap8);
   };
-  // byte offsets of the lane's four rows from the (wavefront-uniform) bases; the rows of call tokens apart
+  // offsets of the lane's four rows from the (wavefront-uniform) bases, in bytes (see reload_far_item), kRows in pieces of
+  // sixteen bytes, which reach everywhere; the rows of call tokens apart
+  constexpr unsigned U = kRows ? 16 : 1;
   const unsigned r = DR == 128 && run ? 0u : (unsigned)lane >> (fp16 ? 4 : 3);
-  const unsigned col = (unsigned)(lane & (fp16 ? DR / 8 - 1 : DR / 16 - 1)) * 16u;
+  const unsigned col = (unsigned)(lane & (fp16 ? DR / 8 - 1 : DR / 16 - 1)) * (16u / U);
   unsigned o[4], so = row0 + (unsigned)(lane & 31);
   int fresh[kRows ? 4 : 1];
   if (run) {
     kb += (size_t)row0 * row_bytes;
     vb += (size_t)row0 * row_bytes;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = (DR == 128 ? (unsigned)lane * 16u : r * row_bytes + col) + q * (8 * DR);
+    for (int q = 0; q < 4; ++q) o[q] = (DR == 128 ? (unsigned)lane * (16u / U) : r * (row_bytes / U) + col) + q * (8 * DR / U);
 #pragma unroll
     for (int q = 0; q < (kRows ? 4 : 1); ++q) fresh[q] = -1;
   } else {
@@ -1248,7 +1250,7 @@ __device__ __forceinline__ void load_item_rows(const CacheView &cv, const TileSo
       unsigned row;
       if (kPaged && !fp16) row = row8(slot);
       else row = (unsigned)ring_row_u(head, slot, cap);
-      o[q] = row * row_bytes + col;
+      o[q] = row * (row_bytes / U) + col;
       if constexpr (kRows) fresh[q] = fp16 ? slot - t.first_new : -1;
     }
     if (!fp16) so = row8(min(base + (lane & 31), end - 1));
@@ -1257,9 +1259,9 @@ __device__ __forceinline__ void load_item_rows(const CacheView &cv, const TileSo
     const int8_t *pk[4], *pv[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const unsigned fo = (unsigned)max(fresh[q], 0) * t.tok + col;
-      pk[q] = fresh[q] >= 0 ? t.kn + fo : kb + o[q];
-      pv[q] = fresh[q] >= 0 ? t.vn + fo : vb + o[q];
+      const size_t off = (size_t)(fresh[q] >= 0 ? (unsigned)fresh[q] * (t.tok / U) + col : o[q]) * U;
+      pk[q] = (fresh[q] >= 0 ? t.kn : kb) + off;
+      pv[q] = (fresh[q] >= 0 ? t.vn : vb) + off;
     }
     tr.k0 = ld_stream16(pk[0]); tr.v0 = ld_stream16(pv[0]);
     tr.k1 = ld_stream16(pk[1]); tr.v1 = ld_stream16(pv[1]);
@@ -1274,6 +1276,26 @@ __device__ __forceinline__ void load_item_rows(const CacheView &cv, const TileSo
   // (an FP16 tile has no scales: its lanes read anything, the tile's own first bytes)
   if (kScales && !known_fp16)
     tr.sc = ld_stream(fp16 ? (const unsigned short *)kb + lane : (lane < 32 ? t.ks : t.vs) + so);
+}
+
+// Rows of an FP16 ring of more than 4 GiB are out of reach of 32-bit offsets from the plane: there an item that is no run of
+// the ring (all others count from their own first row) is requested again, by full addresses, where it is used.  (INT8 rows
+// take half the room.)
+template <int DR>
+__device__ __forceinline__ void reload_far_item(const TileSource &t, const Slice &sl, int lane, int it, TileRegs &tr) {
+  if (__builtin_expect((unsigned)t.cap16 <= 0x80000000u / DR, 1)) return;
+  const int base = sl.lo16 + 16 * (it - t.ntiles), head = sl.h16 - sl.n8;
+  if (base + 16 <= sl.hi16 && ring_row_u(head, base, t.cap16) + 16 <= t.cap16) return;
+  size_t o[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    o[q] = (size_t)ring_row_u(head, min(base + (lane >> 4) + 4 * q, sl.hi16 - 1), t.cap16) * (2 * DR) + (lane & (DR / 8 - 1)) * 16;
+  tr.k0 = ld_stream16(t.k16 + o[0]); tr.v0 = ld_stream16(t.v16 + o[0]);
+  tr.k1 = ld_stream16(t.k16 + o[1]); tr.v1 = ld_stream16(t.v16 + o[1]);
+  tr.k2 = ld_stream16(t.k16 + o[2]); tr.v2 = ld_stream16(t.v16 + o[2]);
+  tr.k3 = ld_stream16(t.k16 + o[3]); tr.v3 = ld_stream16(t.v16 + o[3]);
+  // (awaited here: with these loads last in line the others would wait for all that was requested after their rows)
+  __builtin_amdgcn_s_waitcnt(0x0f70);
 }
 
 // kChan: the INT8 scales are per (unit, channel).  The K scales are folded into the query (a
@@ -1662,6 +1684,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   if constexpr (!kChan) asm volatile("" ::"v"(tr.sc));
   for (; item < nitems; item += kAttWaves) {
     // ---- an FP16 tile: 16 slots ----
+    if constexpr (!kRows) reload_far_item<DR>(ts, sl, lane, item, tr);
     *(int4 *)(Kt + (r4)*kKRow16 + c16 * 16) = tr.k0;
     *(int4 *)(Kt + (4 + r4) * kKRow16 + c16 * 16) = tr.k1;
     *(int4 *)(Kt + (8 + r4) * kKRow16 + c16 * 16) = tr.k2;

@@ -332,6 +332,40 @@ def test_new_token_at_every_place_of_a_tile(lib, torch_cuda, monkeypatch, D, G, 
     _attend_case(lib, torch, D, G, 1, 1, T0, W, splits, seed=T0 + G, scale_mode=scales, two_launch=two_launch, steps=36)
 
 
+@pytest.mark.parametrize("D,G,tq,two_launch", [(128, 4, 1, False), (128, 4, 1, True), (64, 2, 1, False), (128, 2, 4, False),
+                                               (128, 4, 16, False)])
+@pytest.mark.parametrize("first", ["4 GiB", "ring end"])
+def test_fp16_rows_beyond_four_gib(lib, torch_cuda, monkeypatch, D, G, tq, two_launch, first):
+    """A unit whose FP16 ring takes more than 4 GiB per plane, with its rows on both sides of that and of the ring's end."""
+    torch = torch_cuda
+    say(f"FP16 rows beyond 4 GiB: D={D} G={G} tq={tq} two_launch={two_launch} first row at {first}")
+    if two_launch:
+        monkeypatch.setenv("CONF_KV_TWO_LAUNCH", "1")
+    cap = 2**32 // (2 * D) + 64
+    kv = _mk(lib, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=-1, capacity=cap, n_tight=[100], n_loose=[100],
+             max_chunk=tq if tq > 1 else 0)
+    assert kv.attend_splits(0) == (1001 if two_launch else 1)
+    head = cap - (64 + 8 if first == "4 GiB" else 21)
+    for at in (512, 768):                                    # head16 and head8 of the only unit
+        kv.state[at:at + 4].view(torch.int32).fill_(head)
+    rng = np.random.default_rng(D + G + tq)
+    K, V = np.zeros((0, D)), np.zeros((0, D))
+    for t in range(48 // tq):
+        q, k, v = (rng.standard_normal((1, tq, heads, D)).astype(np.float16) for heads in (G, 1, 1))
+        out = torch.zeros(1, tq, G, D, dtype=torch.float16, device="cuda")
+        (kv.attend if tq == 1 else kv.attend_chunk)(0, *(torch.from_numpy(x).cuda() for x in (q, k, v)), out)
+        kv.evict_compact()
+        for i in range(tq):
+            K, V = np.vstack([K, k[0, i]]), np.vstack([V, v[0, i]])
+            p = np.exp(q[0, i].astype(np.float64) @ K.T.astype(np.float64) / math.sqrt(D))
+            ref = (p / p.sum(axis=1, keepdims=True)) @ V
+            np.testing.assert_allclose(out[0, i].cpu().numpy(), ref, rtol=2e-3, atol=1e-3, err_msg=f"token {t * tq + i}")
+    assert kv.lengths()[0][0, 0] == K.shape[0] and kv.counters().device_errors == 0
+    kv.close()
+    del kv, out
+    torch.cuda.empty_cache()
+
+
 def test_single_split_output_is_rounded_once(lib, torch_cuda, monkeypatch):
     """9001 slots of equal score whose values in a channel are k or k + 1, all sums exact: the mean k + c / 9001 lies
     1/18002 from the fp16 tie k + 1/2, closer than half an fp32 step (2^-14), so only a rounding straight to fp16 is right."""
