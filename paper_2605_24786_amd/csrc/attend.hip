@@ -171,10 +171,10 @@ struct Slice {
   __device__ __forceinline__ int slot_of(int t) const { return t < cnt8 ? lo8 + t : lo16 + (t - cnt8); }
 };
 
-// x / ns by the launch's multiplier ceil(2^32 / ns) (0: a single split); exact while x * ns < 2^32, and slots
-// are far fewer than 2^25.  Scalar arithmetic throughout: nothing of a slice depends on the lane.
+// x / ns for any slot number, by the launch's multiplier and shift (0: a single split).  Scalar arithmetic throughout:
+// nothing of a slice depends on the lane.
 __device__ __forceinline__ unsigned div_splits(const AttendLaunch &a, unsigned x) {
-  return a.ns_magic ? __umulhi(x, a.ns_magic) : x;
+  return a.ns_magic ? __umulhi(x, a.ns_magic) >> a.ns_shift : x;
 }
 // floor(x * j / ns) for x = q * ns + r
 __device__ __forceinline__ int share_cut(const AttendLaunch &a, unsigned q, unsigned r, int j) {
@@ -1361,7 +1361,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   // than piecemeal between the dependent loads below
   asm volatile("" ::"s"(cv.k8), "s"(cv.v8), "s"(cv.ks), "s"(cv.vs), "s"(cv.k16), "s"(cv.v16), "s"(cv.len),
                "s"(cv.n8), "s"(cv.head16), "s"(cv.head8), "s"(cv.cap8), "s"(cv.cap16), "s"(cv.Hkv), "s"(cv.B),
-               "s"(a.layer), "s"(a.tq), "s"(a.observe_first), "s"(a.q), "s"(a.knew), "s"(a.vnew), "s"(a.ns_magic), "s"(ns));
+               "s"(a.layer), "s"(a.tq), "s"(a.observe_first), "s"(a.q), "s"(a.knew), "s"(a.vnew), "s"(a.ns_magic), "s"(a.ns_shift), "s"(ns));
   const int t16 = lane & 15, g4 = lane >> 4;    // MFMA operand coordinates of this lane
   // Query operand of the score contraction; k-step s covers channels g4*32 + 8s + [0,8), matching
   // the K bytes this lane reads from the tile below.  Rows past the heads of a group repeat the
@@ -2097,11 +2097,20 @@ size_t attend_spill_floats(int units_per_layer, int G, int cap) {
   return (size_t)units_per_layer * G * (2 * (size_t)cap + (size_t)kAttendMaxSplits * 291);
 }
 
+// With k = ceil(log2 ns) and the multiplier (2^(31 + k) + e) / ns, e < ns <= 2^k, the quotient before rounding down is x / ns plus
+// x e / (ns 2^(31 + k)), which is below 1 / ns for x < 2^31.
+unsigned split_divisor(int ns, int *shift) {
+  int k = 1;
+  while ((1 << k) < ns) ++k;
+  *shift = k - 1;
+  return (unsigned)((((unsigned long long)1 << (31 + k)) + ns - 1) / ns);
+}
+
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const AttendPlan &plan,
                          hipStream_t stream) {
   AttendLaunch a = a_in;
   a.gq_mul = 65536 / std::max(1, a.gq) + 1;
-  a.ns_magic = plan.splits > 1 ? 0xFFFFFFFFu / (unsigned)plan.splits + 1u : 0u;
+  a.ns_magic = plan.splits > 1 ? split_divisor(plan.splits, &a.ns_shift) : 0u;
   if (plan.two_launch || !plan.mfma) a.dbg = nullptr;      // only the single matrix-core kernel is traced
   const dim3 grid = a.kv_major ? dim3(cv.Hkv, plan.splits, cv.B) : dim3(plan.splits, cv.Hkv, cv.B);
   if (plan.two_launch) {

@@ -51,7 +51,8 @@ struct AttendLaunch {
                            // cv.ctl: the sum tags the words the launch publishes (never 0, never reused)
   int spin_limit;          // polls before a wait for the other splits gives up (device error)
   int max_splits;
-  unsigned ns_magic;       // ceil(2^32 / splits), 0 for one split: the kernels' division by the split count
+  unsigned ns_magic;       // the kernels' division by the split count (split_divisor), 0 for one split
+  int ns_shift;
   float sm_scale, ema_decay;
   double mass_gain;        // weight of the step's mass in the EMA update
   unsigned tag_base;       // filled in by the kernels from cv.ctl
@@ -71,6 +72,8 @@ struct AttendLaunch {
 };
 constexpr int kAttendMaxSplits = 64;
 constexpr int kChunkRows = 16;     // query rows per unit of a multi-token call (one matrix-core tile)
+// Multiplier and shift of a division by ns (2 .. 64): x / ns = (high word of x * multiplier) >> shift for all 0 <= x < 2^31.
+unsigned split_divisor(int ns, int *shift);
 bool attend_supported(int D, int G);
 size_t attend_spill_floats(int units_per_layer, int G, int cap);   // scratch the two-launch form needs
 // Largest split count and LDS plan for a unit of at most n_ub tokens (after the append)

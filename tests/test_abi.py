@@ -112,6 +112,19 @@ def test_many_rows_splits_leave_room_for_a_second_call(clib):
     assert splits(16, 16, 2560, 16, 256) == 8 and splits(16, 8, 2560, 16, 256) == 16
 
 
+def test_split_division_is_exact_for_every_slot_number(clib):
+    """Slices are cut with a multiplier and a shift per launch: around multiples of every split count, up to the largest int."""
+    divisor = getattr(clib, "_ZN6confkv13split_divisorEiPi")
+    divisor.restype = C.c_uint32
+    top = 2**31 - 1
+    for ns in range(2, 65):
+        shift = C.c_int(-1)
+        mul = divisor(ns, C.byref(shift))
+        near = {m * ns + d for m in {*range(70), *(2**b // ns for b in range(12, 31)), *range(top // ns - 70, top // ns + 1)} for d in (-1, 0, 1)}
+        wrong = [x for x in sorted(near) if 0 <= x <= top and (x * mul >> 32) >> shift.value != x // ns]
+        assert not wrong, (ns, wrong[0])
+
+
 @pytest.mark.parametrize("bad", [dict(head_dim=96), dict(n_q_heads=34, n_kv_heads=2), dict(n_q_heads=18, n_kv_heads=2, head_dim=64), dict(n_q_heads=7),
                                  dict(capacity=100), dict(capacity=128), dict(vocab=1), dict(alpha=1.5),
                                  dict(n_tight=[200, 64]), dict(protected_window=-1), dict(n_layers=0),
