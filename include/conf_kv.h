@@ -185,6 +185,8 @@ typedef struct conf_kv_stats {
  * others expire (the kernels still end normally; tests of the expiry path);
  * CONF_KV_GRID_KV_MAJOR=0/1 overrides the order of the attention grid (kv-heads first puts all
  * splits of a unit on one XCD and is the default when the number of kv-heads is a multiple of 8);
+ * CONF_KV_EVICT_ONE=0 keeps conf_kv_evict_compact in its separate launches (ranking, compaction,
+ * demotion) where a decode loop on few units otherwise takes one launch for all of it;
  * CONF_KV_COMPACT_PAIRED=0/1 (read at every conf_kv_evict_compact) forces one of the two grid
  * shapes of the compaction kernel, which is otherwise chosen by the number of units;
  * CONF_KV_TEST_TAG_BASE=n starts the device-side tag bases (see conf_kv_tag_state) at n instead

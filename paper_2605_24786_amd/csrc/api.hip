@@ -179,6 +179,7 @@ struct conf_kv_handle {
   bool force_two_launch = false;    // CONF_KV_TWO_LAUNCH at create (tests)
   int withhold = 0;                 // CONF_KV_TEST_WITHHOLD at create (tests of the expiry path)
   int kv_major = 0;                 // splits of a unit on one XCD (eight kv-heads or a multiple; CONF_KV_GRID_KV_MAJOR overrides)
+  bool evict_separate = false;      // CONF_KV_EVICT_ONE=0 at create (tests)
   int spin_limit = kSpinLimitDefault;   // CONF_KV_SPIN_LIMIT at create (tests of the expiry path)
   int last_hip = 0;
 };
@@ -229,6 +230,7 @@ int conf_kv_create(conf_kv_handle **out, const conf_kv_config *cfg, void *dev_st
   h->fresh_len.assign(L, -1);
   if (const char *fs = getenv("CONF_KV_SPLITS")) h->forced_splits = atoi(fs);
   if (const char *tl = getenv("CONF_KV_TWO_LAUNCH")) h->force_two_launch = atoi(tl) != 0;
+  if (const char *eo = getenv("CONF_KV_EVICT_ONE")) h->evict_separate = atoi(eo) == 0;
   if (const char *wh = getenv("CONF_KV_TEST_WITHHOLD")) h->withhold = atoi(wh) != 0;
   h->kv_major = cfg->n_kv_heads % 8 == 0;
   if (const char *km = getenv("CONF_KV_GRID_KV_MAJOR")) h->kv_major = atoi(km) != 0;
@@ -536,6 +538,7 @@ int conf_kv_evict_compact(conf_kv_handle *h, conf_kv_stream stream) {
   opt.seed = h->cfg.ranker_seed;
   opt.shared = h->cfg.rank_scope == CONF_KV_SCOPE_LAYER ? (double *)(h->scratch + h->kl.shared) : nullptr;
   opt.page = h->cfg.evict_page > 1 ? h->cfg.evict_page : 0;
+  opt.separate = h->evict_separate;
   CK_HIP(h, launch_evict_compact(h->cv, m, (double)h->cfg.alpha, opt, (double *)(h->scratch + h->kl.score),
                                  (int32_t *)(h->scratch + h->kl.src),
                                  (int32_t *)(h->scratch + h->kl.sel), n_max, h->attend_launches, h->conf_launches,

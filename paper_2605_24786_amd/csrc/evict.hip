@@ -1751,10 +1751,8 @@ hipError_t launch_load_prefill(const CacheView &cv, int layer, const __half *k16
 // 5000 45.0 and 63.7, 768 of 1003 losing 16 tokens 48.6 and 58.8.  Beyond 768 units the workgroups take turns: 1024 units
 // 0.81 to 1.11 times as long as four launches, 2048 1.06 to 1.23, 8192 1.3 to 2.5.
 static bool evict_in_one(const CacheView &cv, const RankOptions &opt, int U, int n_max, int after_prompt) {
-  if (const char *e = getenv("CONF_KV_EVICT_ONE"))             // test hook: 0 takes the separate launches
-    if (atoi(e) == 0) return false;
-  return !cv.page_lg && opt.page <= 1 && !opt.shared && !opt.random && !after_prompt && small_wg(U, n_max, false, false) &&
-         n_max <= 256 * 20;
+  return !opt.separate && !cv.page_lg && opt.page <= 1 && !opt.shared && !opt.random && !after_prompt &&
+         small_wg(U, n_max, false, false) && n_max <= 256 * 20;
 }
 
 hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, double alpha,

@@ -112,6 +112,25 @@ def test_many_rows_splits_leave_room_for_a_second_call(clib):
     assert splits(16, 16, 2560, 16, 256) == 8 and splits(16, 8, 2560, 16, 256) == 16
 
 
+def test_every_hook_is_in_the_header_and_read_once():
+    """The environment variables of the library (those of trace builds aside): described in the header, and read when a handle
+    is created or the first call planned, but for the one that the header says is read by each call."""
+    header = open(os.path.join(ROOT, "include", "conf_kv.h")).read()
+    csrc = os.path.join(ROOT, "paper_2605_24786_amd", "csrc")
+    read = {}
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        text = re.sub(r"#ifdef CONFKV_TRACE.*?#endif", "", text, flags=re.S)
+        for m in re.finditer(r'getenv\("(\w+)"\)', text):
+            read.setdefault(m.group(1), []).append((name, text[:m.start()]))
+    assert read and all(re.search(rf"\b{hook}=", header) for hook in read), [h for h in read if h not in header]
+    for hook, places in read.items():
+        for name, before in places:
+            # the function at the left margin that the call stands in
+            inside = re.findall(r"^[a-z][\w *&:]*?(\w+)\(", before, flags=re.M)[-1]
+            assert inside in ("conf_kv_create", "device_limits") or hook == "CONF_KV_COMPACT_PAIRED", (hook, name, inside)
+
+
 def test_split_division_is_exact_for_every_slot_number(clib):
     """Slices are cut with a multiplier and a shift per launch: around multiples of every split count, up to the largest int."""
     divisor = getattr(clib, "_ZN6confkv13split_divisorEiPi")

@@ -186,8 +186,11 @@ def test_evict_in_one_launch_matches_the_separate_ones(lib, torch_cuda, monkeypa
     torch = torch_cuda
     say(f"evict in one launch U={L * B * H} D={D} W={W} N={N} tq={tq}")
     cap = (N + 2 * tq + 63) // 64 * 64
-    kvs = [_mk(lib, n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap, vocab=1000,
-               protected_window=8, n_tight=[tight] * L, n_loose=[N] * L, max_chunk=tq if tq > 1 else 0) for _ in range(2)]
+    kvs = []
+    for one in (0, 1):
+        monkeypatch.setenv("CONF_KV_EVICT_ONE", str(one))
+        kvs.append(_mk(lib, n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap, vocab=1000,
+                       protected_window=8, n_tight=[tight] * L, n_loose=[N] * L, max_chunk=tq if tq > 1 else 0))
     g = torch.Generator(device="cuda")
     g.manual_seed(N + W)
     rn = lambda *s: torch.randn(s, generator=g, device="cuda").half()
@@ -202,12 +205,11 @@ def test_evict_in_one_launch_matches_the_separate_ones(lib, torch_cuda, monkeypa
         if t % 2:
             logits[:, 7] += 30                                  # confident: the tight budget
         args = [(rn(*toks, G * H, D), rn(*toks, H, D), rn(*toks, H, D)) for _ in range(L)]
-        for one, kv in enumerate(kvs):
+        for kv in kvs:
             out = torch.empty(*toks, G * H, D, dtype=torch.float16, device="cuda")
             for l in range(L):
                 (kv.attend_chunk if tq > 1 else kv.attend)(l, *args[l], out)
             kv.step(logits, torch.zeros(B, device="cuda"), torch.zeros(B, dtype=torch.uint8, device="cuda"))
-            monkeypatch.setenv("CONF_KV_EVICT_ONE", str(one))
             kv.evict_compact()
         for l, b, h in {(0, 0, 0), (L - 1, B - 1, H - 1), (L // 2, B // 2, H // 2), (0, B - 1, 0)}:
             a, c = (kv.export(l, b, h) for kv in kvs)
