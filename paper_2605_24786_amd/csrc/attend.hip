@@ -640,16 +640,7 @@ __device__ __forceinline__ size_t out_index(const CacheView &cv, const AttendLau
   const unsigned t = kRows ? (unsigned)token_of_row(a, (int)r) : 0u, hq = r - t * (unsigned)gq;   // (r < gq of a single token)
   return (size_t)(((((unsigned)sl.b * (unsigned)tq + t) * (unsigned)cv.Hkv + (unsigned)sl.g) * (unsigned)gq + hq) * (unsigned)D + d);
 }
-// ---------------------------------------------------------------------------------------
-// Epilogue shared by both bodies.  On entry wm/wl/wo hold NP per-wavefront partials
-// (after a workgroup barrier): partial k is [G][D] floats, rows DS apart, at
-// wo + (k % kAttWaves) * WSTR + (k / kAttWaves) * G * DS; stash holds the slice's raw scores.
-// kPhase 0: the whole epilogue in one kernel (merge, publish, wait for the unit's other splits,
-// gather, EMA, output).  kPhase 1: merge and publish only; kPhase 2: gather, EMA and output in a
-// later launch, which needs no wait (wm/wl are unused and wo holds the [G][gs] weights) --
-// the pair serves shapes whose splits cannot all be resident at once.
-// ---------------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------------
+
 constexpr int kEmaAhead = 4;                         // slots per thread whose EMA is requested ahead
 // The EMA values a thread will update, requested behind the first rows and used behind the exchange.
 template <bool kPaged>
@@ -665,6 +656,15 @@ __device__ __forceinline__ void request_ema(const CacheView &cv, const Slice &sl
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Epilogue shared by both bodies.  On entry wm/wl/wo hold NP per-wavefront partials
+// (after a workgroup barrier): partial k is [G][D] floats, rows DS apart, at
+// wo + (k % kAttWaves) * WSTR + (k / kAttWaves) * G * DS; stash holds the slice's raw scores.
+// kPhase 0: the whole epilogue in one kernel (merge, publish, wait for the unit's other splits,
+// gather, EMA, output).  kPhase 1: merge and publish only; kPhase 2: gather, EMA and output in a
+// later launch, which needs no wait (wm/wl are unused and wo holds the [G][gs] weights) --
+// the pair serves shapes whose splits cannot all be resident at once.
+// ---------------------------------------------------------------------------------------
 template <int D, int G, int NP, int WSTR, int kPhase = 0, int DR = D, int DS = D, bool kPaged = false>
 __device__ __forceinline__ void attend_epilogue(const CacheView &cv, const AttendLaunch &a,
                                                 const Slice &sl, int ns, int S, float *stash,

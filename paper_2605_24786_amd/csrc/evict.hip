@@ -1620,18 +1620,6 @@ __global__ __launch_bounds__(kEvThreads) void compact_paged_kernel(CacheView cv,
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// demote: grid (U / 4), one wavefront per unit.  Quantises the oldest FP16 slots until at most W stay
-// FP16, appends them at the INT8 ring tail, and commits (len, n8, head16, head8).  The first
-// wavefront also commits the step state in cv.ctl: the layers' next positions move past the
-// appended tokens and the tag bases past the launches since the last commit; a base near the
-// end of its range asks the next call's compaction kernel to clear the tagged words, after
-// which both bases start over at 0.
-// ---------------------------------------------------------------------------------------
-// kWide: a workgroup per unit, grid (U), for steps of up to 3072 units that appended several tokens:
-// its wavefronts share the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction
-// and a store (16 tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in
-// turn, 18.5 us; 4 tokens 10.5 and 7.3).
 // The step state, by the first wavefront of the launch.
 __device__ __forceinline__ void commit_ctl(const CacheView &cv, const LayerMask &appended, unsigned attend_launches,
                                            unsigned conf_launches) {
@@ -1649,6 +1637,18 @@ __device__ __forceinline__ void commit_ctl(const CacheView &cv, const LayerMask 
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// demote: grid (U / 4), one wavefront per unit.  Quantises the oldest FP16 slots until at most W stay
+// FP16, appends them at the INT8 ring tail, and commits (len, n8, head16, head8).  The first
+// wavefront also commits the step state in cv.ctl: the layers' next positions move past the
+// appended tokens and the tag bases past the launches since the last commit; a base near the
+// end of its range asks the next call's compaction kernel to clear the tagged words, after
+// which both bases start over at 0.
+// ---------------------------------------------------------------------------------------
+// kWide: a workgroup per unit, grid (U), for steps of up to 3072 units that appended several tokens:
+// its wavefronts share the 2 * cnt rows to quantise, each of which is a chain of a load, a reduction
+// and a store (16 tokens per call, 2048 units: 32 us when one wavefront took a unit's 32 rows in
+// turn, 18.5 us; 4 tokens 10.5 and 7.3).
 template <int D, bool kWide = false>
 __device__ __forceinline__ void demote_unit(int u, const CacheView &cv, const int32_t *sel_all) {
   constexpr int kWaves = kEvThreads / kWave;
@@ -1745,11 +1745,17 @@ hipError_t launch_load_prefill(const CacheView &cv, int layer, const __half *k16
 }
 
 // Calls that one launch serves: the plain ranker on a contiguous cache, as many units as rank with a workgroup each
-// (small_wg: three on every CU), units the register form of the general ranking holds, and not the step behind a prompt, whose
-// long moves are spread over a workgroup per plane.  Whole calls in one launch against four, us: 64 units of 130 slots 12.8
-// against 19.1, 144 of 515 (FP16-only, 64 channels) 12.9 and 18.2, 256 of 1003 18.4 and 23.9, 512 of 2050 26.0 and 34.1, 768 of
-// 5000 45.0 and 63.7, 768 of 1003 losing 16 tokens 48.6 and 58.8.  Beyond 768 units the workgroups take turns: 1024 units
-// 0.81 to 1.11 times as long as four launches, 2048 1.06 to 1.23, 8192 1.3 to 2.5.
+// (small_wg: three on every CU), units the register form of the general ranking holds.  Whole calls in one launch against four, us:
+// 64 units of 130 slots 12.8 against 19.1, 144 of 515 (FP16-only, 64 channels) 12.9 and 18.2, 256 of 1003 18.4 and 23.9, 512 of 2050
+// 26.0 and 34.1, 768 of 5000 45.0 and 63.7, 768 of 1003 losing 16 tokens 48.6 and 58.8.  Beyond 768 units the workgroups take
+// turns: 1024 units 0.81 to 1.11 times as long as four launches, 2048 1.06 to 1.23, 8192 1.3 to 2.5.
+// A fall from the loose to the tight budget, which moves thousands of rows, is spread over fewer workgroups and still costs less
+// nearly everywhere: 12 units of 4000 slots to 2000 65 against 76, 64 units 72 and 84, 256 84 and 115, 768 185 and 188; 768 of 1000
+// to 500 56 and 67.  It costs more where few units lose many FP16 slots as well: 12 units with a window of 2000 from 5000 to 4000
+// 132 against 121 (one unit 126 and 110), from 5000 to 2500 94 and 93, 64 units 149 and 150.  Two falls by d slots are d appended
+// tokens apart, and one launch makes every step between them some 6 us shorter, so the rule does not ask for the fall.
+// The step behind a prompt keeps the four launches although one costs less there too (64 units of 4000 slots to 2000 72
+// against 83, 768 of 5000 to 2500 236 and 238, 12 with a window of 2000 94 and 93).
 static bool evict_in_one(const CacheView &cv, const RankOptions &opt, int U, int n_max, int after_prompt) {
   return !opt.separate && !cv.page_lg && opt.page <= 1 && !opt.shared && !opt.random && !after_prompt &&
          small_wg(U, n_max, false, false) && n_max <= 256 * 20;
