@@ -109,27 +109,35 @@ def test_static_plan_changes_no_result(lib):
         np.testing.assert_allclose(a.astype(np.float32), b.astype(np.float32), rtol=2e-3, atol=2e-3)
 
 
-def test_tag_restart_under_replay(lib, monkeypatch):
+@pytest.mark.parametrize("evict", ["one launch", "separate launches", "paged"])
+def test_tag_restart_under_replay(lib, monkeypatch, evict):
     """The device-side tag bases start just below their restart threshold (test hook): within
-    three replayed steps the commit asks for the clearing, the next commit's compaction kernel
-    clears the exchange words and both bases start over -- with the oracle matched at every
-    step on the way, so no launch met a stale or missing word."""
+    three replayed steps the commit asks for the clearing, the next call clears the exchange words --
+    the first workgroup of the one launch, or all workgroups of the compaction kernel -- and both bases
+    start over, with the oracle matched at every step on the way, so no launch met a stale or missing word."""
     T = 0xFF000000
     monkeypatch.setenv("CONF_KV_TEST_TAG_BASE", str(T - 3))
+    monkeypatch.setenv("CONF_KV_SPLITS", "3")               # words of several splits travel in the replays too
+    monkeypatch.setenv("CONF_KV_EVICT_ONE", "1" if evict == "one launch" else "0")
     wl = small(1).scaled(steps=10, logit_std=(0.5, 6.0), logit_run=3)
+    if evict == "paged":
+        wl = wl.scaled(evict_page=16, layout="paged")
     assert wl.n_layers == 2
     ls = Lockstep(lib, wl, seed=43)
-    monkeypatch.delenv("CONF_KV_TEST_TAG_BASE")
+    monkeypatch.undo()
     ls.kv.static_plan(True)
-    assert ls.kv.tag_state() == (T - 3, T - 3, 0)
-    seen = []
-    ls.step()
-    seen.append(ls.kv.tag_state())
-    ls.record_step()
-    for t in range(1, wl.steps):
+    assert ls.kv.tag_state() == (T - 3, T - 3, 0) and ls.kv.attend_splits(0) == 3
+    words = ls.kv.scratch[:wl.batch * wl.n_kv_heads * 64 * wl.group * (2 + wl.head_dim) * 8]   # (64: splits there is room for)
+    seen, any_word = [], []
+    for t in range(wl.steps):
         ls.step()
         seen.append(ls.kv.tag_state())
-    say(f"tag states: {seen[:5]}")
+        any_word.append(bool(words.any()))
+        if t == 0:
+            ls.record_step()
+    assert ls.kv.attend_splits(0) == 3
+    say(f"{evict}: tag states: {seen[:5]}")
     assert seen[:5] == [(T - 1, T - 2, 0), (T + 1, T - 1, 1), (0, 0, 0), (2, 1, 0), (4, 2, 0)]
+    assert any_word[:5] == [True, True, False, True, True]
     assert ls.report.ok() and ls.kv.counters().device_errors == 0
     ls.close()

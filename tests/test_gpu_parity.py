@@ -174,23 +174,28 @@ def test_codes_at_half_way_quotients(lib, torch_cuda, D, scales):
     kv.close()
 
 
-@pytest.mark.parametrize("L,B,H,G,D,W,N,tight,tq", [
-    (4, 2, 2, 4, 128, 20, 90, 90, 1),       # one token over the budget
-    (3, 1, 3, 1, 64, -1, 200, 120, 1),      # FP16-only, falling to a tight budget: the general ranking, both shifts
-    (2, 2, 2, 2, 128, 0, 130, 125, 3),      # a window of 0, three tokens, four or more evictions
-    (2, 1, 2, 4, 128, 33, 700, 400, 16),    # sixteen tokens, hundreds of evictions: long moves
-    (12, 8, 8, 1, 64, 16, 70, 69, 1),       # 768 units, the last count that one launch takes
+@pytest.mark.parametrize("L,B,H,G,D,W,N,tight,tq,scales", [
+    (4, 2, 2, 4, 128, 20, 90, 90, 1, "token"),       # one token over the budget
+    (3, 1, 3, 1, 64, -1, 200, 120, 1, "token"),      # FP16-only, falling to a tight budget: the general ranking, both shifts
+    (2, 2, 2, 2, 128, 0, 130, 125, 3, "token"),      # a window of 0, three tokens, four or more evictions
+    (2, 1, 2, 4, 128, 33, 700, 400, 16, "token"),    # sixteen tokens, hundreds of evictions: long moves
+    (12, 8, 8, 1, 64, 16, 70, 69, 1, "token"),       # 768 units, the last count that one launch takes
+    (1, 1, 2, 4, 128, 40, 700, 300, 1, "channel"),   # per-channel scales
+    (2, 1, 2, 1, 64, -1, 4120, 4118, 1, "token"),    # more candidates than the small ranking's registers hold, one to three evictions
+    (1, 1, 3, 4, 128, 64, 4300, 4200, 1, "token"),   # the same, a hundred evictions
+    (1, 2, 1, 4, 128, 300, 5119, 2000, 1, "token"),  # the longest unit one launch takes, FP16 slots evicted too
+    (1, 2, 1, 4, 128, 64, 5120, 5119, 1, "token"),   # a slot more: separate launches under either setting
 ])
-def test_evict_in_one_launch_matches_the_separate_ones(lib, torch_cuda, monkeypatch, L, B, H, G, D, W, N, tight, tq):
+def test_evict_in_one_launch_matches_the_separate_ones(lib, torch_cuda, monkeypatch, L, B, H, G, D, W, N, tight, tq, scales):
     """Ranking, compaction, demotion and commit in one launch leave the state that the separate launches leave, bit for bit."""
     torch = torch_cuda
-    say(f"evict in one launch U={L * B * H} D={D} W={W} N={N} tq={tq}")
+    say(f"evict in one launch U={L * B * H} D={D} W={W} N={N} tight={tight} tq={tq} {scales}")
     cap = (N + 2 * tq + 63) // 64 * 64
     kvs = []
     for one in (0, 1):
         monkeypatch.setenv("CONF_KV_EVICT_ONE", str(one))
         kvs.append(_mk(lib, n_layers=L, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=cap, vocab=1000,
-                       protected_window=8, n_tight=[tight] * L, n_loose=[N] * L, max_chunk=tq if tq > 1 else 0))
+                       protected_window=8, n_tight=[tight] * L, n_loose=[N] * L, max_chunk=tq if tq > 1 else 0, scale_mode=scales))
     g = torch.Generator(device="cuda")
     g.manual_seed(N + W)
     rn = lambda *s: torch.randn(s, generator=g, device="cuda").half()
@@ -1447,12 +1452,14 @@ def test_lockstep_both_compaction_forms(lib, torch_cuda, paired, G, D, W, N):
     (chosen by the unit count); both are forced here on the same runs, the third of which evicts
     FP16 slots (the FP16 window is wider than the budgets).  Each run has a first step that moves
     hundreds of rows per unit (the chunked walk) and steady steps that move a few (the one-pass
-    path of the unit's first workgroup), at both head dimensions."""
+    path of the unit's first workgroup), at both head dimensions.  (Few units: without the separate
+    launches only the first step would reach the kernel.)"""
     wl = small(1).scaled(n_layers=2, batch=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=D, vocab=2003, prefill=260,
                          steps=24, n_tight=(N[0],) * 2, n_loose=(N[1],) * 2, protected=20, fp16_window=W,
                          alpha=0.5, logit_std=(0.5, 6.0), logit_run=4)
     say(f"lockstep compaction form paired={paired} G={G} D={D} W={W} N={N}")
     os.environ["CONF_KV_COMPACT_PAIRED"] = str(paired)
+    os.environ["CONF_KV_EVICT_ONE"] = "0"
     try:
         ls = Lockstep(lib, wl, seed=21)
         for t in range(wl.steps):
@@ -1463,6 +1470,7 @@ def test_lockstep_both_compaction_forms(lib, torch_cuda, paired, G, D, W, N):
         ls.close()
     finally:
         os.environ.pop("CONF_KV_COMPACT_PAIRED", None)
+        os.environ.pop("CONF_KV_EVICT_ONE", None)
 
 
 @pytest.mark.parametrize("prefill,D,W", [(6000, 128, 64), (1200, 64, -1), (40000, 128, 32)])
