@@ -43,6 +43,7 @@
 // which need no wait inside a kernel.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <map>
 #include <set>
 #include <mutex>

@@ -6,11 +6,11 @@
 // each re-read the whole cache: 4.1 ms per layer.  But the stored cache does not change while its
 // prompt observes it, and the windows' updates telescope to
 //   a_i = gain * sum_{t >= i} lambda^(T-1-t) sum_h p_{t,h,i},
-// so launches over all queries do: the first finds every row's softmax statistics, the second
+// so launches over all queries (those whose weight an fp32 sum can show, observe_first_block) do: the first finds every row's softmax statistics, the second
 // every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
 // chip idle, which two small kernels join.  Both recompute the scores on the matrix cores (nothing of
 // size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
-// wavefront and of 64 slots per workgroup, 170 to 175 us in these four.
+// wavefront and of 64 slots per workgroup, 170 to 175 us in these four with all rows, 111 with those that count.
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
@@ -38,15 +38,15 @@ struct ObserveStats {
 // every workgroup that shares the CU, three at most, the join 6.5 with its launch.  Measured over 77 runs of 20 to 3001 tokens,
 // 1 to 16 heads and 1 to 256 units in 1 to 16 parts, the choice takes 1.012 times the best count's time at the mean and 1.14 at
 // most.  (At least eight tiles a part, and no price for the join: 500 tokens, 1 head and 8 kv-heads in a part of eight tiles and one
-// of one 20.1 us, in six parts 10.7; 64 units of 500 tokens, 2 heads 29.1, uncut 20.3.)
+// of one 20.1 us, in six parts 10.7; 64 units of 500 tokens, 2 heads 29.1, uncut 20.3.)  before: tiles ahead of the first row.
 constexpr int kObsPartsMax = 16;
-static int observe_row_parts(long long items, int tiles, int most, bool chan, int cus) {
-  const double scale = chan ? 0.55 : 1.0, work = 0.5 * items * (tiles + 1);
+static int observe_row_parts(long long items, int before, int tiles, int most, bool chan, int cus) {
+  const double scale = chan ? 0.55 : 1.0, work = 0.5 * items * (before + tiles + 1);
   double cost[kObsPartsMax + 1], best = INFINITY;
   most = std::max(1, std::min(most, kObsPartsMax));
   for (int n = 1; n <= most; ++n) {
     const int len = (tiles + n - 1) / n;
-    const double groups = 0.5 * items * (n + 1), per_cu = groups / cus;
+    const double groups = 0.5 * items * (before / len + n + 1), per_cu = groups / cus;
     cost[n] = scale * (per_cu <= 3.0 ? len * (0.6 + 0.65 * per_cu) : 0.77 * ((work + groups) / cus + 1.8 * len)) + (n > 1 ? 6.5 : 0.0);
     if ((tiles + len - 1) / len != n) cost[n] = INFINITY;
     best = std::min(best, cost[n]);
@@ -61,21 +61,31 @@ static int observe_row_parts(long long items, int tiles, int most, bool chan, in
 // as long as a part's steps and kMassStart.  Measured over 40 shapes of 100 to 3001 tokens in up to twelve part counts of 1 to 32,
 // the choice takes 1.02 times the best of those at the mean; 1.2 for 64 units of 3001 tokens, 4 heads (eight parts 515 us, the
 // three that kMassGroups allows 630) and 256 of 500 tokens, 2 heads (79, uncut 67), 1.16 with per-channel scales (1000 tokens).
-static int observe_mass_parts(int units_per_layer, int G, int T, int most) {
-  const long long tiles = (T + kMassTile - 1) / kMassTile, nb = (T + 15) / 16 * G, steps = (nb + kMassStep - 1) / kMassStep;
+static int observe_mass_parts(int units_per_layer, int G, int T, int b0, int most) {
+  const long long tiles = (T + kMassTile - 1) / kMassTile, nb = (T + 15) / 16 * G - b0, steps = (nb + kMassStep - 1) / kMassStep;
   long long best = 0;
   int parts = 1;
   for (int p = 1; p == 1 || (p <= most && 2 * p <= steps + 1); ++p) {
     const long long len = (steps + p - 1) / p;
     long long groups = 0;
     for (long long t = 0; t < tiles && groups <= 4 * kMassGroups; ++t)
-      groups += p - std::min<long long>(p, t * (kMassTile / 16) * G / (len * kMassStep));
+      groups += p - std::min<long long>(p, std::max<long long>(0, t * (kMassTile / 16) * G - b0) / (len * kMassStep));
     groups *= units_per_layer;
     if (p > 1 && groups > 4 * kMassGroups) break;
     const long long cost = (groups + kMassGroups - 1) / kMassGroups * (len + kMassStart) + (p > 1 ? kMassSum : 0);
     if (p == 1 || cost < best) { best = cost; parts = p; }
   }
   return parts;
+}
+// The first block of rows that counts, 0 for most prompts: a row's weight falls with lambda^(T-1-t), and the rows before it add
+// less than 2^-150 to any slot all together, half of the smallest number that fp32 holds, so the importance is the same to the
+// bit without them (a tie within 2^-150 of a rounding apart).  1001 tokens of 4 heads at lambda = 0.9, 10 500 at 0.99, all at 1.  A layer of
+// 3001 tokens, 32 query heads, 8 kv-heads: statistics 81 -> 47 us, columns 90 -> 55.
+int observe_first_block(int G, int T, double decay, double gain) {
+  if (!(decay < 1.0)) return 0;
+  double reach = 1.0;                                   // rows (tokens) that count
+  if (decay > 0.0 && gain > 0.0) reach = std::ceil((150.0 * M_LN2 + std::log(gain * G / (1.0 - decay))) / -std::log(decay));
+  return reach < T ? (T - std::max(1, (int)reach)) / 16 * G : 0;
 }
 // The final statistics of `cap` tokens.  Parts take what the launch is given beyond those of its own tokens.
 size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
@@ -85,14 +95,16 @@ size_t observe_scratch_floats(int units_per_layer, int G, int cap) {
 // the parts of one kernel at a time (the first kernel's are done with before the second's are written).
 // (A reservation for the most parts that any T could take was 0.1 to 1.6 GB larger than a launch could use on long caches.)
 struct ObservePlan {
+  int b0;                                              // the first block of rows that counts
   int item, tile, per_part, row_parts;                 // first kernel: blocks per workgroup, slots per tile, tiles per part, parts
   bool short_form;                                     // second: the kernel of short prompts, or
   int subtiles, width, parts;                          // subtiles of a unit, per workgroup, parts
   size_t n_rows, stat_floats, floats;
 };
-static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool chan, size_t have, int cus) {
+static ObservePlan observe_plan(int units_per_layer, int G, int T, int b0, int n8, bool chan, size_t have, int cus) {
   ObservePlan p;
-  const int nblocks = (T + 15) / 16 * G;
+  const int nblocks = (T + 15) / 16 * G - b0;
+  p.b0 = b0;
   p.n_rows = (size_t)units_per_layer * G * observe_stride(T);
   p.stat_floats = 3 * p.n_rows;                         // (even: rows come in sixteens)
   const size_t room = have > p.stat_floats ? have - p.stat_floats : 0;
@@ -103,7 +115,7 @@ static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool 
   const int tiles = (n8 + p.tile - 1) / p.tile + (T - n8 + p.tile - 1) / p.tile;
   const bool one = T <= kObsShort && (long long)units_per_layer * ((nblocks + kObsShortItem - 1) / kObsShortItem) <= 2 * cus;
   p.item = one ? kObsShortItem : kObsItem;
-  p.row_parts = one ? 1 : observe_row_parts((long long)units_per_layer * ((nblocks + kObsItem - 1) / kObsItem), tiles,
+  p.row_parts = one ? 1 : observe_row_parts((long long)units_per_layer * ((nblocks + kObsItem - 1) / kObsItem), b0 / G * 16 / p.tile, tiles,
                                             (int)std::min<size_t>(kObsPartsMax, room / (3 * p.n_rows)), chan, cus);
   p.per_part = (tiles + p.row_parts - 1) / p.row_parts;
   // Second kernel.  More than eight blocks per wavefront of the form for short prompts are cut into parts where parts find idle
@@ -119,12 +131,15 @@ static ObservePlan observe_plan(int units_per_layer, int G, int T, int n8, bool 
   p.short_form = !cut && 2 * subtiles <= rounds2 * cus;
   p.width = !p.short_form && !cut && tile ? 1 : kObsWaves;
   const size_t column = 2 * (size_t)units_per_layer * observe_stride(T);
-  p.parts = p.short_form || p.width == 1 ? 1 : observe_mass_parts(units_per_layer, G, T, (int)std::min<size_t>(kMassPartsMax, room / column));
+  p.parts = p.short_form || p.width == 1 ? 1 : observe_mass_parts(units_per_layer, G, T, b0, (int)std::min<size_t>(kMassPartsMax, room / column));
   p.floats = p.stat_floats + std::max(p.row_parts > 1 ? 3 * p.row_parts * p.n_rows : 0, p.parts > 1 ? column * p.parts : 0);
   return p;
 }
+size_t observe_plan_floats(int units_per_layer, int G, int T, int b0, int n8, int chan, size_t have, int cus) {
+  return observe_plan(units_per_layer, G, T, b0, n8, chan != 0, have, cus).floats;
+}
 size_t observe_plan_floats(int units_per_layer, int G, int T, int n8, int chan, size_t have, int cus) {
-  return observe_plan(units_per_layer, G, T, n8, chan != 0, have, cus).floats;
+  return observe_plan_floats(units_per_layer, G, T, 0, n8, chan, have, cus);
 }
 static int device_cus();                                // (below, with the attention plans)
 
@@ -186,7 +201,7 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
 template <bool kChan, int kObsBlocks>
 __global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T,
-                                                                    float sm, double decay, double gain, int per_part, ObserveStats stats) {
+                                                                    float sm, double decay, double gain, int b0, int per_part, ObserveStats stats) {
   constexpr int D = 128, TS = kChan ? 32 : 64, kItem = kObsWaves * kObsBlocks;   // slots per tile, blocks per workgroup
   constexpr int kTileB = TS * kKRow16, kBuf = kTileB * (kChan ? 2 : 1);
   __shared__ __align__(16) uint8_t tiles[2][kBuf];
@@ -198,9 +213,9 @@ void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
   const ObserveUnit un = observe_unit(cv, layer * cv.B * cv.Hkv + ul, T);
   constexpr float kNothing = -1e30f;                    // reference of a lane that has seen no slot
 
-  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks + kItem - 1) / kItem;   // blocks are (token block, head)
+  const int nblocks = (T + 15) / 16 * G, nitems = (nblocks - b0 + kItem - 1) / kItem;   // blocks are (token block, head)
   const int item = nitems - 1 - (int)(blockIdx.x / cv.Hkv) % nitems, part = (int)(blockIdx.x / cv.Hkv) / nitems;
-  const int last_block = min((item + 1) * kItem, nblocks) - 1;
+  const int last_block = min(b0 + (item + 1) * kItem, nblocks) - 1;
   const int slots = min(T, last_block / G * 16 + 16);                // what the workgroup's last token sees
   const int nt8 = (min(un.n8, slots) + TS - 1) / TS;
   const int ntiles = nt8 + (max(0, slots - un.n8) + TS - 1) / TS;
@@ -212,7 +227,7 @@ void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
   half8_t qa[kObsBlocks][4];
 #pragma unroll
   for (int r = 0; r < kObsBlocks; ++r) {
-    const int block = item * kItem + w * kObsBlocks + r;
+    const int block = b0 + item * kItem + w * kObsBlocks + r;
     live[r] = block < nblocks;
     tok0[r] = (live[r] ? block : last_block) / G * 16;
     head[r] = (live[r] ? block : last_block) % G;
@@ -379,14 +394,16 @@ void observe_stats_kernel(CacheView cv, int layer, const __half *__restrict__ q,
 
 // The parts of the rows joined, in order.  (TS: slots per tile of the kernel above.)
 __global__ __launch_bounds__(kObsThreads) void observe_join_kernel(CacheView cv, int layer, int T, int TS, double decay, double gain,
-                                                                   int per_part, ObserveStats stats) {
+                                                                   int b0, int per_part, ObserveStats stats) {
   const int stride = observe_stride(T), G = cv.G;
   const size_t n_rows = (size_t)cv.B * cv.Hkv * G * stride, row = (size_t)blockIdx.x * kObsThreads + threadIdx.x;
   if (row >= n_rows) return;
   const int tok = (int)(row % stride), uh = (int)(row / stride), ul = uh / G;
+  const int block = tok / 16 * G + uh % G;
+  if (block < b0) return;
   const int n8 = min(cv.n8[layer * cv.B * cv.Hkv + ul], T);
-  const int nblocks = stride / 16 * G, item = (tok / 16 * G + uh % G) / kObsItem;
-  const int slots = min(T, (min((item + 1) * kObsItem, nblocks) - 1) / G * 16 + 16);
+  const int nblocks = stride / 16 * G, item = (block - b0) / kObsItem;
+  const int slots = min(T, (min(b0 + (item + 1) * kObsItem, nblocks) - 1) / G * 16 + 16);
   const int ntiles = (min(n8, slots) + TS - 1) / TS + (max(0, slots - n8) + TS - 1) / TS;
   float M = -1e30f;
   double L = 0.0;
@@ -418,13 +435,13 @@ __device__ __forceinline__ MassTile mass_subtile(const ObserveUnit &un, int at, 
   t.lim = t.is8 ? un.n8 : T;
   return t;
 }
-// Blocks per part, and the first block that sees a slot of a subtile.
-__device__ __forceinline__ int mass_part_blocks(int parts, int G, int T) {
-  const int steps = ((T + 15) / 16 * G + kMassStep - 1) / kMassStep;
+// Blocks per part, from block b0 on, and the first block that sees a slot of a subtile.
+__device__ __forceinline__ int mass_part_blocks(int parts, int G, int T, int b0) {
+  const int steps = ((T + 15) / 16 * G - b0 + kMassStep - 1) / kMassStep;
   return (steps + parts - 1) / parts * kMassStep;
 }
-__device__ __forceinline__ int mass_first_block(const ObserveUnit &un, int sub, int G, int T) {
-  return mass_subtile(un, sub, T).base / 16 * G;
+__device__ __forceinline__ int mass_first_block(const ObserveUnit &un, int sub, int G, int T, int b0) {
+  return max(b0, mass_subtile(un, sub, T).base / 16 * G);
 }
 
 // The keys of a subtile as a matrix-core operand, lane (slot t16 of each sixteen, channels 32 s + 8 g4 + [0, 8)), and the
@@ -497,7 +514,7 @@ __device__ __forceinline__ void mass_block(const MassTile &mt, const half8_t (&q
 // a prompt are latency: 100 tokens of 4 heads and 8 kv-heads 18.7 us there (13.8 in four parts with their sum), 9.4 here.
 template <bool kChan>
 __global__ __launch_bounds__(kMassShortThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void observe_mass_short_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, ObserveStats stats) {
+void observe_mass_short_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, int b0, ObserveStats stats) {
   constexpr int D = 128;
   __shared__ double red[kMassShortWaves][kMassWave];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -507,7 +524,7 @@ void observe_mass_short_kernel(CacheView cv, int layer, const __half *__restrict
   const ObserveUnit un = observe_unit(cv, u, T);
   const MassTile mt = mass_subtile(un, blockIdx.x / cv.Hkv, T);
   if (mt.base >= mt.lim) return;
-  const int first = mt.base / 16 * G, last = (T + 15) / 16 * G, stride = observe_stride(T);
+  const int first = max(b0, mt.base / 16 * G), last = (T + 15) / 16 * G, stride = observe_stride(T);
   struct Rows {
     confkv_v4i q[4];
     float4 ref;
@@ -556,7 +573,7 @@ void observe_mass_short_kernel(CacheView cv, int layer, const __half *__restrict
 template <bool kChan>
 __global__ __launch_bounds__(kObsThreads) __attribute__((amdgpu_waves_per_eu(kChan ? 2 : 3, kChan ? 2 : 3)))
 void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, float sm, int ntiles, int width /* subtiles per workgroup */,
-                         int parts, ObserveStats stats) {
+                         int b0, int parts, ObserveStats stats) {
   constexpr int D = 128, kSb = kMassSb, kRows = 16 * kMassStep;
   __shared__ __align__(16) uint8_t rows[2][kRows * kKRow16];
   __shared__ __align__(16) float s_ref[2][kRows];
@@ -566,8 +583,8 @@ void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, 
   const int g = blockIdx.x % cv.Hkv, y = blockIdx.x / cv.Hkv, tile = y % ntiles, part = y / ntiles, b = blockIdx.z, G = cv.G;
   const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
   const ObserveUnit un = observe_unit(cv, u, T);
-  const int len = mass_part_blocks(parts, G, T);
-  const int first = max(part * len, mass_first_block(un, tile * width, G, T)), last = min((part + 1) * len, (T + 15) / 16 * G);
+  const int len = mass_part_blocks(parts, G, T, b0);
+  const int first = max(b0 + part * len, mass_first_block(un, tile * width, G, T, b0)), last = min(b0 + (part + 1) * len, (T + 15) / 16 * G);
   if (first >= last || mass_subtile(un, tile * width, T).base >= T) return;
   // (a tile of one or two subtiles: its wavefronts share the rows of a step, and their sums meet in LDS)
   const int subs = min(width, (un.n8 + kMassWave - 1) / kMassWave + (T - un.n8 + kMassWave - 1) / kMassWave - tile * width);
@@ -675,15 +692,15 @@ void observe_mass_kernel(CacheView cv, int layer, const __half *__restrict__ q, 
 }
 
 // The parts' column sums, in order.
-__global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, int layer, int T, int parts, ObserveStats stats) {
+__global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, int layer, int T, int b0, int parts, ObserveStats stats) {
   const int g = blockIdx.x % cv.Hkv, slot = blockIdx.x / cv.Hkv * kObsThreads + threadIdx.x, b = blockIdx.z;
   const int ul = b * cv.Hkv + g, u = layer * cv.B * cv.Hkv + ul;
   if (slot >= T) return;
   const ObserveUnit un = observe_unit(cv, u, T);
   const int nt8 = (un.n8 + kMassWave - 1) / kMassWave;
   const int sub = slot < un.n8 ? slot / kMassWave : nt8 + (slot - un.n8) / kMassWave;
-  const int len = mass_part_blocks(parts, cv.G, T), from = mass_first_block(un, sub / kObsWaves * kObsWaves, cv.G, T) / len;
-  const int to = ((T + 15) / 16 * cv.G + len - 1) / len;               // (the last parts may be empty)
+  const int len = mass_part_blocks(parts, cv.G, T, b0), from = (mass_first_block(un, sub / kObsWaves * kObsWaves, cv.G, T, b0) - b0) / len;
+  const int to = ((T + 15) / 16 * cv.G - b0 + len - 1) / len;               // (the last parts may be empty)
   const double *src = stats.partial + (size_t)ul * parts * observe_stride(T) + slot;
   double A = 0.0;
 #pragma unroll 8
@@ -694,9 +711,9 @@ __global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, 
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, size_t scratch_floats, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
-  const int nblocks = (T + 15) / 16 * cv.G, units = cv.B * cv.Hkv;
+  const int units = cv.B * cv.Hkv, b0 = observe_first_block(cv.G, T, decay, gain), nblocks = (T + 15) / 16 * cv.G - b0;
   const int n8 = cv.W < 0 ? 0 : std::max(0, T - cv.W);    // (as the prompt was loaded)
-  const ObservePlan plan = observe_plan(units, cv.G, T, n8, cv.chan != 0, scratch_floats, device_cus());
+  const ObservePlan plan = observe_plan(units, cv.G, T, b0, n8, cv.chan != 0, scratch_floats, device_cus());
   if (plan.floats > scratch_floats) return hipErrorInvalidValue;
   const int tile = plan.tile, per_part = plan.per_part, row_parts = plan.row_parts, width = plan.width, parts = plan.parts;
   // (an odd count: a unit's workgroups follow one another on its XCD, and with an even one the tiles of most rows always fall to
@@ -716,18 +733,18 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
   }
   const auto first = cv.chan ? plan.item == kObsShortItem ? observe_stats_kernel<true, 1> : observe_stats_kernel<true, 2>
                              : plan.item == kObsShortItem ? observe_stats_kernel<false, 1> : observe_stats_kernel<false, 2>;
-  hipLaunchKernelGGL(first, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, per_part, stats);
+  hipLaunchKernelGGL(first, rows, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, decay, gain, b0, per_part, stats);
   if (row_parts > 1)
-    hipLaunchKernelGGL(observe_join_kernel, dim3((unsigned)((n_rows + kObsThreads - 1) / kObsThreads)), dim3(kObsThreads), 0, stream, cv, layer, T, tile, decay, gain, per_part, stats);
+    hipLaunchKernelGGL(observe_join_kernel, dim3((unsigned)((n_rows + kObsThreads - 1) / kObsThreads)), dim3(kObsThreads), 0, stream, cv, layer, T, tile, decay, gain, b0, per_part, stats);
   if (plan.short_form) {
     const dim3 grid(cv.Hkv * plan.subtiles, 1, cv.B);
-    if (cv.chan) hipLaunchKernelGGL(observe_mass_short_kernel<true>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, stats);
-    else hipLaunchKernelGGL(observe_mass_short_kernel<false>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, stats);
+    if (cv.chan) hipLaunchKernelGGL(observe_mass_short_kernel<true>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, b0, stats);
+    else hipLaunchKernelGGL(observe_mass_short_kernel<false>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, b0, stats);
     return hipGetLastError();
   }
-  if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
-  else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, parts, stats);
+  if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
+  else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
   if (parts > 1)
-    hipLaunchKernelGGL(observe_sum_kernel, dim3(cv.Hkv * ((T + kObsThreads - 1) / kObsThreads), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, T, parts, stats);
+    hipLaunchKernelGGL(observe_sum_kernel, dim3(cv.Hkv * ((T + kObsThreads - 1) / kObsThreads), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, T, b0, parts, stats);
   return hipGetLastError();
 }

@@ -1,9 +1,11 @@
 """The C-ABI library on a machine without a GPU: it loads, exports every symbol the header
 declares, sizes buffers, and rejects bad arguments before touching the device."""
 import ctypes as C
+import math
 import os
 import re
 
+import numpy as np
 import pytest
 
 import paper_2605_24786_amd as pkg
@@ -87,6 +89,37 @@ def test_prompt_phase_scratch(clib):
                             assert 3 * units * G * -(-T // 16) * 16 <= n <= room, (units, G, cap, T, chan, room)
                             cut += n > 3 * units * G * -(-T // 16) * 16
     assert cut > 1000
+
+
+def test_prompt_phase_rows_that_count(clib):
+    """Rows ahead of the first block add less than half of the smallest number that fp32 holds to any slot, all together
+    (gain times G heads times lambda^k summed over their distances k from the last token); a row more would not be left out.
+    The parts of what is left fit their scratch."""
+    first = getattr(clib, "_ZN6confkv19observe_first_blockEiidd")
+    first.restype, first.argtypes = C.c_int, [C.c_int, C.c_int, C.c_double, C.c_double]
+    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiiiimi")
+    plan.restype, plan.argtypes = C.c_size_t, [C.c_int] * 6 + [C.c_size_t, C.c_int]
+    left_out = 0
+    for G in (1, 3, 16):
+        for T in (1, 16, 151, 1000, 1001, 1017, 3001, 32768, 524288):
+            for lam in (0.0, 0.5, float(np.float32(0.9)), float(np.float32(0.999)), 1.0):
+                for gain in (0.0, 1e-30, 1.0 - lam, 1.0, 1e6):
+                    b0 = first(G, T, lam, gain)
+                    assert 0 <= b0 < -(-T // 16) * G and b0 % G == 0
+                    for chan in (0, 1):
+                        for units in (1, 8, 64):
+                            for room in (3 * units * G * -(-T // 16) * 16, 1 << 40):
+                                assert plan(units, G, T, b0, T // 3, chan, room, 256) <= room
+                    if lam == 1.0:
+                        assert b0 == 0
+                    elif 0.0 < lam and gain > 0.0:
+                        tail = lambda k: math.log2(gain * G / (1.0 - lam)) + k * math.log2(lam)     # of all distances from k on
+                        if b0:
+                            assert tail(T - b0 // G * 16) <= -150.0
+                            left_out += 1
+                        if b0 // G < (T - 1) // 16:              # the next block of tokens reaches further
+                            assert tail(T - (b0 // G + 1) * 16 - 1) > -150.0
+    assert left_out > 50
 
 
 def test_many_rows_splits_leave_room_for_a_second_call(clib):

@@ -724,11 +724,23 @@ def test_observe_prompt_forms(lib, torch_cuda, G, H, B, T0, W, scales):
     _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales)
 
 
-def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales):
+@pytest.mark.parametrize("G,H,B,T0,W,scales,decay", [
+    (4, 2, 2, 1500, 37, "token", 0.9),           # rows and columns in parts, 31 blocks of tokens left out
+    (1, 1, 1, 180, -1, "token", 0.5),            # columns of one tile in parts or of short prompts: 152 tokens reach
+    (2, 4, 17, 230, 64, "token", 0.5),           # a subtile per workgroup
+    (3, 1, 2, 700, 8, "channel", 0.8),           # 32-slot tiles
+    (16, 2, 1, 600, 600, "token", 0.1),          # 46 tokens
+])
+def test_observe_prompt_rows_out_of_reach(lib, torch_cuda, G, H, B, T0, W, scales, decay):
+    """Prompts whose first rows weigh too little to count.  1e-5 as in test_observe_prompt_edges."""
+    _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales, decay)
+
+
+def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales, decay=0.9):
     D = 128
-    say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales}")
+    say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales} decay={decay}")
     kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
-             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales)
+             protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales, ema_decay=decay)
     rng = np.random.default_rng(T0 + G)
     K = rng.standard_normal((B, H, T0, D)).astype(np.float16)
     q = (rng.standard_normal((B, T0, G * H, D)) * 1.5).astype(np.float16)
@@ -737,7 +749,7 @@ def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales):
     for b in range(B):
         for g in range(H):
             u = O.load_prefill(K[b, g], K[b, g], W, scale_mode=scales)
-            O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(0.9))
+            O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(decay))
             e_ref = u.ema.astype(np.float64)
             e_err = np.abs(kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
             assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"unit {(b, g)}: EMA off, max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
