@@ -1798,6 +1798,7 @@ void attend_mfma_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 }
 
 #include "attend_wide.h"
+#include "attend_rows.h"
 #include "attend_observe.h"
 
 // ---------------------------------------------------------------------------------------
@@ -2071,7 +2072,11 @@ int attend_wide_splits(int units_per_layer, int major_kv, int n_ub, int most, in
 // Calls with more than 16 query rows per unit: row groups (a power of two) and split count.  The
 // splits of a unit exchange partials inside the launch, so with more than one split the whole grid
 // must be resident (one workgroup per CU: the tile buffers take most of the LDS).
-bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int forced_splits, AttendPlan *plan) {
+static AttendFn attend_fn_wide(int rg, bool kept) {
+  if (kept) return rg == 1 ? (AttendFn)attend_rows_kernel<1> : (AttendFn)attend_rows_kernel<2>;
+  return rg == 1 ? (AttendFn)attend_wide_kernel<1> : rg == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
+}
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_ub, int forced_splits, AttendPlan *plan) {
   const DeviceLimits &lim = device_limits();
   if (!lim.ok || rows <= kChunkRows || rows > kWideMaxRows) return false;
   int rg = 1;
@@ -2081,9 +2086,10 @@ bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int
     ns = 1;
     while (ns * 2 <= std::min(forced_splits, wide_max_splits(rg * kWideRows)) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
   }
-  AttendFn fn = rg == 1 ? (AttendFn)attend_wide_kernel<1> : rg == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
-  const size_t lds = attend_wide_lds_bytes(rg * kWideRows, ns);
-  if (lds > lim.max_lds || attend_occupancy(fn, lds) < 1) return false;
+  // (wherever they fit: 1.01 to 1.15 times as fast over 22 shapes, of one tile to all 48 / rg)
+  plan->wide_kept = rg <= 2 && rows_tiles(n_ub, n16_ub, ns) <= rows_rounds(rg) * kAttWaves;
+  const size_t lds = plan->wide_kept ? attend_rows_lds_bytes(rg, ns) : attend_wide_lds_bytes(rg * kWideRows, ns);
+  if (lds > lim.max_lds || attend_occupancy(attend_fn_wide(rg, plan->wide_kept), lds) < 1) return false;
   plan->splits = ns;
   plan->stash_tokens = 0;
   plan->lds_bytes = lds;
@@ -2129,11 +2135,9 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a_in, const At
     return hipGetLastError();
   }
   if (plan.wide_groups) {
-    AttendFn wide = plan.wide_groups == 1 ? (AttendFn)attend_wide_kernel<1>
-                    : plan.wide_groups == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
     a.dbg = nullptr;
     a.max_splits = wide_max_splits(plan.wide_groups * kWideRows);
-    hipLaunchKernelGGL(wide, grid, dim3(kAttThreads), plan.lds_bytes, stream, cv.len, cv.n8, cv.head16, cv.head8, a.layer * cv.B * cv.Hkv, cv.Hkv, a.kv_major, cv, a, plan.splits, 0);
+    hipLaunchKernelGGL(attend_fn_wide(plan.wide_groups, plan.wide_kept), grid, dim3(kAttThreads), plan.lds_bytes, stream, cv.len, cv.n8, cv.head16, cv.head8, a.layer * cv.B * cv.Hkv, cv.Hkv, a.kv_major, cv, a, plan.splits, 0);
     return hipGetLastError();
   }
   const bool rows16 = a.tq > 1 || a.observe_first >= 0 || cv.G > 8;

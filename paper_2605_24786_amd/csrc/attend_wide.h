@@ -48,6 +48,154 @@ __host__ __device__ constexpr size_t attend_wide_lds_bytes(int R, int ns) {
   return (size_t)kAttWaves * kWideTileBytes + ((size_t)kAttWaves * kWideRows * 3 + 5 * R + (size_t)ns * R * 2) * 4 + 16;
 }
 
+// A tile's registers into its LDS buffer; factors of the raw scores and value scales go where the kernel keeps them.
+__device__ __forceinline__ void store_wide_tile(uint8_t *Kt, float *factor, float *value, bool is8, int lane, float sm, const TileRegs &tr) {
+  const int c8 = lane & 7, r8 = lane >> 3, c16 = lane & 15, r4 = lane >> 4;
+  uint8_t *Vt = Kt + kWideKBytes;
+  if (is8) {
+    // sixteen codes of a row per lane -> sixteen fp16 values (exact)
+    auto put_k = [&](int row, const int4 &k) {
+      half8_t *dst = (half8_t *)(Kt + row * kKRow16 + c8 * 32);
+      dst[0] = cvt_i8x8_f16x8((unsigned)k.x, (unsigned)k.y);
+      dst[1] = cvt_i8x8_f16x8((unsigned)k.z, (unsigned)k.w);
+    };
+    put_k(4 * r8, tr.k0);
+    put_k(4 * r8 + 1, tr.k1);
+    put_k(4 * r8 + 2, tr.k2);
+    put_k(4 * r8 + 3, tr.k3);
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
+      const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
+      const unsigned t0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u), t1 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
+      const unsigned t2 = __builtin_amdgcn_perm(x3, x2, 0x05010400u), t3 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
+      // byte r of o[e] is slot 8r + r8 at channel 16*c8 + 4*q4 + e: K rows 4*r8 .. 4*r8 + 3
+      const unsigned o[4] = {__builtin_amdgcn_perm(t2, t0, 0x05040100u), __builtin_amdgcn_perm(t2, t0, 0x07060302u),
+                             __builtin_amdgcn_perm(t3, t1, 0x05040100u), __builtin_amdgcn_perm(t3, t1, 0x07060302u)};
+      // K rows 16 sb + 4 g + i are piece g, half sb of the channel's 64 bytes; r8 = 4 sb + g
+      uint8_t *dst = Vt + c8 * kWideVGroup + 4 * q4 * 64 + (((r8 & 3) ^ q4) * 16) + (r8 >> 2) * 8;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        half2_t lo, hi;
+        cvt_i8x4_f16x4(o[e], lo, hi);
+        *(uint2 *)(dst + 64 * e) = make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
+      }
+    }
+    // row 4 * (slot % 8) + slot / 8 of slot lane % 32
+    (lane < 32 ? factor : value)[4 * (lane & 7) + ((lane >> 3) & 3)] = __half2float(__ushort_as_half(tr.sc)) * (lane < 32 ? sm : 1.0f);
+  } else {
+    *(int4 *)(Kt + (4 * r4) * kKRow16 + c16 * 16) = tr.k0;
+    *(int4 *)(Kt + (4 * r4 + 1) * kKRow16 + c16 * 16) = tr.k1;
+    *(int4 *)(Kt + (4 * r4 + 2) * kKRow16 + c16 * 16) = tr.k2;
+    *(int4 *)(Kt + (4 * r4 + 3) * kKRow16 + c16 * 16) = tr.k3;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
+      const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
+      // half r of a channel's word is slot 4r + r4: K rows 4*r4 .. 4*r4 + 3, piece r4 of eight bytes
+      uint8_t *dst = Vt + (c16 >> 1) * kWideVGroup + (8 * (c16 & 1) + 2 * q4) * 64 + r4 * 8;
+      *(uint2 *)dst = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x05040100u), __builtin_amdgcn_perm(x3, x2, 0x05040100u));
+      *(uint2 *)(dst + 64) = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x07060302u), __builtin_amdgcn_perm(x3, x2, 0x07060302u));
+    }
+  }
+}
+
+// Polls of the unit's ns * R * 2 statistics words (bounded).
+__device__ __forceinline__ void gather_statistics(const AttendLaunch &a, const Slice &sl, int ns, int R, unsigned tag, int tid, float *pml, int *s_ok) {
+  // every thread gathers some of the ns * R * 2 statistics words of the unit (bounded poll)
+  const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * R * 2;
+  for (int base = 0; base < ns * R * 2; base += kAttThreads) {
+    const int idx = base + tid;
+    bool here = idx >= ns * R * 2;
+    for (int spins = 0;; ++spins) {
+      if (!here) {
+        const unsigned long long wv = ld_tagged(&words[idx]);
+        if ((unsigned)(wv >> 32) == tag) {
+          pml[idx] = __uint_as_float((unsigned)wv);
+          here = true;
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(!here) == 0ull) break;
+      __builtin_amdgcn_s_sleep(1);
+      if (spins > a.spin_limit) {
+        if (!here) *s_ok = 0;
+        break;
+      }
+    }
+  }
+}
+// The unit's (M, L) of a row; the statistics of (split, row) become the weight of that split's output partial.  A padding row weighs
+// nothing and has the reference `padding`.
+template <typename Weight>
+__device__ __forceinline__ void finish_statistics(const AttendLaunch &a, int ns, int R, int row, int gq, int tq, float padding, float *pml,
+                                                  float *Mrow, float *Irow, Weight *Frow) {
+  constexpr float kNothing = -1e30f;
+  float M = kNothing;
+  for (int s = 0; s < ns; ++s) M = fmaxf(M, pml[(s * R + row) * 2]);
+  double L = 0.0;
+  for (int s = 0; s < ns; ++s) {
+    const float es = exp_nonpos(pml[(s * R + row) * 2] - M);
+    L += (double)es * (double)pml[(s * R + row) * 2 + 1];
+    pml[(s * R + row) * 2] = es;
+  }
+  const double inv = recip_pos(L);
+  Mrow[row] = row / gq < tq ? M : padding;
+  Irow[row] = (float)inv;
+  Frow[row] = row / gq < tq ? (Weight)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - row / gq))) : (Weight)0;
+}
+// The output rows [own0, own1) from the unit's partials; own(row) is this split's, at the thread's channel.
+template <typename Own>
+__device__ __forceinline__ void gather_output(const CacheView &cv, const AttendLaunch &a, const Slice &sl, int ns, int R, unsigned tag, int tid, int own0,
+                                              int own1, const float *pml, const int *Orow, const float *Irow, Own own) {
+  constexpr int D = 128, kRows = kAttThreads / D, kPass = 4;
+  const int ch = tid & (D - 1), lane = tid & 63, first = __builtin_amdgcn_readfirstlane(tid >> 6) / (D / kWave);   // (uniform)
+  // four rows of a thread at a time, one split after the other (the words of several splits requested together are
+  // asked for again as long as one of them is missing: 16 tokens of 4 heads on 64 units 40 against 38 us)
+  for (int r0 = own0 + first; r0 < own1; r0 += kRows * kPass) {
+    float o[kPass];
+#pragma unroll
+    for (int k = 0; k < kPass; ++k) {
+      const int row = min(r0 + k * kRows, own1 - 1);
+      o[k] = own(row) * pml[(sl.j * R + row) * 2];
+    }
+    for (int s = 0; s < ns; ++s) {
+      if (s == sl.j) continue;
+      const unsigned long long *src = a.part_o + ((size_t)sl.ul * a.max_splits + s) * R * D + ch;
+      unsigned long long wv[kPass];
+      auto request = [&]() {
+#pragma unroll
+        for (int k = 0; k < kPass; ++k) wv[k] = ld_tagged(src + (size_t)min(r0 + k * kRows, own1 - 1) * D);
+      };
+      auto ready = [&]() {
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < kPass; ++k) ok &= (unsigned)(wv[k] >> 32) == tag;
+        return ok;
+      };
+      request();
+      bool here = ready();
+      for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull && spins <= a.spin_limit; ++spins) {   // (bounded)
+        __builtin_amdgcn_s_sleep(1);
+        request();
+        here = ready();
+      }
+      const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
+      if (missing && lane == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
+#pragma unroll
+      for (int k = 0; k < kPass; ++k) {
+        const float wgt = pml[(s * R + min(r0 + k * kRows, own1 - 1)) * 2];
+        o[k] = fmaf(wgt > 0.f ? __uint_as_float((unsigned)wv[k]) : 0.f, wgt, o[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kPass; ++k) {
+      const int row = r0 + k * kRows;
+      const int to = __builtin_amdgcn_readfirstlane(Orow[min(row, own1 - 1)]);
+      if (row < own1 && to >= 0) a.out[(size_t)to * D + ch] = __float2half_rn(o[k] * Irow[row]);
+    }
+  }
+}
+
 template <int RG>
 __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns, int /*unused*/) {
@@ -77,8 +225,6 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   int gq = a.gq;
   const float sm = a.sm_scale;
   int t16 = lane & 15, g4 = lane >> 4;
-  const int c8 = lane & 7, r8 = lane >> 3;
-  const int c16 = lane & 15, r4 = lane >> 4;
   // Query rows as a matrix-core operand: lane (row t16, channels 32 g4 + 8 s + [0, 8)).  Requested with the counters, which
   // their place does not depend on.  Padding rows repeat the last token's: nothing reads what comes of them.
   half8_t qa[2][4];
@@ -118,54 +264,8 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   // registers -> this wavefront's LDS buffer
   auto store_item = [&](int it, const TileRegs &tr) {
     uint8_t *Kt = tiles + (size_t)w * kWideTileBytes;
-    uint8_t *Vt = Kt + kWideKBytes;
     float *sc = (float *)(Kt + kWideCoreBytes);
-    if (it < ntiles) {
-      // sixteen codes of a row per lane -> sixteen fp16 values (exact)
-      auto put_k = [&](int row, const int4 &k) {
-        half8_t *dst = (half8_t *)(Kt + row * kKRow16 + c8 * 32);
-        dst[0] = cvt_i8x8_f16x8((unsigned)k.x, (unsigned)k.y);
-        dst[1] = cvt_i8x8_f16x8((unsigned)k.z, (unsigned)k.w);
-      };
-      put_k(4 * r8, tr.k0);
-      put_k(4 * r8 + 1, tr.k1);
-      put_k(4 * r8 + 2, tr.k2);
-      put_k(4 * r8 + 3, tr.k3);
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-        const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-        const unsigned t0 = __builtin_amdgcn_perm(x1, x0, 0x05010400u), t1 = __builtin_amdgcn_perm(x1, x0, 0x07030602u);
-        const unsigned t2 = __builtin_amdgcn_perm(x3, x2, 0x05010400u), t3 = __builtin_amdgcn_perm(x3, x2, 0x07030602u);
-        // byte r of o[e] is slot 8r + r8 at channel 16*c8 + 4*q4 + e: K rows 4*r8 .. 4*r8 + 3
-        const unsigned o[4] = {__builtin_amdgcn_perm(t2, t0, 0x05040100u), __builtin_amdgcn_perm(t2, t0, 0x07060302u),
-                               __builtin_amdgcn_perm(t3, t1, 0x05040100u), __builtin_amdgcn_perm(t3, t1, 0x07060302u)};
-        // K rows 16 sb + 4 g + i are piece g, half sb of the channel's 64 bytes; r8 = 4 sb + g
-        uint8_t *dst = Vt + c8 * kWideVGroup + 4 * q4 * 64 + (((r8 & 3) ^ q4) * 16) + (r8 >> 2) * 8;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          half2_t lo, hi;
-          cvt_i8x4_f16x4(o[e], lo, hi);
-          *(uint2 *)(dst + 64 * e) = make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
-        }
-      }
-      // row 4 * (slot % 8) + slot / 8 of slot lane % 32
-      sc[(lane & 32) + 4 * (lane & 7) + ((lane >> 3) & 3)] = __half2float(__ushort_as_half(tr.sc)) * (lane < 32 ? sm : 1.0f);
-    } else {
-      *(int4 *)(Kt + (4 * r4) * kKRow16 + c16 * 16) = tr.k0;
-      *(int4 *)(Kt + (4 * r4 + 1) * kKRow16 + c16 * 16) = tr.k1;
-      *(int4 *)(Kt + (4 * r4 + 2) * kKRow16 + c16 * 16) = tr.k2;
-      *(int4 *)(Kt + (4 * r4 + 3) * kKRow16 + c16 * 16) = tr.k3;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const unsigned x0 = dword_of(tr.v0, q4), x1 = dword_of(tr.v1, q4);
-        const unsigned x2 = dword_of(tr.v2, q4), x3 = dword_of(tr.v3, q4);
-        // half r of a channel's word is slot 4r + r4: K rows 4*r4 .. 4*r4 + 3, piece r4 of eight bytes
-        uint8_t *dst = Vt + (c16 >> 1) * kWideVGroup + (8 * (c16 & 1) + 2 * q4) * 64 + r4 * 8;
-        *(uint2 *)dst = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x05040100u), __builtin_amdgcn_perm(x3, x2, 0x05040100u));
-        *(uint2 *)(dst + 64) = make_uint2(__builtin_amdgcn_perm(x1, x0, 0x07060302u), __builtin_amdgcn_perm(x3, x2, 0x07060302u));
-      }
-    }
+    store_wide_tile(Kt, sc, sc + kTile, it < ntiles, lane, sm, tr);
   };
 
   // ---------------- pass 1: online softmax and output per row ----------------
@@ -429,99 +529,20 @@ void attend_wide_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 
   // ---------------- exchange between the splits of the unit ----------------
   if (ns > 1) {
-    // every thread gathers some of the ns * R * 2 statistics words of the unit (bounded poll)
-    const unsigned long long *words = a.part_ml + (size_t)sl.ul * a.max_splits * R * 2;
-    for (int base = 0; base < ns * R * 2; base += kAttThreads) {
-      const int idx = base + tid;
-      bool here = idx >= ns * R * 2;
-      for (int spins = 0;; ++spins) {
-        if (!here) {
-          const unsigned long long wv = ld_tagged(&words[idx]);
-          if ((unsigned)(wv >> 32) == tag) {
-            pml[idx] = __uint_as_float((unsigned)wv);
-            here = true;
-          }
-        }
-        if (__builtin_amdgcn_ballot_w64(!here) == 0ull) break;
-        __builtin_amdgcn_s_sleep(1);
-        if (spins > a.spin_limit) {
-          if (!here) s_ok = 0;
-          break;
-        }
-      }
-    }
+    gather_statistics(a, sl, ns, R, tag, tid, pml, &s_ok);
     __syncthreads();
     if (s_ok == 0) {
       if (tid == 0) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
       return;
     }
-    // global (M, L) of row r by thread r; the statistics of (split, row) become the weight of
-    // that split's output partial
-    if (tid < R) {
-      float M = kNothing;
-      for (int s = 0; s < ns; ++s) M = fmaxf(M, pml[(s * R + tid) * 2]);
-      double L = 0.0;
-      for (int s = 0; s < ns; ++s) {
-        const float es = exp_nonpos(pml[(s * R + tid) * 2] - M);
-        L += (double)es * (double)pml[(s * R + tid) * 2 + 1];
-        pml[(s * R + tid) * 2] = es;
-      }
-      const double inv = recip_pos(L);
-      Mrow[tid] = tid / gq < tq ? M : 0.f;
-      Irow[tid] = (float)inv;
-      Frow[tid] = tid / gq < tq ? (float)(inv * pow_count((double)a.ema_decay, (unsigned)(tq - 1 - tid / gq))) : 0.f;
-    }
+    if (tid < R) finish_statistics(a, ns, R, tid, gq, tq, 0.f, pml, Mrow, Irow, Frow);
   }
   if (ns == 1) __syncthreads();                          // (the partials have been read)
 #pragma unroll
   for (int k = 0; k < kQ; ++k) *(confkv_v4i *)(Qs + (k * (kAttThreads / 16) + (tid >> 4)) * kKRow16 + (tid & 15) * 16) = qreg[k];
   __syncthreads();
   if (ns > 1 && a.out) {
-    // four rows of a thread at a time, one split after the other (the words of several splits requested together are
-    // asked for again as long as one of them is missing: 16 tokens of 4 heads on 64 units 40 against 38 us)
-    for (int r0 = own0 + row_w; r0 < own1; r0 += kRows * kPass) {
-      float o[kPass];
-#pragma unroll
-      for (int k = 0; k < kPass; ++k) {
-        const int row = min(r0 + k * kRows, own1 - 1);
-        o[k] = *partial(row / kWideRows, row) * pml[(sl.j * R + row) * 2];
-      }
-      for (int s = 0; s < ns; ++s) {
-        if (s == sl.j) continue;
-        const unsigned long long *src = a.part_o + ((size_t)sl.ul * a.max_splits + s) * R * D + ch;
-        unsigned long long wv[kPass];
-        auto request = [&]() {
-#pragma unroll
-          for (int k = 0; k < kPass; ++k) wv[k] = ld_tagged(src + (size_t)min(r0 + k * kRows, own1 - 1) * D);
-        };
-        auto ready = [&]() {
-          bool ok = true;
-#pragma unroll
-          for (int k = 0; k < kPass; ++k) ok &= (unsigned)(wv[k] >> 32) == tag;
-          return ok;
-        };
-        request();
-        bool here = ready();
-        for (int spins = 0; __builtin_amdgcn_ballot_w64(!here) != 0ull && spins <= a.spin_limit; ++spins) {   // (bounded)
-          __builtin_amdgcn_s_sleep(1);
-          request();
-          here = ready();
-        }
-        const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
-        if (missing && lane == __builtin_ctzll(missing)) atomicAdd(&cv.stats[kStatDeviceErr], 1ull);
-#pragma unroll
-        for (int k = 0; k < kPass; ++k) {
-          const float wgt = pml[(s * R + min(r0 + k * kRows, own1 - 1)) * 2];
-          o[k] = fmaf(wgt > 0.f ? __uint_as_float((unsigned)wv[k]) : 0.f, wgt, o[k]);
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < kPass; ++k) {
-        const int row = r0 + k * kRows;
-        const int to = __builtin_amdgcn_readfirstlane(Orow[min(row, own1 - 1)]);
-        if (row < own1 && to >= 0) a.out[(size_t)to * D + ch] = __float2half_rn(o[k] * Irow[row]);
-      }
-    }
+    gather_output(cv, a, sl, ns, R, tag, tid, own0, own1, pml, Orow, Irow, [&](int row) { return *partial(row / kWideRows, row); });
   }
 
   // ---------------- pass 2: exact mass per slot, EMA ----------------

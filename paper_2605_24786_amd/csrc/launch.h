@@ -40,6 +40,7 @@ struct AttendPlan {
   bool mfma;         // matrix-core body for the INT8 slots
   bool two_launch;   // stream + publish, then merge + EMA in a second launch (scores in scratch)
   int wide_groups;   // > 0: the many-rows kernel with that many groups of 32 query rows per unit
+  bool wide_kept;    // its form that keeps the raw scores in registers
 };
 struct AttendLaunch {
   int layer;
@@ -86,7 +87,7 @@ bool attend_plan(int D, int G, bool chan, bool paged, bool chunk, int units_per_
 // the shape cannot be served.  major_kv: kv-heads of the kv-head-first grid, 0 for the other.
 constexpr int kWideRowsMax = 128;
 int attend_wide_splits(int units_per_layer, int major_kv, int n_ub, int most, int cus);
-bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int forced_splits, AttendPlan *plan);
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_ub, int forced_splits, AttendPlan *plan);
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,

@@ -145,6 +145,27 @@ def test_many_rows_splits_leave_room_for_a_second_call(clib):
     assert splits(16, 16, 2560, 16, 256) == 8 and splits(16, 8, 2560, 16, 256) == 16
 
 
+def test_tiles_of_a_split(clib):
+    """The bound on a split's tiles that decides whether the many-rows kernel can keep its probabilities: no split of a unit
+    of at most n slots, n16 of them FP16, has more (INT8 slots cut at multiples of 32, FP16 slots evenly)."""
+    bound = getattr(clib, "_ZN6confkv10rows_tilesEiii")
+    for ns in (1, 2, 4, 8, 16):
+        for n_ub in (1, 16, 33, 64, 400, 767, 768, 2064, 9001):
+            for n16_ub in {1, 16, 17, 144, n_ub}:
+                most = 0
+                for n in {n_ub, n_ub - 1, n_ub - 31, n_ub // 2 + 1}:
+                    for n16 in {min(n16_ub, n), min(n16_ub, n) - 15, 1}:
+                        if n < 1 or n16 < 1:
+                            continue
+                        n8 = n - n16
+                        for j in range(ns):
+                            lo = n8 * j // ns & ~31
+                            hi = n8 if j == ns - 1 else n8 * (j + 1) // ns & ~31
+                            part16 = n16 * (j + 1) // ns - n16 * j // ns
+                            most = max(most, -(-(hi - lo) // 32) + -(-part16 // 16))
+                assert most <= bound(n_ub, min(n16_ub, n_ub), ns) <= most + 2, (ns, n_ub, n16_ub)
+
+
 def test_every_hook_is_in_the_header_and_read_once():
     """The environment variables of the library (those of trace builds aside): described in the header, and read when a handle
     is created or the first call planned, but for the one that the header says is read by each call."""

@@ -1159,6 +1159,18 @@ def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=23 * G + T0)
 
 
+@pytest.mark.parametrize("G,H,B,T0,W,splits,tqs", [
+    (4, 1, 1, 705, 0, 1, (16, 3)), (4, 1, 1, 706, 0, 1, (16,)),       # 24 tiles of two row groups kept, one more not; a lone INT8 slot
+    (1, 1, 1, 1441, 0, 1, (32, 17)), (1, 1, 1, 1442, 0, 1, (32,)),    # 48 of one row group
+    (4, 1, 1, 352, -1, 1, (16,)), (4, 1, 1, 353, -1, 1, (16,)),       # FP16 tiles only
+    (3, 2, 2, 1500, 100, 4, (17, 9)),                                 # three rounds, the last of FP16 tiles only; 51 and 27 rows
+    (1, 1, 1, 5, 2, 4, (20,)),                                        # splits without a slot
+])
+def test_attend_chunk_scores_kept(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
+    """The many-rows kernel that keeps its probabilities in registers, up to its last tile, and the one beyond."""
+    _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=29 * G + T0)
+
+
 @pytest.mark.parametrize("H,B", [(16, 1), (4, 4)])
 def test_many_rows_calls_on_two_streams(lib, torch_cuda, H, B):
     """Two managers on two streams, each call half of the CUs with splits that wait for one another: the same outputs and
@@ -1245,6 +1257,22 @@ def test_many_rows_kernel_keeps_its_registers(lib, torch_cuda, RG):
 
     clib, attr = lib.load_library(), FuncAttributes()
     kernel = C.c_char.in_dll(clib, f"_ZN6confkv18attend_wide_kernelILi{RG}EEEvPKiS2_S2_S2_iiiNS_9CacheViewENS_12AttendLaunchEii")
+    assert clib.hipFuncGetAttributes(C.byref(attr), C.c_void_p(C.addressof(kernel))) == 0
+    assert attr.maxThreadsPerBlock == 512 and attr.localSizeBytes == 0
+
+
+@pytest.mark.parametrize("RG", [1, 2])
+def test_kept_scores_stay_in_registers(lib, torch_cuda, RG):
+    """No scratch memory: the probabilities of up to six tiles per wavefront are what the registers are for."""
+    import ctypes as C
+
+    class FuncAttributes(C.Structure):
+        _fields_ = [("binaryVersion", C.c_int), ("cacheModeCA", C.c_int), ("constSizeBytes", C.c_size_t), ("localSizeBytes", C.c_size_t),
+                    ("maxDynamicSharedSizeBytes", C.c_int), ("maxThreadsPerBlock", C.c_int), ("numRegs", C.c_int),
+                    ("preferredShmemCarveout", C.c_int), ("ptxVersion", C.c_int), ("sharedSizeBytes", C.c_size_t)]
+
+    clib, attr = lib.load_library(), FuncAttributes()
+    kernel = C.c_char.in_dll(clib, f"_ZN6confkv18attend_rows_kernelILi{RG}EEEvPKiS2_S2_S2_iiiNS_9CacheViewENS_12AttendLaunchEii")
     assert clib.hipFuncGetAttributes(C.byref(attr), C.c_void_p(C.addressof(kernel))) == 0
     assert attr.maxThreadsPerBlock == 512 and attr.localSizeBytes == 0
 
