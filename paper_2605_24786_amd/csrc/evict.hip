@@ -1033,8 +1033,8 @@ void rank_select_reg_kernel(CacheView cv, LayerMask appended, double alpha, int3
 // rank_small: grid (U / 4), one wavefront per unit.  Runs first and settles every unit that
 // evicts nothing or at most kSmallE slots -- the steady state of a decode loop, where a unit
 // is one token over its budget: the e lowest (score, slot) pairs are found by e passes of a
-// running lexicographic minimum, with no histogram, no survivor ranking and a handful of
-// registers, so many wavefronts fit a SIMD.  Same score arithmetic, same decisions as the
+// running lexicographic minimum (at most kLazySlots candidates by the unit's own importance: lowest_lazily), with no histogram,
+// no survivor ranking and few registers, so many wavefronts fit a SIMD.  Same score arithmetic, same decisions as the
 // general kernels, which then skip the settled units (sel[7] = 1) and handle the rest.
 // ---------------------------------------------------------------------------------------
 constexpr int kSmallE = 4;
@@ -1072,9 +1072,128 @@ __device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t
   }
 }
 
+// The e <= kSmallE lowest (key, slot) pairs of a unit of at most kLazySlots candidates by its own importance, one wavefront: all
+// importances are read once, into registers, but only those positions that can matter.  Positions rise with the slot, so the key
+// with the position of a round's first slot (64 slots a round) bounds the keys of the round from below -- every operation of a
+// key is monotonic, rounding included -- and the first round, whose positions are read with the importances, holds
+// e keys that bound the e-th lowest from above.  Rounds with no bound at or below that one are out; a lane keeps its kSmallE lowest
+// keys of the others in order.
+// Before, importances were read twice and positions once more with them for every eviction, three times the bytes for one eviction
+// and nine for four, in batches of eight or 32 rounds.  2048 units of 2052 slots losing four 31.1 -> 14.7 us, of 2049 losing one
+// 12.3 -> 12.0, 8192 of 130 to 2049 losing one or two 24.5 -> 22.0 (what is left there is the chain of a unit: counters, importances,
+// bounds, positions, the selection); whole decode steps 1.00 to 1.04 times as fast on 1024 to 8192 units of 130 to 2200 slots.
+constexpr int kLazyRounds = 32, kLazySlots = kLazyRounds * kWave;
+__device__ __forceinline__ double dpp_min(double v) {      // over the 16 lanes of a row
+#define CONFKV_DPP(v, ctrl)                                                                                   \
+  __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),                         \
+                   __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true))
+  v = fmin(v, CONFKV_DPP(v, 0xB1));     // quad_perm [1,0,3,2]
+  v = fmin(v, CONFKV_DPP(v, 0x4E));     // quad_perm [2,3,0,1]
+  v = fmin(v, CONFKV_DPP(v, 0x141));    // row_half_mirror
+  return fmin(v, CONFKV_DPP(v, 0x140));  // row_mirror
+#undef CONFKV_DPP
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *pos, int hm, int cap, int ncand, int e, double alpha, int lane,
+                                              int (&ev)[kSmallE]) {
+  float a[kLazyRounds];
+  const int pos0 = pos[ring_row_u(hm, min(lane, ncand - 1), cap)];                        // of the first round
+  const int starts = pos[ring_row_u(hm, min((lane & (kLazyRounds - 1)) * kWave, ncand - 1), cap)];   // of round `lane`'s first slot
+  const int p_last = pos[ring_row_u(hm, ncand - 1, cap)];
+#pragma unroll
+  for (int r = 0; r < kLazyRounds; ++r) a[r] = ema[ring_row_u(hm, min(r * kWave + lane, ncand - 1), cap)];   // (past the end: the last one again)
+  float lo = a[0], hi = a[0];
+#pragma unroll
+  for (int r = 1; r < kLazyRounds; ++r) {
+    lo = a[r] < lo ? a[r] : lo;                        // (no NaN in an importance: plain compares)
+    hi = a[r] > hi ? a[r] : hi;
+  }
+  const double a_lo = (double)wave_min(lo), p_lo = (double)__builtin_amdgcn_readfirstlane(pos0);
+  const double a_rng = __dsub_rn((double)wave_max(hi), a_lo), p_rng = __dsub_rn((double)p_last, p_lo);
+  const double oma = __dsub_rn(1.0, alpha);
+  const Divisor a_div = make_divisor(a_rng == 0.0 ? 1.0 : a_rng), p_div = make_divisor(p_rng == 0.0 ? 1.0 : p_rng);
+  auto recency = [&](int ps) { return __dmul_rn(oma, p_rng == 0.0 ? 0.0 : quotient(__dsub_rn((double)ps, p_lo), p_div)); };
+  auto mass = [&](float x) { return __dmul_rn(alpha, a_rng == 0.0 ? 0.0 : quotient(__dsub_rn((double)x, a_lo), a_div)); };
+  // (an infinite importance leaves keys that are no numbers: the largest, as in the other kernels)
+  auto key_of = [&](double m, double r) { return fmin(__dadd_rn(m, r), 1.7976931348623157e308); };
+  double key[kSmallE];
+  int at[kSmallE];
+#pragma unroll
+  for (int k = 0; k < kSmallE; ++k) { key[k] = INFINITY; at[k] = 0x7fffffff; }
+  if (lane < ncand) { key[0] = key_of(mass(a[0]), recency(pos0)); at[0] = lane; }
+  // one key of each row of sixteen lanes: the largest of the four is not below the fourth lowest
+  const double low = dpp_min(key[0]);
+  const double q0 = lane_value(low, 0), q1 = lane_value(low, 16), q2 = lane_value(low, 32), q3 = lane_value(low, 48);
+  const double most = e == 1 ? fmin(fmin(q0, q1), fmin(q2, q3)) : fmax(fmax(q0, q1), fmax(q2, q3));
+  const double first = recency(starts);                // lane r: of round r's first slot
+  asm("" : "+s"(hm));                                  // (rows anew: kept from the importances' loads they would take a register per round)
+  asm("" : "+v"(lane));
+  // (the positions of eight rounds are requested together: a round trip for each took more than the bytes saved)
+  constexpr int kGroup = 8;
+#pragma unroll
+  for (int r0 = 0; r0 < kLazyRounds; r0 += kGroup) {
+    if (r0 * kWave >= ncand) break;
+    unsigned need = 0u;
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+      const int r = r0 + q;
+      const bool low_enough = r > 0 && r * kWave + lane < ncand && key_of(mass(a[r]), lane_value(first, r)) <= most;
+      need |= (__builtin_amdgcn_ballot_w64(low_enough) != 0ull ? 1u : 0u) << q;
+    }
+    if (need == 0u) continue;
+    int ps[kGroup];
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q)
+      if (need >> q & 1u) ps[q] = pos[ring_row_u(hm, min((r0 + q) * kWave + lane, ncand - 1), cap)];
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+      if (!(need >> q & 1u)) continue;
+      int s = (r0 + q) * kWave + lane;
+      double k = s < ncand ? key_of(mass(a[r0 + q]), recency(ps[q])) : INFINITY;
+      // into the lane's list, behind its equals: slots rise within a lane
+#pragma unroll
+      for (int x = 0; x < kSmallE; ++x) {
+        const bool lower = k < key[x];
+        const double kk = key[x];
+        const int ss = at[x];
+        key[x] = lower ? k : kk;
+        at[x] = lower ? s : ss;
+        k = lower ? kk : k;
+        s = lower ? ss : s;
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < kSmallE; ++p) {
+    ev[p] = 0x7fffffff;
+    if (p < e) {                                       // uniform over the wavefront
+      double best = key[0];
+      int slot = at[0];
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        const double ok = __shfl_xor(best, m, kWave);
+        const int oi = __shfl_xor(slot, m, kWave);
+        if (ok < best || (ok == best && oi < slot)) {
+          best = ok;
+          slot = oi;
+        }
+      }
+      ev[p] = slot;
+      if (at[0] == slot) {
+#pragma unroll
+        for (int x = 1; x < kSmallE; ++x) { key[x - 1] = key[x]; at[x - 1] = at[x]; }
+        key[kSmallE - 1] = INFINITY;
+        at[kSmallE - 1] = 0x7fffffff;
+      }
+    }
+  }
+}
+
 // kShared: the importance is the float64 sum over the kv-heads of the (layer, sequence), which
 // shared_mass_kernel left in shared_all (indexed by slot, not by ring row).
-// kBatch: loads a lane has in flight at a time (8 keeps the registers few enough for thousands of
+// kBatch: loads a lane has in flight at a time, of units beyond lowest_lazily (8 keeps the registers few enough for thousands of
 // units per launch; 32 covers a 2048-slot unit in one round trip per pass where there are fewer).
 template <bool kShared, int kBatch = 8, bool kRandom = false>
 __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, LayerMask appended,
@@ -1114,6 +1233,14 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, La
   const double *shared = kShared ? shared_all + (size_t)(u / cv.Hkv) * cv.cap : nullptr;
   const int hm = uw.head, cap = cv.cap;                // slot i of the per-slot planes: ring_row_u(hm, i, cap)
   const int nx = cv.cap8 == 0 ? n : n8;              // slots of the ring a right shift could serve
+  if constexpr (!kShared && !kRandom && kBatch == 8) {
+    if (ncand <= kLazySlots) {
+      int ev[kSmallE];
+      lowest_lazily(ema, pos, hm, cap, ncand, e, alpha, lane, ev);
+      finish_small<kWave>(cv, u, sel, src_all, n, n8, nx, e, ev, lane);
+      return;
+    }
+  }
   // loads go out in batches of kBatch (indices past the end re-read the last candidate), so a
   // long unit costs a few memory round trips per pass and not one per 64 slots
   typedef typename std::conditional<kShared, double, float>::type Imp;   // importance as stored
@@ -1843,7 +1970,7 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
   if (small_wg(U, n_max, false, false))
     hipLaunchKernelGGL((rank_small_wg_kernel<false>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, rr);
-  else if (U <= 4096)    // few wavefronts per SIMD: registers to spare for deeper batches
+  else if (U <= 4096 && n_max - cv.P > kLazySlots)    // few wavefronts per SIMD: registers to spare for deeper batches
     hipLaunchKernelGGL((rank_small_kernel<false, 32>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, U, 0, rr);
   else

@@ -995,6 +995,51 @@ def test_small_ranking_beyond_the_registers(lib, torch_cuda, T0, evict, alpha, l
     kv.close()
 
 
+@pytest.mark.parametrize("n,P,evict,alpha,low,odd", [
+    (2060, 12, 4, 0.65, (), None), (2061, 12, 4, 0.65, (), None),      # 2048 candidates, all in registers, and one more
+    (2060, 12, 4, 1.0, (5, 69, 133, 197, 261), None),                  # equal keys in one lane, one more than it keeps
+    (2060, 12, 3, 0.9, (900, 2040, 2047), None),                       # the last round of 64 slots, to the last candidate
+    (700, 8, 4, 0.0, (), None), (700, 8, 2, 0.02, (), None),           # recency alone; nearly
+    (77, 13, 4, 0.65, (), None), (78, 13, 1, 1.0, (64,), None),        # one round; a slot in the second
+    (9, 5, 4, 0.65, (), None),                                         # every candidate
+    (300, 4, 3, 0.65, (), np.inf),                                     # keys that are no numbers: the oldest go
+])
+def test_small_ranking_reads_positions_that_matter(lib, torch_cuda, n, P, evict, alpha, low, odd):
+    """One wavefront per unit (776 of them): rounds of 64 slots whose bound is above the e-th lowest key of the first are left
+    out.  Importance as loaded (lambda = 1, no gain): many equal ones, some large, rising in one layer and falling in another."""
+    torch = torch_cuda
+    L, H, D = 97, 8, 64
+    T0 = n - 1
+    say(f"lazy ranking n={n} P={P} evict={evict} alpha={alpha} low={low} odd={odd}")
+    kv = _mk(lib, n_layers=L, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=2, capacity=(n + 63) // 64 * 64,
+             protected_window=P, n_tight=[n - evict] * L, n_loose=[n - evict] * L, alpha=alpha, ema_decay=1.0, mass_gain=0.0)
+    rng = np.random.default_rng(n + evict)
+    K = torch.randn((1, H, T0, D), device="cuda", dtype=torch.float16)
+    new = torch.randn((1, H, D), device="cuda", dtype=torch.float16)
+    out = torch.empty_like(new)
+    shapes = [rng.integers(1, 9, (1, H, T0)).astype(np.float32),
+              np.where(rng.random((1, H, T0)) < 0.02, 50.0, rng.random((1, H, T0))).astype(np.float32),
+              np.broadcast_to(np.linspace(1, 2, T0, dtype=np.float32), (1, H, T0)).copy(),
+              np.broadcast_to(np.linspace(2, 1, T0, dtype=np.float32), (1, H, T0)).copy()]
+    for e0 in shapes:
+        e0[..., list(low)] = 0.25
+        if odd is not None:
+            e0[..., n // 2] = odd
+    for l in range(L):
+        kv.load_prefill(l, K, K, torch.from_numpy(shapes[l % 4]).cuda())
+        kv.attend(l, new, new, new, out)
+    kv.evict_compact()
+    pos = np.arange(n - P)
+    for l in (0, 1, 2, 3, 95, 96):
+        for h in range(H):
+            with np.errstate(invalid="ignore"):
+                s = O.rank_scores(shapes[l % 4][0, h].astype(np.float64)[: n - P], pos, f32(alpha))
+            gone = np.argsort(np.where(np.isnan(s), np.inf, s), kind="stable")[:evict]
+            got = kv.export(l, 0, h, planes=("pos",))["pos"]
+            assert np.array_equal(got, np.setdiff1d(np.arange(n), gone).astype(np.int32)), (l, h)
+    kv.close()
+
+
 @pytest.mark.parametrize("L,B,H,ranker,scope,evict", [
     (96, 1, 8, "composite", "kv_head", 3), (97, 1, 8, "composite", "kv_head", 4),      # 768 units and 776
     (27, 38, 4, "composite", "kv_head", 2),                                            # 4104 units
