@@ -79,7 +79,7 @@ static int observe_mass_parts(int units_per_layer, int G, int T, int b0, int mos
 }
 // The first block of rows that counts, 0 for most prompts: a row's weight falls with lambda^(T-1-t), and the rows before it add
 // less than 2^-150 to any slot all together, half of the smallest number that fp32 holds, so the importance is the same to the
-// bit without them (a tie within 2^-150 of a rounding apart).  1001 tokens of 4 heads at lambda = 0.9, 10 500 at 0.99, all at 1.  A layer of
+// bit without them (a tie within 2^-150 of a rounding apart).  1000 tokens of 4 heads at lambda = 0.9, 10 500 at 0.99, all at 1.  A layer of
 // 3001 tokens, 32 query heads, 8 kv-heads: statistics 81 -> 47 us, columns 90 -> 55.
 int observe_first_block(int G, int T, double decay, double gain) {
   if (!(decay < 1.0)) return 0;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
 // are staged once for its eight blocks as fp16 in two alternating LDS buffers (one barrier per tile).
 // Scores come transposed, a lane's rows being slots of one query: one running reference and sum
 // per lane and block, no reduction inside the loop; the sum goes over to 64 bits with every tile.
-// 120 -> 81 us per layer of 3001 tokens and 32 heads; while a CU is busy, vector ALU and matrix cores are at work in
+// 120 -> 81 us per layer of 3001 tokens and 32 heads with all rows, 47 with those that count; while a CU is busy, vector ALU and matrix cores are at work in
 // turn 93 % of the time.
 // Causal work falls along the list of items: long ones are cut into parts of their slots.
 // A score costs a multiply-add, a product with log2 e, one hardware exponential and one addition.
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_join_kernel(CacheView cv,
 // 16 rows -- (token block, head), from the first that sees one of the slots, or a part of them --
 // come through LDS four at a time, staged once for the four wavefronts.  Each wavefront reading the
 // queries for itself asked 622 MB of L2 per layer of 3001 tokens and 32 heads, 5.2 TB/s, and 384 workgroups of
-// falling work ended late: 118 us, 90 now, of which the vector ALU (ten instructions a score) works 55.
+// falling work ended late: 118 us, 90 now (55 with the rows that count), of which the vector ALU (ten instructions a score) works 55.
 // Every probability goes into its column's sum in 64 bits by itself.
 struct MassTile {
   int base, lim;                                       // slots [base, min(base + kMassWave, lim)) of subtile `at`

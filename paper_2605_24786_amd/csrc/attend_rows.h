@@ -12,10 +12,10 @@
 // unit's maximum), one number per row and round, formed in 64 bits.  (Kept as scores, with the exponentials anew,
 // the last part took 8.6 us, now 2.)
 //
-// The launch above: 37.0 -> 31.2 us (kernel trace).  By leaving parts out: 12 for its bytes in three rounds, 5 for scores and
-// probabilities, 3 for the output, 4 for publishing, 4 for the exchange, 2 for the importance.  Rounds are vector instructions
+// The launch above: 37.0 -> 33.4 us (kernel trace).  By leaving parts out: 12 for its bytes in three rounds, 5 for scores and
+// probabilities, 5 for the output (3 with the probabilities rounded to fp16, see there), 4 for publishing, 4 for the exchange, 2 for the importance.  Rounds are vector instructions
 // (conversions, exponentials), LDS and matrix instructions in turn, since four barriers keep the wavefronts in step.  Whole steps of
-// eight layers, 17 to 64 rows, 1 to 192 units of 64 to 9000 slots: 1.01 to 1.15 times as fast.  Scores and probabilities of a round were
+// eight layers, 17 to 64 rows, 1 to 192 units of 64 to 9000 slots: 1.00 to 1.14 times as fast.  Scores and probabilities of a round were
 // written out for each kind of tile at first: 240 KB of code, against 50.
 #pragma once
 
@@ -226,14 +226,16 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
 #pragma unroll
       for (int nt = 0; nt < RG; ++nt) O[r][nt] *= corr;
     }
-    // probabilities times value scales, rounded to fp16, over the tile's keys: [row group][block][lane]
+    // probabilities times value scales over the tile's keys as fp16 head and tail, [head, tail][row group][block][lane].  (Rounded to
+    // fp16 alone, only the largest of a row is exact, where a reference of its own for every stream has one exact in each: outputs of
+    // 16 tokens of 4 heads on 500 slots 2.69e-4 from float64, against 2.48e-4 in the other kernel.)
 #pragma unroll
     for (int k = 0; k < RG; ++k) {
       const int j = st + k * NS, it = it0 + j;
       if (it >= nitems) continue;
       const float *sc = (const float *)(tile_at(j) + kWideCoreBytes);
       const int lim = end_of(it);
-      half8_t p[2] = {};
+      half8_t p[2] = {}, tail[2] = {};
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
         if (sb > 0 && it >= ntiles) break;
@@ -254,32 +256,48 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
               if (slot_of(it, sb, i) >= min(lim, seen[r])) e[i] = 0.f;
           }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) p[r][4 * sb + i] = (_Float16)(e[i] * vs[i]);
+          for (int i = 0; i < 4; ++i) {
+            const float v = e[i] * vs[i];
+            p[r][4 * sb + i] = (_Float16)v;
+            tail[r][4 * sb + i] = (_Float16)(v - (float)p[r][4 * sb + i]);
+          }
           l[r] += (e[0] + e[1]) + (e[2] + e[3]);
           S[sup][k][r][sb] = e;
         }
       }
 #pragma unroll
-      for (int r = 0; r < 2; ++r) *(half8_t *)(tile_at(j) + (2 * rg + r) * 1024 + lane * 16) = p[r];
+      for (int r = 0; r < 2; ++r) {
+        *(half8_t *)(tile_at(j) + (2 * rg + r) * 1024 + lane * 16) = p[r];
+        *(half8_t *)(tile_at(j) + (2 * (RG + rg) + r) * 1024 + lane * 16) = tail[r];
+      }
     }
     lds_barrier();
     // the wavefront's channels of all tiles
     auto contract = [&](int j, bool is8) {
       const uint8_t *Kt = tile_at(j), *Vt = Kt + kWideKBytes + st * RG * kWideVGroup + t16 * 64;
-      half8_t p[2];
+      static_assert(4 * RG * 1024 <= kWideKBytes, "probabilities fit the tile's keys");
+      half8_t p[2], tail[2];
 #pragma unroll
-      for (int r = 0; r < 2; ++r) p[r] = *(const half8_t *)(Kt + (2 * rg + r) * 1024 + lane * 16);
+      for (int r = 0; r < 2; ++r) {
+        p[r] = *(const half8_t *)(Kt + (2 * rg + r) * 1024 + lane * 16);
+        tail[r] = *(const half8_t *)(Kt + (2 * (RG + rg) + r) * 1024 + lane * 16);
+      }
 #pragma unroll
       for (int nt = 0; nt < RG; ++nt) {
         if (is8) {
           const half8_t vf = *(const half8_t *)(Vt + nt * kWideVGroup + ((g4 ^ (t16 >> 2)) * 16));
 #pragma unroll
-          for (int r = 0; r < 2; ++r) O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, p[r], O[r][nt], 0, 0, 0);
+          for (int r = 0; r < 2; ++r) {
+            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, tail[r], O[r][nt], 0, 0, 0);
+            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, p[r], O[r][nt], 0, 0, 0);
+          }
         } else {
           const half4_t vf = *(const half4_t *)(Vt + nt * kWideVGroup + g4 * 8);
 #pragma unroll
-          for (int r = 0; r < 2; ++r)
+          for (int r = 0; r < 2; ++r) {
+            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{tail[r][0], tail[r][1], tail[r][2], tail[r][3]}, O[r][nt], 0, 0, 0);
             O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{p[r][0], p[r][1], p[r][2], p[r][3]}, O[r][nt], 0, 0, 0);
+          }
         }
       }
     };
