@@ -368,7 +368,8 @@ static int plan_for_layer(conf_kv_handle *h, int layer, int tq, AttendPlan *plan
   const int n16_ub = W < 0 ? n_ub : std::min(n_ub, observe ? W : W + tq);
   // a chunk runs on the matrix-core body with all 16 tile rows as query rows
   if (tq * h->cv.G > kChunkRows) {                         // more rows than one tile: the many-rows kernel
-    if (!attend_wide_plan(tq * h->cv.G, h->cfg.batch * h->cfg.n_kv_heads, h->kv_major ? h->cfg.n_kv_heads : 0, n_ub, n16_ub, h->forced_splits, plan))
+    const int n16_least = W < 0 ? n_ub : observe ? 0 : tq;   // (the call's own tokens, which an observation does not append)
+    if (!attend_wide_plan(tq * h->cv.G, h->cfg.batch * h->cfg.n_kv_heads, h->kv_major ? h->cfg.n_kv_heads : 0, n_ub, n16_least, n16_ub, h->forced_splits, plan))
       return CONF_KV_ERR_BAD_SHAPE;
     return CONF_KV_OK;
   }

@@ -2076,7 +2076,7 @@ static AttendFn attend_fn_wide(int rg, bool kept) {
   if (kept) return rg == 1 ? (AttendFn)attend_rows_kernel<1> : (AttendFn)attend_rows_kernel<2>;
   return rg == 1 ? (AttendFn)attend_wide_kernel<1> : rg == 2 ? (AttendFn)attend_wide_kernel<2> : (AttendFn)attend_wide_kernel<4>;
 }
-bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_ub, int forced_splits, AttendPlan *plan) {
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_least, int n16_ub, int forced_splits, AttendPlan *plan) {
   const DeviceLimits &lim = device_limits();
   if (!lim.ok || rows <= kChunkRows || rows > kWideMaxRows) return false;
   int rg = 1;
@@ -2087,7 +2087,7 @@ bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int
     while (ns * 2 <= std::min(forced_splits, wide_max_splits(rg * kWideRows)) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
   }
   // (wherever they fit: 1.00 to 1.14 times as fast over 22 shapes, of one tile to all 48 / rg)
-  plan->wide_kept = rg <= 2 && rows_tiles(n_ub, n16_ub, ns) <= rows_rounds(rg) * kAttWaves;
+  plan->wide_kept = rg <= 2 && rows_tiles(n_ub, n16_least, n16_ub, ns) <= rows_rounds(rg) * kAttWaves;
   const size_t lds = plan->wide_kept ? attend_rows_lds_bytes(rg, ns) : attend_wide_lds_bytes(rg * kWideRows, ns);
   if (lds > lim.max_lds || attend_occupancy(attend_fn_wide(rg, plan->wide_kept), lds) < 1) return false;
   plan->splits = ns;

@@ -29,10 +29,14 @@ __host__ __device__ constexpr size_t attend_rows_lds_bytes(int RG, int ns) {
   return (size_t)kAttWaves * kWideTileBytes +
          ((size_t)rows_rounds(RG) * kAttWaves * kTile + 2 * kAttWaves * kWideRows + (5 + rows_rounds(RG)) * RG * kWideRows + (size_t)ns * RG * kWideRows * 2) * 4 + 16;
 }
-// Tiles a split of a unit of at most n slots, n16 of them FP16, may have (make_slice: INT8 slots cut at multiples of 32).
-int rows_tiles(int n, int n16, int ns) {
-  const int c8 = (std::max(0, n - n16) + ns - 1) / ns + 31, c16 = (n16 + ns - 1) / ns;
-  return (c8 + kTile - 1) / kTile + (c16 + 15) / 16;
+// The most tiles that a split of a unit of at most n slots, least16 to n16 of them FP16, may have (make_slice: INT8 slots cut at
+// multiples of 32, FP16 slots evenly).  Fewer FP16 slots than n16 -- an eviction took some, an import brought few, an observation
+// ends ahead of the last ones -- are more INT8 slots: a tile more, as long as the FP16 share still fills t16.  So the INT8 slots
+// counted are those beside the fewest FP16 slots that do.  (Every FP16 tile less makes room for half an INT8 tile.)
+int rows_tiles(int n, int least16, int n16, int ns) {
+  const int t16 = ((n16 + ns - 1) / ns + 15) / 16;
+  const int n8 = n - std::min(n16, std::max(least16, 16 * ns * (t16 - 1) + 1));
+  return (least16 < n ? ((n8 + ns - 1) / ns + 31 + kTile - 1) / kTile : 0) + t16;
 }
 
 // Sum over the sixteen lanes of a row of eight values, each of which ends in a pair of lanes: value 4 (t16 / 8) + (t16 / 2) % 4.

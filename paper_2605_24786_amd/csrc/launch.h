@@ -85,9 +85,10 @@ bool attend_plan(int D, int G, bool chan, bool paged, bool chunk, int units_per_
                  bool force_two_launch, size_t extra_lds, AttendPlan *plan);
 // Plan of a call with more than kChunkRows query rows per unit (at most kWideRowsMax); false when
 // the shape cannot be served.  major_kv: kv-heads of the kv-head-first grid, 0 for the other.
+// n_ub: the most slots of a unit; n16_least, n16_ub: the fewest and the most FP16 ones.
 constexpr int kWideRowsMax = 128;
 int attend_wide_splits(int units_per_layer, int major_kv, int n_ub, int most, int cus);
-bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_ub, int forced_splits, AttendPlan *plan);
+bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int n16_least, int n16_ub, int forced_splits, AttendPlan *plan);
 hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const AttendPlan &plan,
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,

@@ -147,23 +147,38 @@ def test_many_rows_splits_leave_room_for_a_second_call(clib):
 
 def test_tiles_of_a_split(clib):
     """The bound on a split's tiles that decides whether the many-rows kernel can keep its probabilities: no split of a unit
-    of at most n slots, n16 of them FP16, has more (INT8 slots cut at multiples of 32, FP16 slots evenly)."""
-    bound = getattr(clib, "_ZN6confkv10rows_tilesEiii")
-    for ns in (1, 2, 4, 8, 16):
-        for n_ub in (1, 16, 33, 64, 400, 767, 768, 2064, 9001):
-            for n16_ub in {1, 16, 17, 144, n_ub}:
-                most = 0
-                for n in {n_ub, n_ub - 1, n_ub - 31, n_ub // 2 + 1}:
-                    for n16 in {min(n16_ub, n), min(n16_ub, n) - 15, 1}:
-                        if n < 1 or n16 < 1:
-                            continue
-                        n8 = n - n16
-                        for j in range(ns):
-                            lo = n8 * j // ns & ~31
-                            hi = n8 if j == ns - 1 else n8 * (j + 1) // ns & ~31
-                            part16 = n16 * (j + 1) // ns - n16 * j // ns
-                            most = max(most, -(-(hi - lo) // 32) + -(-part16 // 16))
-                assert most <= bound(n_ub, min(n16_ub, n_ub), ns) <= most + 2, (ns, n_ub, n16_ub)
+    of at most n slots, with any number of FP16 slots up to n16, has more (INT8 slots cut at multiples of 32, FP16 slots evenly),
+    and the bound is at most one too large.  Every count of FP16 slots, at lengths around the limits of 24 and 48 tiles."""
+    bound = getattr(clib, "_ZN6confkv10rows_tilesEiiii")
+    def need(n, ns):                                             # with any number of FP16 slots
+        n16 = np.arange(min(n, max(windows)) + 1)
+        n8, most = n - n16, np.zeros(len(n16), int)
+        for j in range(ns):
+            lo = n8 * j // ns & ~31
+            hi = n8 if j == ns - 1 else n8 * (j + 1) // ns & ~31
+            part16 = n16 * (j + 1) // ns - n16 * j // ns
+            most = np.maximum(most, -(-(hi - lo) // 32) + -(-part16 // 16))
+        return most
+
+    windows = (0, 1, 15, 16, 17, 31, 32, 33, 48, 64, 79, 80, 112, 128, 144, 145, 300)
+    at_limit = 0
+    for ns in (1, 2, 3, 4, 8, 16):
+        lengths = {*range(1, 300)}
+        for tiles in (24, 48):
+            lengths |= {*range(max(1, 32 * ns * (tiles - 1) - 40 * ns), 32 * ns * tiles + 2, 1 if ns <= 4 else 3)}
+        for n in sorted(lengths):
+            most = need(n, ns)
+            for n16_ub in {min(w, n) for w in windows}:
+                for least in {min(w, n16_ub) for w in (0, 5, 16, n16_ub)}:
+                    top, got = most[least:n16_ub + 1].max(), bound(n, least, n16_ub, ns)
+                    assert top <= got <= top + 1, (ns, n, least, n16_ub, got, top)
+                    at_limit += got in (24, 48)
+        for n in range(1, 32 * ns * 24, 7):
+            for least in (0, 16):                                # what a shorter unit needs is there
+                assert need(n, ns)[min(n, least):145].max() <= bound(n + 1, min(n + 1, least), min(n + 1, 144), ns), (ns, n, least)
+                assert bound(n, min(n, least), min(n, 144), ns) <= bound(n + 40, min(n + 40, least), min(n + 40, 144), ns), (ns, n, least)
+            assert bound(n, n, n, ns) == -(-(-(-n // ns)) // 16)   # FP16-only: no INT8 slots
+    assert at_limit > 1000
 
 
 def test_every_hook_is_in_the_header_and_read_once():

@@ -564,6 +564,7 @@ def _observe_case(lib, torch, G, H, B, T0, W, splits, windows, seed, scale_mode=
             # (seeded inputs: no score pair at the cut is closer than the EMA tolerance)
             assert np.array_equal(ex["pos"], u.pos.astype(np.int32)), f"decode {step} unit {(b, g)}: kept set differs"
         pos += 1
+    assert kv.counters(check=False).device_errors == 0
     kv.close()
 
 
@@ -1207,13 +1208,79 @@ def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
 @pytest.mark.parametrize("G,H,B,T0,W,splits,tqs", [
     (4, 1, 1, 705, 0, 1, (16, 3)), (4, 1, 1, 706, 0, 1, (16,)),       # 24 tiles of two row groups kept, one more not; a lone INT8 slot
     (1, 1, 1, 1441, 0, 1, (32, 17)), (1, 1, 1, 1442, 0, 1, (32,)),    # 48 of one row group
-    (4, 1, 1, 352, -1, 1, (16,)), (4, 1, 1, 353, -1, 1, (16,)),       # FP16 tiles only
+    (4, 1, 1, 352, -1, 1, (16,)), (4, 1, 1, 353, -1, 1, (16,)), (4, 1, 1, 368, -1, 1, (16,)), (4, 1, 1, 369, -1, 1, (16,)),   # FP16 tiles only
     (3, 2, 2, 1500, 100, 4, (17, 9)),                                 # three rounds, the last of FP16 tiles only; 51 and 27 rows
-    (1, 1, 1, 5, 2, 4, (20,)),                                        # splits without a slot
+    (1, 1, 1, 5, 2, 4, (20,)),                                        # 25 slots
 ])
 def test_attend_chunk_scores_kept(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     """The many-rows kernel that keeps its probabilities in registers, up to its last tile, and the one beyond."""
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=29 * G + T0)
+
+
+def _imported_chunk(lib, torch, G, tq, splits, W, units, seed):
+    """One call of tq tokens on imported units (a sequence each): units[b] = (slots, FP16 ones of them)."""
+    D, B = 128, len(units)
+    room = max(n for n, _ in units) + tq
+    os.environ["CONF_KV_SPLITS"] = str(splits)
+    try:
+        kv = _mk(lib, batch=B, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=W, capacity=(room + tq + 71) // 64 * 64, protected_window=4,
+                 n_tight=[room], n_loose=[room], max_chunk=tq)
+    finally:
+        os.environ.pop("CONF_KV_SPLITS", None)
+    rng = np.random.default_rng(seed)
+    normal = lambda *shape: rng.standard_normal(shape).astype(np.float16)
+    held = []
+    for b, (n, n16) in enumerate(units):
+        u = O.load_prefill(normal(n, D), normal(n, D), n16, rng.random(n).astype(np.float32))
+        kv.import_unit(0, b, 0, {x: getattr(u, x) for x in ("n", "pos", "ema", "is16", "k16", "v16", "k8", "v8", "ks", "vs")})
+        held.append(u)
+    q, kn, vn = normal(B, tq, G, D), normal(B, tq, 1, D), normal(B, tq, 1, D)
+    out = torch.zeros((B, tq, G, D), dtype=torch.float16, device="cuda")
+    kv.attend_chunk(0, torch.from_numpy(q).cuda(), torch.from_numpy(kn).cuda(), torch.from_numpy(vn).cuda(), out)
+    got = out.cpu().numpy().astype(np.float64)
+    assert kv.counters(check=False).device_errors == 0
+    for b, u in enumerate(held):
+        ref, _ = O.attend_chunk_unit(u, q[b], kn[b, :, 0], vn[b, :, 0], max(n for n, _ in units), f32(1 / math.sqrt(D)), f32(0.9))
+        err = np.max(np.abs(got[b] - ref) / (1e-3 + 2e-3 * np.abs(ref)))
+        assert err <= 1.0, f"sequence {b}: out off by {err:.3g} x tol"
+        ex, e_ref = kv.export(0, b, 0, planes=("pos", "ema")), u.ema.astype(np.float64)
+        assert np.array_equal(ex["pos"], u.pos.astype(np.int32))
+        e_err = np.abs(ex["ema"].astype(np.float64) - e_ref)
+        assert np.all(e_err <= 1e-8 + 5e-6 * e_ref), f"sequence {b}: EMA off, max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
+    kv.close()
+
+
+@pytest.mark.parametrize("G,tq,splits,W,n,n16", [
+    (4, 16, 2, 144, 1314, 129), (4, 16, 4, 32, 2865, 16), (4, 16, 4, 96, 2786, 65), (4, 16, 8, 64, 5720, 16),
+    (4, 16, 16, 128, 11424, 24), (4, 8, 4, 32, 5929, 8), (4, 8, 8, 64, 11856, 8),          # a tile more than with a full window
+    (4, 16, 2, 128, 1283, 97), (4, 16, 4, 32, 2821, 16), (4, 16, 8, 64, 5641, 16),
+    (4, 8, 2, 64, 2883, 33), (4, 8, 4, 32, 5893, 8),                                       # all that are kept
+])
+def test_many_rows_units_with_fewer_fp16_slots(lib, torch_cuda, G, tq, splits, W, n, n16):
+    """A unit that an import left with fewer FP16 slots than its window has more INT8 tiles: one more than the 48 / (groups of 32
+    rows) that the kernel with kept probabilities holds, or just those.  (n slots with the call's own, n16 of them FP16.)"""
+    say(f"fewer FP16 slots G={G} tq={tq} splits={splits} W={W} n={n} n16={n16}")
+    _imported_chunk(lib, torch_cuda, G, tq, splits, W, [(n - tq, n16 - tq)], seed=n)
+
+
+@pytest.mark.parametrize("G,tq,splits,units", [
+    (4, 5, 8, ((700, 20), (0, 0), (1, 1), (40, 3))),       # 20 rows: five, six FP16 slots in eight splits
+    (4, 9, 16, ((1500, 8), (0, 0), (2, 0), (33, 0))),      # 36 rows: nine in sixteen
+])
+def test_many_rows_splits_without_a_slot(lib, torch_cuda, G, tq, splits, units):
+    """A long unit asks for splits that a short one in the same layer has no slot for: they publish statistics of nothing."""
+    say(f"splits without a slot G={G} tq={tq} splits={splits} units={units}")
+    _imported_chunk(lib, torch_cuda, G, tq, splits, 32, units, seed=tq)
+
+
+@pytest.mark.parametrize("G,H,B,T0,W,splits,first,tq", [
+    (4, 8, 8, 2849, 128, 0, 2784, 16),                     # 64 units, the default four splits
+    (4, 1, 1, 2858, 128, 4, 2800, 16), (4, 1, 1, 2881, 32, 4, 2834, 16), (4, 1, 1, 5985, 64, 4, 5920, 8),
+])
+def test_observe_ahead_of_the_last_fp16_slots(lib, torch_cuda, G, H, B, T0, W, splits, first, tq):
+    """A window that ends inside the FP16 slots sees fewer of them than the cache holds, and a tile more than the kernel with
+    kept probabilities has room for."""
+    _observe_case(lib, torch_cuda, G, H, B, T0, W, splits, ((first, tq),), seed=T0, decode_after=0)
 
 
 @pytest.mark.parametrize("H,B", [(16, 1), (4, 4)])
