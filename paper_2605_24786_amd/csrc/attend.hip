@@ -592,6 +592,15 @@ __device__ __forceinline__ float exp_nonpos(float x) {
   const float r = __builtin_amdgcn_exp2f(p);
   return fmaf(r, d, r);
 }
+// The same to the bit down to -100, where a NaN must show and -inf must weigh nothing (probabilities of an output, whose sum nothing
+// else carries a NaN into).  Not the argument is bounded, whose maximum would take a NaN for -100, but the correction, which
+// is no number where the argument is infinite.
+__device__ __forceinline__ float exp_nonpos_or_nan(float x) {
+  const float p = x * 1.44269502e+00f;
+  const float d = fmaxf(fmaf(-p, -1.90465430e-09f, fmaf(-p, 6.93147182e-01f, x)), -1e-4f);
+  const float r = __builtin_amdgcn_exp2f(p);
+  return fmaf(r, d, r);
+}
 // 1 / x for a positive, finite double to about 1e-15 relative: the fp32 reciprocal estimate and two
 // Newton steps (a correctly rounded division costs ten times the instructions and nothing
 // downstream is that exact).

@@ -253,7 +253,7 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
         for (int r = 0; r < 2; ++r) {
           floatx4_t e;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) e[i] = exp_nonpos(x[r][i]);
+          for (int i = 0; i < 4; ++i) e[i] = exp_nonpos_or_nan(x[r][i]);
           if (is_edge(it)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)

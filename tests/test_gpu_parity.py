@@ -1283,6 +1283,79 @@ def test_observe_ahead_of_the_last_fp16_slots(lib, torch_cuda, G, H, B, T0, W, s
     _observe_case(lib, torch_cuda, G, H, B, T0, W, splits, ((first, tq),), seed=T0, decode_after=0)
 
 
+_ODD_CALLS = ["nan key", "inf key", "nan new key", "nan query", "nan value", "nan key scale"]
+
+
+def _odd_call(lib, torch, kind, G, T0, W, tq):
+    """A call of tq tokens on a cache or with inputs that hold one value that is no finite number: NaN, both infinities and
+    finite numbers where the single-token steps that define the call have them."""
+    D = 128
+    say(f"odd call {kind} G={G} T0={T0} W={W} tq={tq}")
+    rng = np.random.default_rng(T0 + tq)
+    normal = lambda *shape: rng.standard_normal(shape).astype(np.float16)
+    K, V, q, kn, vn = normal(T0, D), normal(T0, D), normal(tq, G, D), normal(tq, D), normal(tq, D)
+    u = O.load_prefill(K, V, T0 if W < 0 else W, rng.random(T0).astype(np.float32))
+    at = T0 - 20                                            # an FP16 slot ahead of the last ones
+    if kind == "nan key":
+        u.k16[at, 3] = np.nan
+    elif kind == "inf key":
+        u.k16[at, 3] = np.inf                               # (rows whose third channel is negative score -inf there: no weight)
+    elif kind == "nan new key":
+        kn[9, 100] = np.nan
+    elif kind == "nan query":
+        q[5, G - 1, 7] = np.nan
+    elif kind == "nan value":
+        u.v16[at, 3] = np.nan
+    elif kind == "inf value":
+        u.v16[at, 3], u.v16[at, 90] = np.inf, -np.inf
+    elif kind == "nan key scale":
+        u.ks[5] = np.nan
+    elif kind == "inf value scale":
+        u.vs[5] = np.inf
+    view = {x: getattr(u, x) for x in ("n", "pos", "ema", "is16", "k16", "v16", "k8", "v8", "ks", "vs")}
+    on = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    got = []
+    os.environ["CONF_KV_SPLITS"] = "1"
+    try:
+        for chunk in (tq, 1):
+            kv = _mk(lib, n_q_heads=G, n_kv_heads=1, head_dim=D, fp16_window=W, capacity=(2 * T0 + 2 * tq + 63) // 64 * 64, protected_window=4,
+                     n_tight=[T0 + tq], n_loose=[T0 + tq], max_chunk=chunk)
+            kv.import_unit(0, 0, 0, view)
+            out = torch.zeros((1, tq, G, D), dtype=torch.float16, device="cuda")
+            for t in range(0, tq, chunk):
+                o = out[:, t:t + chunk].clone()
+                if chunk > 1:
+                    kv.attend_chunk(0, on(q[None]), on(kn[None, :, None]), on(vn[None, :, None]), o)
+                else:
+                    kv.attend(0, on(q[None, t]), on(kn[None, t, None]), on(vn[None, t, None]), o)
+                    if t + 1 < tq:
+                        kv.evict_compact()
+                out[:, t:t + chunk] = o
+            assert kv.counters(check=False).device_errors == 0
+            got.append((out.cpu().numpy().astype(np.float64)[0], kv.export(0, 0, 0, planes=("ema",))["ema"].astype(np.float64)))
+            kv.close()
+    finally:
+        os.environ.pop("CONF_KV_SPLITS", None)
+    (x, ema), (y, ema_ref) = got
+    for odd in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(odd(x), odd(y)), f"{odd.__name__} in {odd(x).sum()} places, {odd(y).sum()} expected"
+    fine = np.isfinite(y)
+    assert not fine.all() and np.all(np.abs(x - y)[fine] <= (2e-3 + 4e-3 * np.abs(y))[fine])
+    # (a row that is no number marks the call's later tokens too: one sum over all rows)
+    assert np.array_equal(np.isnan(ema[:T0]), np.isnan(ema_ref[:T0])) and np.isnan(ema)[np.isnan(ema_ref)].all()
+
+
+@pytest.mark.parametrize("kind", _ODD_CALLS)
+@pytest.mark.parametrize("G,T0,W,tq", [
+    (1, 200, 40, 16), (1, 200, 40, 17), (4, 300, 40, 16),  # one matrix-core tile of rows; kept probabilities, one and two groups
+    (1, 1700, 40, 20),                                     # two passes
+])
+def test_calls_with_values_that_are_no_numbers(lib, torch_cuda, G, T0, W, tq, kind):
+    """A broken value shows in the same rows and slots however many tokens a call carries.  (Single steps demote as they go, to
+    behind the odd slot: what the two differ by is the rounding of some codes.)"""
+    _odd_call(lib, torch_cuda, kind, G, T0, W, tq)
+
+
 @pytest.mark.parametrize("H,B", [(16, 1), (4, 4)])
 def test_many_rows_calls_on_two_streams(lib, torch_cuda, H, B):
     """Two managers on two streams, each call half of the CUs with splits that wait for one another: the same outputs and
