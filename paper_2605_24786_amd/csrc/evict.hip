@@ -1083,15 +1083,19 @@ __device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t
 // 12.3 -> 12.0, 8192 of 130 to 2049 losing one or two 24.5 -> 22.0 (what is left there is the chain of a unit: counters, importances,
 // bounds, positions, the selection); whole decode steps 1.00 to 1.04 times as fast on 1024 to 8192 units of 130 to 2200 slots.
 constexpr int kLazyRounds = 32, kLazySlots = kLazyRounds * kWave;
-__device__ __forceinline__ double dpp_min(double v) {      // over the 16 lanes of a row
+typedef unsigned long long rank_key_t;                 // of a score that is no negative number: its bits (a NaN: behind all)
+__device__ __forceinline__ rank_key_t dpp_min(rank_key_t v) {   // over the 16 lanes of a row
 #define CONFKV_DPP(v, ctrl)                                                                                   \
-  __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),                         \
-                   __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true))
-  v = fmin(v, CONFKV_DPP(v, 0xB1));     // quad_perm [1,0,3,2]
-  v = fmin(v, CONFKV_DPP(v, 0x4E));     // quad_perm [2,3,0,1]
-  v = fmin(v, CONFKV_DPP(v, 0x141));    // row_half_mirror
-  return fmin(v, CONFKV_DPP(v, 0x140));  // row_mirror
+  ((rank_key_t)(unsigned)__builtin_amdgcn_mov_dpp((int)(v >> 32), ctrl, 0xf, 0xf, true) << 32 |               \
+   (unsigned)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xf, 0xf, true))
+  v = min(v, CONFKV_DPP(v, 0xB1));      // quad_perm [1,0,3,2]
+  v = min(v, CONFKV_DPP(v, 0x4E));      // quad_perm [2,3,0,1]
+  v = min(v, CONFKV_DPP(v, 0x141));     // row_half_mirror
+  return min(v, CONFKV_DPP(v, 0x140));  // row_mirror
 #undef CONFKV_DPP
+}
+__device__ __forceinline__ rank_key_t lane_value(rank_key_t v, int lane) {
+  return (rank_key_t)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32 | (unsigned)__builtin_amdgcn_readlane((int)v, lane);
 }
 __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
@@ -1104,10 +1108,10 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
   const int p_last = pos[ring_row_u(hm, ncand - 1, cap)];
 #pragma unroll
   for (int r = 0; r < kLazyRounds; ++r) a[r] = ema[ring_row_u(hm, min(r * kWave + lane, ncand - 1), cap)];   // (past the end: the last one again)
-  float lo = a[0], hi = a[0];
+  float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-  for (int r = 1; r < kLazyRounds; ++r) {
-    lo = a[r] < lo ? a[r] : lo;                        // (no NaN in an importance: plain compares)
+  for (int r = 0; r < kLazyRounds; ++r) {
+    lo = a[r] < lo ? a[r] : lo;                        // (plain compares leave a NaN out, as in the other kernels)
     hi = a[r] > hi ? a[r] : hi;
   }
   const double a_lo = (double)wave_min(lo), p_lo = (double)__builtin_amdgcn_readfirstlane(pos0);
@@ -1116,17 +1120,18 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
   const Divisor a_div = make_divisor(a_rng == 0.0 ? 1.0 : a_rng), p_div = make_divisor(p_rng == 0.0 ? 1.0 : p_rng);
   auto recency = [&](int ps) { return __dmul_rn(oma, p_rng == 0.0 ? 0.0 : quotient(__dsub_rn((double)ps, p_lo), p_div)); };
   auto mass = [&](float x) { return __dmul_rn(alpha, a_rng == 0.0 ? 0.0 : quotient(__dsub_rn((double)x, a_lo), a_div)); };
-  // (an infinite importance leaves keys that are no numbers: the largest, as in the other kernels)
-  auto key_of = [&](double m, double r) { return fmin(__dadd_rn(m, r), 1.7976931348623157e308); };
-  double key[kSmallE];
+  // (bits, as in the other kernels: scores that are no numbers, of importances that are not finite, are the largest)
+  auto key_of = [&](double m, double r) { return (rank_key_t)__double_as_longlong(__dadd_rn(m, r)); };
+  constexpr rank_key_t kNone = ~0ull;
+  rank_key_t key[kSmallE];
   int at[kSmallE];
 #pragma unroll
-  for (int k = 0; k < kSmallE; ++k) { key[k] = INFINITY; at[k] = 0x7fffffff; }
+  for (int k = 0; k < kSmallE; ++k) { key[k] = kNone; at[k] = 0x7fffffff; }
   if (lane < ncand) { key[0] = key_of(mass(a[0]), recency(pos0)); at[0] = lane; }
   // one key of each row of sixteen lanes: the largest of the four is not below the fourth lowest
-  const double low = dpp_min(key[0]);
-  const double q0 = lane_value(low, 0), q1 = lane_value(low, 16), q2 = lane_value(low, 32), q3 = lane_value(low, 48);
-  const double most = e == 1 ? fmin(fmin(q0, q1), fmin(q2, q3)) : fmax(fmax(q0, q1), fmax(q2, q3));
+  const rank_key_t low = dpp_min(key[0]);
+  const rank_key_t q0 = lane_value(low, 0), q1 = lane_value(low, 16), q2 = lane_value(low, 32), q3 = lane_value(low, 48);
+  const rank_key_t most = e == 1 ? min(min(q0, q1), min(q2, q3)) : max(max(q0, q1), max(q2, q3));
   const double first = recency(starts);                // lane r: of round r's first slot
   asm("" : "+s"(hm));                                  // (rows anew: kept from the importances' loads they would take a register per round)
   asm("" : "+v"(lane));
@@ -1151,12 +1156,12 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
     for (int q = 0; q < kGroup; ++q) {
       if (!(need >> q & 1u)) continue;
       int s = (r0 + q) * kWave + lane;
-      double k = s < ncand ? key_of(mass(a[r0 + q]), recency(ps[q])) : INFINITY;
+      rank_key_t k = s < ncand ? key_of(mass(a[r0 + q]), recency(ps[q])) : kNone;
       // into the lane's list, behind its equals: slots rise within a lane
 #pragma unroll
       for (int x = 0; x < kSmallE; ++x) {
         const bool lower = k < key[x];
-        const double kk = key[x];
+        const rank_key_t kk = key[x];
         const int ss = at[x];
         key[x] = lower ? k : kk;
         at[x] = lower ? s : ss;
@@ -1169,11 +1174,11 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
   for (int p = 0; p < kSmallE; ++p) {
     ev[p] = 0x7fffffff;
     if (p < e) {                                       // uniform over the wavefront
-      double best = key[0];
+      rank_key_t best = key[0];
       int slot = at[0];
 #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) {
-        const double ok = __shfl_xor(best, m, kWave);
+        const rank_key_t ok = __shfl_xor(best, m, kWave);
         const int oi = __shfl_xor(slot, m, kWave);
         if (ok < best || (ok == best && oi < slot)) {
           best = ok;
@@ -1184,7 +1189,7 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
       if (at[0] == slot) {
 #pragma unroll
         for (int x = 1; x < kSmallE; ++x) { key[x - 1] = key[x]; at[x - 1] = at[x]; }
-        key[kSmallE - 1] = INFINITY;
+        key[kSmallE - 1] = kNone;
         at[kSmallE - 1] = 0x7fffffff;
       }
     }

@@ -1041,6 +1041,45 @@ def test_small_ranking_reads_positions_that_matter(lib, torch_cuda, n, P, evict,
     kv.close()
 
 
+@pytest.mark.parametrize("n,P,evict,odd", [
+    (400, 8, 3, range(64)), (400, 8, 4, range(0, 130)), (2060, 12, 4, range(5, 700)), (300, 4, 2, (0, 150, 295)), (70, 6, 1, range(64)),
+    (2061, 12, 4, range(64)),                                          # one candidate beyond the registers
+    (40, 4, 3, range(36)), (100, 4, 4, range(96)),                     # no finite importance at all
+])
+def test_small_ranking_of_nan_importances(lib, torch_cuda, n, P, evict, odd):
+    """Slots whose importance is NaN rank last, by slot, and the others by what is finite, whichever kernel has the units: a workgroup
+    per unit (768 of them) or a wavefront (776)."""
+    torch = torch_cuda
+    H, D, T0 = 8, 64, n - 1
+    say(f"ranking with NaN n={n} P={P} evict={evict} odd={odd}")
+    rng = np.random.default_rng(n + evict)
+    ema = rng.random((1, H, T0)).astype(np.float32)
+    ema[..., list(odd)] = np.nan
+    K = torch.randn((1, H, T0, D), device="cuda", dtype=torch.float16)
+    new = torch.randn((1, H, D), device="cuda", dtype=torch.float16)
+    out = torch.empty_like(new)
+    pos = np.arange(n - P)
+    for L in (96, 97):
+        kv = _mk(lib, n_layers=L, n_q_heads=H, n_kv_heads=H, head_dim=D, fp16_window=2, capacity=(n + 63) // 64 * 64,
+                 protected_window=P, n_tight=[n - evict] * L, n_loose=[n - evict] * L, alpha=0.65, ema_decay=1.0, mass_gain=0.0)
+        for l in range(L):
+            kv.load_prefill(l, K, K, torch.from_numpy(ema).cuda())
+            kv.attend(l, new, new, new, out)
+        kv.evict_compact()
+        for l in (0, L - 1):
+            for h in range(H):
+                e = ema[0, h, :n - P].astype(np.float64)
+                fine = ~np.isnan(e)
+                s = np.full(n - P, np.inf)
+                if fine.any():                                         # (ranges over the candidates whose importance is a number)
+                    lo, rng_ = e[fine].min(), np.ptp(e[fine])
+                    s[fine] = f32(0.65) * ((e[fine] - lo) / rng_) + (1.0 - f32(0.65)) * (pos[fine] / (n - P - 1))
+                gone = np.argsort(s, kind="stable")[:evict]
+                got = kv.export(l, 0, h, planes=("pos",))["pos"]
+                assert np.array_equal(got, np.setdiff1d(np.arange(n), gone).astype(np.int32)), (L, l, h)
+        kv.close()
+
+
 @pytest.mark.parametrize("L,B,H,ranker,scope,evict", [
     (96, 1, 8, "composite", "kv_head", 3), (97, 1, 8, "composite", "kv_head", 4),      # 768 units and 776
     (27, 38, 4, "composite", "kv_head", 2),                                            # 4104 units
