@@ -1198,9 +1198,10 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
 
 // kShared: the importance is the float64 sum over the kv-heads of the (layer, sequence), which
 // shared_mass_kernel left in shared_all (indexed by slot, not by ring row).
-// kBatch: loads a lane has in flight at a time, of units beyond lowest_lazily (8 keeps the registers few enough for thousands of
+// kBatch: loads a lane has in flight at a time (8 keeps the registers few enough for thousands of
 // units per launch; 32 covers a 2048-slot unit in one round trip per pass where there are fewer).
-template <bool kShared, int kBatch = 8, bool kRandom = false>
+// kLazy: launches whose units all have at most kLazySlots candidates (an instantiation of its own: it takes 35 registers more).
+template <bool kShared, int kBatch = 8, bool kRandom = false, bool kLazy = false>
 __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, LayerMask appended,
                                                                 double alpha,
                                                                 const double *__restrict__ shared_all,
@@ -1238,13 +1239,16 @@ __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, La
   const double *shared = kShared ? shared_all + (size_t)(u / cv.Hkv) * cv.cap : nullptr;
   const int hm = uw.head, cap = cv.cap;                // slot i of the per-slot planes: ring_row_u(hm, i, cap)
   const int nx = cv.cap8 == 0 ? n : n8;              // slots of the ring a right shift could serve
-  if constexpr (!kShared && !kRandom && kBatch == 8) {
-    if (ncand <= kLazySlots) {
-      int ev[kSmallE];
-      lowest_lazily(ema, pos, hm, cap, ncand, e, alpha, lane, ev);
-      finish_small<kWave>(cv, u, sel, src_all, n, n8, nx, e, ev, lane);
+  if constexpr (kLazy) {
+    static_assert(!kShared && !kRandom, "the unit's own importance");
+    if (ncand > kLazySlots) {                          // (the launch's bound says there is none)
+      if (lane == 0) sel[7] = 0;
       return;
     }
+    int ev[kSmallE];
+    lowest_lazily(ema, pos, hm, cap, ncand, e, alpha, lane, ev);
+    finish_small<kWave>(cv, u, sel, src_all, n, n8, nx, e, ev, lane);
+    return;
   }
   // loads go out in batches of kBatch (indices past the end re-read the last candidate), so a
   // long unit costs a few memory round trips per pass and not one per 64 slots
@@ -1975,7 +1979,10 @@ hipError_t launch_evict_compact(const CacheView &cv, const LayerMask &appended, 
   if (small_wg(U, n_max, false, false))
     hipLaunchKernelGGL((rank_small_wg_kernel<false>), dim3(U), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, rr);
-  else if (U <= 4096 && n_max - cv.P > kLazySlots)    // few wavefronts per SIMD: registers to spare for deeper batches
+  else if (n_max - cv.P <= kLazySlots)
+    hipLaunchKernelGGL((rank_small_kernel<false, 8, false, true>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended,
+                       alpha, (const double *)nullptr, src, sel, U, 0, rr);
+  else if (U <= 4096)    // few wavefronts per SIMD: registers to spare for deeper batches
     hipLaunchKernelGGL((rank_small_kernel<false, 32>), dim3((U + 3) / 4), dim3(kEvThreads), 0, stream, cv, appended,
                        alpha, (const double *)nullptr, src, sel, U, 0, rr);
   else
