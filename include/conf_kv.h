@@ -292,11 +292,12 @@ int conf_kv_observe(conf_kv_handle *h, int32_t layer, int32_t first, int32_t tq,
  * prompt-phase observation as the neighbouring idea, the paper's own update is "using A" per
  * decode step): every prompt query observes the prompt causally, as conf_kv_observe over the
  * consecutive windows first = 0, max_chunk, 2 max_chunk, .. covering all T0 cached tokens would
- * leave it, in one to four launches.  dev_q16: fp16 [B][T0][Hq][D], the queries of all prompt
+ * leave it, in one to five launches.  dev_q16: fp16 [B][T0][Hq][D], the queries of all prompt
  * tokens.  The result is what T0 single-token decode steps over the stored prompt would have left
  * (see conf_kv_attend_chunk for the telescoped update), rounded to fp32 once; normalisers and the
  * sums over heads and tokens are float64 (queries so far back that all of them together add less than
- * half of the smallest fp32 number to any slot are left out).  (A prompt that fits one conf_kv_observe call may run as
+ * half of the smallest fp32 number to any slot are left out; one that is NaN or infinite still makes the
+ * importance of every slot its token sees NaN).  (A prompt that fits one conf_kv_observe call may run as
  * one, with that kernel's sums.)  Same call order rules and errors as conf_kv_observe; needs
  * max_chunk >= 2 (or a group of more than 8 heads). */
 int conf_kv_observe_prompt(conf_kv_handle *h, int32_t layer, const void *dev_q16, conf_kv_stream stream);

@@ -10,7 +10,8 @@
 // every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
 // chip idle, which two small kernels join.  Both recompute the scores on the matrix cores (nothing of
 // size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
-// wavefront and of 64 slots per workgroup, 170 to 175 us in these four with all rows, 111 with those that count.
+// wavefront and of 64 slots per workgroup, 170 to 175 us in these four with all rows; with those that count
+// 111, and 6 for the fifth launch, which looks at the other rows' queries (observe_odd_kernel).
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
@@ -708,6 +709,44 @@ __global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, 
   cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, slot)] = (float)A;
 }
 
+// The rows ahead of the first that counts (observe_first_block) weigh nothing, unless they are no numbers: a query that is NaN or
+// infinite leaves no number in any slot that its token sees, as in the kernels above.  Reads the queries of those tokens once, a
+// workgroup kOddTokens of a kv-head (3001 tokens of 32 heads, 23 MB: 4.6 us); nearly always that is all.
+constexpr int kOddTokens = 32, kOddBatch = 8;
+__global__ __launch_bounds__(kObsThreads) void observe_odd_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, int tokens) {
+  constexpr int D = 128, kPieces = D / 8;
+  __shared__ int s_last;
+  const int tid = threadIdx.x, g = blockIdx.x % cv.Hkv, tok0 = (int)(blockIdx.x / cv.Hkv) * kOddTokens, b = blockIdx.z, G = cv.G;
+  const int pieces = (min(tok0 + kOddTokens, tokens) - tok0) * G * kPieces;
+  if (tid == 0) s_last = -1;
+  __syncthreads();
+  int last = -1;
+  for (int base = tid; base < pieces; base += kOddBatch * kObsThreads) {
+    confkv_v4i x[kOddBatch];
+    int tok[kOddBatch];
+#pragma unroll
+    for (int k = 0; k < kOddBatch; ++k) {
+      const int p = min(base + k * kObsThreads, pieces - 1), row = p / kPieces, head = row % G;
+      tok[k] = tok0 + row / G;
+      x[k] = *(const confkv_v4i *)(q + ((((size_t)b * T + tok[k]) * cv.Hkv + g) * G + head) * D + p % kPieces * 8);
+    }
+#pragma unroll
+    for (int k = 0; k < kOddBatch; ++k) {
+      half2_t sum = {0, 0};                              // finite numbers times 0
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, (int)x[k][i]), half2_t{0, 0}, sum);
+      if (!(sum[0] == 0 && sum[1] == 0)) last = tok[k];  // (tokens rise)
+    }
+  }
+  if (last >= 0) atomicMax(&s_last, last);
+  __syncthreads();
+  if (s_last < 0) return;
+  const int u = (layer * cv.B + b) * cv.Hkv + g;
+  const ObserveUnit un = observe_unit(cv, u, T);
+  for (int slot = tid; slot <= s_last; slot += kObsThreads)
+    cv.ema[(size_t)u * cv.cap + slot_row(cv, cv.pt, un.h8, un.n8, un.h16, slot)] = NAN;
+}
+
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, size_t scratch_floats, hipStream_t stream) {
   if (cv.D != 128 || cv.page_lg || T < 1) return hipErrorInvalidValue;
@@ -740,11 +779,13 @@ hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q
     const dim3 grid(cv.Hkv * plan.subtiles, 1, cv.B);
     if (cv.chan) hipLaunchKernelGGL(observe_mass_short_kernel<true>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, b0, stats);
     else hipLaunchKernelGGL(observe_mass_short_kernel<false>, grid, dim3(kMassShortThreads), 0, stream, cv, layer, q, T, sm, b0, stats);
-    return hipGetLastError();
+  } else {
+    if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
+    else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
+    if (parts > 1)
+      hipLaunchKernelGGL(observe_sum_kernel, dim3(cv.Hkv * ((T + kObsThreads - 1) / kObsThreads), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, T, b0, parts, stats);
   }
-  if (cv.chan) hipLaunchKernelGGL(observe_mass_kernel<true>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
-  else hipLaunchKernelGGL(observe_mass_kernel<false>, slots, dim3(kObsThreads), 0, stream, cv, layer, q, T, sm, ntiles, width, b0, parts, stats);
-  if (parts > 1)
-    hipLaunchKernelGGL(observe_sum_kernel, dim3(cv.Hkv * ((T + kObsThreads - 1) / kObsThreads), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, T, b0, parts, stats);
+  if (const int tokens = b0 / cv.G * 16)
+    hipLaunchKernelGGL(observe_odd_kernel, dim3(cv.Hkv * ((tokens + kOddTokens - 1) / kOddTokens), 1, cv.B), dim3(kObsThreads), 0, stream, cv, layer, q, T, tokens);
   return hipGetLastError();
 }

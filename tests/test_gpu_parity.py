@@ -737,22 +737,41 @@ def test_observe_prompt_rows_out_of_reach(lib, torch_cuda, G, H, B, T0, W, scale
     _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales, decay)
 
 
-def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales, decay=0.9):
+@pytest.mark.parametrize("G,H,B,T0,W,scales,decay,odd", [
+    (4, 2, 2, 1500, 37, "token", 0.9, ((1, 100, 3, np.nan), (0, 700, 5, np.inf), (0, 31, 4, np.nan))),
+    (1, 2, 1, 180, -1, "token", 0.5, ((0, 15, 1, -np.inf),)),          # the last token that is left out
+    (1, 2, 1, 180, -1, "token", 0.5, ((0, 16, 0, np.nan),)),           # the first that counts
+    (2, 4, 17, 230, 64, "token", 0.5, ((0, 0, 0, np.nan), (16, 63, 7, np.inf))),
+    (3, 1, 2, 700, 8, "channel", 0.8, ((1, 543, 2, np.nan),)),
+    (16, 2, 1, 600, 600, "token", 0.1, ((0, 320, 17, np.nan), (0, 99, 31, np.inf), (0, 321, 20, -np.inf))),
+])
+def test_observe_prompt_odd_queries_out_of_reach(lib, torch_cuda, G, H, B, T0, W, scales, decay, odd):
+    """A query that is no finite number leaves no number in the slots that its token sees, however little its row weighs."""
+    _observe_prompt_units(lib, torch_cuda, G, H, B, T0, W, scales, decay, odd)
+
+
+def _observe_prompt_units(lib, torch, G, H, B, T0, W, scales, decay=0.9, odd=()):
     D = 128
-    say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales} decay={decay}")
+    say(f"observe_prompt units G={G} Hkv={H} B={B} T0={T0} W={W} scales={scales} decay={decay} odd={odd}")
     kv = _mk(lib, batch=B, n_q_heads=G * H, n_kv_heads=H, head_dim=D, fp16_window=W, capacity=((T0 + 71) // 64) * 64,
              protected_window=4, n_tight=[T0], n_loose=[T0], max_chunk=2, scale_mode=scales, ema_decay=decay)
     rng = np.random.default_rng(T0 + G)
     K = rng.standard_normal((B, H, T0, D)).astype(np.float16)
     q = (rng.standard_normal((B, T0, G * H, D)) * 1.5).astype(np.float16)
     kv.load_prefill(0, torch.from_numpy(K).cuda(), torch.from_numpy(K).cuda())
-    kv.observe_prompt(0, torch.from_numpy(q).cuda())
+    q_in = q.copy()
+    for n, (b, tok, head, value) in enumerate(odd):
+        q_in[b, tok, head, (37 * n + 127) % D] = value
+    kv.observe_prompt(0, torch.from_numpy(q_in).cuda())
     for b in range(B):
         for g in range(H):
             u = O.load_prefill(K[b, g], K[b, g], W, scale_mode=scales)
             O.observe_unit(u, q[b, :, g * G:(g + 1) * G], 0, f32(1 / math.sqrt(D)), f32(decay))
-            e_ref = u.ema.astype(np.float64)
-            e_err = np.abs(kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64) - e_ref)
+            seen = max((tok + 1 for ob, tok, head, _ in odd if (ob, head // G) == (b, g)), default=0)
+            got = kv.export(0, b, g, planes=("ema",))["ema"].astype(np.float64)
+            assert np.isnan(got[:seen]).all(), f"unit {(b, g)}: {np.isnan(got).sum()} slots of {seen} show the query"
+            e_ref = u.ema.astype(np.float64)[seen:]
+            e_err = np.abs(got[seen:] - e_ref)
             assert np.all(e_err <= 1e-8 + 1e-5 * e_ref), f"unit {(b, g)}: EMA off, max rel {np.max(e_err / (e_ref + 1e-30)):.3g}"
     assert kv.counters().device_errors == 0
     kv.close()
