@@ -139,9 +139,6 @@ static ObservePlan observe_plan(int units_per_layer, int G, int T, int b0, int n
 size_t observe_plan_floats(int units_per_layer, int G, int T, int b0, int n8, int chan, size_t have, int cus) {
   return observe_plan(units_per_layer, G, T, b0, n8, chan != 0, have, cus).floats;
 }
-size_t observe_plan_floats(int units_per_layer, int G, int T, int n8, int chan, size_t have, int cus) {
-  return observe_plan_floats(units_per_layer, G, T, 0, n8, chan, have, cus);
-}
 static int device_cus();                                // (below, with the attention plans)
 
 // The slots of a unit come in tiles: first the INT8 ones, then the FP16 ones.

@@ -40,7 +40,7 @@ struct AttendPlan {
   bool mfma;         // matrix-core body for the INT8 slots
   bool two_launch;   // stream + publish, then merge + EMA in a second launch (scores in scratch)
   int wide_groups;   // > 0: the many-rows kernel with that many groups of 32 query rows per unit
-  bool wide_kept;    // its form that keeps the raw scores in registers
+  bool wide_kept;    // its form that keeps the probabilities in registers
 };
 struct AttendLaunch {
   int layer;
@@ -98,7 +98,6 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const Atten
 size_t observe_scratch_floats(int units_per_layer, int G, int cap);
 int observe_first_block(int G, int T, double decay, double gain);
 size_t observe_plan_floats(int units_per_layer, int G, int T, int b0, int n8, int chan, size_t have, int cus);
-size_t observe_plan_floats(int units_per_layer, int G, int T, int n8, int chan, size_t have, int cus);
 hipError_t launch_observe_prompt(const CacheView &cv, int layer, const __half *q, int T, float sm, double decay, double gain,
                                  float *scratch, size_t scratch_floats, hipStream_t stream);
 

@@ -71,9 +71,11 @@ def test_prompt_phase_scratch(clib):
                        n_tight=[cap // 4] * L, n_loose=[cap // 2] * L, max_chunk=2)
         assert clib.conf_kv_scratch_bytes(C.byref(cfg)) / 1e6 == pytest.approx(mb, abs=1e-3)
     have = getattr(clib, "_ZN6confkv22observe_scratch_floatsEiii")
-    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiiimi")
+    plan = getattr(clib, "_ZN6confkv19observe_plan_floatsEiiiiiimi")
+    first = getattr(clib, "_ZN6confkv19observe_first_blockEiidd")
     have.restype = plan.restype = C.c_size_t
-    have.argtypes, plan.argtypes = [C.c_int] * 3, [C.c_int] * 5 + [C.c_size_t, C.c_int]
+    have.argtypes, plan.argtypes = [C.c_int] * 3, [C.c_int] * 6 + [C.c_size_t, C.c_int]
+    first.restype, first.argtypes = C.c_int, [C.c_int, C.c_int, C.c_double, C.c_double]
     cut = 0
     for units in (1, 2, 3, 8, 40, 64, 256, 384):
         for G in (1, 3, 4, 8, 16):
@@ -85,9 +87,10 @@ def test_prompt_phase_scratch(clib):
                         continue
                     for chan in (0, 1):
                         for room in (3 * rows, 3 * rows + 5000, 6 * rows, 1 << 40):
-                            n = plan(units, G, T, T // 3, chan, room, 256)
-                            assert 3 * units * G * -(-T // 16) * 16 <= n <= room, (units, G, cap, T, chan, room)
-                            cut += n > 3 * units * G * -(-T // 16) * 16
+                            for b0 in {0, first(G, T, 0.9, 0.1)}:        # all rows, and those that count at lambda = 0.9
+                                n = plan(units, G, T, b0, T // 3, chan, room, 256)
+                                assert 3 * units * G * -(-T // 16) * 16 <= n <= room, (units, G, cap, T, b0, chan, room)
+                                cut += n > 3 * units * G * -(-T // 16) * 16
     assert cut > 1000
 
 

@@ -1270,7 +1270,7 @@ def test_attend_chunk_row_groups(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     (3, 2, 2, 1500, 100, 4, (17, 9)),                                 # three rounds, the last of FP16 tiles only; 51 and 27 rows
     (1, 1, 1, 5, 2, 4, (20,)),                                        # 25 slots
 ])
-def test_attend_chunk_scores_kept(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
+def test_attend_chunk_probabilities_kept(lib, torch_cuda, G, H, B, T0, W, splits, tqs):
     """The many-rows kernel that keeps its probabilities in registers, up to its last tile, and the one beyond."""
     _chunk_case(lib, torch_cuda, G, H, B, T0, W, splits, tqs, seed=29 * G + T0)
 
@@ -1509,7 +1509,7 @@ def test_many_rows_kernel_keeps_its_registers(lib, torch_cuda, RG):
 
 
 @pytest.mark.parametrize("RG", [1, 2])
-def test_kept_scores_stay_in_registers(lib, torch_cuda, RG):
+def test_kept_probabilities_stay_in_registers(lib, torch_cuda, RG):
     """No scratch memory: the probabilities of up to six tiles per wavefront are what the registers are for."""
     import ctypes as C
 
