@@ -169,7 +169,8 @@ typedef struct conf_kv_stats {
   uint64_t demoted;          /* tokens quantised FP16 -> INT8 by conf_kv_evict_compact         */
   uint64_t tight_steps;      /* sequence-steps that selected the tight budget                  */
   uint64_t loose_steps;      /* sequence-steps that selected the loose budget                  */
-  uint64_t device_errors;    /* bounded waits that expired inside kernels (0 in a healthy run) */
+  uint64_t device_errors;    /* bounded waits that expired inside kernels, and launches whose plan
+                                did not fit what they found (0 in a healthy run)               */
   uint64_t compact_bytes;    /* bytes read + written by the compaction's in-place row moves    */
 } conf_kv_stats;
 

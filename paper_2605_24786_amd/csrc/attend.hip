@@ -2095,7 +2095,7 @@ bool attend_wide_plan(int rows, int units_per_layer, int major_kv, int n_ub, int
     ns = 1;
     while (ns * 2 <= std::min(forced_splits, wide_max_splits(rg * kWideRows)) && ns * 2 * units_per_layer <= lim.cus && n_ub / (ns * 2) >= 64) ns *= 2;
   }
-  // (wherever they fit: 1.00 to 1.14 times as fast over 22 shapes, of one tile to all 48 / rg)
+  // (wherever they fit: 1.00 to 1.15 times as fast over 23 shapes, of one tile to all 48 / rg)
   plan->wide_kept = rg <= 2 && rows_tiles(n_ub, n16_least, n16_ub, ns) <= rows_rounds(rg) * kAttWaves;
   const size_t lds = plan->wide_kept ? attend_rows_lds_bytes(rg, ns) : attend_wide_lds_bytes(rg * kWideRows, ns);
   if (lds > lim.max_lds || attend_occupancy(attend_fn_wide(rg, plan->wide_kept), lds) < 1) return false;

@@ -6,12 +6,12 @@
 // each re-read the whole cache: 4.1 ms per layer.  But the stored cache does not change while its
 // prompt observes it, and the windows' updates telescope to
 //   a_i = gain * sum_{t >= i} lambda^(T-1-t) sum_h p_{t,h,i},
-// so launches over all queries (those whose weight an fp32 sum can show, observe_first_block) do: the first finds every row's softmax statistics, the second
-// every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
+// so launches over all queries whose weight an fp32 sum can show (observe_first_block) do: the first finds every row's softmax statistics,
+// the second every slot's weighted column sum, both in parts where one piece of work per rows or slots would leave the
 // chip idle, which two small kernels join.  Both recompute the scores on the matrix cores (nothing of
 // size T x T is stored).  A layer of that prompt with 32 query heads: 254 us in two launches of 16 rows per
 // wavefront and of 64 slots per workgroup, 170 to 175 us in these four with all rows; with those that count
-// 111, and 6 for the fifth launch, which looks at the other rows' queries (observe_odd_kernel).
+// 113, and 5 for the fifth launch, which looks at the other rows' queries (observe_odd_kernel).
 #pragma once
 
 constexpr int kObsThreads = 256, kObsWaves = kObsThreads / kWave;
@@ -81,7 +81,7 @@ static int observe_mass_parts(int units_per_layer, int G, int T, int b0, int mos
 // The first block of rows that counts, 0 for most prompts: a row's weight falls with lambda^(T-1-t), and the rows before it add
 // less than 2^-150 to any slot all together, half of the smallest number that fp32 holds, so the importance is the same to the
 // bit without them (a tie within 2^-150 of a rounding apart).  1000 tokens of 4 heads at lambda = 0.9, 10 500 at 0.99, all at 1.  A layer of
-// 3001 tokens, 32 query heads, 8 kv-heads: statistics 81 -> 47 us, columns 90 -> 55.
+// 3001 tokens, 32 query heads, 8 kv-heads: statistics 79 -> 48 us, columns 90 -> 56.
 int observe_first_block(int G, int T, double decay, double gain) {
   if (!(decay < 1.0)) return 0;
   double reach = 1.0;                                   // rows (tokens) that count
@@ -188,8 +188,8 @@ __device__ __forceinline__ void finish_row(const ObserveStats &stats, size_t row
 // are staged once for its eight blocks as fp16 in two alternating LDS buffers (one barrier per tile).
 // Scores come transposed, a lane's rows being slots of one query: one running reference and sum
 // per lane and block, no reduction inside the loop; the sum goes over to 64 bits with every tile.
-// 120 -> 81 us per layer of 3001 tokens and 32 heads with all rows, 47 with those that count; while a CU is busy, vector ALU and matrix cores are at work in
-// turn 93 % of the time.
+// 120 -> 79 us per layer of 3001 tokens and 32 heads with all rows, 48 with those that count; while a CU is busy, vector ALU and matrix
+// cores are at work in turn 88 % of the time.
 // Causal work falls along the list of items: long ones are cut into parts of their slots.
 // A score costs a multiply-add, a product with log2 e, one hardware exponential and one addition.
 // (log2 e folded into the slots' factors would save the product, but rounds the factor once more: an
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_join_kernel(CacheView cv,
 // 16 rows -- (token block, head), from the first that sees one of the slots, or a part of them --
 // come through LDS four at a time, staged once for the four wavefronts.  Each wavefront reading the
 // queries for itself asked 622 MB of L2 per layer of 3001 tokens and 32 heads, 5.2 TB/s, and 384 workgroups of
-// falling work ended late: 118 us, 90 now (55 with the rows that count), of which the vector ALU (ten instructions a score) works 55.
+// falling work ended late: 118 us, 90 with all rows and 56 with those that count, of which the vector ALU (ten instructions a score) works 70 %.
 // Every probability goes into its column's sum in 64 bits by itself.
 struct MassTile {
   int base, lim;                                       // slots [base, min(base + kMassWave, lim)) of subtile `at`
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kObsThreads) void observe_sum_kernel(CacheView cv, 
 
 // The rows ahead of the first that counts (observe_first_block) weigh nothing, unless they are no numbers: a query that is NaN or
 // infinite leaves no number in any slot that its token sees, as in the kernels above.  Reads the queries of those tokens once, a
-// workgroup kOddTokens of a kv-head (3001 tokens of 32 heads, 23 MB: 4.6 us); nearly always that is all.
+// workgroup kOddTokens of a kv-head (2000 of 3001 tokens with 32 heads, 16 MB: 4.7 us); nearly always that is all.
 constexpr int kOddTokens = 32, kOddBatch = 8;
 __global__ __launch_bounds__(kObsThreads) void observe_odd_kernel(CacheView cv, int layer, const __half *__restrict__ q, int T, int tokens) {
   constexpr int D = 128, kPieces = D / 8;

@@ -3,8 +3,8 @@
 // many-rows kernel (attend_wide.h), whose tiles and exchange it shares.
 //
 // That kernel gives every wavefront rows and a stream of tiles, so eight output partials meet in LDS, and a score is formed twice,
-// since no place holds rows x slots of them through the exchange: its second pass (keys read again, products again) is 10 us of
-// 37 for 64 rows against 64 units of 2064 slots in four splits.  Here a wavefront scores the tiles of its stream for its 32 rows,
+// since no place holds rows x slots of them through the exchange: its second pass (keys read again, products again) is 8 us of
+// 35 for 64 rows against 64 units of 2064 slots in four splits.  Here a wavefront scores the tiles of its stream for its 32 rows,
 // but the output it sums is 16 RG channels of those rows over ALL tiles: the probabilities of a round of eight tiles go
 // through LDS (over the keys, which have been used by then) against a reference that the streams share.  The output
 // takes 8 RG registers instead of 64, the probabilities 96 in their place, and nothing is merged at the end.  The importance
@@ -12,10 +12,10 @@
 // unit's maximum), one number per row and round, formed in 64 bits.  (Kept as scores, with the exponentials anew,
 // the last part took 8.6 us, now 2.)
 //
-// The launch above: 37.0 -> 33.4 us (kernel trace).  By leaving parts out: 12 for its bytes in three rounds, 5 for scores and
+// The launch above: 35.3 -> 33.5 us (medians of kernel traces; 33.0 without the look at infinite values).  By leaving parts out: 12 for its bytes in three rounds, 5 for scores and
 // probabilities, 5 for the output (3 with the probabilities rounded to fp16, see there), 4 for publishing, 4 for the exchange, 2 for the importance.  Rounds are vector instructions
 // (conversions, exponentials), LDS and matrix instructions in turn, since four barriers keep the wavefronts in step.  Whole steps of
-// eight layers, 17 to 64 rows, 1 to 192 units of 64 to 9000 slots: 1.00 to 1.14 times as fast.  Scores and probabilities of a round were
+// eight layers, 23 shapes of 17 to 64 rows, 1 to 192 units of 64 to 9000 slots: 1.00 to 1.15 times as fast (1.00 to 1.16 without that look).  Scores and probabilities of a round were
 // written out for each kind of tile at first: 240 KB of code, against 50.
 #pragma once
 

@@ -18,10 +18,11 @@
 // slot's column over the rows (weights lambda^(tq-1-token)) in its own registers and updates the
 // EMA: no barrier, no LDS but the rows' statistics.  Key bytes are therefore read twice, value bytes once.
 //
-// 64 rows against 64 units of 2064 slots in four splits (16 tokens of 4 heads): 35.5 us per launch in the kernel trace, of which
-// 17 for the first pass -- 5 until the first tiles are in LDS, then a round of eight in 3.5 to 5 -- 4.5 for the merge and
-// publishing, 4.5 for the exchange and 8 for the second pass; one sequence of 30 000 slots 79 us.  It uses all 256 registers, and
-// what must outlive the first pass is formed anew behind it: with 7 to 10 of them spilled the launch was 40 us.  With sixteen
+// Calls of up to 64 rows whose splits have at most 48 / RG tiles go to the kernel in attend_rows.h; this one serves the rest.
+// 64 rows against 64 units of 4112 slots in four splits (16 tokens of 4 heads): 54 us per launch in the kernel trace; one sequence of
+// 30 000 slots 79 us.  Of 35.3 against 2064 slots, which it served before: 17 for the first pass -- 5 until the first tiles are in
+// LDS, then a round of eight in 3.5 to 5 -- 4.5 for the merge and publishing, 4.5 for the exchange and 8 for the second pass.  It uses all 256 registers, and
+// what must outlive the first pass is formed anew behind it: with 7 to 10 of them spilled that launch was 40 us.  With sixteen
 // rows per wavefront, the scores the other way round, value codes converted by every reader and the second pass through
 // the same tiles and barriers it was 50 us (and 203).  Slower too: the second pass's keys requested ahead of the exchange, whose
 // polls then wait for them, and three splits' partials at once, 1.08 each.

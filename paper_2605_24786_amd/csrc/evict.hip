@@ -1080,7 +1080,7 @@ __device__ __forceinline__ void finish_small(const CacheView &cv, int u, int32_t
 // keys of the others in order.
 // Before, importances were read twice and positions once more with them for every eviction, three times the bytes for one eviction
 // and nine for four, in batches of eight or 32 rounds.  2048 units of 2052 slots losing four 31.1 -> 14.7 us, of 2049 losing one
-// 12.3 -> 12.0, 8192 of 130 to 2049 losing one or two 24.5 -> 22.0 (what is left there is the chain of a unit: counters, importances,
+// 14.6 -> 13.5, 8192 of them 39.9 -> 32.7, of 600 21.6 -> 20.9 (what is left there is the chain of a unit: counters, importances,
 // bounds, positions, the selection); whole decode steps 1.00 to 1.04 times as fast on 1024 to 8192 units of 130 to 2200 slots.
 constexpr int kLazyRounds = 32, kLazySlots = kLazyRounds * kWave;
 typedef unsigned long long rank_key_t;                 // of a score that is no negative number: its bits (a NaN: behind all)
@@ -1200,7 +1200,8 @@ __device__ __forceinline__ void lowest_lazily(const float *ema, const int32_t *p
 // shared_mass_kernel left in shared_all (indexed by slot, not by ring row).
 // kBatch: loads a lane has in flight at a time (8 keeps the registers few enough for thousands of
 // units per launch; 32 covers a 2048-slot unit in one round trip per pass where there are fewer).
-// kLazy: launches whose units all have at most kLazySlots candidates (an instantiation of its own: it takes 35 registers more).
+// kLazy: launches whose units all have at most kLazySlots candidates.  An instantiation of its own: it takes 37 registers more, with which
+// the loop for longer units has four wavefronts per SIMD instead of five (4104 units of 4096 slots losing one 46.4 us, 40.7 without).
 template <bool kShared, int kBatch = 8, bool kRandom = false, bool kLazy = false>
 __global__ __launch_bounds__(kEvThreads) void rank_small_kernel(CacheView cv, LayerMask appended,
                                                                 double alpha,

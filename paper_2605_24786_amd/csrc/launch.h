@@ -93,8 +93,7 @@ hipError_t launch_attend(const CacheView &cv, const AttendLaunch &a, const Atten
                          hipStream_t stream);
 // Importance of a freshly loaded prompt of T tokens from all its queries q [B][T][Hq][D] (D = 128,
 // contiguous layout).  scratch: scratch_floats floats, at least observe_scratch_floats(B * Hkv, G, T); with more the
-// work is cut into parts, observe_plan_floats(B * Hkv, G, T, first block of rows, INT8 slots, chan, scratch_floats, CUs) of them are used
-// (without the first block: every row counts).
+// work is cut into parts, observe_plan_floats(B * Hkv, G, T, first block of rows, INT8 slots, chan, scratch_floats, CUs) of them are used.
 size_t observe_scratch_floats(int units_per_layer, int G, int cap);
 int observe_first_block(int G, int T, double decay, double gain);
 size_t observe_plan_floats(int units_per_layer, int G, int T, int b0, int n8, int chan, size_t have, int cus);
